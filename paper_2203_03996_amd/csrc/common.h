@@ -74,7 +74,9 @@ struct MaskPassArgs {
     int up;                      // > 1: nearest upsampling of the input mask by this factor (k = 1)
     int bilinear;                // with up > 1: bilinear upsampling instead (sources that carry weight)
     int32_t* zero_count;         // optional counter the pass resets to 0 (survivor count of the layer)
-    int emit_only;               // 1: mask_in is final and its chunk counts are in the workspace already
+    int emit_only;               // 1: mask_in is final and its flags have been counted: counts_per_chunk numbers per chunk of
+    const int32_t* counts;       //    pixels, in `counts`
+    int counts_per_chunk;
     uint32_t* taps_out;          // optional [n*oh*ow]: per list entry, which window taps are flagged (k*k <= 25 bits);
                                  // bit 30: the entry's pixel is flagged in mask_b
     int b_stride, b_h, b_w;      // b_stride > 0: mask_b is [n,b_h,b_w] and output pixel (y,x) looks at (y,x)*b_stride

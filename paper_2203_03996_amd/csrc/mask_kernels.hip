@@ -301,6 +301,7 @@ struct EmitArgs {
     uint32_t* taps_out;
     int h, w, oh, ow, k, stride, pad;
     int b_stride, b_h, b_w;
+    int counts_per_chunk;         // chunk_counts holds this many numbers per chunk
 };
 
 // The three rows of input flags that the tap words of pixels p0 .. p0+7 are cut from (3x3 windows on rows a
@@ -418,7 +419,7 @@ __global__ __launch_bounds__(kMaskThreads) void emit_kernel(EmitArgs a) {
     // every load the block needs is requested up front: the counts of the chunks before it, its own flags and
     // the rows its tap words come from
     int part = 0;
-    for (int i = threadIdx.x; i < chunk; i += kMaskThreads) part += a.chunk_counts[i];
+    for (int i = threadIdx.x; i < chunk * a.counts_per_chunk; i += kMaskThreads) part += a.chunk_counts[i];
     const int64_t p0 = (int64_t)chunk * kChunk + (int64_t)threadIdx.x * kPxPerThread;
     uint64_t word = 0;
     if (p0 + kPxPerThread <= a.pixels) {
@@ -495,7 +496,8 @@ static dcnn_status mask_compact_on(dcnn_ctx* ctx, const MaskPassArgs& m, const W
         emit_mask = a.mask_out;
     }
     if (m.idx_out == nullptr) return DCNN_OK;
-    EmitArgs e{emit_mask, ws.chunk_counts, m.idx_out, m.count_out, out_pixels};
+    EmitArgs e{emit_mask, m.emit_only ? m.counts : ws.chunk_counts, m.idx_out, m.count_out, out_pixels};
+    e.counts_per_chunk = m.emit_only ? m.counts_per_chunk : 1;
     e.tap_mask = m.mask_in; e.taps_out = (m.emit_only || m.up > 1 || m.k * m.k > 25 || m.kw > 0) ? nullptr : m.taps_out;
     e.h = m.h; e.w = m.w; e.oh = m.oh; e.ow = m.ow; e.k = m.k; e.stride = m.stride; e.pad = m.pad;
     e.mask_b = m.mask_b; e.b_stride = m.b_stride; e.b_h = m.b_h; e.b_w = m.b_w;
