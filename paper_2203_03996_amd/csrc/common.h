@@ -95,7 +95,14 @@ dcnn_status launch_fill_i32(dcnn_ctx* ctx, int32_t* p, int32_t v, int64_t n);
 dcnn_status launch_mask_sum(dcnn_ctx* ctx, const uint8_t* mask, int64_t pixels, int32_t* out);
 // flags[p] = 1 iff row p of `data` ([pixels, c] elements) has a non-zero bit.
 dcnn_status launch_row_flags(dcnn_ctx* ctx, int dtype, const void* data, uint8_t* flags, int64_t pixels, int c);
-dcnn_status launch_fill_u8(dcnn_ctx* ctx, uint8_t* p, uint8_t v, int64_t n);
+// Zeroes a set of 16-byte aligned pieces of device memory (lengths are rounded up to 16 bytes): the mask, count and flag
+// arrays of one layer or of a whole network, one launch for up to kClearPieces of them.
+struct ClearPiece {
+    void* p;
+    int64_t bytes;
+};
+constexpr int kClearPieces = 120;
+dcnn_status launch_clear(dcnn_ctx* ctx, const ClearPiece* pieces, int n);
 
 // Element-wise tail shared by CONV / ACT: (+bias) (+residual) activation, truncation, state.
 struct EpilogueArgs {

@@ -56,4 +56,11 @@ namespace dcnn {
 dcnn_status layer_create(dcnn_ctx* ctx, const dcnn_layer_desc* desc, const void* weights_dev, const void* bias_dev,
                          const void* proj_weights_dev, const void* proj_bias_dev, void* state_dev, size_t state_bytes,
                          dcnn_layer** out);
+// dcnn_layer_init; with clear = false the caller has cleared the layer's pieces (collect_clears) itself.
+dcnn_status layer_init(dcnn_layer* L, const void* const* dense_in, int32_t n_in, void* dense_out, bool clear);
+// The pieces of the layer's state that are zero before its first sparse step: masks, counts, x^T row flags.
+constexpr int kMaxLayerClears = 5;
+int collect_clears(const dcnn_layer* L, bool with_flags, ClearPiece* out);
+// Host-side bookkeeping that goes with cleared pieces.
+void sparse_output_cleared(dcnn_layer* L);
 }  // namespace dcnn

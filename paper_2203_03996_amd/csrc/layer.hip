@@ -199,16 +199,25 @@ static void carve(dcnn_layer* L, void* state) {
 constexpr int kXtIoOffset = 16;                                  // in int32 units
 constexpr int kStatsScratchOffset = 8;                           // where dcnn_layer_stats counts a mask that came without a count
 
-static dcnn_status clear_sparse_output(dcnn_layer* L) {
-    if (L->alias_mask) return DCNN_OK;
-    dcnn_status st = launch_fill_u8(L->ctx, L->out_mask, 0, (int64_t)align_up((size_t)L->out_pixels, 4));
-    if (st == DCNN_OK && L->out_mask_alt) st = launch_fill_u8(L->ctx, L->out_mask_alt, 0, (int64_t)align_up((size_t)L->out_pixels, 4));
-    L->mask_phase = 0;
-    if (st != DCNN_OK) return st;
-    st = launch_fill_i32(L->ctx, L->out_count, 0, kXtIoOffset + 4);     // the count, the statistics scratch and the x^T row counters behind it
-    if (st != DCNN_OK) return st;
-    if (L->list_count && L->list_count != L->out_count) st = launch_fill_i32(L->ctx, L->list_count, 0, 1);
-    return st;
+int collect_clears(const dcnn_layer* L, bool with_flags, ClearPiece* out) {
+    int n = 0;
+    if (!L->alias_mask) {
+        out[n++] = {L->out_mask, L->out_pixels};
+        if (L->out_mask_alt) out[n++] = {L->out_mask_alt, L->out_pixels};
+        out[n++] = {L->out_count, (kXtIoOffset + 4) * (int64_t)sizeof(int32_t)};   // the count, the statistics scratch and the x^T row counters behind it
+        if (L->list_count && L->list_count != L->out_count) out[n++] = {L->list_count, (int64_t)sizeof(int32_t)};
+    }
+    if (with_flags && L->xt_flags) out[n++] = {L->xt_flags, L->out_pixels};
+    return n;
+}
+
+void sparse_output_cleared(dcnn_layer* L) { L->mask_phase = 0; }
+
+static dcnn_status clear_sparse_output(dcnn_layer* L, bool with_flags) {
+    ClearPiece pieces[kMaxLayerClears];
+    const int n = collect_clears(L, with_flags, pieces);
+    sparse_output_cleared(L);
+    return launch_clear(L->ctx, pieces, n);
 }
 
 static ListArgs full_list(int64_t pixels) {
@@ -333,7 +342,7 @@ dcnn_status layer_create(dcnn_ctx* ctx, const dcnn_layer_desc* desc, const void*
         delete L;
         return fail(ctx, DCNN_EINVAL, "layer_create: input-mask dilation radius %d out of range (0..15)", desc->dilate_r);
     }
-    st = clear_sparse_output(L);
+    st = clear_sparse_output(L, false);
     if (st == DCNN_OK) st = launch_fill_i32(ctx, L->counters, 0, kAlign / sizeof(int32_t));
     if (st != DCNN_OK) { delete L; return st; }
     *out = L;
@@ -408,11 +417,16 @@ dcnn_status dcnn_layer_timing(dcnn_layer* L, float* total_ms, int32_t* launches)
 dcnn_status dcnn_layer_reset(dcnn_layer* layer) {
     if (!layer) return DCNN_EINVAL;
     layer->inited = false;
-    return clear_sparse_output(layer);
+    return clear_sparse_output(layer, false);
 }
 
 dcnn_status dcnn_layer_init(dcnn_layer* L, const void* const* dense_in, int32_t n_in, void* dense_out) {
-    if (!L) return DCNN_EINVAL;
+    return L ? dcnn::layer_init(L, dense_in, n_in, dense_out, true) : DCNN_EINVAL;
+}
+
+}  // extern "C"
+
+dcnn_status dcnn::layer_init(dcnn_layer* L, const void* const* dense_in, int32_t n_in, void* dense_out, bool clear) {
     dcnn_ctx* ctx = L->ctx;
     const dcnn_layer_desc& d = L->d;
     const int want_in = d.kind == DCNN_DELTAGEN ? 1 : d.n_in;
@@ -451,7 +465,7 @@ dcnn_status dcnn_layer_init(dcnn_layer* L, const void* const* dense_in, int32_t 
             e.res_data = d.n_in == 2 ? (has_proj(d) ? dense_out : dense_in[1]) : nullptr; e.res_mask = nullptr;
             e.xA = L->buf0; e.xT = L->buf1; e.out_data = dense_out; e.out_mask = nullptr; e.surv = nullptr;
             st = launch_conv(ctx, d.dtype, true, full_list(L->out_pixels), c, e);
-            if (st == DCNN_OK && d.fuse_accum) st = launch_copy(ctx, L->buf2, dense_out, L->buf2_bytes);
+            if (st == DCNN_OK && d.fuse_accum && dense_out != L->buf2) st = launch_copy(ctx, L->buf2, dense_out, L->buf2_bytes);
             break;
         }
         case DCNN_ACT: {
@@ -495,13 +509,9 @@ dcnn_status dcnn_layer_init(dcnn_layer* L, const void* const* dense_in, int32_t 
     }
     (void)es;
     if (st != DCNN_OK) return st;
-    st = clear_sparse_output(L);
+    if (clear) st = clear_sparse_output(L, true);
     if (st != DCNN_OK) return st;
-    if (L->xt_flags) {                                        // the first frame leaves x^T all zero
-        st = launch_fill_u8(ctx, L->xt_flags, 0, L->out_pixels);
-        if (st != DCNN_OK) return st;
-        L->xt_flags_stale = false;
-    }
+    L->xt_flags_stale = false;                                // the first frame leaves x^T all zero, and its row flags clear
     L->inited = true;
     L->last_in_count = nullptr;
     L->last_in2_count = nullptr;
@@ -511,6 +521,8 @@ dcnn_status dcnn_layer_init(dcnn_layer* L, const void* const* dense_in, int32_t 
     L->view = dcnn_delta{};
     return DCNN_OK;
 }
+
+extern "C" {
 
 dcnn_status dcnn_layer_step(dcnn_layer* L, const dcnn_delta* const* in, int32_t n_in) {
     if (!L) return DCNN_EINVAL;

@@ -125,6 +125,22 @@ dcnn_status lanes_end(dcnn_net* net) {
     return DCNN_OK;
 }
 
+// Clears what is zero before the first sparse step in every layer, on the caller's stream (every lane starts behind it).
+dcnn_status clear_layers(dcnn_net* net, bool with_flags) {
+    ClearPiece pieces[kClearPieces];
+    int n = 0;
+    for (auto& p : net->plan) {
+        if (n + kMaxLayerClears > kClearPieces) {
+            const dcnn_status st = launch_clear(net->ctx, pieces, n);
+            if (st != DCNN_OK) return st;
+            n = 0;
+        }
+        n += collect_clears(p.layer, with_flags, pieces + n);
+        sparse_output_cleared(p.layer);
+    }
+    return launch_clear(net->ctx, pieces, n);
+}
+
 }  // namespace
 
 extern "C" {
@@ -430,20 +446,27 @@ dcnn_status dcnn_net_init(dcnn_net* net, const void* frame_dev, void* out_dev) {
     if (!net->bound) return fail(ctx, DCNN_ESTATE, "net_init: bind an arena first");
     if (!frame_dev) return fail(ctx, DCNN_EINVAL, "net_init: null frame");
     // during the dense first frame every layer writes its dense output into its own (dense-shaped)
-    // delta buffer, which the consumers read; afterwards those buffers hold sparse updates again
-    dcnn_status st = lanes_begin(net);
+    // delta buffer, which the consumers read; afterwards those buffers hold sparse updates again.  (The input layer's
+    // consumers read the frame itself, and a layer with a folded output layer writes O.)
+    dcnn_status st = clear_layers(net, true);
+    if (st == DCNN_OK) st = lanes_begin(net);
     if (st != DCNN_OK) return st;
+    const bool frame_direct = reinterpret_cast<uintptr_t>(frame_dev) % 16 == 0;
+    auto dense_of = [&](const Planned& q) -> const void* {
+        if (q.d.kind == DCNN_DELTAGEN && frame_direct) return frame_dev;
+        return q.d.fuse_accum ? q.layer->buf2 : q.layer->out_data;
+    };
     for (auto& p : net->plan) {
         const void* ins[2] = {nullptr, nullptr};
         int n_in = 0;
         if (p.d.kind == DCNN_DELTAGEN) {
             ins[0] = frame_dev; n_in = 1;
         } else {
-            for (int in : p.in_nodes) ins[n_in++] = net->plan[net->layer_of_node[in]].layer->out_data;
+            for (int in : p.in_nodes) ins[n_in++] = dense_of(net->plan[net->layer_of_node[in]]);
         }
-        void* dense_out = p.d.kind == DCNN_ACCUM ? out_dev : p.layer->out_data;
+        void* dense_out = p.d.kind == DCNN_ACCUM ? out_dev : const_cast<void*>(dense_of(p));
         st = lane_wait_inputs(net, p);
-        if (st == DCNN_OK) st = dcnn_layer_init(p.layer, ins, n_in, dense_out);
+        if (st == DCNN_OK) st = dcnn::layer_init(p.layer, ins, n_in, dense_out, false);
         if (st == DCNN_OK && p.d.fuse_accum && out_dev) st = launch_copy(net->lane_ctx[p.lane], out_dev, p.layer->buf2, p.layer->buf2_bytes);
         if (st != DCNN_OK) return lane_fail(net, p, st);
         st = lane_mark_done(net, p);
@@ -499,12 +522,9 @@ dcnn_status dcnn_net_step(dcnn_net* net, const void* frame_dev, void* out_dev) {
 dcnn_status dcnn_net_reset(dcnn_net* net) {
     if (!net) return DCNN_EINVAL;
     if (!net->bound) return fail(net->ctx, DCNN_ESTATE, "net_reset: bind an arena first");
-    for (auto& p : net->plan) {
-        dcnn_status st = dcnn_layer_reset(p.layer);
-        if (st != DCNN_OK) return st;
-    }
+    for (auto& p : net->plan) p.layer->inited = false;
     net->inited = false;
-    return DCNN_OK;
+    return clear_layers(net, false);
 }
 
 dcnn_status dcnn_net_output(const dcnn_net* net, dcnn_delta* out_view) {

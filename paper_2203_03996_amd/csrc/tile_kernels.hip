@@ -1144,15 +1144,36 @@ dcnn_status launch_fill_i32(dcnn_ctx* ctx, int32_t* p, int32_t v, int64_t n) {
     return check_hip(ctx, hipGetLastError(), "fill_kernel launch");
 }
 
-dcnn_status launch_fill_u8(dcnn_ctx* ctx, uint8_t* p, uint8_t v, int64_t n) {
-    // fill 4 bytes at a time where the length allows (buffers are 256-byte aligned)
-    if (n % 4 == 0) {
-        const int32_t w = (int32_t)(0x01010101u * v);
-        return launch_fill_i32(ctx, reinterpret_cast<int32_t*>(p), w, n / 4);
+// A launch costs ~4 us whatever it clears, and a layer has up to five pieces: the table travels in the kernel's arguments
+// so that a network of 74 layers clears all of its pieces with three launches instead of 270 (first frame of the
+// ResNet-50-shaped network at 8 streams 3.56 -> TBD ms).  blockIdx.y: piece; blockIdx.x: a share of it.
+struct ClearTable {
+    ClearPiece piece[kClearPieces];
+};
+__global__ __launch_bounds__(256) void clear_kernel(ClearTable t) {
+    const ClearPiece c = t.piece[blockIdx.y];
+    uint4* p = static_cast<uint4*>(c.p);
+    const int64_t n16 = (c.bytes + 15) / 16;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n16; i += (int64_t)gridDim.x * blockDim.x)
+        p[i] = make_uint4(0u, 0u, 0u, 0u);
+}
+
+dcnn_status launch_clear(dcnn_ctx* ctx, const ClearPiece* pieces, int n) {
+    for (int first = 0; first < n; first += kClearPieces) {
+        ClearTable t{};
+        const int m = n - first < kClearPieces ? n - first : kClearPieces;
+        int64_t longest = 16;
+        for (int i = 0; i < m; ++i) {
+            t.piece[i] = pieces[first + i];
+            if (t.piece[i].bytes > longest) longest = t.piece[i].bytes;
+        }
+        const int64_t want = cdiv(longest, 256 * 16);
+        const int grid = (int)(want < 256 ? want : 256);
+        hipLaunchKernelGGL(clear_kernel, dim3(grid, m), dim3(256), 0, ctx->stream, t);
+        const dcnn_status st = check_hip(ctx, hipGetLastError(), "clear_kernel launch");
+        if (st != DCNN_OK) return st;
     }
-    int grid = (int)(cdiv(n, 256) < 2048 ? cdiv(n, 256) : 2048);
-    hipLaunchKernelGGL((fill_kernel<uint8_t>), dim3(grid > 0 ? grid : 1), dim3(256), 0, ctx->stream, p, v, n);
-    return check_hip(ctx, hipGetLastError(), "fill_kernel launch");
+    return DCNN_OK;
 }
 
 dcnn_status launch_copy(dcnn_ctx* ctx, void* dst, const void* src, size_t bytes) {
