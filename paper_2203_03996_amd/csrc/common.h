@@ -158,6 +158,7 @@ struct ConvArgs {
     // result is added to this one's before the epilogue; its update flag is bit 30 of the list's tap words
     const void* in2_data;        // nullptr: none
     const void* wpacked2;
+    const void* bias2;           // first frame only
     int h2, w2, cin2, stride2, kch2;
 };
 dcnn_status launch_conv(dcnn_ctx* ctx, int dtype, bool init, const ListArgs& l, const ConvArgs& c,

@@ -1,0 +1,335 @@
+// The dense first frame of a convolution with dense weights: an implicit GEMM over every output pixel, with bias, the
+// optional residual or projection of a second input, and the first-frame form of the activation (x^A <- v, x^T <- 0, output
+// f(v); Fig. 2).  No pixel is decided on, so the output channels need not meet and the work splits freely over
+// pixels AND channels -- which is what the sparse kernels, whose tail wants the whole pixel, cannot do.
+//
+// A wave owns 64 pixels x 64 output channels (2 x 2 MFMA 32x32 blocks): four 16-byte operands per lane and K-step feed four
+// MFMAs, straight from global memory / L2 into registers, a ring of kFirstRing K-steps in flight.  With enough such
+// tiles the four waves of a workgroup take four pixel tiles of the same channels (they share the weights in the
+// vector cache); with too few -- the deep stages of a backbone: 512 pixels, K = 4608 -- they split the K-steps of ONE
+// tile and add their partial sums in LDS in a fixed order.
+// Bound: HBM for the narrow layers of wide maps (64 streams of 128x128, 64->256 with its projection, x^A, x^T and O: 1.6 GB
+// written and 0.27 GB read in 530 us, 3.5 TB/s; two launches of the plain kernel took 1030 us, the projection's result
+// going through memory), memory latency for the deep ones (3x3 512->512 on 512 pixels 30 us, was 79).
+#include "conv_plan.h"
+
+namespace dcnn {
+
+constexpr int kFirstWaves = 4;
+constexpr int kFirstPx = 64, kFirstCh = 64;                    // tile of a wave
+constexpr int kFirstRing = 4;                                  // K-steps whose operands are in registers or on their way
+
+struct FirstArgs {
+    int nb;                        // column blocks per packed channel group (the layer's plan)
+    int ngroups;                   // packed channel groups
+    int wc;                        // waves of a workgroup side by side over the channels (1, 2 or 4), the others over pixels
+    int cgroups;                   // channel tiles per pixel, in groups of wc
+    int64_t units;                 // workgroups: groups of pixel tiles x groups of channel tiles
+    int64_t pixels;
+    const void* bias2;             // bias of the projection
+};
+
+template <typename T> constexpr int first_stage_stride() { return kFirstCh * (int)sizeof(T) + kStagePad; }
+
+template <typename T, int SPLIT>
+__global__ __launch_bounds__(kFirstWaves* kWave, 2) void conv_first_kernel(ConvArgs c, EpilogueArgs e, FirstArgs f) {
+    typedef typename Mma<T>::Vec Vec;
+    constexpr int V = Elem<T>::VEC;
+    typedef typename RawOf<T, V>::type Raw;
+    constexpr int ES = (int)sizeof(T);
+    constexpr int TP = kFirstPx / 32, TC = kFirstCh / 32, D = kFirstRing;
+    constexpr int stage_stride = first_stage_stride<T>();
+    static_assert(SPLIT == 1 || SPLIT == kFirstWaves, "one tile per wave or one tile per workgroup");
+    static_assert(TP * TC == kFirstWaves, "after a split every wave sums one block");
+    extern __shared__ __align__(16) unsigned char smem[];
+
+    // One tile per wave: units in launch order.  (A contiguous eighth per XCD, workgroup b running on XCD b % 8, keeps
+    // neighbours in one L2 but spreads the eight fronts over memory a power of two apart: 563 -> 530 us for the layer above
+    // without it.)  One tile per workgroup: the XCDs do take an eighth each, so that a weight slice is fetched by few L2s.
+    const int64_t per = (f.units + kXcd - 1) / kXcd;
+    const int64_t in_xcd = blockIdx.x / kXcd;
+    const int64_t unit = SPLIT == 1 ? (int64_t)blockIdx.x : (int64_t)(blockIdx.x % kXcd) * per + in_xcd;
+    if (in_xcd >= per || unit >= f.units) return;              // uniform for the workgroup
+    const int lane = threadIdx.x % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int col = lane % 32, g = lane / 32;
+    const int64_t pg = unit / f.cgroups;
+    const int cg = (int)(unit - pg * f.cgroups);
+    const int64_t pt = SPLIT == 1 ? pg * (kFirstWaves / f.wc) + wave / f.wc : pg;
+    const int ct = SPLIT == 1 ? cg * f.wc + wave % f.wc : cg;
+    const int64_t px0 = pt * kFirstPx;
+    const int ch0 = ct * kFirstCh;
+    if (SPLIT == 1 && (px0 >= f.pixels || ch0 >= e.c)) return;   // (no workgroup barrier below in this case)
+    const int cols = f.nb * 32;
+
+    // the lane's pixels: origin of their windows
+    struct Px { int iy0, ix0; uint32_t base, base2; bool on; };
+    Px px[TP];
+    const int cin_bytes = c.cin * ES, cin2_bytes = c.cin2 * ES;
+#pragma unroll
+    for (int i = 0; i < TP; ++i) {
+        const int64_t p = px0 + i * 32 + col;
+        px[i].on = p < f.pixels;
+        const uint32_t pu = px[i].on ? (uint32_t)p : 0u;
+        const uint32_t t1 = fast_div(pu, c.div_ow);
+        const int ox = (int)(pu - t1 * (uint32_t)c.ow);
+        const uint32_t n = fast_div(t1, c.div_oh);
+        const int oy = (int)(t1 - n * (uint32_t)c.oh);
+        px[i].iy0 = oy * c.stride - c.pad;
+        px[i].ix0 = ox * c.stride - c.pad;
+        px[i].base = (uint32_t)(((int)n * c.h + px[i].iy0) * c.w + px[i].ix0) * (uint32_t)cin_bytes + (uint32_t)g * 16u;
+        px[i].base2 = (uint32_t)(((int)n * c.h2 + oy * c.stride2) * c.w2 + ox * c.stride2) * (uint32_t)cin2_bytes + (uint32_t)g * 16u;
+    }
+    // column blocks of the tile in the packed weights (a block past the last one repeats it; its channels are not stored)
+    auto block_of = [&](int b) {
+        const int cb = ch0 / 32 + b, last = f.ngroups * f.nb - 1;
+        return cb < last ? cb : last;
+    };
+
+    f32x16 acc[TP][TC];
+    auto zero_acc = [&]() {
+#pragma unroll
+        for (int i = 0; i < TP; ++i)
+#pragma unroll
+            for (int b = 0; b < TC; ++b)
+#pragma unroll
+                for (int q = 0; q < 16; ++q) acc[i][b][q] = 0.0f;
+    };
+    // acc += window of `data` x packed weights, over this wave's share of the K-steps.  `proj`: the 1x1 second input.
+    auto k_loop = [&](bool proj) __attribute__((always_inline)) {
+        const int ksz = proj ? 1 : c.k, kch = proj ? c.kch2 : c.kch;
+        const int rowb = proj ? cin2_bytes : cin_bytes, iw = proj ? c.w2 : c.w;
+        const int ksteps = ksz * ksz * kch;
+        const __amdgpu_buffer_rsrc_t rs_in = proj ? ws_rsrc(c.in2_data, (uint64_t)c.n * c.h2 * c.w2 * cin2_bytes)
+                                                  : ws_rsrc(c.in_data, (uint64_t)c.n * c.h * c.w * cin_bytes);
+        const __amdgpu_buffer_rsrc_t rs_w = ws_rsrc(proj ? c.wpacked2 : c.wpacked, (uint64_t)f.ngroups * ksteps * 2 * cols * 16);
+        uint32_t wlane[TC];
+#pragma unroll
+        for (int b = 0; b < TC; ++b) {
+            const int cb = block_of(b);
+            wlane[b] = ((uint32_t)(cb / f.nb) * (uint32_t)ksteps * 2u * (uint32_t)cols + (uint32_t)g * (uint32_t)cols +
+                        (uint32_t)(cb % f.nb) * 32u + (uint32_t)col) * 16u;
+        }
+        const int share = SPLIT == 1 ? 0 : wave;
+        const int first = (int)((int64_t)ksteps * share / SPLIT), last = (int)((int64_t)ksteps * (share + 1) / SPLIT);
+        struct Cur { int s, kc, dy, dx; };
+        Cur cu;
+        cu.s = first;
+        {
+            const int tap = first / kch;
+            cu.kc = first - tap * kch;
+            cu.dy = tap / ksz; cu.dx = tap - cu.dy * ksz;
+        }
+        // Every load is issued unconditionally: a pixel outside the map, padding channels and steps past the end read zeros
+        // from an offset outside the descriptor, so the number of loads in flight at each wait is known.
+        auto issue = [&](Vec (&x)[TP], Vec (&w)[TC]) {
+            const bool live = cu.s < last;
+            const bool chan_ok = live && (2 * cu.kc + g) * 16 < rowb;
+            const uint32_t uni = (uint32_t)((cu.dy * iw + cu.dx) * rowb + cu.kc * 32);
+#pragma unroll
+            for (int i = 0; i < TP; ++i) {
+                const bool in = proj || ((unsigned)(px[i].iy0 + cu.dy) < (unsigned)c.h && (unsigned)(px[i].ix0 + cu.dx) < (unsigned)c.w);
+                uint32_t off = (chan_ok && px[i].on && in) ? (proj ? px[i].base2 : px[i].base) + uni : kOob;
+                asm volatile("" : "+v"(off));
+                x[i] = ws_load16<Vec>(rs_in, off);
+            }
+            const uint32_t wstep = (uint32_t)(live ? cu.s : first) * (uint32_t)(2 * cols * 16);
+#pragma unroll
+            for (int b = 0; b < TC; ++b) w[b] = ws_load16<Vec>(rs_w, wlane[b] + wstep);
+            ++cu.s;
+            if (++cu.kc == kch) {
+                cu.kc = 0;
+                if (++cu.dx == ksz) { cu.dx = 0; ++cu.dy; }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto mma = [&](const Vec (&x)[TP], const Vec (&w)[TC]) {
+#pragma unroll
+            for (int b = 0; b < TC; ++b)
+#pragma unroll
+                for (int i = 0; i < TP; ++i) Mma<T>::run(acc[i][b], w[b], x[i]);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        Vec x[D][TP], w[D][TC];
+#pragma unroll
+        for (int i = 0; i < D - 1; ++i) issue(x[i], w[i]);
+        for (int s = first; s < last; s += D) {
+#pragma unroll
+            for (int j = 0; j < D; ++j) {
+                issue(x[(j + D - 1) % D], w[(j + D - 1) % D]);
+                mma(x[j], w[j]);
+            }
+        }
+    };
+
+    // staging tile [pixel][channel] in the storage type: one per wave, or one for the workgroup behind the partial sums
+    unsigned char* stage = smem + (SPLIT == 1 ? (size_t)wave * kFirstPx * stage_stride : (size_t)kFirstWaves * TP * TC * 4 * kWave * 16);
+    f32x4* partial = reinterpret_cast<f32x4*>(smem);
+    // sums (+ bias) of one 32x32 block -> rounded to the storage type -> staging tile; with `add` onto what it holds
+    typedef T Quad __attribute__((ext_vector_type(4)));
+    auto stage_block = [&](const f32x16& a, int i, int b, const T* bias, bool add) __attribute__((always_inline)) {
+        unsigned char* row = stage + (size_t)(i * 32 + col) * stage_stride;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int ch = ch0 + b * 32 + 8 * q + 4 * g;       // (channels are a multiple of 4: all four exist or none)
+            Quad* dst = reinterpret_cast<Quad*>(reinterpret_cast<T*>(row) + b * 32 + 8 * q + 4 * g);
+            Quad bv, v, old;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) { bv[k] = (T)0.0f; old[k] = (T)0.0f; }
+            if (bias != nullptr && ch < e.c) bv = *reinterpret_cast<const Quad*>(bias + ch);
+            if (add) old = *dst;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                v[k] = (T)(a[4 * q + k] + (float)bv[k]);
+                if (add) v[k] = (T)((float)old[k] + (float)v[k]);
+            }
+            *dst = v;
+        }
+    };
+    auto deliver = [&](const T* bias, bool add) __attribute__((always_inline)) {
+        if constexpr (SPLIT == 1) {
+#pragma unroll
+            for (int i = 0; i < TP; ++i)
+#pragma unroll
+                for (int b = 0; b < TC; ++b) stage_block(acc[i][b], i, b, bias, add);
+        } else {
+            // partial sums meet in LDS: wave w adds block w of all waves, in wave order
+#pragma unroll
+            for (int i = 0; i < TP; ++i)
+#pragma unroll
+                for (int b = 0; b < TC; ++b)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        f32x4 v;
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) v[k] = acc[i][b][4 * q + k];
+                        partial[((wave * (TP * TC) + i * TC + b) * 4 + q) * kWave + lane] = v;
+                    }
+            lds_block_sync();
+            f32x16 sum;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                f32x4 v = partial[(wave * 4 + q) * kWave + lane];
+#pragma unroll
+                for (int o = 1; o < kFirstWaves; ++o) {
+                    const f32x4 u = partial[((o * (TP * TC) + wave) * 4 + q) * kWave + lane];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) v[k] += u[k];
+                }
+#pragma unroll
+                for (int k = 0; k < 4; ++k) sum[4 * q + k] = v[k];
+            }
+            stage_block(sum, wave / TC, wave % TC, bias, add);
+            lds_block_sync();                                  // (the partial sums may be overwritten, the staged tile may be read)
+        }
+    };
+
+    zero_acc();
+    k_loop(false);
+    deliver(static_cast<const T*>(e.bias), false);
+    if (c.in2_data != nullptr) {                               // the projection: rounded on its own, then added
+        zero_acc();
+        k_loop(true);
+        deliver(static_cast<const T*>(f.bias2), true);
+    }
+    lds_wave_sync();
+
+    // tail: 64 channels of a pixel are NV vectors, neighbouring lanes hold neighbouring vectors
+    constexpr int NV = kFirstCh / V;
+    constexpr int NLANES = SPLIT == 1 ? kWave : kFirstWaves * kWave;
+    constexpr int PPI = NLANES / NV, NIT = kFirstPx / PPI;
+    const int me = SPLIT == 1 ? lane : (int)threadIdx.x;
+    const int sub = me % NV, grp = me / NV;
+    const int ch = ch0 + sub * V;
+    const bool stateful = e.act != DCNN_ACT_NONE;
+    Raw lo_v, hi_v;
+#pragma unroll
+    for (int k = 0; k < V; ++k) { lo_v[k] = (T)0.0f; hi_v[k] = (T)act_hi(e.act); }
+    const T* res = static_cast<const T*>(e.res_data);
+    T* xA = static_cast<T*>(e.xA);
+    T* xT = static_cast<T*>(e.xT);
+    T* out = static_cast<T*>(e.out_data);
+    if (ch >= e.c) return;                                     // (channels are a multiple of V)
+    constexpr int HB = NIT < 8 ? NIT : 8;                      // residual rows requested together
+#pragma unroll
+    for (int it0 = 0; it0 < NIT; it0 += HB) {
+        Raw rr[HB];
+#pragma unroll
+        for (int h = 0; h < HB; ++h) {
+            const int64_t p = px0 + (it0 + h) * PPI + grp;
+            rr[h] = raw_zero<T, V>();
+            if (res != nullptr && p < f.pixels) rr[h] = raw_load<T, V>(res + p * e.c + ch);
+        }
+#pragma unroll
+        for (int h = 0; h < HB; ++h) {
+            const int row = (it0 + h) * PPI + grp;
+            const int64_t p = px0 + row;
+            if (p >= f.pixels) continue;
+            const Raw d0 = raw_load<T, V>(reinterpret_cast<const T*>(stage + (size_t)row * stage_stride) + sub * V);
+            Raw o_a = d0;
+            if (res != nullptr) {
+#pragma unroll
+                for (int k = 0; k < V; ++k) raw_set<T, V>(o_a, k, raw_get<T, V>(d0, k) + raw_get<T, V>(rr[h], k));
+            }
+            // f of a stored value is exact in the storage type: clamped there, two elements an instruction in fp16
+            const Raw o_y = stateful ? __builtin_elementwise_min(__builtin_elementwise_max(o_a, lo_v), hi_v) : o_a;
+            const int64_t off = p * e.c + ch;
+            if (stateful) {
+                __builtin_nontemporal_store(o_a, reinterpret_cast<Raw*>(xA + off));
+                if (xT != nullptr) __builtin_nontemporal_store(raw_zero<T, V>(), reinterpret_cast<Raw*>(xT + off));
+            }
+            raw_store<T, V>(out + off, o_y);
+        }
+    }
+}
+
+bool conv_first_supported(int dtype, const ConvArgs& c, int cout, bool flat) {
+    const size_t es = dtype_size(dtype);
+    const int vec = dtype == DCNN_F16 ? 8 : 4;
+    if (flat || cout % vec != 0 || ((size_t)c.cin * es) % 16 != 0) return false;
+    if ((uint64_t)c.n * c.h * c.w * c.cin * es > kWsMaxBytes) return false;
+    return c.in2_data == nullptr || (((size_t)c.cin2 * es) % 16 == 0 && (uint64_t)c.n * c.h2 * c.w2 * c.cin2 * es <= kWsMaxBytes);
+}
+
+template <typename T>
+static dcnn_status launch_conv_first_t(dcnn_ctx* ctx, const ConvArgs& c, const EpilogueArgs& e, const ConvPlan& p, const void* bias2) {
+    FirstArgs f{};
+    f.nb = p.nb; f.ngroups = p.npass * p.cs;
+    const int ctiles = (int)cdiv(e.c, kFirstCh);
+    f.pixels = (int64_t)c.n * c.oh * c.ow;
+    f.bias2 = bias2;
+    const int64_t ptiles = cdiv(f.pixels, kFirstPx);
+    // The waves of a workgroup share a tile's K-steps where ONE stream has fewer tiles than the chip has compute units and K
+    // is long enough to be worth cutting.  The number of streams stays out of the rule on purpose: the order of the sum
+    // must not depend on it (a stream gives the same bits alone and in a batch).
+    const bool split = cdiv((int64_t)c.oh * c.ow, kFirstPx) * ctiles < 256 && c.k * c.k * c.kch >= 8 * kFirstWaves;
+    f.wc = split ? 1 : (ctiles >= 4 ? 4 : ctiles);             // (three tiles: two side by side, then one)
+    if (f.wc == 3) f.wc = 2;
+    f.cgroups = (int)cdiv(ctiles, f.wc);
+    f.units = (split ? ptiles : cdiv(ptiles, kFirstWaves / f.wc)) * f.cgroups;
+    const size_t stage = (size_t)kFirstPx * first_stage_stride<T>();
+    const size_t lds = split ? (size_t)kFirstWaves * 4 * 4 * kWave * 16 + stage : kFirstWaves * stage;
+    const int64_t grid = cdiv(f.units, kXcd) * kXcd;
+    if (grid > INT32_MAX) return fail(ctx, DCNN_ESHAPE, "first frame: %lld workgroups", (long long)grid);
+    hipError_t err = hipSuccess;
+#define DCNN_FIRST_LAUNCH(SPLIT)                                                                                 \
+    do {                                                                                                         \
+        auto kern = conv_first_kernel<T, SPLIT>;                                                                 \
+        static bool attr_set = false;                                                                            \
+        if (!attr_set) {                                                                                         \
+            err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes); \
+            attr_set = (err == hipSuccess);                                                                      \
+        }                                                                                                        \
+        if (err == hipSuccess) hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kFirstWaves * kWave), lds, ctx->stream, c, e, f); \
+    } while (0)
+    if (split) DCNN_FIRST_LAUNCH(kFirstWaves); else DCNN_FIRST_LAUNCH(1);
+#undef DCNN_FIRST_LAUNCH
+    if (err != hipSuccess) return check_hip(ctx, err, "hipFuncSetAttribute(conv_first_kernel)");
+    return check_hip(ctx, hipGetLastError(), "conv_first_kernel launch");
+}
+
+dcnn_status launch_conv_first(dcnn_ctx* ctx, int dtype, const ConvArgs& c, const EpilogueArgs& e, const ConvPlan& p, const void* bias2) {
+    return dtype == DCNN_F16 ? launch_conv_first_t<f16>(ctx, c, e, p, bias2) : launch_conv_first_t<float>(ctx, c, e, p, bias2);
+}
+
+}  // namespace dcnn

@@ -113,6 +113,9 @@ DCNN_DECL_ALL(f16)
 DCNN_DECL_ALL(f32)
 #undef DCNN_DECL_ALL
 #undef DCNN_DECL
+// conv_first.hip
+bool conv_first_supported(int dtype, const ConvArgs& c, int cout, bool flat);
+dcnn_status launch_conv_first(dcnn_ctx* ctx, int dtype, const ConvArgs& c, const EpilogueArgs& e, const ConvPlan& p, const void* bias2);
 
 dcnn_status launch_conv(dcnn_ctx* ctx, int dtype, bool init, const ListArgs& l, const ConvArgs& c_in,
                         const EpilogueArgs& e) {
@@ -129,6 +132,10 @@ dcnn_status launch_conv(dcnn_ctx* ctx, int dtype, bool init, const ListArgs& l, 
     c.kch2 = c.in2_data ? (int)cdiv(c.cin2, dtype == DCNN_F16 ? 16 : 8) : 0;
     c.div_ow = make_fastdiv((uint32_t)c.ow);
     c.div_oh = make_fastdiv((uint32_t)c.oh);
+    // The dense first frame over 16-byte pixels and channel vectors (tensors below 2 GiB) splits over channels as well as
+    // pixels; everything else of a first frame stays with the plain kernel.
+    if (init && p.w_bytes <= kWsMaxBytes && conv_first_supported(dtype, c, c.cout, p.flat)) return launch_conv_first(ctx, dtype, c, e, p, c.bias2);
+    if (init && c.in2_data) return fail(ctx, DCNN_EUNSUPPORTED, "first frame of a convolution with a fused projection: shape not covered");
 #define DCNN_CASE(NB) case NB: return dtype == DCNN_F16 ? launch_conv_f16_nb##NB(ctx, init, l, c, e, p) : launch_conv_f32_nb##NB(ctx, init, l, c, e, p);
     switch (p.nb) {
         DCNN_CASE(1) DCNN_CASE(2) DCNN_CASE(3) DCNN_CASE(4)

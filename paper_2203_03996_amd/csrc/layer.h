@@ -35,8 +35,7 @@ struct dcnn_layer {
     mutable bool xt_flags_stale = false;  // the state memory was handed out: the flags are rebuilt from x^T before the next step
     void* wpacked;
     void* bias;
-    void* wpacked2;                     // fused projection: weights in the main plan's column grouping (sparse steps)
-    void* wpacked2_dense;               // ... and packed as a convolution of its own (dense first frame)
+    void* wpacked2;                     // fused projection: weights in the main plan's column grouping
     void* bias2;
     int32_t* counters;
     // bookkeeping of the last step

@@ -129,7 +129,7 @@ static void carve(dcnn_layer* L, void* state) {
     L->out_data = nullptr; L->out_mask = nullptr; L->out_idx = nullptr; L->out_count = nullptr;
     L->out_mask_alt = nullptr; L->mask_phase = 0;
     L->list = nullptr; L->list_count = nullptr; L->taps = nullptr; L->wpacked = nullptr; L->bias = nullptr;
-    L->wpacked2 = nullptr; L->wpacked2_dense = nullptr; L->bias2 = nullptr; L->xt_flags = nullptr;
+    L->wpacked2 = nullptr; L->bias2 = nullptr; L->xt_flags = nullptr;
     L->counters = static_cast<int32_t*>(cv.take(kAlign));      // stays all zero: doubles as the zero page of the gathers
     switch (d.kind) {
         case DCNN_DELTAGEN:
@@ -188,7 +188,6 @@ static void carve(dcnn_layer* L, void* state) {
         L->bias = cv.take((size_t)L->oc * es);
         if (has_proj(d)) {
             L->wpacked2 = cv.take(conv_proj_weight_bytes(d.dtype, d.kh, d.c, d.proj_c, L->oc));
-            L->wpacked2_dense = cv.take(conv_packed_weight_bytes(d.dtype, 1, d.proj_c, L->oc, 0, false));
             L->bias2 = cv.take((size_t)L->oc * es);
         }
     }
@@ -325,7 +324,6 @@ dcnn_status layer_create(dcnn_ctx* ctx, const dcnn_layer_desc* desc, const void*
             if (!proj_weights_dev) { delete L; return fail(ctx, DCNN_EINVAL, "layer_create: fused projection without weights"); }
             const void* w2 = proj_weights_dev;
             st = launch_pack_weights_proj(ctx, desc->dtype, w2, L->wpacked2, desc->kh, desc->c, desc->proj_c, L->oc);
-            if (st == DCNN_OK) st = launch_pack_weights(ctx, desc->dtype, w2, L->wpacked2_dense, 1, desc->proj_c, L->oc, 0, false);
             if (st == DCNN_OK && proj_bias_dev) st = launch_copy(ctx, L->bias2, proj_bias_dev, (size_t)L->oc * es);
             L->has_bias2 = proj_bias_dev != nullptr;
         }
@@ -443,26 +441,17 @@ dcnn_status dcnn::layer_init(dcnn_layer* L, const void* const* dense_in, int32_t
             break;
         case DCNN_CONV:
         case DCNN_DWCONV: {
-            if (has_proj(d)) {
-                // the projection runs as a dense convolution of its own into the output buffer, which the
-                // main convolution then reads as its residual (each pixel is read before it is rewritten)
-                ConvArgs c2{};
-                c2.in_data = dense_in[1]; c2.in_mask = nullptr; c2.wpacked = L->wpacked2_dense; c2.zero_page = L->counters;
-                c2.n = d.n; c2.h = d.proj_h; c2.w = d.proj_w; c2.cin = d.proj_c; c2.oh = L->oh; c2.ow = L->ow; c2.cout = L->oc;
-                c2.k = 1; c2.stride = d.proj_stride; c2.pad = 0; c2.depthwise = 0;
-                EpilogueArgs e2{};
-                e2.c = L->oc; e2.act = DCNN_ACT_NONE; e2.eps = 0.0f; e2.bias = L->has_bias2 ? L->bias2 : nullptr;
-                e2.out_data = dense_out;
-                st = launch_conv(ctx, d.dtype, true, full_list(L->out_pixels), c2, e2);
-                if (st != DCNN_OK) break;
-            }
             ConvArgs c{};
+            if (has_proj(d)) {                                    // a second K loop of the same kernel
+                c.in2_data = dense_in[1]; c.wpacked2 = L->wpacked2; c.bias2 = L->has_bias2 ? L->bias2 : nullptr;
+                c.h2 = d.proj_h; c.w2 = d.proj_w; c.cin2 = d.proj_c; c.stride2 = d.proj_stride;
+            }
             c.in_data = dense_in[0]; c.in_mask = nullptr; c.wpacked = L->wpacked; c.zero_page = L->counters;
             c.n = d.n; c.h = d.h; c.w = d.w; c.cin = d.c; c.oh = L->oh; c.ow = L->ow; c.cout = L->oc;
             c.k = d.kh; c.stride = d.stride; c.pad = d.pad; c.depthwise = d.kind == DCNN_DWCONV;
             EpilogueArgs e{};
             e.c = L->oc; e.act = d.act; e.eps = d.eps; e.bias = L->has_bias ? L->bias : nullptr;
-            e.res_data = d.n_in == 2 ? (has_proj(d) ? dense_out : dense_in[1]) : nullptr; e.res_mask = nullptr;
+            e.res_data = (d.n_in == 2 && !has_proj(d)) ? dense_in[1] : nullptr; e.res_mask = nullptr;
             e.xA = L->buf0; e.xT = L->buf1; e.out_data = dense_out; e.out_mask = nullptr; e.surv = nullptr;
             st = launch_conv(ctx, d.dtype, true, full_list(L->out_pixels), c, e);
             if (st == DCNN_OK && d.fuse_accum && dense_out != L->buf2) st = launch_copy(ctx, L->buf2, dense_out, L->buf2_bytes);

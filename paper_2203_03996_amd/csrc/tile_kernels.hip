@@ -345,7 +345,7 @@ __global__ __launch_bounds__(kTileThreads) void act_wide_kernel(ListArgs l, ActA
 
 // ---- activation + truncation (+ add) ----------------------------------------------------------
 template <typename T, int V, int VPL>
-__global__ __launch_bounds__(kTileThreads) void act_kernel(ListArgs l, ActArgs a, EpilogueArgs e, int init) {
+__global__ __launch_bounds__(kTileThreads) void act_kernel(ListArgs l, ActArgs a, EpilogueArgs e) {
     typedef typename RawOf<T, V>::type Raw;
     constexpr int UB = (V * VPL >= 16) ? 2 : 4;
     clear_ahead(e);
@@ -365,12 +365,45 @@ __global__ __launch_bounds__(kTileThreads) void act_kernel(ListArgs l, ActArgs a
         const int64_t base = tile * kTile;
         if (base >= count) continue;
         const int p_mine = list_pixel(l.list, base + lane % kTile, count);
-        const uint32_t bits = act_trunc_tile<T, V, VPL, UB, false>(e, init != 0, p_mine, lane, dx, 0, e.c, e.c, MaxExchange{nullptr, 1, 0});
+        const uint32_t bits = act_trunc_tile<T, V, VPL, UB, false>(e, false, p_mine, lane, dx, 0, e.c, e.c, MaxExchange{nullptr, 1, 0});
         if (e.surv) { if (lane == 0) e.surv[tile] = bits; }
         else survivors += __popc(bits);
     }
     // one atomic per wave: a counter bumped once per tile by every wave serialises in L2
     if (e.out_count && !e.surv && lane == 0 && survivors) atomicAdd(e.out_count, survivors);
+}
+
+// The dense first frame of the same layers: v = dx (+ second input), x^A <- v, x^T <- 0, output f(v) at every pixel.
+// Nothing is decided per pixel, so it is a plain stream over the elements (HBM bound).  The list-driven kernel
+// gave a workgroup 128 pixels whatever their width: 512 pixels of 2048 channels kept 4 workgroups busy for 102 us
+// (now 5), 2048 of 1024 57 us (5), 32768 of 256 36 us (7).
+template <typename T, int V>
+__global__ __launch_bounds__(256) void act_first_kernel(ActArgs a, EpilogueArgs e, int64_t nvecs) {
+    typedef typename RawOf<T, V>::type Raw;
+    const Raw* in = static_cast<const Raw*>(a.in_data);
+    const Raw* res = static_cast<const Raw*>(e.res_data);
+    Raw* xA = static_cast<Raw*>(e.xA);
+    Raw* xT = static_cast<Raw*>(e.xT);
+    Raw* out = static_cast<Raw*>(e.out_data);
+    const bool stateful = e.act != DCNN_ACT_NONE;
+    const float hi = act_hi(e.act);
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nvecs; i += (int64_t)gridDim.x * blockDim.x) {
+        const Raw d0 = in[i];
+        const Raw r0 = res != nullptr ? res[i] : raw_zero<T, V>();
+        Raw o_a, o_y;
+#pragma unroll
+        for (int k = 0; k < V; ++k) {
+            float d = raw_get<T, V>(d0, k);
+            if (res != nullptr) d = round_store<T>(d + raw_get<T, V>(r0, k));
+            raw_set<T, V>(o_a, k, d);
+            raw_set<T, V>(o_y, k, stateful ? act_clamp(d, hi) : d);
+        }
+        if (stateful) {
+            __builtin_nontemporal_store(o_a, xA + i);
+            if (xT != nullptr) __builtin_nontemporal_store(raw_zero<T, V>(), xT + i);
+        }
+        out[i] = o_y;
+    }
 }
 
 template <typename T>
@@ -379,10 +412,21 @@ static dcnn_status launch_act_t(dcnn_ctx* ctx, bool init, const ListArgs& l, con
     const bool vec = (e.c % VEC) == 0;
     const int nvec = vec ? e.c / VEC : e.c;
     const int vpl = (int)cdiv(nvec, kWave);
+    if (vpl > (vec && sizeof(T) == 4 ? 8 : 4))
+        return vec ? fail(ctx, DCNN_EUNSUPPORTED, "activation: %d channels exceed the supported 8 KB per pixel", e.c)
+                   : fail(ctx, DCNN_EUNSUPPORTED, "activation: %d unaligned channels exceed 256 per pixel", e.c);
+    if (init) {
+        const int64_t nvecs = l.count_host * nvec;
+        const int64_t want = cdiv(nvecs, 256), cap = (int64_t)ctx->num_cu * 32;
+        const dim3 fg((unsigned)(want < cap ? want : cap));
+        if (vec) hipLaunchKernelGGL((act_first_kernel<T, VEC>), fg, dim3(256), 0, ctx->stream, a, e, nvecs);
+        else hipLaunchKernelGGL((act_first_kernel<T, 1>), fg, dim3(256), 0, ctx->stream, a, e, nvecs);
+        return check_hip(ctx, hipGetLastError(), "act_first_kernel launch");
+    }
     // sparse steps over vector channels, tensors below 2 GiB: the buffer-addressed kernel
     const uint64_t map_bytes = (uint64_t)(l.max_count > 0 ? l.max_count : 0) * e.c * sizeof(T);
     // wide pixels on maps of at most 64 K pixels: the channels of a pixel are split over the waves of a workgroup
-    if (!init && vec && nvec >= 2 * kWave && nvec % kTileWaves == 0 && nvec <= kWave * kTileWaves && map_bytes > 0 &&
+    if (vec && nvec >= 2 * kWave && nvec % kTileWaves == 0 && nvec <= kWave * kTileWaves && map_bytes > 0 &&
         map_bytes <= kWsMaxBytes && l.max_count <= 65536) {
         const int64_t units = cdiv(l.max_count, kWideRun);
         const int64_t cap = (int64_t)ctx->num_cu * 8;
@@ -391,7 +435,7 @@ static dcnn_status launch_act_t(dcnn_ctx* ctx, bool init, const ListArgs& l, con
         hipLaunchKernelGGL((act_wide_kernel<T, VEC, 1>), dim3(wgrid), dim3(kTileThreads), 0, ctx->stream, l, a, e, mb, px);
         return check_hip(ctx, hipGetLastError(), "act_wide_kernel launch");
     }
-    if (!init && vec && vpl <= 4 && map_bytes > 0 && map_bytes <= kWsMaxBytes) {
+    if (vec && vpl <= 4 && map_bytes > 0 && map_bytes <= kWsMaxBytes) {
         const int vpl_used = vpl <= 1 ? 1 : (vpl <= 2 ? 2 : 4);
         const int ub = vpl_used == 4 ? 2 : 4;
         const TailShape shape = tail_shape(nvec, vpl_used, ub);
@@ -406,21 +450,16 @@ static dcnn_status launch_act_t(dcnn_ctx* ctx, bool init, const ListArgs& l, con
     }
     const int grid = list_grid(ctx, l.max_count, kTileWaves * kTile, 8);
     dim3 g(grid), b(kTileThreads);
-    const int ini = init ? 1 : 0;
-#define DCNN_ACT_LAUNCH(V, VPL) hipLaunchKernelGGL((act_kernel<T, V, VPL>), g, b, 0, ctx->stream, l, a, e, ini)
+#define DCNN_ACT_LAUNCH(V, VPL) hipLaunchKernelGGL((act_kernel<T, V, VPL>), g, b, 0, ctx->stream, l, a, e)
     if (vec) {
         if (vpl <= 1) DCNN_ACT_LAUNCH(VEC, 1);
         else if (vpl <= 2) DCNN_ACT_LAUNCH(VEC, 2);
         else if (vpl <= 4) DCNN_ACT_LAUNCH(VEC, 4);
-        else if (vpl <= 8 && sizeof(T) == 4) {
-            if constexpr (sizeof(T) == 4) DCNN_ACT_LAUNCH(VEC, 8);     // (fp32 only: 2048 channels = 8 KB per pixel)
-        }
-        else return fail(ctx, DCNN_EUNSUPPORTED, "activation: %d channels exceed the supported 8 KB per pixel", e.c);
+        else if constexpr (sizeof(T) == 4) DCNN_ACT_LAUNCH(VEC, 8);    // (fp32 only: 2048 channels = 8 KB per pixel)
     } else {
         if (vpl <= 1) DCNN_ACT_LAUNCH(1, 1);
         else if (vpl <= 2) DCNN_ACT_LAUNCH(1, 2);
-        else if (vpl <= 4) DCNN_ACT_LAUNCH(1, 4);
-        else return fail(ctx, DCNN_EUNSUPPORTED, "activation: %d unaligned channels exceed 256 per pixel", e.c);
+        else DCNN_ACT_LAUNCH(1, 4);
     }
 #undef DCNN_ACT_LAUNCH
     return check_hip(ctx, hipGetLastError(), "act_kernel launch");
@@ -604,6 +643,76 @@ __global__ __launch_bounds__(kTileThreads) void dwconv_kernel(ListArgs l, ConvAr
     if (e.out_count && !e.surv && lane == 0 && survivors) atomicAdd(e.out_count, survivors);
 }
 
+// The dense first frame of windows up to 3x3 over vector channels (input below 2 GiB): a thread owns one vector of
+// channels of DWP neighbouring pixels of the flat pixel order -- the weights of its channels are fetched once for all of
+// them -- and requests all their taps back to back, a tap outside the map with an out-of-range offset.  Bias joins the fp32
+// sum before its one rounding; x^A <- v, x^T <- 0, output f(v).  HBM bound.
+constexpr int kDwPixels = 4;
+template <typename T, int V, int KS>
+__global__ __launch_bounds__(256) void dwconv_first_kernel(ConvArgs c, EpilogueArgs e, FastDiv div_nvec, int64_t pixels, uint32_t items) {
+    typedef typename RawOf<T, V>::type Raw;
+    const uint32_t item = blockIdx.x * 256u + threadIdx.x;     // (item = pixel group x vector; below 2^31)
+    if (item >= items) return;
+    const uint32_t group = fast_div(item, div_nvec);
+    const int c0 = (int)(item - group * div_nvec.d) * V;
+    const T* wgt = static_cast<const T*>(c.wpacked);           // [k][k][C], unpacked
+    const T* bias = static_cast<const T*>(e.bias);
+    const T* res = static_cast<const T*>(e.res_data);
+    T* xA = static_cast<T*>(e.xA);
+    T* xT = static_cast<T*>(e.xT);
+    T* out = static_cast<T*>(e.out_data);
+    const uint32_t row_bytes = (uint32_t)e.c * (uint32_t)sizeof(T);
+    const __amdgpu_buffer_rsrc_t rs_in = ws_rsrc(c.in_data, (uint64_t)c.n * c.h * c.w * row_bytes);
+    const bool stateful = e.act != DCNN_ACT_NONE;
+    const float hi = act_hi(e.act);
+    Raw w[KS * KS], x[kDwPixels][KS * KS], rr[kDwPixels];
+#pragma unroll
+    for (int t = 0; t < KS * KS; ++t) w[t] = raw_load<T, V>(wgt + (int64_t)t * e.c + c0);
+#pragma unroll
+    for (int u = 0; u < kDwPixels; ++u) {
+        const int64_t p = (int64_t)group * kDwPixels + u;
+        const bool on = p < pixels;
+        const uint32_t pu = on ? (uint32_t)p : 0u;
+        const uint32_t t1 = fast_div(pu, c.div_ow);
+        const int ox = (int)(pu - t1 * (uint32_t)c.ow);
+        const uint32_t n = fast_div(t1, c.div_oh);
+        const int oy = (int)(t1 - n * (uint32_t)c.oh);
+        const int iy0 = oy * c.stride - c.pad, ix0 = ox * c.stride - c.pad;
+        const uint32_t base = (uint32_t)(((int)n * c.h + iy0) * c.w + ix0) * row_bytes + (uint32_t)c0 * (uint32_t)sizeof(T);
+#pragma unroll
+        for (int t = 0; t < KS * KS; ++t) {
+            const int dy = t / KS, dx = t % KS;
+            const bool in = on && (unsigned)(iy0 + dy) < (unsigned)c.h && (unsigned)(ix0 + dx) < (unsigned)c.w;
+            x[u][t] = ws_load16<Raw>(rs_in, in ? base + (uint32_t)(dy * c.w + dx) * row_bytes : kOob);
+        }
+        rr[u] = (res != nullptr && on) ? raw_load<T, V>(res + p * e.c + c0) : raw_zero<T, V>();
+    }
+    const Raw bv = bias != nullptr ? raw_load<T, V>(bias + c0) : raw_zero<T, V>();
+#pragma unroll
+    for (int u = 0; u < kDwPixels; ++u) {
+        const int64_t p = (int64_t)group * kDwPixels + u;
+        if (p >= pixels) break;
+        Raw o_a, o_y;
+#pragma unroll
+        for (int i = 0; i < V; ++i) {
+            float acc = 0.0f;
+#pragma unroll
+            for (int t = 0; t < KS * KS; ++t) acc = fmaf(raw_get<T, V>(x[u][t], i), raw_get<T, V>(w[t], i), acc);
+            if (bias != nullptr) acc += raw_get<T, V>(bv, i);
+            float d = round_store<T>(acc);
+            if (res != nullptr) d = round_store<T>(d + raw_get<T, V>(rr[u], i));
+            raw_set<T, V>(o_a, i, d);
+            raw_set<T, V>(o_y, i, stateful ? act_clamp(d, hi) : d);
+        }
+        const int64_t off = p * e.c + c0;
+        if (stateful) {
+            __builtin_nontemporal_store(o_a, reinterpret_cast<Raw*>(xA + off));
+            if (xT != nullptr) __builtin_nontemporal_store(raw_zero<T, V>(), reinterpret_cast<Raw*>(xT + off));
+        }
+        raw_store<T, V>(out + off, o_y);
+    }
+}
+
 template <typename T>
 static dcnn_status launch_dwconv_t(dcnn_ctx* ctx, bool init, const ListArgs& l, const ConvArgs& c, const EpilogueArgs& e) {
     constexpr int VEC = Elem<T>::VEC;
@@ -614,6 +723,21 @@ static dcnn_status launch_dwconv_t(dcnn_ctx* ctx, bool init, const ListArgs& l, 
     const uint64_t map_bytes = (uint64_t)(l.max_count > 0 ? l.max_count : 0) * e.c * sizeof(T);
     const uint64_t in_pixels = (uint64_t)c.n * c.h * c.w, in_bytes = in_pixels * e.c * sizeof(T);
     const size_t w_bytes = (size_t)c.k * c.k * e.c * sizeof(T);
+    const int64_t out_px = (int64_t)c.n * c.oh * c.ow;
+    const int64_t items = cdiv(out_px, kDwPixels) * nvec;
+    if (init && vec && vpl <= 4 && c.k <= 3 && in_bytes <= kWsMaxBytes && items <= INT32_MAX) {
+        ConvArgs cf = c;
+        cf.div_ow = make_fastdiv((uint32_t)c.ow);
+        cf.div_oh = make_fastdiv((uint32_t)c.oh);
+        const FastDiv dn = make_fastdiv((uint32_t)nvec);
+        const dim3 fg((unsigned)cdiv(items, 256));
+#define DCNN_DW_FIRST(KS) hipLaunchKernelGGL((dwconv_first_kernel<T, VEC, KS>), fg, dim3(256), 0, ctx->stream, cf, e, dn, out_px, (uint32_t)items)
+        if (c.k == 3) DCNN_DW_FIRST(3);
+        else if (c.k == 2) DCNN_DW_FIRST(2);
+        else DCNN_DW_FIRST(1);
+#undef DCNN_DW_FIRST
+        return check_hip(ctx, hipGetLastError(), "dwconv_first_kernel launch");
+    }
     if (!init && vec && vpl <= 4 && c.k >= 1 && c.k <= 3 && map_bytes > 0 && map_bytes <= kWsMaxBytes && in_bytes <= kWsMaxBytes &&
         w_bytes <= 64 * 1024) {
         const int vpl_used = vpl <= 1 ? 1 : (vpl <= 2 ? 2 : 4);
@@ -1146,7 +1270,7 @@ dcnn_status launch_fill_i32(dcnn_ctx* ctx, int32_t* p, int32_t v, int64_t n) {
 
 // A launch costs ~4 us whatever it clears, and a layer has up to five pieces: the table travels in the kernel's arguments
 // so that a network of 74 layers clears all of its pieces with three launches instead of 270 (first frame of the
-// ResNet-50-shaped network at 8 streams 3.56 -> TBD ms).  blockIdx.y: piece; blockIdx.x: a share of it.
+// ResNet-50-shaped network at 8 streams 3.55 -> 3.27 ms).  blockIdx.y: piece; blockIdx.x: a share of it.
 struct ClearTable {
     ClearPiece piece[kClearPieces];
 };

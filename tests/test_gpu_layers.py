@@ -163,7 +163,7 @@ def test_add_act(S, act, shape):
     eps = 0.4
     radd, ract = orc.Add(S), orc.ActTrunc(act, eps, S)
     ctx = pkg.Context(n * h * w)
-    layer = pkg.Layer(ctx, pkg.make_desc(pkg.ACT, DT[S], n, h, w, c, act=pkg.ACT_CODES[act], eps=eps, n_in=2))
+    layer = pkg.Layer(ctx, pkg.make_desc(pkg.ACT, DT[S], n, h, w, c, act=pkg.ACT_RELU if act == "relu" else pkg.ACT_NONE, eps=eps, n_in=2))
     a0 = rng.normal(0, 1, shape).astype(NP_DTYPE[S])
     b0 = rng.normal(0, 1, shape).astype(NP_DTYPE[S])
     r0 = radd.init(a0, b0)
@@ -833,3 +833,86 @@ def test_error_paths():
                                      act=pkg.ACT_RELU, eps=0.1),
                   torch.zeros((1, 1, 64, 2048), dtype=torch.float16, device="cuda"))
     assert e.value.status == 7
+
+
+@pytest.mark.parametrize("S,k,stride,cin,cout,nhw,mode", [
+    ("f16", 1, 1, 64, 64, (1, 8, 9), "plain"),           # 72 pixels: a tile and a remainder of 8
+    ("f16", 3, 1, 64, 200, (3, 17, 13), "act"),          # channel tile remainder, pixels over stream borders
+    ("f16", 3, 2, 256, 136, (2, 15, 15), "residual"),    # K-steps split over the waves, odd stride-2 border
+    ("f32", 3, 1, 64, 64, (1, 16, 5), "act"),            # fp32, split
+    ("f32", 7, 2, 8, 12, (1, 21, 19), "plain"),          # wide window, 12 channels
+    ("f16", 1, 1, 32, 256, (2, 12, 11), "projection"),   # second K loop, four channel tiles side by side
+    ("f32", 1, 1, 16, 64, (1, 9, 31), "projection"),
+])
+def test_first_frame_tiles(S, k, stride, cin, cout, nhw, mode):
+    """The dense first frame at the edges of its tiles (64 pixels x 64 channels, with and without split K), and the same
+    bits for a stream alone as in the batch."""
+    n, h, w = nhw
+    pad = k // 2
+    rng = np.random.default_rng(91)
+    dt = NP_DTYPE[S]
+    wgt = (rng.standard_normal((k, k, cin, cout)) * np.sqrt(2.0 / (k * k * cin))).astype(dt)
+    bias = rng.normal(0, 0.5, cout).astype(dt)
+    x = rng.standard_normal((n, h, w, cin)).astype(dt)
+    conv = orc.Conv(wgt, bias, stride, pad, False, S)
+    y = np.asarray(conv.init(x))
+    slack = sum_slack(conv, x, bias=True) + ulp(y, S)
+    oh, ow = y.shape[1:3]
+    second, w2, b2, proj = [], [], [], None
+    if mode == "residual":
+        second = [rng.standard_normal(y.shape).astype(dt)]
+        y = (y.astype(np.float64) + second[0].astype(np.float64)).astype(dt)
+    elif mode == "projection":
+        second = [rng.standard_normal((n, oh, ow, 24)).astype(dt)]
+        pw = (rng.standard_normal((1, 1, 24, cout)) * np.sqrt(2.0 / 24)).astype(dt)
+        pb = rng.normal(0, 0.5, cout).astype(dt)
+        pc = orc.Conv(pw, pb, 1, 0, False, S)
+        z = np.asarray(pc.init(second[0]))
+        slack = slack + sum_slack(pc, second[0], bias=True) + ulp(z, S)
+        y = (y.astype(np.float64) + z.astype(np.float64)).astype(dt)
+        w2, b2, proj = [pw.reshape(-1)], [pb], (24, oh, ow, 1)
+    act = "none" if mode == "plain" else "relu"
+    slack = slack + ulp(y, S)
+
+    def run(streams):
+        m = len(streams)
+        ctx = pkg.Context(m * max(h * w, oh * ow))
+        layer = pkg.Layer(ctx, pkg.make_desc(pkg.CONV, DT[S], m, h, w, cin, k=k, stride=stride, pad=pad, cout=cout,
+                                             act=pkg.ACT_RELU if act == "relu" else pkg.ACT_NONE, eps=0.05, n_in=1 + len(second), proj=proj),
+                          torch.from_numpy(np.concatenate([wgt.reshape(-1)] + w2)).cuda(),
+                          torch.from_numpy(np.concatenate([bias] + b2)).cuda())
+        out = layer.init([torch.from_numpy(np.ascontiguousarray(a[streams])).cuda() for a in [x] + second])
+        ctx.sync()
+        state = [to_np(layer.state_tensor(i)) for i in (0, 1)] if act == "relu" else []
+        return to_np(out), state
+
+    got, state = run(list(range(n)))
+    ref = np.maximum(y, dt(0)) if act == "relu" else y
+    assert rel_err(got, ref, slack=slack) <= TOL[S]
+    if act == "relu":
+        assert rel_err(state[0], y, slack=slack) <= TOL[S]
+        assert not state[1].any()
+    alone, _ = run([n - 1])
+    assert np.array_equal(alone[0], got[n - 1])
+
+
+@pytest.mark.parametrize("S", ["f32", "f16"])
+@pytest.mark.parametrize("k,stride,c,hw", [(3, 1, 16, (5, 7)), (3, 2, 200, (9, 6)), (2, 2, 8, (6, 6)), (1, 1, 24, (3, 1))])
+def test_depthwise_first_frame_pixel_groups(S, k, stride, c, hw):
+    """Four neighbouring pixels of the flat order per thread: groups that straddle rows and streams, and the last one."""
+    n, (h, w), pad = 3, hw, k // 2 if k == 3 else 0
+    rng = np.random.default_rng(17)
+    dt = NP_DTYPE[S]
+    wgt = rng.standard_normal((k, k, c)).astype(dt)
+    bias = rng.normal(0, 0.5, c).astype(dt)
+    x = rng.standard_normal((n, h, w, c)).astype(dt)
+    conv = orc.Conv(wgt, bias, stride, pad, True, S)
+    y = np.asarray(conv.init(x))
+    ctx = pkg.Context(n * h * w)
+    layer = pkg.Layer(ctx, pkg.make_desc(pkg.DWCONV, DT[S], n, h, w, c, k=k, stride=stride, pad=pad, cout=c,
+                                         act=pkg.ACT_RELU6, eps=0.05), torch.from_numpy(wgt).cuda(), torch.from_numpy(bias).cuda())
+    out = layer.init([torch.from_numpy(x).cuda()])
+    ctx.sync()
+    slack = sum_slack(conv, x, bias=True) + ulp(y, S)
+    assert rel_err(to_np(out), np.clip(y, dt(0), dt(6)), slack=slack) <= TOL[S]
+    assert rel_err(to_np(layer.state_tensor(0)), y, slack=slack) <= TOL[S]
