@@ -136,7 +136,37 @@ struct ListArgs {
     int64_t max_count;           // upper bound used to size the grid
     const uint32_t* taps;        // optional, per entry: bit t set iff window tap t of the entry's pixel is in
                                  // bounds and flagged in the input mask (written with the list by the mask pass)
+    // The kernel builds the list itself from the masks (self_list.h); list, count and taps are then null.
+    int self;
+    int want_taps;               // ... with the entries' tap words (bit 30: flagged in m_b)
+    const uint8_t* m_in;         // input mask [n, m_h, m_w]
+    const uint8_t* m_b;          // second mask, as in MaskPassArgs, or nullptr
+    int m_in_px, m_out_px, m_h, m_w, m_oh, m_ow, m_k, m_stride, m_pad, m_up;
+    int b_stride, b_h, b_w;
+    FastDiv div_ow, div_oh, div_iw, div_ih, div_up;
+    uint8_t* mask_out;           // what the kernel writes for others, each may be null: the flags of the list,
+    int32_t* idx_out;            // the ascending list,
+    int32_t* count_out;          // its length
+    int lds_scratch, lds_list;   // byte offsets into the kernel's dynamic LDS (set by the launchers)
+    int lds_entries;             // room for this many entries
 };
+
+// ---- work lists built by the kernel itself (host side; self_list.h has the device side) ---------------------------
+constexpr int64_t kListMaxPixels = 65536;    // mask_list_kernel: input and output pixels (positions are kept in 16 bits)
+// Layers whose own kernel builds the list: every workgroup repeats the work, which costs it 3-4 us up to 16 K pixels and 5-8
+// beyond, against ~6 us for a launch of mask_list_kernel and ~5 for a compaction of survivors.  (8 streams of a
+// four-resolution network: activation on 55 K pixels 16.1 us against 15.6 in two launches, on 13.8 K 11.8 against 19.6;
+// upsampling 20.0 against 11.5 and 9.0 against 15.1; a 1x1 layer on 32 K pixels of 256 channels 19.8 against 16.4.)
+constexpr int64_t kSelfMaxPixels = 16384;
+inline size_t self_scratch_bytes(int64_t in_px, int64_t out_px) {
+    return align_up(128 + 4 * (size_t)(2 * cdiv(in_px, 32) + cdiv(out_px, 32)) + 2 * (size_t)cdiv(out_px, 32), 16);
+}
+// entries of the groups that one workgroup of `grid` owns at most (tile ranges per XCD, or a plain stride over the grid)
+inline int64_t self_local_entries(int64_t out_px, int64_t entries_per_group, int grid, bool per_xcd) {
+    const int64_t groups = cdiv(out_px, entries_per_group);
+    const int64_t mine = per_xcd ? cdiv(cdiv(groups, kXcd), grid / kXcd) : cdiv(groups, grid);
+    return (mine < 1 ? 1 : mine) * entries_per_group;
+}
 
 // Statistics (never on a timed path): x^T rows a convolution that keeps row flags reads and writes in one step.
 // phase 0, before the step's kernel: before[j] = flag of list entry j's pixel, io[0] = their number (rows read);
@@ -175,6 +205,9 @@ bool conv_supported(const dcnn_ctx* ctx, int dtype, int k, int cin, int cout, in
 bool conv_ws_supported(const dcnn_ctx* ctx, int dtype, int k, int cin, int cout, int64_t in_elems, int64_t out_elems);
 bool conv_proj_supported(const dcnn_ctx* ctx, int dtype, int k, int cin, int cin2, int cout, int64_t in_elems,
                          int64_t in2_elems, int64_t out_elems);
+// Can the sparse steps of this convolution build their work list in the kernel?  (LDS room in every kernel that may serve them.)
+bool conv_self_fits(const dcnn_ctx* ctx, int dtype, int k, int cin, int cout, bool fused, int cin2, int64_t in_px, int64_t out_px,
+                    bool want_taps);
 size_t conv_proj_weight_bytes(int dtype, int k, int cin, int cin2, int cout);
 // Packs the projection's [cin2][cout] weights in the column grouping of the main convolution's plan.
 dcnn_status launch_pack_weights_proj(dcnn_ctx* ctx, int dtype, const void* w2, void* wpacked2, int k, int cin, int cin2,
@@ -188,6 +221,9 @@ dcnn_status launch_act(dcnn_ctx* ctx, int dtype, bool init, const ListArgs& l, c
                        const EpilogueArgs& e);
 dcnn_status launch_dwconv(dcnn_ctx* ctx, int dtype, bool init, const ListArgs& l, const ConvArgs& c,
                           const EpilogueArgs& e);
+// Do the sparse steps of such a layer run on a kernel that can build its work list?
+bool act_self_fits(int dtype, int channels, int64_t pixels);
+bool dwconv_self_fits(int dtype, int k, int channels, int64_t in_px, int64_t out_px);
 
 struct DeltaGenArgs {
     const void* frame;
@@ -200,6 +236,7 @@ struct DeltaGenArgs {
     int n, h, w, c;
     float eps;
     int dilate_r;
+    int mask_only;               // 1: nobody walks the list, only mask and values are written (dilate_r == 0)
 };
 dcnn_status launch_deltagen(dcnn_ctx* ctx, int dtype, const DeltaGenArgs& a);
 dcnn_status launch_copy(dcnn_ctx* ctx, void* dst, const void* src, size_t bytes);

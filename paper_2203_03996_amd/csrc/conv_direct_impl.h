@@ -16,6 +16,7 @@
 #pragma once
 
 #include "conv_plan.h"
+#include "self_list.h"
 
 namespace dcnn {
 
@@ -29,9 +30,9 @@ constexpr int kDirectWaves = 4;
 // first and the last column of a tile, whose neighbours sit in other tiles, fetch theirs, both through ONE extra load
 // per tile (the two edges are different lanes).  A third of the gather traffic of a kernel that L2 bounds, and the
 // weight operands of a row's three taps are multiplied with the same gathered registers.
-template <typename T, int NB, int KS, int TI, int D, bool ROW>
+template <typename T, int NB, int KS, int TI, int D, bool ROW, bool SELF>
 __device__ __forceinline__ void conv_direct_body(const ListArgs& l, const ConvArgs& c, const EpilogueArgs& e, int npass, int cs,
-                                                 int64_t count, unsigned char* smem) {
+                                                 int64_t count, unsigned char* smem, const SelfBits& sb) {
     typedef typename Mma<T>::Vec Vec;
     constexpr int V = Elem<T>::VEC;
     typedef typename RawOf<T, V>::type Raw;
@@ -44,6 +45,12 @@ __device__ __forceinline__ void conv_direct_body(const ListArgs& l, const ConvAr
     const int units_per_iter = NW / cs;                        // groups of TI tiles per workgroup iteration
     const int64_t ntiles = (count + kTile - 1) / kTile;
     const WgTileRange r = wg_tile_range((ntiles + units_per_iter * TI - 1) / (units_per_iter * TI));
+    const int32_t* self_px = reinterpret_cast<const int32_t*>(smem + l.lds_list);
+    const uint32_t* self_tap = reinterpret_cast<const uint32_t*>(smem + l.lds_list) + l.lds_entries;
+    const int group = units_per_iter * TI * kTile;
+    if constexpr (SELF)
+        self_emit<kDirectWaves * kWave>(l, sb, (int)count, SelfSpan{(int)r.begin, (int)r.end, (int)r.step, group},
+                                        const_cast<int32_t*>(self_px), const_cast<uint32_t*>(self_tap));
     if (r.begin >= r.end) return;
 
     const int lane = threadIdx.x % kWave;
@@ -73,22 +80,28 @@ __device__ __forceinline__ void conv_direct_body(const ListArgs& l, const ConvAr
         return ((int)n * c.h + oy * c.stride - c.pad) * c.w + ox * c.stride - c.pad;
     };
     auto tile_of = [&](int64_t wt, int ti) { return (wt * units_per_iter + slot) * TI + ti; };
-    auto entry = [&](int64_t wt, int ti) { return wt < r.end ? list_pixel(l.list, tile_of(wt, ti) * kTile + col, count) : -1; };
-    auto tap_word = [&](int64_t wt, int ti, int p32) -> uint32_t {
+    // (a list built here: round wt is group (wt - begin) / step of this workgroup's entries)
+    auto entry = [&](int64_t wt, int ti, int round) {
+        if (wt >= r.end) return -1;
+        return SELF ? self_px[round * group + (slot * TI + ti) * kTile + col] : list_pixel(l.list, tile_of(wt, ti) * kTile + col, count);
+    };
+    auto tap_word = [&](int64_t wt, int ti, int p32, int round) -> uint32_t {
+        if (SELF && l.want_taps) return self_tap[round * group + (slot * TI + ti) * kTile + col] & ((1u << (KS * KS)) - 1u);
         if (l.taps == nullptr) return p32 >= 0 ? 1u : 0u;      // a 1x1 layer on its input's own list: its one tap
         const int64_t j = tile_of(wt, ti) * kTile + col;
         return (wt < r.end && j < count) ? (l.taps[j] & ((1u << (KS * KS)) - 1u)) : 0u;
     };
 
     int survivors = 0;
-    for (int64_t wt = r.begin; wt < r.end; wt += r.step) {
+    int round = 0;
+    for (int64_t wt = r.begin; wt < r.end; wt += r.step, ++round) {
         int p32[TI];
         uint32_t tb[TI], base00[TI];
         uint32_t any = 0;
 #pragma unroll
         for (int ti = 0; ti < TI; ++ti) {
-            p32[ti] = entry(wt, ti);
-            tb[ti] = tap_word(wt, ti, p32[ti]);
+            p32[ti] = entry(wt, ti, round);
+            tb[ti] = tap_word(wt, ti, p32[ti], round);
             base00[ti] = (uint32_t)origin(p32[ti]) * (uint32_t)cin_bytes + (uint32_t)g * 16u;
             any |= tb[ti];
         }
@@ -279,12 +292,21 @@ __device__ __forceinline__ void conv_direct_body(const ListArgs& l, const ConvAr
 
 // Lists too short to keep the chip busy with TI tiles per wave run one tile per wave and a deeper ring instead
 // (more waves, more loads in flight); the length of the list is only known on the device.
-template <typename T, int NB, int KS, int TI>
+template <typename T, int NB, int KS, int TI, bool SELF>
 __global__ __launch_bounds__(kDirectWaves* kWave, 2) void conv_direct_kernel(ListArgs l, ConvArgs c, EpilogueArgs e, int npass, int cs,
                                                                              int blocked_min_tiles) {
     extern __shared__ __align__(16) unsigned char smem[];
     clear_ahead(e);
-    const int64_t count = list_count(l);
+    int64_t count;
+    SelfBits sb;
+    int nin = -1;                                              // flagged input pixels, if known
+    if constexpr (SELF) {
+        sb = self_carve(l, smem + l.lds_scratch);
+        count = self_build<kDirectWaves * kWave>(l, sb, &nin);
+    } else {
+        count = list_count(l);
+        if (c.in_count) nin = *c.in_count;
+    }
     if (count >= (int64_t)blocked_min_tiles * kTile) {
         if constexpr (KS == 3 && NB <= 2) {
             // Row gathers pay when most taps of the listed windows are flagged.  Every flagged input pixel is a tap
@@ -292,16 +314,15 @@ __global__ __launch_bounds__(kDirectWaves* kWave, 2) void conv_direct_kernel(Lis
             // per window.  Measured on 3x3 128->128, 256x256 maps, uniform-random masks: all taps flagged 0.40 ->
             // 0.30 ms, half of them 0.231 -> 0.243 ms, a tenth 0.127 -> 0.156 ms; hence three quarters.
             // (an input that comes without a count: the rule of the resident-weight kernel, most of the map listed)
-            const bool dense_taps = c.in_count ? (int64_t)*c.in_count * 4 >= count * 3
-                                               : count * 4 >= (int64_t)c.n * c.oh * c.ow * 3;
+            const bool dense_taps = nin >= 0 ? (int64_t)nin * 4 >= count * 3 : count * 4 >= (int64_t)c.n * c.oh * c.ow * 3;
             if (c.stride == 1 && c.pad == 1 && dense_taps) {
-                conv_direct_body<T, NB, KS, (TI > 3 ? 3 : TI), 2, true>(l, c, e, npass, cs, count, smem);   // 3 tiles: two operand sets of 12 vectors fit beside 96 accumulators
+                conv_direct_body<T, NB, KS, (TI > 3 ? 3 : TI), 2, true, SELF>(l, c, e, npass, cs, count, smem, sb);   // 3 tiles: two operand sets of 12 vectors fit beside 96 accumulators
                 return;
             }
         }
-        conv_direct_body<T, NB, KS, TI, 3, false>(l, c, e, npass, cs, count, smem);
+        conv_direct_body<T, NB, KS, TI, 3, false, SELF>(l, c, e, npass, cs, count, smem, sb);
     } else {
-        conv_direct_body<T, NB, KS, 1, (NB >= 4 ? 6 : 8), false>(l, c, e, npass, cs, count, smem);
+        conv_direct_body<T, NB, KS, 1, (NB >= 4 ? 6 : 8), false, SELF>(l, c, e, npass, cs, count, smem, sb);
     }
 }
 

@@ -47,8 +47,20 @@ __global__ __launch_bounds__(WMODE == 2 ? 256 : DCNN_CONV_BOUNDS) void conv_mfma
 
     const int nwaves = blockDim.x / kWave, nthreads = blockDim.x;
     const int tiles_per_iter = nwaves / cs;
-    const int64_t count = list_count(l);
+    constexpr int kThreads = WMODE == 2 ? 256 : DCNN_CONV_BOUNDS;   // (the launcher's block size)
+    const int32_t* self_px = reinterpret_cast<const int32_t*>(smem + l.lds_list);
+    int64_t count;
+    SelfBits sb;
+    if (l.self) {
+        sb = self_carve(l, smem + l.lds_scratch);
+        count = self_build<kThreads>(l, sb, nullptr);
+    } else {
+        count = list_count(l);
+    }
     const WgTileRange r = wg_tile_range((count + tiles_per_iter * kTile - 1) / (tiles_per_iter * kTile));
+    if (l.self)
+        self_emit<kThreads>(l, sb, (int)count, SelfSpan{(int)r.begin, (int)r.end, (int)r.step, tiles_per_iter * kTile},
+                            const_cast<int32_t*>(self_px), nullptr);
     if (r.begin >= r.end) return;                              // nothing for this workgroup: skip the weight load
 
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
@@ -129,14 +141,17 @@ __global__ __launch_bounds__(WMODE == 2 ? 256 : DCNN_CONV_BOUNDS) void conv_mfma
             }
         }
     };
-    auto entry = [&](int64_t wt_) {
-        return wt_ < r.end ? list_pixel(l.list, (wt_ * tiles_per_iter + slot) * kTile + col, count) : -1;
+    auto entry = [&](int64_t wt_, int round) {
+        if (wt_ >= r.end) return -1;
+        return l.self ? self_px[(round * tiles_per_iter + slot) * kTile + col]
+                      : list_pixel(l.list, (wt_ * tiles_per_iter + slot) * kTile + col, count);
     };
-    TileGeom g_next = geometry(entry(r.begin));
-    int p32_next2 = entry(r.begin + r.step);
+    TileGeom g_next = geometry(entry(r.begin, 0));
+    int p32_next2 = entry(r.begin + r.step, 1);
+    int round = 0;
     uint8_t flag_next[NFLAG];
     request_flags(g_next, flag_next);
-    for (int64_t wt = r.begin; wt < r.end; wt += r.step) {
+    for (int64_t wt = r.begin; wt < r.end; wt += r.step, ++round) {
         // ---- the tile: pixel of this lane's column, window origin, which taps are needed ---------
         // (pixel indices fit 31 bits; only the final element offset is 64-bit)
         const int64_t tile = wt * tiles_per_iter + slot;
@@ -160,7 +175,7 @@ __global__ __launch_bounds__(WMODE == 2 ? 256 : DCNN_CONV_BOUNDS) void conv_mfma
         }
         // requests for the tiles to come
         g_next = geometry(p32_next2);
-        p32_next2 = entry(wt + 2 * r.step);
+        p32_next2 = entry(wt + 2 * r.step, round + 2);
         request_flags(g_next, flag_next);
 
         // Wave-uniform cursor over groups of GK K-steps: tap t = (dy, dx), first K-step kc0 of the group.
@@ -413,8 +428,9 @@ __global__ __launch_bounds__(WMODE == 2 ? 256 : DCNN_CONV_BOUNDS) void conv_mfma
 }
 
 template <typename T, int NB>
-static dcnn_status launch_conv_nb(dcnn_ctx* ctx, bool init, const ListArgs& l, const ConvArgs& c, const EpilogueArgs& e,
+static dcnn_status launch_conv_nb(dcnn_ctx* ctx, bool init, const ListArgs& l_in, const ConvArgs& c, const EpilogueArgs& e,
                                   const ConvPlan& p) {
+    ListArgs l = l_in;
     constexpr int VEC = Elem<T>::VEC;
     const bool vec_out = (e.c % VEC) == 0;
     const bool aligned = ((size_t)c.cin * sizeof(T)) % 16 == 0;
@@ -445,6 +461,19 @@ static dcnn_status launch_conv_nb(dcnn_ctx* ctx, bool init, const ListArgs& l, c
     const int ini = init ? 1 : 0;
     hipError_t err = hipSuccess;
     bool launched = false;
+    // A list built by the kernel: its scratch memory shares the space from `shared` on (staging, not in use yet), its entries
+    // follow.  Returns the LDS size; the caller has made sure that it fits (conv_self_fits).
+    auto place_list = [&](size_t total, size_t shared, int64_t group, int g) -> size_t {
+        if (!l.self) return total;
+        const size_t scratch_end = shared + self_scratch_bytes(l.m_in_px, l.m_out_px);
+        const size_t at = align_up(total > scratch_end ? total : scratch_end, 16);
+        l.lds_scratch = (int)shared;
+        l.lds_list = (int)at;
+        l.lds_entries = (int)self_local_entries(l.m_out_px, group, g, true);
+        return at + (size_t)l.lds_entries * (l.want_taps ? 8 : 4);
+    };
+    const size_t shared_weights = p.stream || direct ? 0 : p.w_bytes;
+    const size_t plain_lds = place_list(lds_bytes, shared_weights, tiles_per_iter * kTile, grid);
 #define DCNN_CONV_LAUNCH(V, AL, WM, KS)                                                                          \
     do {                                                                                                         \
         auto kern = conv_mfma_kernel<T, NB, V, AL, WM, KS>;                                                      \
@@ -455,7 +484,7 @@ static dcnn_status launch_conv_nb(dcnn_ctx* ctx, bool init, const ListArgs& l, c
             attr_set = (err == hipSuccess);                                                                      \
         }                                                                                                        \
         if (err == hipSuccess)                                                                                   \
-            hipLaunchKernelGGL(kern, dim3(grid, grid_y), dim3(waves * kWave), lds_bytes, ctx->stream, l, c, e, ini, p.npass, p.cs, pass_split); \
+            hipLaunchKernelGGL(kern, dim3(grid, grid_y), dim3(waves * kWave), plain_lds, ctx->stream, l, c, e, ini, p.npass, p.cs, pass_split); \
         launched = true;                                                                                         \
     } while (0)
     // resident weights, vector-aligned channels, one pass, sparse step: the wave-specialised kernel
@@ -465,11 +494,11 @@ static dcnn_status launch_conv_nb(dcnn_ctx* ctx, bool init, const ListArgs& l, c
     const uint64_t in2_bytes = dual ? (uint64_t)c.n * c.h2 * c.w2 * c.cin2 * sizeof(T) : 0;
     const uint64_t out_bytes = (uint64_t)c.n * c.oh * c.ow * e.c * sizeof(T);
     // (a window wider than 1x1, or a 1x1 walk over a list that is not the input's own, needs the tap words)
-    const bool ws_taps = l.taps != nullptr || (c.k == 1 && c.stride == 1 && l.list != nullptr && c.in_mask != nullptr);
+    const bool ws_taps = l.self || l.taps != nullptr || (c.k == 1 && c.stride == 1 && l.list != nullptr && c.in_mask != nullptr);
     const bool ws_ok = vec_out && aligned && ws_lds != 0 && !init && ws_taps && in_bytes <= kWsMaxBytes &&
                        in2_bytes <= kWsMaxBytes && out_bytes <= kWsMaxBytes;
     const bool accum = e.accum_O != nullptr;
-    if (dual && (!ws_ok || l.taps == nullptr || e.res_data != nullptr || ((size_t)c.cin2 * sizeof(T)) % 16 != 0))
+    if (dual && (!ws_ok || !(l.taps != nullptr || (l.self && l.want_taps)) || e.res_data != nullptr || ((size_t)c.cin2 * sizeof(T)) % 16 != 0))
         return fail(ctx, DCNN_EUNSUPPORTED, "conv %dx%d %d->%d with a fused projection of %d channels: shape not covered", c.k,
                     c.k, c.cin, c.cout, c.cin2);
     if (accum && (!ws_ok || e.res_data != nullptr || e.act == DCNN_ACT_NONE))
@@ -482,9 +511,16 @@ static dcnn_status launch_conv_nb(dcnn_ctx* ctx, bool init, const ListArgs& l, c
         const int64_t ws_want = cdiv(l.max_count > 0 ? l.max_count : 1, (kWsProducers / p.cs) * kTile);
         const int64_t ws_cap = ctx->num_cu;                    // 16 waves of up to 128 registers fill a compute unit
         const int ws_grid = (int)(cdiv(ws_want < ws_cap ? ws_want : ws_cap, kXcd) * kXcd);
+        const size_t ws_w_bytes = p.w_bytes + (dual ? (size_t)c.kch2 * 2 * p.cout_pad * 16 : 0);
+        const size_t ws_all = place_list(ws_lds, ws_w_bytes, (kWsProducers / p.cs) * kTile, ws_grid);
+        if (ws_all > kLdsBytes) return fail(ctx, DCNN_EUNSUPPORTED, "conv: a work list built in place does not fit LDS");
 #define DCNN_WS_LAUNCH(KS, AUX, DUAL)                                                                            \
     do {                                                                                                         \
-        auto kern = conv_ws_kernel<T, NB, KS, AUX, DUAL>;                                                        \
+        if (l.self) DCNN_WS_LAUNCH_S(KS, AUX, DUAL, true); else DCNN_WS_LAUNCH_S(KS, AUX, DUAL, false);          \
+    } while (0)
+#define DCNN_WS_LAUNCH_S(KS, AUX, DUAL, SELF)                                                                    \
+    do {                                                                                                         \
+        auto kern = conv_ws_kernel<T, NB, KS, AUX, DUAL, SELF>;                                                        \
         static bool attr_set = false;                                                                            \
         if (!attr_set) {                                                                                         \
             err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, \
@@ -492,7 +528,7 @@ static dcnn_status launch_conv_nb(dcnn_ctx* ctx, bool init, const ListArgs& l, c
             attr_set = (err == hipSuccess);                                                                      \
         }                                                                                                        \
         if (err == hipSuccess)                                                                                   \
-            hipLaunchKernelGGL(kern, dim3(ws_grid), dim3(kWsWaves * kWave), ws_lds, ctx->stream, l, c, e, p.cs); \
+            hipLaunchKernelGGL(kern, dim3(ws_grid), dim3(kWsWaves * kWave), ws_all, ctx->stream, l, c, e, p.cs); \
     } while (0)
 #define DCNN_WS_PICK(KS)                                                                                         \
     do {                                                                                                         \
@@ -504,6 +540,7 @@ static dcnn_status launch_conv_nb(dcnn_ctx* ctx, bool init, const ListArgs& l, c
         if (c.k == 1) DCNN_WS_PICK(1); else DCNN_WS_PICK(3);
 #undef DCNN_WS_PICK
 #undef DCNN_WS_LAUNCH
+#undef DCNN_WS_LAUNCH_S
         if (err != hipSuccess) return check_hip(ctx, err, "hipFuncSetAttribute(conv_ws_kernel)");
         return check_hip(ctx, hipGetLastError(), "conv_ws_kernel launch");
     }
@@ -522,9 +559,18 @@ static dcnn_status launch_conv_nb(dcnn_ctx* ctx, bool init, const ListArgs& l, c
         const int blocked_min_tiles = (int)((int64_t)ctx->num_cu * 4 * TI / p.cs);
         const int64_t b_cap = (int64_t)ctx->num_cu * 2;        // 4 waves of up to 256 registers: two workgroups per compute unit
         const int b_grid = (int)(cdiv(b_want < b_cap ? b_want : b_cap, kXcd) * kXcd);
-#define DCNN_BLOCKED_LAUNCH(KS)                                                                                  \
+        // (the number of tiles per wave is chosen on the device: room for whichever groups give one workgroup the most entries)
+        int64_t b_group = 0, most = 0;
+        for (int ti = 1; ti <= TI; ++ti) {
+            const int64_t ge = (kDirectWaves / p.cs) * ti * kTile;
+            const int64_t ents = l.self ? self_local_entries(l.m_out_px, ge, b_grid, true) : 1;
+            if (ents > most) { most = ents; b_group = ge; }
+        }
+        const size_t b_all = place_list(b_lds, 0, b_group, b_grid);
+        if (b_all > kLdsBytes) return fail(ctx, DCNN_EUNSUPPORTED, "conv: a work list built in place does not fit LDS");
+#define DCNN_BLOCKED_LAUNCH(KS, SELF)                                                                            \
     do {                                                                                                         \
-        auto kern = conv_direct_kernel<T, NB, KS, TI>;                                                           \
+        auto kern = conv_direct_kernel<T, NB, KS, TI, SELF>;                                                           \
         static bool attr_set = false;                                                                            \
         if (!attr_set) {                                                                                         \
             err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, \
@@ -532,14 +578,16 @@ static dcnn_status launch_conv_nb(dcnn_ctx* ctx, bool init, const ListArgs& l, c
             attr_set = (err == hipSuccess);                                                                      \
         }                                                                                                        \
         if (err == hipSuccess)                                                                                   \
-            hipLaunchKernelGGL(kern, dim3(b_grid), dim3(kDirectWaves* kWave), b_lds, ctx->stream, l, c, e, p.npass, p.cs, \
+            hipLaunchKernelGGL(kern, dim3(b_grid), dim3(kDirectWaves* kWave), b_all, ctx->stream, l, c, e, p.npass, p.cs, \
                                blocked_min_tiles);                                                       \
     } while (0)
-        if (c.k == 1) DCNN_BLOCKED_LAUNCH(1); else DCNN_BLOCKED_LAUNCH(3);
+        if (c.k == 1) { if (l.self) DCNN_BLOCKED_LAUNCH(1, true); else DCNN_BLOCKED_LAUNCH(1, false); }
+        else { if (l.self) DCNN_BLOCKED_LAUNCH(3, true); else DCNN_BLOCKED_LAUNCH(3, false); }
 #undef DCNN_BLOCKED_LAUNCH
         if (err != hipSuccess) return check_hip(ctx, err, "hipFuncSetAttribute(conv_direct_kernel)");
         return check_hip(ctx, hipGetLastError(), "conv_direct_kernel launch");
     }
+    if (plain_lds > kLdsBytes) return fail(ctx, DCNN_EUNSUPPORTED, "conv: a work list built in place does not fit LDS");
     // instantiated combinations: the common case (16-byte aligned input pixels, vector-width output
     // channels) is specialised on the window size; odd shapes take the generic-window kernels
     if (vec_out && aligned) {

@@ -1,6 +1,7 @@
 // Host side of the convolution: plan queries, weight packing and dispatch to the per-variant
 // translation units (conv_inst.hip).
 #include "conv_ws_impl.h"
+#include "conv_direct_impl.h"
 
 namespace dcnn {
 
@@ -83,6 +84,27 @@ bool conv_proj_supported(const dcnn_ctx* ctx, int dtype, int k, int cin, int cin
     if (!p.ok || conv_ws_lds_bytes(p, dtype, k, cout, cin2) == 0) return false;
     const uint64_t lim = kWsMaxBytes / es;
     return (uint64_t)in_elems <= lim && (uint64_t)in2_elems <= lim && (uint64_t)out_elems <= lim;
+}
+
+bool conv_self_fits(const dcnn_ctx* ctx, int dtype, int k, int cin, int cout, bool fused, int cin2, int64_t in_px, int64_t out_px,
+                    bool want_taps) {
+    const ConvPlan p = conv_plan(dtype, k, cin, cout, fused);
+    if (!p.ok) return false;
+    const size_t scratch = self_scratch_bytes(in_px, out_px);
+    const int64_t cus = ctx->num_cu;
+    auto fits = [&](size_t own, size_t shared, int64_t group, int64_t grid_cap) {
+        const int64_t want = cdiv(out_px, group);
+        const int grid = (int)(cdiv(want < grid_cap ? want : grid_cap, kXcd) * kXcd);
+        const size_t at = align_up(own > shared + scratch ? own : shared + scratch, 16);
+        return at + (size_t)self_local_entries(out_px, group, grid, true) * (want_taps ? 8 : 4) <= kLdsBytes;
+    };
+    const size_t ws_lds = conv_ws_lds_bytes(p, dtype, k, cout, cin2);
+    const size_t ws_w = p.w_bytes + (size_t)cdiv(cin2, dtype == DCNN_F16 ? 16 : 8) * 2 * p.cout_pad * 16;
+    if (ws_lds != 0 && !fits(ws_lds, ws_w, (kWsProducers / p.cs) * kTile, cus)) return false;
+    const size_t direct_lds = conv_stage_bytes(kDirectWaves, p.nb, dtype) + conv_xchg_bytes(kDirectWaves);
+    for (int ti = 1; ti <= 4; ++ti)
+        if (!fits(direct_lds, 0, (kDirectWaves / p.cs) * ti * kTile, 2 * cus)) return false;
+    return fits(p.lds_bytes, p.stream ? 0 : p.w_bytes, (p.waves / p.cs) * kTile, cus);
 }
 
 size_t conv_proj_weight_bytes(int dtype, int k, int cin, int cin2, int cout) {

@@ -33,6 +33,7 @@
 #include <type_traits>
 
 #include "conv_plan.h"
+#include "self_list.h"
 
 namespace dcnn {
 
@@ -58,7 +59,8 @@ inline size_t conv_ws_lds_bytes(const ConvPlan& p, int dtype, int k, int cout, i
 
 // AUX: third per-pixel stream of the tail -- 0 none, 1 residual delta (added before the activation),
 // 2 dense accumulated output O of a final layer (O += emitted delta; the delta itself is not stored).
-template <typename T, int NB, int KS, int AUX, bool DUAL>
+// SELF: the kernel builds its work list (a compile-time variant: the code costs the others 3 % through their registers).
+template <typename T, int NB, int KS, int AUX, bool DUAL, bool SELF>
 __global__ __launch_bounds__(kWsWaves* kWave) void conv_ws_kernel(ListArgs l, ConvArgs c, EpilogueArgs e, int cs) {
     typedef typename Mma<T>::Vec Vec;
     constexpr int V = Elem<T>::VEC;
@@ -77,15 +79,18 @@ __global__ __launch_bounds__(kWsWaves* kWave) void conv_ws_kernel(ListArgs l, Co
     clear_ahead(e);
 
     const int tiles_per_iter = NP / cs;
-    const int64_t count = list_count(l);
-    const WgTileRange r = wg_tile_range((count + tiles_per_iter * kTile - 1) / (tiles_per_iter * kTile));
-    if (r.begin >= r.end) return;                              // nothing for this workgroup: skip the weight load
-    const int rounds = (int)((r.end - r.begin + r.step - 1) / r.step);
-
-    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-    const bool producer = wave < NP;
-    const int ww = producer ? wave : wave - NP;
-    const int slot = ww / cs, part = ww % cs;                  // which tile of the round; channel slice / pixel slice
+    // (a list built here: its scratch memory is the staging area, which nothing uses yet; the entries follow everything else)
+    const int32_t* self_px = reinterpret_cast<const int32_t*>(smem + l.lds_list);
+    const uint32_t* self_tap = reinterpret_cast<const uint32_t*>(smem + l.lds_list) + l.lds_entries;
+    int64_t count;
+    SelfBits sb;
+    SelfAhead ahead;
+    if constexpr (SELF) {
+        sb = self_carve(l, smem + l.lds_scratch);
+        self_request(l, ahead);
+    } else {
+        count = list_count(l);
+    }
     const int taps = KS * KS, kch = c.kch;
     const int ksteps = taps * kch;
     const int w1_vecs = cs * ksteps * 2 * COLS;
@@ -95,30 +100,6 @@ __global__ __launch_bounds__(kWsWaves* kWave) void conv_ws_kernel(ListArgs l, Co
     constexpr int stage_stride = COLS * ES + kStagePad;
     constexpr int stage_tile = kTile * stage_stride;
     unsigned char* stage0 = smem + (size_t)w_vecs * 16;        // [2][NP][32 pixels][stage_stride]
-    // Hand-over of result tiles.  A tile slot is the business of its cs producers and cs consumers only, so instead of
-    // a workgroup barrier per round (every wave waiting for the slowest of sixteen, round after round) each slot keeps
-    // two counters in LDS: `staged` (bumped by a producer once its slice of a tile is in the staging buffer) and
-    // `consumed` (bumped by a consumer once it has read its pixels of a tile).  A consumer starts tile r when staged
-    // >= cs*(r+1); a producer overwrites the buffer of tile r-2 when consumed >= cs*(r-1).  Tiles 0 and 1 need no
-    // wait, every wave bumps its counter once per tile, so by induction over r every wait ends; the poll limit only
-    // bounds the damage of a programming error (a kernel that gives wrong results instead of one that never ends).
-    uint32_t* staged_ctr = reinterpret_cast<uint32_t*>(stage0 + (size_t)2 * NP * stage_tile) + slot;
-    uint32_t* consumed_ctr = staged_ctr + kWsProducers;
-    auto bump = [&](uint32_t* ctr) {
-        // release at workgroup scope: this wave's LDS accesses so far are complete before the counter moves
-        if (lane == 0) __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-    };
-    auto await = [&](uint32_t* ctr, int target) {
-        if (target <= 0) return;
-        for (int spin = 0; spin < kWsSpinLimit; ++spin) {
-            if ((int)__hip_atomic_load(ctr, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) >= target) return;
-            __builtin_amdgcn_s_sleep(2);
-        }
-    };
-    // pixel of entry `j` of the work list of round `rd` (this wave's tile), -1 beyond the list
-    auto tile_of = [&](int rd) { return (r.begin + (int64_t)rd * r.step) * tiles_per_iter + slot; };
-    auto list_entry = [&](int rd, int j) { return rd < rounds ? list_pixel(l.list, tile_of(rd) * kTile + j, count) : -1; };
-
     // The weights travel global -> LDS once per workgroup.  Every wave calls this exactly once, right after it
     // has requested the list entries of its first tiles, so that round trip hides behind the copy.
     // Four loads are in flight per lane before the first is stored: the copy costs a couple of memory round trips
@@ -144,6 +125,49 @@ __global__ __launch_bounds__(kWsWaves* kWave) void conv_ws_kernel(ListArgs l, Co
         if constexpr (DUAL) copy_weights(static_cast<const Vec*>(c.wpacked2), w_lds + w1_vecs, w2_vecs);
         if (threadIdx.x < 2 * kWsProducers) reinterpret_cast<uint32_t*>(stage0 + (size_t)2 * NP * stage_tile)[threadIdx.x] = 0u;
         lds_block_sync();
+    };
+
+    if constexpr (SELF) {
+        // (fetching the weights together with the mask was measured: every workgroup then fetches them, also those that turn
+        // out to have no tile, and a one-stream step went from 49.7 to 53.0 us)
+        count = self_build<kWsWaves * kWave>(l, sb, nullptr, &ahead);
+    }
+    const WgTileRange r = wg_tile_range((count + tiles_per_iter * kTile - 1) / (tiles_per_iter * kTile));
+    if constexpr (SELF)
+        self_emit<kWsWaves * kWave>(l, sb, (int)count, SelfSpan{(int)r.begin, (int)r.end, (int)r.step, tiles_per_iter * kTile},
+                                    const_cast<int32_t*>(self_px), const_cast<uint32_t*>(self_tap));
+    if (r.begin >= r.end) return;                              // nothing for this workgroup: skip the weight load
+    const int rounds = (int)((r.end - r.begin + r.step - 1) / r.step);
+
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    const bool producer = wave < NP;
+    const int ww = producer ? wave : wave - NP;
+    const int slot = ww / cs, part = ww % cs;                  // which tile of the round; channel slice / pixel slice
+    // Hand-over of result tiles.  A tile slot is the business of its cs producers and cs consumers only, so instead of
+    // a workgroup barrier per round (every wave waiting for the slowest of sixteen, round after round) each slot keeps
+    // two counters in LDS: `staged` (bumped by a producer once its slice of a tile is in the staging buffer) and
+    // `consumed` (bumped by a consumer once it has read its pixels of a tile).  A consumer starts tile r when staged
+    // >= cs*(r+1); a producer overwrites the buffer of tile r-2 when consumed >= cs*(r-1).  Tiles 0 and 1 need no
+    // wait, every wave bumps its counter once per tile, so by induction over r every wait ends; the poll limit only
+    // bounds the damage of a programming error (a kernel that gives wrong results instead of one that never ends).
+    uint32_t* staged_ctr = reinterpret_cast<uint32_t*>(stage0 + (size_t)2 * NP * stage_tile) + slot;
+    uint32_t* consumed_ctr = staged_ctr + kWsProducers;
+    auto bump = [&](uint32_t* ctr) {
+        // release at workgroup scope: this wave's LDS accesses so far are complete before the counter moves
+        if (lane == 0) __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    auto await = [&](uint32_t* ctr, int target) {
+        if (target <= 0) return;
+        for (int spin = 0; spin < kWsSpinLimit; ++spin) {
+            if ((int)__hip_atomic_load(ctr, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) >= target) return;
+            __builtin_amdgcn_s_sleep(2);
+        }
+    };
+    // pixel of entry `j` of the work list of round `rd` (this wave's tile), -1 beyond the list
+    auto tile_of = [&](int rd) { return (r.begin + (int64_t)rd * r.step) * tiles_per_iter + slot; };
+    auto list_entry = [&](int rd, int j) {
+        if (rd >= rounds) return -1;
+        return SELF ? self_px[(rd * tiles_per_iter + slot) * kTile + j] : list_pixel(l.list, tile_of(rd) * kTile + j, count);
     };
 
     // The only workgroup barrier is the one behind the weight copy; after it the roles meet through the counters.
@@ -191,7 +215,8 @@ __global__ __launch_bounds__(kWsWaves* kWave) void conv_ws_kernel(ListArgs l, Co
         const int kgroups2 = DUAL ? (c.kch2 + GK - 1) / GK : 1;
         (void)rs_in2; (void)cin2_bytes; (void)origin2; (void)kgroups2;
         auto tap_word = [&](int rd, int p32) -> uint32_t {
-            if (l.taps == nullptr) return p32 >= 0 ? 1u : 0u;
+            if (SELF ? !l.want_taps : l.taps == nullptr) return p32 >= 0 ? 1u : 0u;
+            if (SELF) return rd < rounds ? self_tap[(rd * tiles_per_iter + slot) * kTile + col] : 0u;
             const int64_t j = tile_of(rd) * kTile + col;
             return (rd < rounds && j < count) ? l.taps[j] : 0u;
         };

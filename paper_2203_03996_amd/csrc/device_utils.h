@@ -515,6 +515,10 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t ws_rsrc(const void* p, uint64_
     // raw buffer (stride 0), 32-bit data format; a null pointer gives an empty range
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, p ? (int)bytes : 0, 0x00020000);
 }
+// (the second form adds a wave-uniform offset that lives in a scalar register)
+template <typename Raw> __device__ __forceinline__ Raw ws_load16(__amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t uniform) {
+    return __builtin_bit_cast(Raw, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, (int)uniform, 0));
+}
 template <typename Raw> __device__ __forceinline__ Raw ws_load16(__amdgpu_buffer_rsrc_t r, uint32_t off) {
     return __builtin_bit_cast(Raw, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
 }

@@ -14,6 +14,8 @@ struct dcnn_layer {
     bool inited;
     bool alias_mask;            // output mask / index list are those of input 0
     bool has_bias;
+    bool self = false;          // sparse steps build their work list in the layer's own kernel (self_list.h)
+    bool skip_list = false;     // input layer of a network in which nobody walks its list: only the mask is written
     bool has_bias2 = false;     // bias of the fused projection
     size_t state_bytes;
     // pieces of the caller-provided state memory
@@ -54,7 +56,11 @@ namespace dcnn {
 // dcnn_layer_create with the weights and bias of a fused projection passed on their own.
 dcnn_status layer_create(dcnn_ctx* ctx, const dcnn_layer_desc* desc, const void* weights_dev, const void* bias_dev,
                          const void* proj_weights_dev, const void* proj_bias_dev, void* state_dev, size_t state_bytes,
-                         dcnn_layer** out);
+                         bool self, dcnn_layer** out);
+// Can the layer's sparse steps build their work list in their own kernel, so that nobody has to hand one over?  `walker`:
+// also if the layer would otherwise walk its input's list.  (Not if the ordered list of the pixels that stayed flagged
+// is wanted: that is compacted from a stored list.)
+bool layer_lists_itself(const dcnn_ctx* ctx, const dcnn_layer_desc& d, bool walker);
 // dcnn_layer_init; with clear = false the caller has cleared the layer's pieces (collect_clears) itself.
 dcnn_status layer_init(dcnn_layer* L, const void* const* dense_in, int32_t n_in, void* dense_out, bool clear);
 // The pieces of the layer's state that are zero before its first sparse step: masks, counts, x^T row flags.

@@ -61,6 +61,29 @@ static dcnn_status out_shape(const dcnn_layer_desc& d, int* oh, int* ow, int* oc
     }
 }
 
+bool layer_lists_itself(const dcnn_ctx* ctx, const dcnn_layer_desc& d, bool walker) {
+    const bool own = own_list(d), act = has_act(d);
+    if ((!own && !walker) || (act && d.want_idx)) return false;
+    int oh, ow, oc;
+    if (out_shape(d, &oh, &ow, &oc) != DCNN_OK) return false;
+    const int64_t in_px = (int64_t)d.n * d.h * d.w, out_px = (int64_t)d.n * oh * ow;
+    if (in_px > kSelfMaxPixels || out_px > kSelfMaxPixels) return false;
+    // windows that work on whole words of flags (1x1, 3x3 with padding 1); any other is tested pixel by pixel and is
+    // worth it on small maps only
+    auto window = [&]() {
+        if ((d.kh == 1 && d.pad == 0) || (d.kh == 3 && d.pad == 1)) return true;
+        return out_px * d.kh <= 12288;
+    };
+    switch (d.kind) {
+        case DCNN_CONV:
+            return window() && conv_self_fits(ctx, d.dtype, d.kh, d.c, oc, act, d.proj_c, in_px, out_px, own && (d.kh == 1 || d.kh == 3));
+        case DCNN_DWCONV: return own && window() && dwconv_self_fits(d.dtype, d.kh, oc, in_px, out_px);
+        case DCNN_ACT: return act_self_fits(d.dtype, oc, out_px);
+        case DCNN_UPSAMPLE: return d.factor > 1;
+        default: return false;
+    }
+}
+
 static dcnn_status validate_desc(const dcnn_layer_desc& d) {
     if (d.kind < DCNN_DELTAGEN || d.kind > DCNN_GAVGPOOL) return DCNN_EINVAL;
     if (d.dtype != DCNN_F32 && d.dtype != DCNN_F16) return DCNN_EDTYPE;
@@ -166,7 +189,9 @@ static void carve(dcnn_layer* L, void* state) {
             // A convolution or activation that walks its input's own list and truncates needs an output mask that is 0
             // wherever it does not write.  Instead of a mask pass per step it alternates between two masks, and
             // its kernel clears the one of the next step while it runs (clear_ahead).
-            if (act && !own && (d.kind == DCNN_CONV || d.kind == DCNN_ACT))
+            // So does a layer that builds its list in its own kernel (which of the layers with a list of their own do is
+            // decided when the layer is created; the memory is there for all that could).
+            if (act && (own ? !d.want_idx : d.kind != DCNN_DWCONV))
                 L->out_mask_alt = static_cast<uint8_t*>(cv.take((size_t)L->out_pixels));
         }
         if (own) {
@@ -271,7 +296,8 @@ dcnn_status dcnn_layer_create(dcnn_ctx* ctx, const dcnn_layer_desc* desc, const 
         w2 = static_cast<const char*>(weights_dev) + (size_t)desc->kh * desc->kh * desc->c * desc->cout * es;
         if (bias_dev) b2 = static_cast<const char*>(bias_dev) + (size_t)desc->cout * es;
     }
-    return dcnn::layer_create(ctx, desc, weights_dev, bias_dev, w2, b2, state_dev, state_bytes, out);
+    const bool self = validate_desc(*desc) == DCNN_OK && layer_lists_itself(ctx, *desc, false);
+    return dcnn::layer_create(ctx, desc, weights_dev, bias_dev, w2, b2, state_dev, state_bytes, self, out);
 }
 
 }  // extern "C"
@@ -280,7 +306,7 @@ namespace dcnn {
 
 dcnn_status layer_create(dcnn_ctx* ctx, const dcnn_layer_desc* desc, const void* weights_dev, const void* bias_dev,
                          const void* proj_weights_dev, const void* proj_bias_dev, void* state_dev, size_t state_bytes,
-                         dcnn_layer** out) {
+                         bool self, dcnn_layer** out) {
     *out = nullptr;
     dcnn_status st = validate_desc(*desc);
     if (st != DCNN_OK) return fail(ctx, st, "layer_create: invalid descriptor (kind %d)", desc->kind);
@@ -294,6 +320,7 @@ dcnn_status layer_create(dcnn_ctx* ctx, const dcnn_layer_desc* desc, const void*
     L->in_pixels = (int64_t)desc->n * desc->h * desc->w;
     L->out_pixels = (int64_t)desc->n * L->oh * L->ow;
     L->inited = false;
+    L->self = self;
     carve(L, state_dev);
     if (L->state_bytes > state_bytes) {
         st = fail(ctx, DCNN_ENOMEM, "layer_create: state memory of %zu bytes, need %zu", state_bytes, L->state_bytes);
@@ -521,7 +548,7 @@ dcnn_status dcnn_layer_step(dcnn_layer* L, const dcnn_delta* const* in, int32_t 
     const int want_in = d.kind == DCNN_DELTAGEN ? 1 : d.n_in;
     if (!in || n_in != want_in) return fail(ctx, DCNN_EINVAL, "step: expected %d inputs, got %d", want_in, n_in);
     const bool act = has_act(d), own = own_list(d);
-    dcnn_status st = check_input(L, in[0], 0, d.h, d.w, d.c, !own || d.kind == DCNN_MAXPOOL);
+    dcnn_status st = check_input(L, in[0], 0, d.h, d.w, d.c, (!own && !L->self) || d.kind == DCNN_MAXPOOL);
     if (st != DCNN_OK) return st;
     if (n_in == 2) {
         st = has_proj(d) ? check_input(L, in[1], 1, d.proj_h, d.proj_w, d.proj_c, false)
@@ -538,8 +565,9 @@ dcnn_status dcnn_layer_step(dcnn_layer* L, const dcnn_delta* const* in, int32_t 
     v.n = d.n; v.h = L->oh; v.w = L->ow; v.c = L->oc; v.dtype = d.dtype;
     v.data = d.fuse_accum ? L->buf2 : L->out_data;
     // (a layer with two output masks: this step writes one, which is all zero, and clears the other for the next step)
-    uint8_t* const mask_cur = (L->out_mask_alt && L->mask_phase) ? L->out_mask_alt : L->out_mask;
-    uint8_t* const mask_next = L->out_mask_alt ? (L->mask_phase ? L->out_mask : L->out_mask_alt) : nullptr;
+    const bool alternates = L->out_mask_alt && (!own || L->self);
+    uint8_t* const mask_cur = (alternates && L->mask_phase) ? L->out_mask_alt : L->out_mask;
+    uint8_t* const mask_next = alternates ? (L->mask_phase ? L->out_mask : L->out_mask_alt) : nullptr;
     v.mask = L->alias_mask ? in[0]->mask : mask_cur;
     v.idx = L->alias_mask ? in[0]->idx : L->out_idx;
     // A layer with an activation whose output list nobody walks (want_idx == 0) does not count its flagged outputs:
@@ -556,8 +584,10 @@ dcnn_status dcnn_layer_step(dcnn_layer* L, const dcnn_delta* const* in, int32_t 
         a.frame = in[0]->data; a.P = L->buf0; a.out_data = L->out_data; a.out_mask = L->out_mask;
         a.out_idx = L->out_idx; a.out_count = L->out_count; a.pixels = L->in_pixels;
         a.n = d.n; a.h = d.h; a.w = d.w; a.c = d.c; a.eps = d.eps; a.dilate_r = d.dilate_r;
+        a.mask_only = L->skip_list ? 1 : 0;
+        if (L->skip_list) v.count = nullptr;
         L->last_in_count = nullptr;
-        L->last_work_count = L->out_count;
+        L->last_work_count = L->skip_list ? nullptr : L->out_count;
         // optional timing: the generation pass together with the list emission that belongs to it
         const bool timed_gen = L->events_used < L->events.size();
         if (timed_gen) {
@@ -575,10 +605,33 @@ dcnn_status dcnn_layer_step(dcnn_layer* L, const dcnn_delta* const* in, int32_t 
     // ---- work list -----------------------------------------------------------------------------
     ListArgs l{};
     l.max_count = L->out_pixels;
-    if (own) {
+    // (16-byte loads of the masks; the statistics mode wants a list in memory)
+    const bool masks_aligned = (reinterpret_cast<uintptr_t>(in[0]->mask) | reinterpret_cast<uintptr_t>(n_in == 2 ? in[1]->mask : nullptr)) % 16 == 0;
+    const bool self = L->self && masks_aligned && !(L->counting && L->xt_flags);
+    if (self) {
+        l.self = 1;
+        l.want_taps = own && d.kind == DCNN_CONV && (d.kh == 1 || d.kh == 3);
+        l.m_in = in[0]->mask; l.m_b = n_in == 2 ? in[1]->mask : nullptr;
+        l.m_in_px = (int)L->in_pixels; l.m_out_px = (int)L->out_pixels;
+        l.m_h = d.h; l.m_w = d.w; l.m_oh = L->oh; l.m_ow = L->ow;
+        l.m_k = 1; l.m_stride = 1; l.m_pad = 0; l.m_up = 1;
+        if (d.kind == DCNN_CONV || d.kind == DCNN_DWCONV) { l.m_k = d.kh; l.m_stride = d.stride; l.m_pad = d.pad; }
+        if (d.kind == DCNN_UPSAMPLE) l.m_up = d.factor;
+        if (has_proj(d) && !(d.proj_stride == 1 && d.proj_h == L->oh && d.proj_w == L->ow)) {
+            l.b_stride = d.proj_stride; l.b_h = d.proj_h; l.b_w = d.proj_w;
+        }
+        l.div_ow = make_fastdiv((uint32_t)L->ow); l.div_oh = make_fastdiv((uint32_t)L->oh);
+        l.div_iw = make_fastdiv((uint32_t)d.w); l.div_ih = make_fastdiv((uint32_t)d.h);
+        l.div_up = make_fastdiv((uint32_t)l.m_up);
+        if (!act && own) { l.mask_out = L->out_mask; l.idx_out = L->out_idx; l.count_out = L->out_count; }
+        else if (act) l.count_out = own ? L->list_count : L->out_count;       // the list's length, for the statistics
+    } else if (own || L->self) {
+        // (a layer that would build its list itself but has to have one in memory this time: its own output list serves,
+        // nobody walks that)
         MaskPassArgs m{};
         m.mask_in = in[0]->mask; m.mask_b = n_in == 2 ? in[1]->mask : nullptr;
-        m.mask_out = L->out_mask; m.idx_out = L->list; m.count_out = L->list_count;
+        m.mask_out = alternates ? nullptr : L->out_mask;
+        m.idx_out = own ? L->list : L->out_idx; m.count_out = own ? L->list_count : L->out_count;
         m.n = d.n; m.h = d.h; m.w = d.w; m.oh = L->oh; m.ow = L->ow;
         m.k = 1; m.stride = 1; m.pad = 0; m.up = 1; m.emit_only = 0;
         m.zero_count = nullptr;
@@ -591,7 +644,7 @@ dcnn_status dcnn_layer_step(dcnn_layer* L, const dcnn_delta* const* in, int32_t 
         }
         st = launch_mask_compact(ctx, m);
         if (st != DCNN_OK) return st;
-        l.list = L->list; l.count = L->list_count; l.taps = L->taps;
+        l.list = m.idx_out; l.count = m.count_out; l.taps = own ? L->taps : nullptr;
     } else {
         l.list = in[0]->idx; l.count = in[0]->count;
         if (act && !mask_next) {
@@ -604,7 +657,7 @@ dcnn_status dcnn_layer_step(dcnn_layer* L, const dcnn_delta* const* in, int32_t 
             if (st != DCNN_OK) return st;
         }
     }
-    L->last_work_count = l.count;
+    L->last_work_count = self ? l.count_out : l.count;
 
     // ---- compute -------------------------------------------------------------------------------
     const bool timed = L->events_used < L->events.size();
@@ -759,7 +812,8 @@ dcnn_status dcnn_layer_stats(dcnn_layer* L, dcnn_stats* s) {
     s->pixels_in_total = L->in_pixels;
     s->pixels_in2_total = L->d.n_in == 2 ? (L->d.proj_c > 0 ? (int64_t)L->d.n * L->d.proj_h * L->d.proj_w : L->out_pixels) : 0;
     // an update that comes without a count (see dcnn_layer_step): its mask is counted here, off every step's path
-    int32_t* scratch = L->out_count ? L->out_count + kStatsScratchOffset : nullptr;
+    // (a layer that forwards its input's mask has no such place of its own: the workspace, which is idle here)
+    int32_t* scratch = L->out_count ? L->out_count + kStatsScratchOffset : reinterpret_cast<int32_t*>(ctx->ws);
     auto read_or_count = [&](const int32_t* p, const uint8_t* mask, int64_t pixels, int64_t* dst) -> dcnn_status {
         if (p || !mask || !scratch) return read(p, dst);
         dcnn_status r = launch_mask_sum(ctx, mask, pixels, scratch);
@@ -769,7 +823,9 @@ dcnn_status dcnn_layer_stats(dcnn_layer* L, dcnn_stats* s) {
     st = read_or_count(L->last_in_count, L->last_in_mask, s->pixels_in_total, &s->pixels_in);
     if (st == DCNN_OK) st = read_or_count(L->last_in2_count, L->last_in2_mask, s->pixels_in2_total, &s->pixels_in2);
     if (st == DCNN_OK) st = read(L->last_work_count, &s->pixels_work);
+    if (L->self && L->last_work_count == nullptr) s->pixels_work = s->pixels_in;   // a list nobody stored: the input's own
     if (st == DCNN_OK) st = read_or_count(L->view.count, L->view.mask, L->out_pixels, &s->pixels_out);
+    if (L->skip_list) s->pixels_work = s->pixels_out;
     s->kind = L->d.kind; s->act = L->d.act; s->n_in = L->d.n_in;
     s->c_in = L->d.c; s->c_out = L->oc;
     const bool window = L->d.kind == DCNN_CONV || L->d.kind == DCNN_DWCONV || L->d.kind == DCNN_MAXPOOL;

@@ -9,6 +9,7 @@
 //              flagged, so the convolution does not have to test the window again.
 // emit_sublist: list space; keeps the entries of a work list whose survivor bit is set.
 #include "device_utils.h"
+#include "self_list.h"
 
 namespace dcnn {
 
@@ -465,6 +466,53 @@ __global__ __launch_bounds__(kMaskThreads) void mask_emit_kernel(MaskKernelArgs 
     if (total != 0) emit_entries(e, p0, word, prefix + loc, er);
 }
 
+// ---- lists of maps of up to 64 K pixels in one launch -------------------------------------------------------------------
+// Every workgroup forms ALL flags of the map as bits in LDS (self_list.h: the mask is at most 64 KB of bytes, the rest works
+// on whole words) and knows the list position of every pixel, so it writes its share of mask, list and tap words without
+// waiting for anybody.  Against the two passes (or the one of a single chunk): one launch instead of two.
+constexpr int kListThreads = 1024;
+constexpr int kListShare = 64;                                 // words of flags per workgroup
+__global__ __launch_bounds__(kListThreads) void mask_list_kernel(ListArgs l, uint32_t* taps_out) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    SelfAhead ahead;
+    self_request(l, ahead);
+    const SelfBits s = self_carve(l, smem);
+    const int count = self_build<kListThreads>(l, s, nullptr, &ahead);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *l.count_out = count;
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    const int w_end = min(((int)blockIdx.x + 1) * kListShare, s.out_words);
+    if (l.mask_out != nullptr) {
+        for (int i = (int)blockIdx.x * kListShare * 8 + (int)threadIdx.x; i < w_end * 8; i += kListThreads) {    // four pixels each
+            const uint32_t f = (s.obits[i / 8] >> (4 * (i % 8))) & 15u;
+            const uint32_t v = (f & 1u) | (f & 2u) << 7 | (f & 4u) << 14 | (f & 8u) << 21;
+            if (i * 4 + 4 <= l.m_out_px) *reinterpret_cast<uint32_t*>(l.mask_out + i * 4) = v;
+            else for (int k = 0; i * 4 + k < l.m_out_px; ++k) l.mask_out[i * 4 + k] = (uint8_t)((f >> k) & 1u);
+        }
+    }
+    // two words of flags per wave and step, a pixel per lane
+    for (int w0 = (int)blockIdx.x * kListShare + 2 * wave; w0 < w_end; w0 += 2 * kListThreads / kWave) {
+        const int w = w0 + lane / 32;
+        if (w >= w_end) continue;
+        const uint32_t bits = s.obits[w];
+        if (!((bits >> (lane & 31)) & 1u)) continue;
+        const int j = (int)s.prefix[w] + __popc(bits & ((1u << (lane & 31)) - 1u)), p = w * 32 + (lane & 31);
+        l.idx_out[j] = p;
+        if (taps_out != nullptr) {
+            uint32_t t = self_taps(l, s.ibits, s.in_words, p);
+            if (l.m_b != nullptr && self_b_flag(l, p)) t |= 1u << 30;
+            taps_out[j] = t;
+        }
+    }
+}
+
+static bool list_kernel_serves(const MaskPassArgs& m, int64_t in_px, int64_t out_px) {
+    if (m.emit_only || m.idx_out == nullptr || m.kw > 0 || in_px > kListMaxPixels || out_px > kListMaxPixels) return false;
+    if (m.up > 1) { if (m.bilinear || m.mask_b != nullptr) return false; }
+    else if (m.stride > 2 || !((m.k == 1 && m.pad == 0) || (m.k == 3 && m.pad == 1))) return false;
+    if (m.b_stride > 0 && out_px > kSelfMaxPixels) return false;        // (sampled pixel by pixel by every workgroup)
+    return (reinterpret_cast<uintptr_t>(m.mask_in) | reinterpret_cast<uintptr_t>(m.mask_b) | reinterpret_cast<uintptr_t>(m.mask_out)) % 16 == 0;
+}
+
 // The pass on explicit scratch memory: ws.chunk_counts (one int per chunk; every entry the list emission reads
 // has been written by the mask pass of the same call, nothing has to start at zero) and ws.scratch_mask (the
 // output mask when the caller does not want one).
@@ -473,6 +521,21 @@ static dcnn_status mask_compact_on(dcnn_ctx* ctx, const MaskPassArgs& m, const W
     dcnn_status st = DCNN_OK;
     const int nchunks = (int)cdiv(out_pixels, kChunk);
     const uint8_t* emit_mask = m.mask_in;
+    const int64_t in_px = (int64_t)m.n * m.h * m.w;
+    if (list_kernel_serves(m, in_px, out_pixels)) {
+        ListArgs l{};
+        l.m_in = m.mask_in; l.m_b = m.mask_b; l.m_in_px = (int)in_px; l.m_out_px = (int)out_pixels;
+        l.m_h = m.h; l.m_w = m.w; l.m_oh = m.oh; l.m_ow = m.ow;
+        l.m_k = m.k; l.m_stride = m.stride; l.m_pad = m.pad; l.m_up = m.up > 1 ? m.up : 1;
+        l.b_stride = m.b_stride; l.b_h = m.b_h; l.b_w = m.b_w;
+        l.div_ow = make_fastdiv((uint32_t)m.ow); l.div_oh = make_fastdiv((uint32_t)m.oh);
+        l.div_iw = make_fastdiv((uint32_t)m.w); l.div_ih = make_fastdiv((uint32_t)m.h);
+        l.div_up = make_fastdiv((uint32_t)l.m_up);
+        l.mask_out = m.mask_out; l.idx_out = m.idx_out; l.count_out = m.count_out;
+        hipLaunchKernelGGL(mask_list_kernel, dim3((unsigned)cdiv(out_pixels, 32 * kListShare)), dim3(kListThreads),
+                           self_scratch_bytes(in_px, out_pixels), ctx->stream, l, m.up > 1 ? nullptr : m.taps_out);
+        return check_hip(ctx, hipGetLastError(), "mask_list_kernel launch");
+    }
     // one launch for small maps; large maps keep the two passes
     const bool fused = !m.emit_only && m.idx_out != nullptr && nchunks <= kFusedMaxChunks;
     MaskKernelArgs a{};

@@ -30,6 +30,8 @@ struct Planned {
     const void* b2;
     size_t state_off, state_bytes;
     dcnn_layer* layer;
+    bool self = false;              // the layer's kernel builds its work list (layer_lists_itself)
+    bool skip_list = false;         // input layer whose list nobody walks
     int lane = 0;                   // which of the network's streams runs the layer (0: the context's own)
     hipEvent_t done = nullptr;      // recorded behind the layer when a layer on another lane consumes its output
 };
@@ -320,13 +322,21 @@ dcnn_status dcnn_net_finalize(dcnn_net* net, int32_t fuse, size_t* arena_bytes) 
             if (net->layer_of_node[in] < 0) return fail(ctx, DCNN_EINVAL, "net_finalize: internal: node %d was fused away but is still consumed", in);
     // which outputs need an index list: consumers that walk their input's list as it is
     for (auto& p : net->plan) p.d.want_idx = (fuse & 2) ? 1 : 0;
-    for (auto& p : net->plan) {
-        if (p.in_nodes.empty()) continue;
+    // (from the back: a layer's own want_idx is final once its consumers have been seen.  On small maps a layer's kernel
+    // builds its list from the masks and needs nobody's; a stateless 1x1 convolution hands its input's list on to
+    // whoever walks it.)
+    for (size_t a = net->plan.size(); a-- > 0;) {
+        Planned& p = net->plan[a];
         const dcnn_layer_desc& d = p.d;
-        const bool walks_input_list = d.kind == DCNN_ACCUM || d.kind == DCNN_MAXPOOL ||
-                                      (is_conv(d) && d.kh == 1 && d.stride == 1 && d.n_in == 1) ||
-                                      (d.kind == DCNN_ACT && d.n_in == 1);
-        if (walks_input_list) net->plan[net->layer_of_node[p.in_nodes[0]]].d.want_idx = 1;
+        p.self = layer_lists_itself(ctx, d, true);
+        if (p.in_nodes.empty()) {
+            p.skip_list = d.kind == DCNN_DELTAGEN && d.dilate_r == 0 && !d.want_idx;
+            continue;
+        }
+        const bool walker_conv = is_conv(d) && d.kh == 1 && d.stride == 1 && d.n_in == 1;
+        const bool walks_input_list = d.kind == DCNN_ACCUM || d.kind == DCNN_MAXPOOL || walker_conv || (d.kind == DCNN_ACT && d.n_in == 1);
+        const bool forwards_list = walker_conv && d.act == DCNN_ACT_NONE && d.want_idx;
+        if ((walks_input_list && !p.self) || forwards_list) net->plan[net->layer_of_node[p.in_nodes[0]]].d.want_idx = 1;
     }
     size_t off = 0;
     for (auto& p : net->plan) {
@@ -427,7 +437,8 @@ dcnn_status dcnn_net_bind(dcnn_net* net, void* arena_dev, size_t arena_bytes) {
     }
     for (auto& p : net->plan) {
         if (st != DCNN_OK) break;
-        st = dcnn::layer_create(net->lane_ctx[p.lane], &p.d, p.w, p.b, p.w2, p.b2, static_cast<char*>(arena_dev) + p.state_off, p.state_bytes, &p.layer);
+        st = dcnn::layer_create(net->lane_ctx[p.lane], &p.d, p.w, p.b, p.w2, p.b2, static_cast<char*>(arena_dev) + p.state_off, p.state_bytes, p.self, &p.layer);
+        if (st == DCNN_OK) p.layer->skip_list = p.skip_list;
         if (st != DCNN_OK) st = lane_fail(net, p, st);
     }
     if (st == DCNN_OK) st = lanes_end(net);

@@ -1,0 +1,352 @@
+// Work lists that a kernel builds for itself, on small maps.
+//
+// On maps of up to kSelfMaxPixels pixels the mask pass, the list emission and the compaction of survivors cost more than
+// what they serve: each is a launch of its own with two or three dependent round trips to memory (4-6 us; a layer of a
+// network of small maps took 12-20 us, half of it spent on lists).  A mask of 16 K pixels is 2 KB of bits, though,
+// so every workgroup of the layer's own kernel can hold ALL flags in LDS: it reads the input mask (one round trip of
+// 16-byte loads), forms the flagged output pixels as bits (a 3x3 window on whole words), takes the prefix sums of the
+// words' counts -- the position of every pixel in the ascending list -- and keeps the entries of its own tiles.  The
+// tiles are those of the stored list (same order, same partition), so results do not depend on which form is used.
+// What other kernels need is written by the workgroups in shares: the output mask and, where the caller asked for it,
+// the ascending list and its length.
+#pragma once
+
+#include "device_utils.h"
+
+namespace dcnn {
+
+// 32 mask bytes -> 32 bits, any non-zero byte counts
+__device__ __forceinline__ uint32_t self_pack(const uint4& a, const uint4& b) {
+    auto pack8 = [](uint64_t v) -> uint32_t {
+        v |= v >> 4; v |= v >> 2; v |= v >> 1;
+        v &= 0x0101010101010101ull;
+        return (uint32_t)((v * 0x0102040810204080ull) >> 56);
+    };
+    return pack8((uint64_t)a.x | (uint64_t)a.y << 32) | pack8((uint64_t)a.z | (uint64_t)a.w << 32) << 8 |
+           pack8((uint64_t)b.x | (uint64_t)b.y << 32) << 16 | pack8((uint64_t)b.z | (uint64_t)b.w << 32) << 24;
+}
+// flags of pixels 32*w .. 32*w+31 of a mask of `px` bytes (16-byte aligned)
+__device__ __forceinline__ uint32_t self_mask_word(const uint8_t* mask, int w, int px) {
+    const int p0 = w * 32;
+    if (p0 + 32 <= px)
+        return self_pack(*reinterpret_cast<const uint4*>(mask + p0), *reinterpret_cast<const uint4*>(mask + p0 + 16));
+    uint32_t bits = 0;
+    for (int i = 0; p0 + i < px; ++i) bits |= (mask[p0 + i] ? 1u : 0u) << i;
+    return bits;
+}
+
+// 32 bits from bit position `pos` on; positions outside the array read some word of it (callers mask those bits)
+__device__ __forceinline__ uint32_t self_bits32(const uint32_t* words, int nwords, int pos) {
+    const int i = pos >> 5, sh = pos & 31;
+    const int lo = min(max(i, 0), nwords - 1), hi = min(max(i + 1, 0), nwords - 1);
+    return (uint32_t)((((uint64_t)words[hi] << 32) | words[lo]) >> sh);
+}
+
+struct SelfSpan { int begin, end, step, entries; };            // this workgroup's groups of `entries` list entries
+
+// floor(a / b) for 0 <= a < 2^17, 0 < b < 2^12 (the quotient's distance from the next integer exceeds the rounding error)
+__device__ __forceinline__ int self_div(int a, float inv_b) { return (int)(((float)a + 0.5f) * inv_b); }
+
+// Window taps of output pixel p, bit ky*k+kx, from the bits of the input mask.
+__device__ __forceinline__ uint32_t self_taps(const ListArgs& l, const uint32_t* ibits, int in_words, int p) {
+    const uint32_t t1 = fast_div((uint32_t)p, l.div_ow);
+    const int ox = p - (int)t1 * l.m_ow;
+    const int n = (int)fast_div(t1, l.div_oh);
+    const int oy = (int)t1 - n * l.m_oh;
+    const int iy0 = oy * l.m_stride - l.m_pad, ix0 = ox * l.m_stride - l.m_pad;
+    uint32_t cols = (1u << l.m_k) - 1u;                        // window columns inside the map
+    if (ix0 < 0) cols &= ~((1u << -ix0) - 1u);
+    if (ix0 + l.m_k > l.m_w) cols &= (1u << (l.m_w - ix0)) - 1u;
+    uint32_t taps = 0;
+    for (int ky = 0; ky < l.m_k; ++ky) {
+        const int iy = iy0 + ky;
+        if (iy < 0 || iy >= l.m_h) continue;
+        taps |= (self_bits32(ibits, in_words, (n * l.m_h + iy) * l.m_w + ix0) & cols) << (l.m_k > 5 ? 0 : ky * l.m_k);   // (windows above 5x5 are only asked whether any tap is set)
+    }
+    return taps;
+}
+
+__device__ __forceinline__ bool self_b_flag(const ListArgs& l, int p) {
+    if (l.b_stride <= 0) return l.m_b[p] != 0;
+    const uint32_t t1 = fast_div((uint32_t)p, l.div_ow);
+    const int ox = p - (int)t1 * l.m_ow;
+    const int n = (int)fast_div(t1, l.div_oh);
+    const int oy = (int)t1 - n * l.m_oh;
+    return l.m_b[((int64_t)n * l.b_h + oy * l.b_stride) * l.b_w + ox * l.b_stride] != 0;
+}
+
+// Inclusive sums over the 16 lanes of a row / the 64 lanes of the wave, by DPP lane shifts (register to register).
+template <int CTRL, int ROWS> __device__ __forceinline__ int self_dpp_add(int v) {
+    return v + __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false);
+}
+__device__ __forceinline__ int self_row_scan(int v) {
+    v = self_dpp_add<0x111, 0xf>(v);        // row_shr:1
+    v = self_dpp_add<0x112, 0xf>(v);        // row_shr:2
+    v = self_dpp_add<0x114, 0xf>(v);        // row_shr:4
+    return self_dpp_add<0x118, 0xf>(v);     // row_shr:8
+}
+__device__ __forceinline__ int self_scan(int v) {
+    v = self_row_scan(v);
+    v = self_dpp_add<0x142, 0xa>(v);        // row_bcast:15 into rows 1 and 3
+    return self_dpp_add<0x143, 0xc>(v);     // row_bcast:31 into rows 2 and 3
+}
+
+struct SelfBits {
+    uint32_t* ibits;
+    uint32_t* obits;
+    uint32_t* dil;             // strided 3x3: the flags dilated at the input's resolution
+    uint16_t* prefix;          // flagged pixels before each word of obits
+    int* red;
+    int in_words, out_words;
+    int top;                   // power of two, at least out_words
+};
+__device__ __forceinline__ SelfBits self_carve(const ListArgs& l, unsigned char* scratch) {
+    SelfBits s;
+    s.in_words = (l.m_in_px + 31) / 32;
+    s.out_words = (l.m_out_px + 31) / 32;
+    s.top = 1;
+    while (s.top < s.out_words) s.top <<= 1;
+    s.red = reinterpret_cast<int*>(scratch);                   // 128 bytes
+    s.ibits = reinterpret_cast<uint32_t*>(scratch + 128);
+    s.obits = s.ibits + s.in_words;
+    s.dil = s.obits + s.out_words;
+    s.prefix = reinterpret_cast<uint16_t*>(s.dil + (l.m_stride == 2 ? s.in_words : 0));
+    return s;
+}
+
+// 3x3 dilation of the bits of the input map, whole words: the rows above, at and below, each OR-ed with itself moved by
+// one column; what lies beyond a border of the map is masked out by the columns and rows the word's pixels are in.
+__device__ __forceinline__ uint32_t self_dilate_word(const ListArgs& l, const SelfBits& s, int w, const FastDiv& div_w, const FastDiv& div_h) {
+    const int p0 = w * 32;
+    const uint32_t t1 = fast_div((uint32_t)p0, div_w);
+    int x = p0 - (int)t1 * l.m_w;
+    int y = (int)t1 - (int)fast_div(t1, div_h) * l.m_h;
+    uint32_t first_col = 0, last_col = 0, first_row = 0, last_row = 0;
+    for (int pos = 0; pos < 32;) {
+        const int run = min(l.m_w - x, 32 - pos);
+        const uint32_t seg = (run == 32 ? 0xffffffffu : ((1u << run) - 1u)) << pos;
+        if (x == 0) first_col |= 1u << pos;
+        if (x + run == l.m_w) last_col |= 1u << (pos + run - 1);
+        if (y == 0) first_row |= seg;
+        if (y == l.m_h - 1) last_row |= seg;
+        pos += run;
+        x = 0;
+        if (++y == l.m_h) y = 0;
+    }
+    uint32_t hit = 0;
+#pragma unroll
+    for (int dy = -1; dy <= 1; ++dy) {
+        const int pos = p0 + dy * l.m_w;
+        uint32_t row = self_bits32(s.ibits, s.in_words, pos) | (self_bits32(s.ibits, s.in_words, pos - 1) & ~first_col) |
+                       (self_bits32(s.ibits, s.in_words, pos + 1) & ~last_col);
+        if (dy < 0) row &= ~first_row;
+        if (dy > 0) row &= ~last_row;
+        hit |= row;
+    }
+    if (p0 + 32 > l.m_in_px) hit &= (1u << (l.m_in_px - p0)) - 1u;
+    return hit;
+}
+
+// The input mask on its way: requested before the kernel does anything else that waits (two words per thread of a
+// workgroup of 1024; the last, incomplete word of a mask is read when it is needed).
+constexpr int kSelfAhead = 2;
+struct SelfAhead { uint4 a[kSelfAhead], b[kSelfAhead]; };
+__device__ __forceinline__ void self_request(const ListArgs& l, SelfAhead& v) {
+#pragma unroll
+    for (int i = 0; i < kSelfAhead; ++i) {
+        const int p0 = ((int)threadIdx.x + i * 1024) * 32;
+        v.a[i] = v.b[i] = make_uint4(0u, 0u, 0u, 0u);
+        if (p0 + 32 <= l.m_in_px) {
+            v.a[i] = *reinterpret_cast<const uint4*>(l.m_in + p0);
+            v.b[i] = *reinterpret_cast<const uint4*>(l.m_in + p0 + 16);
+        }
+    }
+}
+
+// Phase 1: all flags and list positions.  Returns the length of the list; *in_count (if wanted): flagged input pixels.  Every thread
+// of the workgroup (NT of them) calls it; ends with a barrier.
+template <int NT>
+__device__ __forceinline__ int self_build(const ListArgs& l, const SelfBits& s, int* in_count, const SelfAhead* ahead = nullptr) {
+    constexpr int NWV = NT / kWave;
+    const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+    const bool copy = l.m_k == 1 && l.m_stride == 1 && l.m_up == 1;
+    const bool win3 = l.m_k == 3 && l.m_stride == 1 && l.m_pad == 1 && l.m_up == 1;   // (up > 1 comes with k = 1)
+    int nin = 0;
+    static_assert(NT == 1024 || NT <= 512, "self_request assumes 1024 threads");
+    int i = 0;
+#pragma unroll 2
+    for (int w = tid; w < s.in_words; w += NT, ++i) {
+        uint32_t v;
+        if (ahead != nullptr && w * 32 + 32 <= l.m_in_px) v = i == 0 ? self_pack(ahead->a[0], ahead->b[0]) : self_pack(ahead->a[1], ahead->b[1]);
+        else v = self_mask_word(l.m_in, w, l.m_in_px);
+        s.ibits[w] = v;
+        nin += __popc(v);
+        if (copy) s.obits[w] = v | ((l.m_b && l.b_stride <= 0) ? self_mask_word(l.m_b, w, l.m_out_px) : 0u);
+    }
+    lds_block_sync();
+    if (win3) {
+        for (int w = tid; w < s.out_words; w += NT) {
+            uint32_t hit = self_dilate_word(l, s, w, l.div_ow, l.div_oh);      // (input and output maps have one shape)
+            if (l.m_b && l.b_stride <= 0) hit |= self_mask_word(l.m_b, w, l.m_out_px);
+            s.obits[w] = hit;
+        }
+    } else if (l.m_up > 1) {
+        // nearest upsampling: runs of equal flags, cut at words and rows
+        for (int w = tid; w < s.out_words; w += NT) {
+            const int p0 = w * 32;
+            const uint32_t t1 = fast_div((uint32_t)p0, l.div_ow);
+            int x = p0 - (int)t1 * l.m_ow;
+            int n = (int)fast_div(t1, l.div_oh);
+            int y = (int)t1 - n * l.m_oh;
+            uint32_t bits = 0;
+            int q = (n * l.m_h + (int)fast_div((uint32_t)y, l.div_up)) * l.m_w + (int)fast_div((uint32_t)x, l.div_up);
+            int left = l.m_up - (x - (int)fast_div((uint32_t)x, l.div_up) * l.m_up);     // pixels until the next source
+            const int end = min(32, l.m_out_px - p0);
+            for (int pos = 0; pos < end;) {
+                const int run = min(left, end - pos);
+                if ((s.ibits[q >> 5] >> (q & 31)) & 1u) bits |= (uint32_t)(((1ull << run) - 1ull) << pos);
+                pos += run;
+                x += run;
+                ++q;
+                left = l.m_up;
+                if (x >= l.m_ow) {                             // next row: a source row further every m_up of them
+                    x = 0;
+                    if (++y == l.m_oh) { y = 0; ++n; }
+                    q = (n * l.m_h + (int)fast_div((uint32_t)y, l.div_up)) * l.m_w;
+                }
+            }
+            s.obits[w] = bits;
+        }
+    } else if (!copy) {
+        // stride 2: the flags dilated at the input's resolution, then one bit per output pixel; any other window: its
+        // taps pixel by pixel.  A pixel per lane, 64 flags per wave and step.
+        const bool sample = l.m_stride == 2 && ((l.m_k == 3 && l.m_pad == 1) || (l.m_k == 1 && l.m_pad == 0));
+        if (sample && l.m_k == 3) {
+            for (int w = tid; w < s.in_words; w += NT) s.dil[w] = self_dilate_word(l, s, w, l.div_iw, l.div_ih);
+            lds_block_sync();
+        }
+        const uint32_t* from = l.m_k == 3 ? s.dil : s.ibits;
+        for (int base = wave * kWave; base < l.m_out_px; base += NT) {
+            const int p = base + lane;
+            bool f = false;
+            if (p < l.m_out_px) {
+                if (sample) {
+                    const uint32_t t1 = fast_div((uint32_t)p, l.div_ow);
+                    const int ox = p - (int)t1 * l.m_ow;
+                    const int n = (int)fast_div(t1, l.div_oh);
+                    const int oy = (int)t1 - n * l.m_oh;
+                    const int q = (n * l.m_h + 2 * oy) * l.m_w + 2 * ox;
+                    f = (from[q >> 5] >> (q & 31)) & 1u;
+                } else {
+                    f = self_taps(l, s.ibits, s.in_words, p) != 0;
+                }
+                if (l.m_b && l.b_stride <= 0) f = f || l.m_b[p] != 0;
+            }
+            const uint64_t bits = __ballot(f);
+            if (lane == 0) s.obits[base / 32] = (uint32_t)bits;
+            if (lane == 1 && base / 32 + 1 < s.out_words) s.obits[base / 32 + 1] = (uint32_t)(bits >> 32);
+        }
+    }
+    if (l.m_b && l.b_stride > 0) {                             // a second mask of another size: sampled pixel by pixel
+        lds_block_sync();
+        for (int base = wave * kWave; base < l.m_out_px; base += NT) {
+            const int p = base + lane;
+            const uint64_t bits = __ballot(p < l.m_out_px && self_b_flag(l, p));
+            if (lane == 0) s.obits[base / 32] |= (uint32_t)bits;
+            if (lane == 1 && base / 32 + 1 < s.out_words) s.obits[base / 32 + 1] |= (uint32_t)(bits >> 32);
+        }
+    }
+    lds_block_sync();
+    // exclusive prefix over the words: W consecutive words per thread, a scan over threads, then within them
+    const int W = (s.out_words + NT - 1) / NT;
+    int mine = 0;
+    for (int i = 0; i < W; ++i) {
+        const int w = tid * W + i;
+        if (w < s.out_words) mine += __popc(s.obits[w]);
+    }
+    const int inc = self_scan(mine);
+    if (lane == kWave - 1) s.red[wave] = inc;
+    if (in_count != nullptr) {
+        const int sum_in = self_scan(nin);
+        if (lane == kWave - 1) s.red[16 + wave] = sum_in;
+    }
+    lds_block_sync();
+    // (at most 16 waves: their totals fit one row of lanes, every wave scans them again)
+    const int waves = self_row_scan(lane < NWV ? s.red[lane] : 0);
+    const int total = __builtin_amdgcn_readlane(waves, NWV - 1);
+    const int before = wave == 0 ? 0 : __builtin_amdgcn_readlane(waves, __builtin_amdgcn_readfirstlane(wave > 0 ? wave - 1 : 0));
+    int run = before + inc - mine;
+    for (int i = 0; i < W; ++i) {
+        const int w = tid * W + i;
+        if (w < s.out_words) { s.prefix[w] = (uint16_t)run; run += __popc(s.obits[w]); }
+    }
+    if (in_count != nullptr) *in_count = __builtin_amdgcn_readlane(self_row_scan(lane < NWV ? s.red[16 + lane] : 0), NWV - 1);
+    lds_block_sync();
+    return total;
+}
+
+// Pixel of list entry j (below the list's length): the last word with no more than j flagged pixels before it, then the
+// bit of that rank in it.
+__device__ __forceinline__ int self_select(const SelfBits& s, int j) {
+    int w = 0;
+    for (int half = s.top >> 1; half >= 1; half >>= 1) {
+        const int m = w + half;
+        if (m < s.out_words && (int)s.prefix[m] <= j) w = m;
+    }
+    uint32_t bits = s.obits[w];
+    int rank = j - (int)s.prefix[w], at = 0;
+#pragma unroll
+    for (int half = 16; half >= 1; half >>= 1) {
+        const int below = __popc(bits & ((1u << half) - 1u));
+        if (rank >= below) { rank -= below; bits >>= half; at += half; }
+    }
+    return w * 32 + at;
+}
+
+// Phase 2: the entries of this workgroup's groups -> px (and tap words) in LDS, group after group; the shared outputs.
+// Ends with a barrier, after which the scratch memory of phase 1 is free.
+template <int NT>
+__device__ __forceinline__ void self_emit(const ListArgs& l, const SelfBits& s, int count, SelfSpan span, int32_t* px, uint32_t* taps) {
+    const int tid = threadIdx.x;
+    const int groups = span.begin < span.end ? (span.end - span.begin + span.step - 1) / span.step : 0;
+    const int nloc = groups * span.entries;
+    const float inv_e = 1.0f / (float)span.entries;
+    for (int i = tid; i < nloc; i += NT) {
+        const int q = self_div(i, inv_e);
+        const int j = (span.begin + q * span.step) * span.entries + (i - q * span.entries);
+        int p = -1;
+        uint32_t t = 0;
+        if (j < count) {
+            p = self_select(s, j);
+            if (taps != nullptr && l.want_taps) {
+                t = self_taps(l, s.ibits, s.in_words, p);
+                if (l.m_b != nullptr && self_b_flag(l, p)) t |= 1u << 30;
+            }
+        }
+        px[i] = p;
+        if (taps != nullptr && l.want_taps) taps[i] = t;
+    }
+    // shares of what other kernels read
+    if (blockIdx.y == 0) {
+        const int per = (s.out_words + (int)gridDim.x - 1) / (int)gridDim.x;
+        const int w1 = min(((int)blockIdx.x + 1) * per, s.out_words);
+        if (l.mask_out != nullptr) {
+            for (int i = (int)blockIdx.x * per * 8 + tid; i < w1 * 8; i += NT) {     // four pixels per step
+                const uint32_t f = (s.obits[i / 8] >> (4 * (i % 8))) & 15u;
+                const uint32_t v = (f & 1u) | (f & 2u) << 7 | (f & 4u) << 14 | (f & 8u) << 21;
+                if (i * 4 + 4 <= l.m_out_px) *reinterpret_cast<uint32_t*>(l.mask_out + i * 4) = v;
+                else for (int k = 0; i * 4 + k < l.m_out_px; ++k) l.mask_out[i * 4 + k] = (uint8_t)((f >> k) & 1u);
+            }
+        }
+        if (l.idx_out != nullptr) {
+            for (int w = (int)blockIdx.x * per + tid; w < w1; w += NT) {
+                int j = s.prefix[w];
+                for (uint32_t rest = s.obits[w]; rest; rest &= rest - 1) l.idx_out[j++] = w * 32 + __builtin_ctz(rest);
+            }
+        }
+        if (l.count_out != nullptr && blockIdx.x == 0 && tid == 0) *l.count_out = count;
+    }
+    lds_block_sync();
+}
+
+}  // namespace dcnn

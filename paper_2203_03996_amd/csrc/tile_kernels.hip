@@ -3,11 +3,14 @@
 // final accumulation.  All of them walk a compacted work list of flagged pixels; LP lanes share
 // one pixel so every access is a coalesced 16-byte vector of channels (NHWC).
 #include "device_utils.h"
+#include "self_list.h"
+#include "tail_impl.h"
 
 namespace dcnn {
 
 constexpr int kTileWaves = 4;                       // waves (tiles) per workgroup
 constexpr int kTileThreads = kTileWaves * kWave;
+constexpr int kSelfWgPerCu = 4;                     // workgroups per compute unit that each build the list: more repeat the work more often
 
 static int list_grid(const dcnn_ctx* ctx, int64_t max_count, int entries_per_wg, int wg_per_cu) {
     int64_t want = cdiv(max_count > 0 ? max_count : 1, entries_per_wg);
@@ -16,157 +19,35 @@ static int list_grid(const dcnn_ctx* ctx, int64_t max_count, int entries_per_wg,
     return (int)(cdiv(g, kXcd) * kXcd);
 }
 
-// ---- sparse-step tail with buffer addressing ---------------------------------------------------
-// Activation + truncation (Eqs. 4-6) of one run of tile entries, for the sparse steps of layers whose channel
-// count is a multiple of the vector width and whose tensors stay below 2 GiB.  Same arithmetic, rounding and
-// decisions as act_trunc_tile; what differs is how memory is reached: every flag a load depends on has been
-// fetched for the whole tile beforehand (one round trip, entry lane%32 per lane), and every load and store
-// goes through a buffer descriptor with an out-of-range offset where a lane has nothing to do.  A batch of
-// UB iterations therefore issues all its loads back to back and costs one round trip to memory.
-//
-// `Src` delivers the first delta stream: select(ub, ent) runs in wave-uniform control flow and picks the
-// per-entry values of iteration ub (lane shuffles); issue(ub, v, c0, on, off) requests the values of the
-// lane's vector v; finish(ub, v, c0) returns them, rounded to the storage type.
-struct TailRsrc {
-    __amdgpu_buffer_rsrc_t res, xA, xT, out, omask;
-};
-
-template <typename T, int V, int VPL, int UB, class Src>
-__device__ __forceinline__ uint32_t sparse_tile_tail(const EpilogueArgs& e, const TailRsrc& rs, Src& src, int LP, int p_mine,
-                                                    int rflag_mine, int ent_first, int ent_end, int nbatch, int lane) {
-    typedef typename RawOf<T, V>::type Raw;
-    constexpr uint32_t ES = sizeof(T);
-    const int PPI = kWave / LP;
-    const int sub = lane % LP, grp = lane / LP;
-    const int nvec = e.c / V;
-    const uint32_t row_bytes = (uint32_t)e.c * ES;
-    const bool stateful = e.act != DCNN_ACT_NONE;
-    const bool has_res = e.res_data != nullptr;
-    const float hi = act_hi(e.act);
-    uint32_t bits = 0;
-    for (int b = 0; b < nbatch; ++b) {
-        int pix[UB];
-        uint32_t off[UB][VPL];
-        Raw rr[UB][VPL], ra[UB][VPL], rt[UB][VPL];
-        // ---- phase 1: every load of the batch ----------------------------------------------------
-#pragma unroll
-        for (int ub = 0; ub < UB; ++ub) {
-            const int ent = ent_first + (b * UB + ub) * PPI + grp;
-            const int p_any = __shfl(p_mine, ent & (kTile - 1), kWave);
-            const int rf = __shfl(rflag_mine, ent & (kTile - 1), kWave);
-            src.select(ub, ent & (kTile - 1));
-            const int p = ent < ent_end ? p_any : -1;
-            pix[ub] = p;
-#pragma unroll
-            for (int v = 0; v < VPL; ++v) {
-                const int vi = sub + v * LP;
-                const bool on = p >= 0 && vi < nvec;
-                const int c0 = vi * V;
-                const uint32_t o = on ? (uint32_t)p * row_bytes + (uint32_t)c0 * ES : kOob;
-                off[ub][v] = o;
-                src.issue(ub, v, c0, on, o);
-                rr[ub][v] = ws_load16<Raw>(rs.res, rf ? o : kOob);          // empty descriptor without a second stream
-                ra[ub][v] = ws_load16_nt<Raw>(rs.xA, o);                     // empty descriptors without an activation
-                rt[ub][v] = ws_load16_nt<Raw>(rs.xT, o);
-            }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        // ---- phase 2: arithmetic, per-pixel maximum, decision, stores -----------------------------
-#pragma unroll
-        for (int ub = 0; ub < UB; ++ub) {
-            Raw o_a[VPL], o_t[VPL], o_y[VPL], o_r[VPL];
-            float u = 0.0f;
-#pragma unroll
-            for (int v = 0; v < VPL; ++v) {
-                const Raw d0 = src.finish(ub, v, (sub + v * LP) * V);
-                o_r[v] = raw_zero<T, V>();
-#pragma unroll
-                for (int i = 0; i < V; ++i) {
-                    float d = raw_get<T, V>(d0, i);
-                    if (has_res) d = round_store<T>(d + raw_get<T, V>(rr[ub][v], i));
-                    if (stateful) {
-                        const float a = raw_get<T, V>(ra[ub][v], i), t = raw_get<T, V>(rt[ub][v], i);
-                        const float sum = (a + t) + d;
-                        const float dy = act_clamp(sum, hi) - act_clamp(a, hi);
-                        u = fmaxf(u, fabsf(dy));
-                        raw_set<T, V>(o_a[v], i, sum);
-                        raw_set<T, V>(o_t[v], i, t + d);                       // x^T if the pixel is truncated
-                        raw_set<T, V>(o_y[v], i, dy);
-                        if (e.carry) raw_set<T, V>(o_r[v], i, round_residue<T>(sum));   // x^T if it is updated and keeps the residue
-                    } else {
-                        raw_set<T, V>(o_y[v], i, d);
-                    }
-                }
-            }
-            bool upd = true;
-            if (stateful) {
-                for (int m = LP >> 1; m >= 1; m >>= 1) u = fmaxf(u, __shfl_xor(u, m, kWave));
-                upd = u >= e.eps;
-            }
-#pragma unroll
-            for (int v = 0; v < VPL; ++v) {
-                const uint32_t o = off[ub][v];
-                if (stateful) {
-                    const uint32_t o_upd = upd ? o : kOob;
-                    ws_store16_nt<Raw>(rs.xA, o_upd, o_a[v]);
-                    // (an x^T that already is all zero bits is not rewritten by an update that leaves zeros)
-                    ws_store16_nt<Raw>(rs.xT, (upd && all_bits_zero(rt[ub][v]) && all_bits_zero(o_r[v])) ? kOob : o, upd ? o_r[v] : o_t[v]);
-                    ws_store16<Raw>(rs.out, o_upd, o_y[v]);
-                } else {
-                    ws_store16<Raw>(rs.out, o, o_y[v]);
-                }
-            }
-            const bool lead = pix[ub] >= 0 && sub == 0;
-            if (stateful) __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(upd ? 1 : 0), rs.omask, lead ? pix[ub] : (int)kOob, 0, 0);
-            const int ent = ent_first + (b * UB + ub) * PPI + grp;
-            if (lead && upd) bits |= 1u << (ent & (kTile - 1));
-        }
-    }
-#pragma unroll
-    for (int m = kWave >> 1; m >= 1; m >>= 1) bits |= __shfl_xor(bits, m, kWave);
-    return bits;
+// Work lists built by the kernel itself (self_list.h), for the kernels of kTileThreads threads: the length of the list, and
+// the entries of this workgroup's groups.
+__device__ __forceinline__ int64_t tile_list_count(const ListArgs& l, unsigned char* smem, SelfBits& sb) {
+    if (!l.self) return list_count(l);
+    sb = self_carve(l, smem + l.lds_scratch);
+    return self_build<kTileThreads>(l, sb, nullptr);
 }
-
-// How the entries of a tile are spread over waves and batches for a pixel of `nvec` vectors.
-struct TailShape {
-    int lp;        // lanes per pixel
-    int run;       // consecutive tile entries per wave (8, 16 or 32)
-    int nbatch;    // batches of UB iterations per wave
-};
-static TailShape tail_shape(int nvec, int vpl, int ub) {
-    TailShape s;
-    int lp = 1;
-    while (lp < (int)cdiv(nvec, vpl)) lp <<= 1;
-    s.lp = lp < 2 ? 2 : (lp > kWave ? kWave : lp);
-    const int per_batch = ub * (kWave / s.lp);                 // entries one batch covers
-    s.run = per_batch < 8 ? 8 : (per_batch > kTile ? kTile : per_batch);
-    s.nbatch = (int)cdiv(s.run, per_batch);
-    return s;
+__device__ __forceinline__ const int32_t* tile_list_emit(const ListArgs& l, unsigned char* smem, const SelfBits& sb, int64_t count,
+                                                         int64_t begin, int64_t end, int64_t step, int entries) {
+    int32_t* px = reinterpret_cast<int32_t*>(smem + l.lds_list);
+    if (l.self) self_emit<kTileThreads>(l, sb, (int)count, SelfSpan{(int)begin, (int)end, (int)step, entries}, px, nullptr);
+    return px;
 }
-
-__device__ __forceinline__ void store_survivors(uint32_t* surv, int64_t tile, int part, int parts, uint32_t bits) {
-    if (parts == 1) surv[tile] = bits;
-    else if (parts == 2) reinterpret_cast<uint16_t*>(surv)[tile * 2 + part] = (uint16_t)(bits >> (16 * part));
-    else reinterpret_cast<uint8_t*>(surv)[tile * 4 + part] = (uint8_t)(bits >> (8 * part));
+// Dynamic LDS of such a launch behind `used` bytes of the kernel's own, and where the pieces lie.
+static size_t tile_list_lds(ListArgs& l, size_t used, int64_t entries, int grid, bool per_xcd) {
+    if (!l.self) return used;
+    l.lds_scratch = (int)align_up(used, 16);
+    l.lds_list = l.lds_scratch + (int)self_scratch_bytes(l.m_in_px, l.m_out_px);
+    l.lds_entries = (int)self_local_entries(l.m_out_px, entries, grid, per_xcd);
+    return (size_t)l.lds_list + (size_t)l.lds_entries * 4;
 }
-
-// Activation + truncation (+ add) of a sparse step: the first stream is a stored delta map.
-template <typename T, int V, int VPL, int UB> struct ActSrc {
-    typedef typename RawOf<T, V>::type Raw;
-    __amdgpu_buffer_rsrc_t in;
-    int flag_mine;                       // update flag of the first stream at entry lane%32
-    int flag[UB];
-    Raw d[UB][VPL];
-    __device__ __forceinline__ void select(int ub, int ent) { flag[ub] = __shfl(flag_mine, ent, kWave); }
-    __device__ __forceinline__ void issue(int ub, int v, int, bool, uint32_t o) { d[ub][v] = ws_load16<Raw>(in, flag[ub] ? o : kOob); }
-    __device__ __forceinline__ Raw finish(int ub, int v, int) const { return d[ub][v]; }
-};
 
 template <typename T, int V, int VPL, int UB>
 __global__ __launch_bounds__(kTileThreads) void act_sparse_kernel(ListArgs l, ActArgs a, EpilogueArgs e, TailShape shape,
                                                                    uint32_t map_bytes, uint32_t pixels) {
+    extern __shared__ __align__(16) unsigned char list_smem[];
     clear_ahead(e);
-    const int64_t count = list_count(l);
+    SelfBits sb;
+    const int64_t count = tile_list_count(l, list_smem, sb);
     const int lane = threadIdx.x % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     TailRsrc rs;
@@ -179,14 +60,15 @@ __global__ __launch_bounds__(kTileThreads) void act_sparse_kernel(ListArgs l, Ac
     int survivors = 0;
     const int64_t ntiles = (count + kTile - 1) / kTile;
     const WgTileRange r = wg_tile_range((ntiles * parts + kTileWaves - 1) / kTileWaves);
-    for (int64_t wt = r.begin; wt < r.end; wt += r.step) {
+    const int32_t* self_px = tile_list_emit(l, list_smem, sb, count, r.begin, r.end, r.step, kTileWaves * shape.run);
+    for (int64_t wt = r.begin; wt < r.end; wt += r.step, self_px += kTileWaves * shape.run) {
         const int64_t unit = wt * kTileWaves + wave;
         const int64_t tile = unit / parts;
         const int part = (int)(unit - tile * parts);
         const int64_t base = tile * kTile;
         if (base >= count) continue;
         const int j = lane % kTile;
-        const int p_mine = (j / shape.run == part) ? list_pixel(l.list, base + j, count) : -1;
+        const int p_mine = (j / shape.run == part) ? (l.self ? self_px[wave * shape.run + j % shape.run] : list_pixel(l.list, base + j, count)) : -1;
         const int p_off = p_mine >= 0 ? p_mine : (int)kOob;
         // a stream without a mask is flagged wherever the list points
         const int rflag = e.res_mask ? __builtin_amdgcn_raw_buffer_load_b8(rs_rmask, p_off, 0, 0) : 1;
@@ -214,8 +96,10 @@ __global__ __launch_bounds__(kTileThreads) void act_wide_kernel(ListArgs l, ActA
     typedef typename RawOf<T, V>::type Raw;
     constexpr uint32_t ES = sizeof(T);
     __shared__ float s_max[2][kWideRun][kTileWaves];
+    extern __shared__ __align__(16) unsigned char list_smem[];
     clear_ahead(e);
-    const int64_t count = list_count(l);
+    SelfBits sb;
+    const int64_t count = tile_list_count(l, list_smem, sb);
     const int lane = threadIdx.x % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const __amdgpu_buffer_rsrc_t rs_in = ws_rsrc(a.in_data, map_bytes), rs_res = ws_rsrc(e.res_data, map_bytes);
@@ -232,12 +116,13 @@ __global__ __launch_bounds__(kTileThreads) void act_wide_kernel(ListArgs l, ActA
     const int64_t units = ntiles * (kTile / kWideRun);
     int survivors = 0;
     int parity = 0;
-    for (int64_t unit = blockIdx.x; unit < units; unit += gridDim.x, parity ^= 1) {
+    const int32_t* self_px = tile_list_emit(l, list_smem, sb, count, blockIdx.x, units, gridDim.x, kWideRun);
+    for (int64_t unit = blockIdx.x; unit < units; unit += gridDim.x, parity ^= 1, self_px += kWideRun) {
         const int64_t tile = unit / (kTile / kWideRun);
         const int part = (int)(unit - tile * (kTile / kWideRun));
         const int64_t base = tile * kTile + part * kWideRun;
         // entry lane % 8 of the run: pixel and the update flags of both streams (one round trip for the run)
-        const int p_mine = list_pixel(l.list, base + lane % kWideRun, count);
+        const int p_mine = l.self ? self_px[lane % kWideRun] : list_pixel(l.list, base + lane % kWideRun, count);
         const int p_off = p_mine >= 0 ? p_mine : (int)kOob;
         const int rflag_mine = e.res_mask ? __builtin_amdgcn_raw_buffer_load_b8(rs_rmask, p_off, 0, 0) : 1;
         const int iflag_mine = a.in_mask ? __builtin_amdgcn_raw_buffer_load_b8(rs_imask, p_off, 0, 0) : 1;
@@ -407,7 +292,8 @@ __global__ __launch_bounds__(256) void act_first_kernel(ActArgs a, EpilogueArgs 
 }
 
 template <typename T>
-static dcnn_status launch_act_t(dcnn_ctx* ctx, bool init, const ListArgs& l, const ActArgs& a, const EpilogueArgs& e) {
+static dcnn_status launch_act_t(dcnn_ctx* ctx, bool init, const ListArgs& l_in, const ActArgs& a, const EpilogueArgs& e) {
+    ListArgs l = l_in;
     constexpr int VEC = Elem<T>::VEC;
     const bool vec = (e.c % VEC) == 0;
     const int nvec = vec ? e.c / VEC : e.c;
@@ -432,22 +318,25 @@ static dcnn_status launch_act_t(dcnn_ctx* ctx, bool init, const ListArgs& l, con
         const int64_t cap = (int64_t)ctx->num_cu * 8;
         const int wgrid = (int)(units < cap ? units : cap);
         const uint32_t mb = (uint32_t)map_bytes, px = (uint32_t)l.max_count;
-        hipLaunchKernelGGL((act_wide_kernel<T, VEC, 1>), dim3(wgrid), dim3(kTileThreads), 0, ctx->stream, l, a, e, mb, px);
+        const size_t lds = tile_list_lds(l, 0, kWideRun, wgrid, false);
+        hipLaunchKernelGGL((act_wide_kernel<T, VEC, 1>), dim3(wgrid), dim3(kTileThreads), lds, ctx->stream, l, a, e, mb, px);
         return check_hip(ctx, hipGetLastError(), "act_wide_kernel launch");
     }
     if (vec && vpl <= 4 && map_bytes > 0 && map_bytes <= kWsMaxBytes) {
         const int vpl_used = vpl <= 1 ? 1 : (vpl <= 2 ? 2 : 4);
         const int ub = vpl_used == 4 ? 2 : 4;
         const TailShape shape = tail_shape(nvec, vpl_used, ub);
-        const int sgrid = list_grid(ctx, l.max_count, kTileWaves * shape.run, 8);
+        const int sgrid = list_grid(ctx, l.max_count, kTileWaves * shape.run, l.self ? kSelfWgPerCu : 8);
         const uint32_t mb = (uint32_t)map_bytes, px = (uint32_t)l.max_count;
-#define DCNN_ACT_SPARSE(VPL, UB) hipLaunchKernelGGL((act_sparse_kernel<T, VEC, VPL, UB>), dim3(sgrid), dim3(kTileThreads), 0, ctx->stream, l, a, e, shape, mb, px)
+        const size_t lds = tile_list_lds(l, 0, kTileWaves * shape.run, sgrid, true);
+#define DCNN_ACT_SPARSE(VPL, UB) hipLaunchKernelGGL((act_sparse_kernel<T, VEC, VPL, UB>), dim3(sgrid), dim3(kTileThreads), lds, ctx->stream, l, a, e, shape, mb, px)
         if (vpl_used == 1) DCNN_ACT_SPARSE(1, 4);
         else if (vpl_used == 2) DCNN_ACT_SPARSE(2, 4);
         else DCNN_ACT_SPARSE(4, 2);
 #undef DCNN_ACT_SPARSE
         return check_hip(ctx, hipGetLastError(), "act_sparse_kernel launch");
     }
+    if (l.self) return fail(ctx, DCNN_EUNSUPPORTED, "activation: this shape does not build its work list in place");
     const int grid = list_grid(ctx, l.max_count, kTileWaves * kTile, 8);
     dim3 g(grid), b(kTileThreads);
 #define DCNN_ACT_LAUNCH(V, VPL) hipLaunchKernelGGL((act_kernel<T, V, VPL>), g, b, 0, ctx->stream, l, a, e)
@@ -463,6 +352,18 @@ static dcnn_status launch_act_t(dcnn_ctx* ctx, bool init, const ListArgs& l, con
     }
 #undef DCNN_ACT_LAUNCH
     return check_hip(ctx, hipGetLastError(), "act_kernel launch");
+}
+
+bool act_self_fits(int dtype, int channels, int64_t pixels) {
+    const int vec = dtype == DCNN_F16 ? 8 : 4;
+    return channels % vec == 0 && cdiv(channels / vec, kWave) <= 4 && (uint64_t)pixels * channels * dtype_size(dtype) <= kWsMaxBytes;
+}
+bool dwconv_self_fits(int dtype, int k, int channels, int64_t in_px, int64_t out_px) {
+    const int vec = dtype == DCNN_F16 ? 8 : 4;
+    const size_t es = dtype_size(dtype), w_bytes = (size_t)k * k * channels * es;
+    return k >= 1 && k <= 3 && channels % vec == 0 && cdiv(channels / vec, kWave) <= 4 &&
+           (uint64_t)(in_px > out_px ? in_px : out_px) * channels * es <= kWsMaxBytes &&
+           w_bytes + self_scratch_bytes(in_px, out_px) + 8 * 1024 <= 64 * 1024;
 }
 
 dcnn_status launch_act(dcnn_ctx* ctx, int dtype, bool init, const ListArgs& l, const ActArgs& a, const EpilogueArgs& e) {
@@ -527,7 +428,9 @@ __global__ __launch_bounds__(kTileThreads) void dwconv_sparse_kernel(ListArgs l,
         for (int i = threadIdx.x; i < nv; i += kTileThreads) reinterpret_cast<Raw*>(w_lds)[i] = wsrc[i];
     }
     __syncthreads();
-    const int64_t count = list_count(l);
+    clear_ahead(e);
+    SelfBits sb;
+    const int64_t count = tile_list_count(l, dw_smem, sb);
     const int lane = threadIdx.x % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     TailRsrc rs;
@@ -541,14 +444,15 @@ __global__ __launch_bounds__(kTileThreads) void dwconv_sparse_kernel(ListArgs l,
     int survivors = 0;
     const int64_t ntiles = (count + kTile - 1) / kTile;
     const WgTileRange r = wg_tile_range((ntiles * parts + kTileWaves - 1) / kTileWaves);
-    for (int64_t wt = r.begin; wt < r.end; wt += r.step) {
+    const int32_t* self_px = tile_list_emit(l, dw_smem, sb, count, r.begin, r.end, r.step, kTileWaves * shape.run);
+    for (int64_t wt = r.begin; wt < r.end; wt += r.step, self_px += kTileWaves * shape.run) {
         const int64_t unit = wt * kTileWaves + wave;
         const int64_t tile = unit / parts;
         const int part = (int)(unit - tile * parts);
         const int64_t base = tile * kTile;
         if (base >= count) continue;
         const int j = lane % kTile;
-        const int p_mine = (j / shape.run == part) ? list_pixel(l.list, base + j, count) : -1;
+        const int p_mine = (j / shape.run == part) ? (l.self ? self_px[wave * shape.run + j % shape.run] : list_pixel(l.list, base + j, count)) : -1;
         const int rflag = e.res_mask ? __builtin_amdgcn_raw_buffer_load_b8(rs_rmask, p_mine >= 0 ? p_mine : (int)kOob, 0, 0) : 1;
         // tap word of this lane's entry: all flags of the window requested together
         uint32_t word = 0;
@@ -714,7 +618,8 @@ __global__ __launch_bounds__(256) void dwconv_first_kernel(ConvArgs c, EpilogueA
 }
 
 template <typename T>
-static dcnn_status launch_dwconv_t(dcnn_ctx* ctx, bool init, const ListArgs& l, const ConvArgs& c, const EpilogueArgs& e) {
+static dcnn_status launch_dwconv_t(dcnn_ctx* ctx, bool init, const ListArgs& l_in, const ConvArgs& c, const EpilogueArgs& e) {
+    ListArgs l = l_in;
     constexpr int VEC = Elem<T>::VEC;
     const bool vec = (e.c % VEC) == 0;
     const int nvec = vec ? e.c / VEC : e.c;
@@ -743,9 +648,10 @@ static dcnn_status launch_dwconv_t(dcnn_ctx* ctx, bool init, const ListArgs& l, 
         const int vpl_used = vpl <= 1 ? 1 : (vpl <= 2 ? 2 : 4);
         const int ub = 4 / vpl_used;
         const TailShape shape = tail_shape(nvec, vpl_used, ub);
-        const int sgrid = list_grid(ctx, l.max_count, kTileWaves * shape.run, 8);
+        const int sgrid = list_grid(ctx, l.max_count, kTileWaves * shape.run, l.self ? kSelfWgPerCu : 8);
+        const size_t lds = tile_list_lds(l, w_bytes, kTileWaves * shape.run, sgrid, true);
         const uint32_t ib = (uint32_t)in_bytes, ip = (uint32_t)in_pixels, mb = (uint32_t)map_bytes, px = (uint32_t)l.max_count;
-#define DCNN_DW_SPARSE(VPL, UB, KS) hipLaunchKernelGGL((dwconv_sparse_kernel<T, VEC, VPL, UB, KS>), dim3(sgrid), dim3(kTileThreads), w_bytes, ctx->stream, l, c, e, shape, ib, ip, mb, px)
+#define DCNN_DW_SPARSE(VPL, UB, KS) hipLaunchKernelGGL((dwconv_sparse_kernel<T, VEC, VPL, UB, KS>), dim3(sgrid), dim3(kTileThreads), lds, ctx->stream, l, c, e, shape, ib, ip, mb, px)
 #define DCNN_DW_SPARSE_K(VPL, UB)                                                                                  \
     do {                                                                                                           \
         if (c.k == 3) DCNN_DW_SPARSE(VPL, UB, 3);                                                                  \
@@ -759,6 +665,7 @@ static dcnn_status launch_dwconv_t(dcnn_ctx* ctx, bool init, const ListArgs& l, 
 #undef DCNN_DW_SPARSE
         return check_hip(ctx, hipGetLastError(), "dwconv_sparse_kernel launch");
     }
+    if (l.self) return fail(ctx, DCNN_EUNSUPPORTED, "depthwise conv: this shape does not build its work list in place");
     const int grid = list_grid(ctx, l.max_count, kTileWaves * kTile, 8);
     dim3 g(grid), b(kTileThreads);
     const int ini = init ? 1 : 0;
@@ -984,19 +891,29 @@ __global__ __launch_bounds__(256) void maxpool_commit_kernel(ListArgs l, PoolArg
     }
 }
 
+constexpr int kUpRun = 32;
 template <typename T, int V>
 __global__ __launch_bounds__(256) void upsample_kernel(ListArgs l, UpsampleArgs a) {
-    const int64_t count = list_count(l);
+    extern __shared__ __align__(16) unsigned char list_smem[];
+    SelfBits sb;
+    const int64_t count = tile_list_count(l, list_smem, sb);
     const int C = a.c;
     const int nvec = (C + V - 1) / V;
     const T* in = static_cast<const T*>(a.in_data);
     T* out = static_cast<T*>(a.out_data);
     const int ow = a.w * a.factor, oh = a.h * a.factor;
-    const int64_t total = count * nvec;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
+    // (a list built here: groups of kUpRun entries, strided over the grid; their pixels are in LDS)
+    const int64_t groups = (count + kUpRun - 1) / kUpRun;
+    const int32_t* self_px = tile_list_emit(l, list_smem, sb, count, blockIdx.x, groups, gridDim.x, kUpRun);
+    const int64_t mine = (int64_t)blockIdx.x < groups ? (groups - blockIdx.x + gridDim.x - 1) / gridDim.x * kUpRun : 0;
+    const int64_t total = (l.self ? mine : count) * nvec;
+    const int64_t first = l.self ? threadIdx.x : (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t stride = l.self ? blockDim.x : (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = first; i < total; i += stride) {
         const int64_t j = i / nvec;
         const int vi = (int)(i - j * nvec);
-        const int64_t p = l.list ? (int64_t)l.list[j] : j;
+        const int64_t p = l.self ? (int64_t)self_px[j] : (l.list ? (int64_t)l.list[j] : j);
+        if (p < 0) continue;                                   // past the end of the list
         const int ox = (int)(p % ow);
         const int64_t t = p / ow;
         const int oy = (int)(t % oh);
@@ -1136,7 +1053,19 @@ dcnn_status launch_maxpool_commit(dcnn_ctx* ctx, int dtype, const ListArgs& l, c
     return check_hip(ctx, hipGetLastError(), "maxpool_commit_kernel launch");
 }
 
-dcnn_status launch_upsample(dcnn_ctx* ctx, int dtype, const ListArgs& l, const UpsampleArgs& a) {
+dcnn_status launch_upsample(dcnn_ctx* ctx, int dtype, const ListArgs& l_in, const UpsampleArgs& a) {
+    ListArgs l = l_in;
+    if (l.self) {
+        const int64_t want = cdiv(l.max_count, kUpRun), cap = (int64_t)ctx->num_cu * kSelfWgPerCu;
+        const int grid = (int)(want < cap ? want : cap);
+        const size_t lds = tile_list_lds(l, 0, kUpRun, grid, false);
+        const bool vec = a.c % (dtype == DCNN_F16 ? 8 : 4) == 0;
+#define DCNN_UP_SELF(T, V) hipLaunchKernelGGL((upsample_kernel<T, V>), dim3(grid), dim3(256), lds, ctx->stream, l, a)
+        if (dtype == DCNN_F16) { if (vec) DCNN_UP_SELF(f16, 8); else DCNN_UP_SELF(f16, 1); }
+        else { if (vec) DCNN_UP_SELF(float, 4); else DCNN_UP_SELF(float, 1); }
+#undef DCNN_UP_SELF
+        return check_hip(ctx, hipGetLastError(), "upsample_kernel launch");
+    }
     DCNN_FLAT_DISPATCH(upsample_kernel, a.c, l.max_count, l, a);
     return check_hip(ctx, hipGetLastError(), "upsample_kernel launch");
 }
@@ -1222,6 +1151,7 @@ dcnn_status launch_deltagen(dcnn_ctx* ctx, int dtype, const DeltaGenArgs& a_in) 
         DCNN_FLAT_DISPATCH(deltagen_apply_kernel, a_in.c, l.max_count, l, a_in);
         return check_hip(ctx, hipGetLastError(), "deltagen_apply_kernel launch");
     }
+    if (a.mask_only) return DCNN_OK;
     // ordered emission of the flagged pixels from the mask just written and the chunk counts
     MaskPassArgs m{};
     m.mask_in = a.out_mask;

@@ -916,3 +916,25 @@ def test_depthwise_first_frame_pixel_groups(S, k, stride, c, hw):
     slack = sum_slack(conv, x, bias=True) + ulp(y, S)
     assert rel_err(to_np(out), np.clip(y, dt(0), dt(6)), slack=slack) <= TOL[S]
     assert rel_err(to_np(layer.state_tensor(0)), y, slack=slack) <= TOL[S]
+
+
+@pytest.mark.parametrize("n,h,w", [(1, 1, 1), (2, 9, 9), (1, 3, 31), (3, 33, 18), (4, 128, 128), (1, 257, 255), (5, 64, 205)])
+@pytest.mark.parametrize("k,stride,pad", [(1, 1, 0), (1, 2, 0), (3, 1, 1), (3, 2, 1)])
+@pytest.mark.parametrize("second", [False, True])
+def test_mask_compact_on_words_of_flags(n, h, w, k, stride, pad, second):
+    """Maps whose rows, words of 32 flags and streams do not line up, up to and just past the 64 K pixels that one launch
+    serves (4 x 128 x 128 = 65536; 257 x 255 = 65535; 5 x 64 x 205 = 65600)."""
+    rng = np.random.default_rng(n * 1000 + w)
+    mask = (rng.random((n, h, w)) < 0.07).astype(np.uint8)
+    mask[:, 0, 0] = mask[:, -1, -1] = 1
+    want = orc.window_mask(mask, k, stride, pad)
+    mask_b = (rng.random(want.shape) < 0.03).astype(np.uint8) if second else None
+    if second:
+        want = want | mask_b
+    ctx = pkg.Context(n * h * w)
+    got, idx, count = ctx.mask_compact(torch.from_numpy(mask).cuda(), k, stride, pad, torch.from_numpy(mask_b).cuda() if second else None)
+    ctx.sync()
+    assert np.array_equal(to_np(got), want)
+    flat = np.flatnonzero(want.reshape(-1))
+    assert int(to_np(count)[0]) == flat.size
+    assert np.array_equal(to_np(idx)[:flat.size], flat)

@@ -811,3 +811,40 @@ def test_frames_of_the_wrong_shape_are_refused_before_any_launch():
             net.step(bad)
     net.step(good)
     ctx.sync()
+
+
+@pytest.mark.parametrize("spec_fn", [_small_hrnet, _small_resnet, lambda: wl.mobilenet_stack(eps=0.05, h=50, w=45, frames=4),
+                                     lambda: wl.bottleneck_block(eps=0.08, h=61, w=33, frames=4),
+                                     lambda: wl.tiny_mixed_net(eps=0.05, dtype="f16"), lambda: wl.tiny_mixed_net(eps=0.05)])
+@pytest.mark.parametrize("streams", [1, 3])
+def test_lists_built_in_the_kernels_change_nothing(spec_fn, streams):
+    """Small maps: with every layer's list in memory (flag bit 1) and with the lists built by the layers' own kernels the dense
+    output, the stored frame, every x^A and every mask are the same bits, frame after frame and after a reset."""
+    spec = spec_fn()
+    S, seed = spec["dtype"], 77
+    wts = wl.make_weights(spec, seed)
+    vid = wl.make_batch(spec["video"], seed, streams).astype(NP_DTYPE[S])
+    ctx = pkg.Context(max(streams * h * w for h, w, _ in wl.node_shapes(spec)))
+    nets = [pkg.Net(ctx, spec, wts, streams, flags) for flags in (1, 3)]
+    for t in list(range(vid.shape[0])) + [0, 1, 2]:
+        frame = torch.from_numpy(vid[t]).cuda()
+        for net in nets:
+            if t == 0:
+                net.reset()
+                net.init(frame)
+            else:
+                net.step(frame)
+        ctx.sync()
+        assert np.array_equal(to_np(nets[0].output().data), to_np(nets[1].output().data)), f"frame {t}: dense output"
+        plans = [{net.layer_node(i): i for i in range(net.num_layers)} for net in nets]
+        for node in plans[0].keys() & plans[1].keys():
+            views = [net.layer_output(p[node])[1] for net, p in zip(nets, plans)]
+            if t > 0:
+                assert np.array_equal(to_np(views[0].mask), to_np(views[1].mask)), f"frame {t} node {node}: mask"
+            a, b = (net.layer_state(p[node], 0) for net, p in zip(nets, plans))
+            if a is not None and b is not None:
+                assert np.array_equal(to_np(a), to_np(b)), f"frame {t} node {node}: buffer"
+        if t > 0:
+            for s0, s1 in zip(nets[0].stats(), nets[1].stats()):
+                for key in ("pixels_in", "pixels_in2", "pixels_work", "pixels_out"):
+                    assert s0[key] == s1[key], f"frame {t}: {key} of a layer of kind {s0['kind']}: {s0[key]} and {s1[key]}"
