@@ -11,7 +11,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIBDIR = os.path.join(HERE, "lib")
 LIB = os.path.join(LIBDIR, "libdeltacnn.so")
 SOURCES = [("ctx.hip", "ctx.o", []), ("mask_kernels.hip", "mask_kernels.o", []), ("tile_kernels.hip", "tile_kernels.o", []),
-           ("conv_kernels.hip", "conv_kernels.o", []), ("conv_first.hip", "conv_first.o", []), ("layer.hip", "layer.o", []), ("net.hip", "net.o", [])]
+           ("conv_kernels.hip", "conv_kernels.o", []), ("conv_first.hip", "conv_first.o", []), ("conv_unit.hip", "conv_unit.o", []), ("layer.hip", "layer.o", []), ("net.hip", "net.o", [])]
 # the MFMA convolution kernels: one object per (element type, accumulator block count), built in parallel
 for _t, _tn in (("f16", "f16"), ("float", "f32")):
     for _nb in (4, 3, 2, 1):

@@ -205,6 +205,8 @@ bool conv_supported(const dcnn_ctx* ctx, int dtype, int k, int cin, int cout, in
 bool conv_ws_supported(const dcnn_ctx* ctx, int dtype, int k, int cin, int cout, int64_t in_elems, int64_t out_elems);
 bool conv_proj_supported(const dcnn_ctx* ctx, int dtype, int k, int cin, int cin2, int cout, int64_t in_elems,
                          int64_t in2_elems, int64_t out_elems);
+// Maps on which layers with streamed weights run one wave per (tile, channel block) (conv_unit.hip).
+constexpr int64_t kUnitMaxPixels = 16384;
 // Can the sparse steps of this convolution build their work list in the kernel?  (LDS room in every kernel that may serve them.)
 bool conv_self_fits(const dcnn_ctx* ctx, int dtype, int k, int cin, int cout, bool fused, int cin2, int64_t in_px, int64_t out_px,
                     bool want_taps);

@@ -137,6 +137,9 @@ DCNN_DECL_ALL(f32)
 #undef DCNN_DECL
 // conv_first.hip
 bool conv_first_supported(int dtype, const ConvArgs& c, int cout, bool flat);
+// conv_unit.hip
+bool conv_unit_supported(const dcnn_ctx* ctx, int dtype, const ListArgs& l, const ConvArgs& c, const EpilogueArgs& e, const ConvPlan& p);
+dcnn_status launch_conv_unit(dcnn_ctx* ctx, int dtype, const ListArgs& l, const ConvArgs& c, const EpilogueArgs& e, const ConvPlan& p);
 dcnn_status launch_conv_first(dcnn_ctx* ctx, int dtype, const ConvArgs& c, const EpilogueArgs& e, const ConvPlan& p, const void* bias2);
 
 dcnn_status launch_conv(dcnn_ctx* ctx, int dtype, bool init, const ListArgs& l, const ConvArgs& c_in,
@@ -157,6 +160,7 @@ dcnn_status launch_conv(dcnn_ctx* ctx, int dtype, bool init, const ListArgs& l, 
     // The dense first frame over 16-byte pixels and channel vectors (tensors below 2 GiB) splits over channels as well as
     // pixels; everything else of a first frame stays with the plain kernel.
     if (init && p.w_bytes <= kWsMaxBytes && conv_first_supported(dtype, c, c.cout, p.flat)) return launch_conv_first(ctx, dtype, c, e, p, c.bias2);
+    if (!init && conv_unit_supported(ctx, dtype, l, c, e, p)) return launch_conv_unit(ctx, dtype, l, c, e, p);
     if (init && c.in2_data) return fail(ctx, DCNN_EUNSUPPORTED, "first frame of a convolution with a fused projection: shape not covered");
 #define DCNN_CASE(NB) case NB: return dtype == DCNN_F16 ? launch_conv_f16_nb##NB(ctx, init, l, c, e, p) : launch_conv_f32_nb##NB(ctx, init, l, c, e, p);
     switch (p.nb) {

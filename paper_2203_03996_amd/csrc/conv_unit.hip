@@ -1,0 +1,235 @@
+// Sparse delta convolution on small maps with weights too large for LDS: one wave per (pixel tile, 32 output channels).
+//
+// The deep layers of a backbone multiply a few hundred listed pixels with megabytes of weights.  What sets the pace there
+// is the vector memory path of the compute units that take part: ~70 GB/s each (a 1 KB load instruction occupies it for
+// ~35 clocks whether its lines hit or not), so a 3x3 512->512 layer on 16 tiles that ran on 32 workgroups of four waves,
+// each pulling 0.9 MB, took 54 us.  Here the work is cut as fine as it goes without splitting a sum -- the order of
+// every sum is that of the other kernels, so a stream gives the same bits whichever kernel its batch size selects --
+// and spread over the chip: unit u = (tile u / G, channel group u % G), and since workgroup b runs on XCD b % 8, a group's
+// weights are fetched into the L2 of one XCD only (of 8 / G, for fewer than 8 groups).
+//
+// Layers without an activation only: a decision needs all channels of a pixel.  (Groups that leave their sums in memory and
+// a tail done by the last of a tile to arrive were built: the device-scope release and acquire that it takes cost
+// ~15 us a layer, 3x3 256->256 44 us against 32 in one workgroup.)
+#include "conv_plan.h"
+#include "self_list.h"
+
+namespace dcnn {
+
+constexpr int kUnitGroup = 8;                                  // K-steps whose operands are requested together
+constexpr int kUnitMaxWaves = 4;
+
+struct UnitArgs {
+    int nb;                        // column blocks per packed channel group (the layer's plan)
+    int blocks;                    // 32-channel blocks of the output
+    int groups;                    // groups of one block per wave of the workgroup
+    uint32_t map_bytes, out_pixels;
+};
+
+// LDS: staging rows per wave | flags and prefix sums of a list built here
+constexpr int kUnitStageRow(int es) { return 32 * es + kStagePad; }
+inline size_t unit_stage_bytes(int waves, int dtype) { return (size_t)waves * kTile * kUnitStageRow((int)dtype_size(dtype)); }
+
+template <typename T, int KS>
+__global__ __launch_bounds__(kUnitMaxWaves* kWave) void conv_unit_kernel(ListArgs l, ConvArgs c, EpilogueArgs e, UnitArgs a) {
+    typedef typename Mma<T>::Vec Vec;
+    constexpr int V = Elem<T>::VEC;
+    typedef typename RawOf<T, V>::type Raw;
+    constexpr int ES = (int)sizeof(T);
+    constexpr int kNoTap = 31;
+    constexpr int stage_row = kUnitStageRow(ES);
+    extern __shared__ __align__(16) unsigned char smem[];
+    clear_ahead(e);
+
+    const int lane = threadIdx.x % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int nwaves = blockDim.x / kWave;
+    const int col = lane % 32, g = lane / 32;
+    unsigned char* stage = smem + (size_t)wave * kTile * stage_row;
+
+    int count;
+    SelfBits sb;
+    if (l.self) {
+        sb = self_carve(l, smem + l.lds_scratch);
+        // (the workgroup's size is a launch parameter here: the list code is written for a fixed number of threads)
+        if (nwaves == 1) count = self_build<kWave>(l, sb, nullptr);
+        else if (nwaves == 2) count = self_build<2 * kWave>(l, sb, nullptr);
+        else count = self_build<4 * kWave>(l, sb, nullptr);
+        if (nwaves == 1) self_emit<kWave>(l, sb, count, SelfSpan{0, 0, 1, 1}, nullptr, nullptr);
+        else if (nwaves == 2) self_emit<2 * kWave>(l, sb, count, SelfSpan{0, 0, 1, 1}, nullptr, nullptr);
+        else self_emit<4 * kWave>(l, sb, count, SelfSpan{0, 0, 1, 1}, nullptr, nullptr);
+    } else {
+        count = (int)list_count(l);
+    }
+    const int ntiles = (count + kTile - 1) / kTile;
+    const int kch = c.kch, ksteps = KS * KS * kch, cols = a.nb * 32;
+    const int cin_bytes = c.cin * ES;
+    const __amdgpu_buffer_rsrc_t rs_in = ws_rsrc(c.in_data, (uint64_t)c.n * c.h * c.w * cin_bytes);
+    const __amdgpu_buffer_rsrc_t rs_w = ws_rsrc(c.wpacked, (uint64_t)(c.cout_pad / cols) * ksteps * 2 * cols * 16);
+    const __amdgpu_buffer_rsrc_t rs_out = ws_rsrc(e.out_data, a.map_bytes), rs_res = ws_rsrc(e.res_data, a.map_bytes);
+    const __amdgpu_buffer_rsrc_t rs_rmask = ws_rsrc(e.res_mask, a.out_pixels);
+    const bool whole_groups = kch % kUnitGroup == 0 && kch * 32 == cin_bytes;   // no K-step of a group reaches past the pixel's channels
+    const uint32_t wstride = (uint32_t)(2 * cols * 16);        // weights of one K-step
+    const uint32_t row_bytes = (uint32_t)e.c * ES;
+
+    for (int u = blockIdx.x; u < ntiles * a.groups; u += gridDim.x) {
+        const int tile = u / a.groups;
+        const int cb = (u - tile * a.groups) * nwaves + wave;  // this wave's channel block
+        const bool cb_on = cb < a.blocks;
+        const int j = tile * kTile + col;
+        int p = -1;
+        uint32_t taps = 0;
+        if (j < count) {
+            if (l.self) {
+                p = self_select(sb, j);
+                taps = l.want_taps ? self_taps(l, sb.ibits, sb.in_words, p) : 1u;
+            } else {
+                p = l.list ? l.list[j] : j;
+                taps = l.taps ? l.taps[j] & ((1u << (KS * KS)) - 1u) : 1u;
+            }
+        }
+        const int rflag = e.res_mask ? __builtin_amdgcn_raw_buffer_load_b8(rs_rmask, p >= 0 ? p : (int)kOob, 0, 0) : 1;
+        uint32_t base;                                         // this lane's 16 bytes of tap (0,0), K-step 0
+        {
+            const uint32_t pu = p >= 0 ? (uint32_t)p : 0u;
+            const uint32_t t1 = fast_div(pu, c.div_ow);
+            const int ox = (int)(pu - t1 * (uint32_t)c.ow);
+            const uint32_t n = fast_div(t1, c.div_oh);
+            const int oy = (int)(t1 - n * (uint32_t)c.oh);
+            base = (uint32_t)(((int)n * c.h + oy * c.stride - c.pad) * c.w + ox * c.stride - c.pad) * (uint32_t)cin_bytes + (uint32_t)g * 16u;
+        }
+        uint32_t wave_taps = 0;                                // taps any lane of the wave needs
+#pragma unroll
+        for (int t = 0; t < KS * KS; ++t)
+            if (__ballot((taps >> t) & 1)) wave_taps |= 1u << t;
+        const uint32_t wlane = ((uint32_t)(cb_on ? cb / a.nb : 0) * (uint32_t)ksteps * 2u * (uint32_t)cols + (uint32_t)g * (uint32_t)cols +
+                                (uint32_t)(cb_on ? cb % a.nb : 0) * 32u + (uint32_t)col) * 16u;
+        f32x16 acc[1];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[0][i] = 0.0f;
+        // Groups of kUnitGroup K-steps of one tap, two register sets.  One wave per SIMD has its own instructions to wait for
+        // (4-8 clocks each), so a group's addresses are formed once: the gathers of its steps differ by an immediate, the
+        // weights by a scalar offset.  With a cursor advanced and an address formed per step the loop took 310 clocks a
+        // step, whatever the memory did (requesting all lines ahead, by either operand, changed nothing).
+        struct Cur { uint32_t rest; int t, kg; };
+        const int kgroups = (kch + kUnitGroup - 1) / kUnitGroup;
+        auto advance = [&](Cur& q) __attribute__((always_inline)) {
+            if (++q.kg == kgroups) {
+                q.kg = 0;
+                q.rest &= q.rest - 1;
+                q.t = q.rest ? __builtin_ctz(q.rest) : kNoTap;
+            }
+        };
+        struct Set { Vec x[kUnitGroup], w[kUnitGroup]; };
+        // Every load is issued unconditionally: a lane whose tap is not flagged, channel padding and groups past the end
+        // read zeros from an offset outside the descriptor.
+        auto issue = [&](const Cur& q, Set& st) __attribute__((always_inline)) {
+            const bool live = q.t != kNoTap;
+            const int t = live ? q.t : 0;
+            const int dy = t / KS, dx = t - dy * KS;
+            uint32_t off = (live && ((taps >> t) & 1u)) ? base + (uint32_t)((dy * c.w + dx) * cin_bytes + q.kg * (kUnitGroup * 32)) : kOob;
+            asm volatile("" : "+v"(off));                      // one load at a computed offset, not a load per case
+            uint32_t wstep = (uint32_t)(t * kch + q.kg * kUnitGroup) * wstride;
+            if (whole_groups) {
+#pragma unroll
+                for (int i = 0; i < kUnitGroup; ++i) {
+                    st.x[i] = ws_load16<Vec>(rs_in, off + (uint32_t)i * 32u);
+                    st.w[i] = ws_load16<Vec>(rs_w, wlane, wstep);
+                    wstep += wstride;
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < kUnitGroup; ++i) {
+                    const int kc = q.kg * kUnitGroup + i;
+                    st.x[i] = ws_load16<Vec>(rs_in, (2 * kc + g) * 16 < cin_bytes ? off + (uint32_t)i * 32u : kOob);
+                    st.w[i] = ws_load16<Vec>(rs_w, wlane, wstep);
+                    if (kc + 1 < kch) wstep += wstride;        // (a step past the last one repeats its weights and meets zeros)
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto mma = [&](const Set& st) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < kUnitGroup; ++i) Mma<T>::run(acc[0], st.w[i], st.x[i]);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        if (cb_on && wave_taps) {
+            Set sa, sb2;
+            Cur cg{wave_taps, __builtin_ctz(wave_taps), 0};
+            int left = __popc(wave_taps) * kgroups;
+            issue(cg, sa); advance(cg);
+            while (left > 0) {
+                issue(cg, sb2); advance(cg);
+                mma(sa);
+                issue(cg, sa); advance(cg);
+                mma(sb2);
+                left -= 2;
+            }
+        }
+        // rounded sums -> staging rows -> the pixels' rows, 16 bytes per lane
+        stage_accumulators<T, 1>(acc, stage + (size_t)col * stage_row, g);
+        lds_wave_sync();
+        constexpr int LPB = 32 / V;                            // lanes per pixel
+#pragma unroll
+        for (int it = 0; it < kTile * LPB / kWave; ++it) {
+            const int ent = it * (kWave / LPB) + lane / LPB, vi = lane % LPB;
+            const int pe = __shfl(p, ent, kWave), rf = __shfl(rflag, ent, kWave);
+            const int ch = cb * 32 + vi * V;
+            const uint32_t o = (pe >= 0 && cb_on && ch < e.c) ? (uint32_t)pe * row_bytes + (uint32_t)ch * ES : kOob;
+            Raw d = raw_load<T, V>(reinterpret_cast<const T*>(stage + (size_t)ent * stage_row) + vi * V);
+            if (e.res_data != nullptr) {
+                const Raw rr = ws_load16<Raw>(rs_res, rf ? o : kOob);
+#pragma unroll
+                for (int k = 0; k < V; ++k) raw_set<T, V>(d, k, raw_get<T, V>(d, k) + raw_get<T, V>(rr, k));
+            }
+            ws_store16<Raw>(rs_out, o, d);
+        }
+        lds_wave_sync();                                       // (the staging rows are free again)
+    }
+}
+
+// Fewer waves per workgroup (finer units) until the chip has two workgroups per compute unit.
+static int unit_waves(const dcnn_ctx* ctx, int64_t tiles, int blocks) {
+    int w = kUnitMaxWaves;
+    while (w > 1 && (w > blocks || tiles * cdiv(blocks, w) < 2 * (int64_t)ctx->num_cu)) w >>= 1;
+    return w;
+}
+
+bool conv_unit_supported(const dcnn_ctx*, int dtype, const ListArgs& l, const ConvArgs& c, const EpilogueArgs& e, const ConvPlan& p) {
+    const size_t es = dtype_size(dtype);
+    const int vec = dtype == DCNN_F16 ? 8 : 4;
+    if (!p.stream || p.flat || (c.k != 1 && c.k != 3) || e.c % vec != 0 || ((size_t)c.cin * es) % 16 != 0) return false;
+    if (e.act != DCNN_ACT_NONE || c.in2_data != nullptr || e.accum_O != nullptr || e.xt_flags != nullptr) return false;
+    if (!l.self && l.taps == nullptr && !(c.k == 1 && c.stride == 1 && l.list != nullptr)) return false;
+    const int64_t out_px = (int64_t)c.n * c.oh * c.ow;
+    return out_px <= kUnitMaxPixels && (uint64_t)c.n * c.h * c.w * c.cin * es <= kWsMaxBytes && (uint64_t)out_px * e.c * es <= kWsMaxBytes &&
+           p.w_bytes <= kWsMaxBytes;
+}
+
+template <typename T>
+static dcnn_status launch_conv_unit_t(dcnn_ctx* ctx, const ListArgs& l_in, const ConvArgs& c, const EpilogueArgs& e, const ConvPlan& p) {
+    ListArgs l = l_in;
+    const int dtype = sizeof(T) == 2 ? DCNN_F16 : DCNN_F32;
+    const int64_t out_px = (int64_t)c.n * c.oh * c.ow, tiles = cdiv(out_px, kTile);
+    UnitArgs a{};
+    a.nb = p.nb;
+    a.blocks = (int)cdiv(e.c, 32);
+    const int waves = unit_waves(ctx, tiles, a.blocks);
+    a.groups = (int)cdiv(a.blocks, waves);
+    a.map_bytes = (uint32_t)((uint64_t)out_px * e.c * sizeof(T));
+    a.out_pixels = (uint32_t)out_px;
+    const int64_t want = tiles * a.groups, cap = (int64_t)ctx->num_cu * 8;
+    const int grid = (int)(cdiv(want < cap ? want : cap, kXcd) * kXcd);
+    size_t lds = unit_stage_bytes(waves, dtype);
+    if (l.self) { l.lds_scratch = (int)lds; lds += self_scratch_bytes(l.m_in_px, l.m_out_px); }
+    const dim3 g(grid), b(waves * kWave);
+    if (c.k == 1) hipLaunchKernelGGL((conv_unit_kernel<T, 1>), g, b, lds, ctx->stream, l, c, e, a);
+    else hipLaunchKernelGGL((conv_unit_kernel<T, 3>), g, b, lds, ctx->stream, l, c, e, a);
+    return check_hip(ctx, hipGetLastError(), "conv_unit_kernel launch");
+}
+
+dcnn_status launch_conv_unit(dcnn_ctx* ctx, int dtype, const ListArgs& l, const ConvArgs& c, const EpilogueArgs& e, const ConvPlan& p) {
+    return dtype == DCNN_F16 ? launch_conv_unit_t<f16>(ctx, l, c, e, p) : launch_conv_unit_t<float>(ctx, l, c, e, p);
+}
+
+}  // namespace dcnn

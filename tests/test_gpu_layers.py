@@ -938,3 +938,42 @@ def test_mask_compact_on_words_of_flags(n, h, w, k, stride, pad, second):
     flat = np.flatnonzero(want.reshape(-1))
     assert int(to_np(count)[0]) == flat.size
     assert np.array_equal(to_np(idx)[:flat.size], flat)
+
+
+@pytest.mark.parametrize("S,k,stride,cin,cout,nhw,res", [
+    ("f16", 3, 1, 256, 512, (2, 8, 9), False),       # whole groups of K-steps, 16 channel blocks
+    ("f16", 1, 1, 520, 776, (3, 7, 11), False),      # a K-step past the pixel's channels, a block of 8 channels
+    ("f16", 3, 2, 136, 1032, (1, 13, 15), False),    # nine K-steps per tap, stride 2 on odd sizes
+    ("f16", 1, 1, 1024, 512, (2, 5, 6), True),       # residual without an activation
+    ("f32", 3, 1, 132, 260, (1, 9, 10), False),
+    ("f32", 1, 2, 512, 516, (2, 12, 7), False),
+])
+def test_conv_per_channel_block(S, k, stride, cin, cout, nhw, res):
+    """Weights too large for LDS on a small map, no activation: a wave per (tile, 32 channels)."""
+    n, h, w = nhw
+    pad = k // 2
+    rng = np.random.default_rng(cin + cout)
+    dt = NP_DTYPE[S]
+    wgt = (rng.standard_normal((k, k, cin, cout)) * np.sqrt(2.0 / (k * k * cin))).astype(dt)
+    conv = orc.Conv(wgt, None, stride, pad, False, S)
+    x0 = np.zeros((n, h, w, cin), dt)
+    y0 = np.asarray(conv.init(x0))
+    ctx = pkg.Context(n * h * w)
+    layer = pkg.Layer(ctx, pkg.make_desc(pkg.CONV, DT[S], n, h, w, cin, k=k, stride=stride, pad=pad, cout=cout, n_in=2 if res else 1),
+                      torch.from_numpy(wgt).cuda(), None)
+    layer.init([torch.from_numpy(a).cuda() for a in [x0] + ([np.zeros_like(y0)] if res else [])])
+    for dens in (0.05, 0.6, 1.0, 0.0):
+        d = _rand_delta(rng, (n, h, w, cin), dens, S)
+        want = conv.step(d)
+        slack = sum_slack(conv, d.zero_filled())
+        ins = [_upload(d)]
+        if res:
+            r = _rand_delta(rng, y0.shape, 0.4, S)
+            ins.append(_upload(r))
+            base = np.where(want.mask[..., None] == 1, np.nan_to_num(want.data), dt(0))
+            total = (base.astype(np.float64) + r.zero_filled().astype(np.float64)).astype(dt)
+            slack = slack + ulp(base, S)
+            want = ODelta(total, want.mask | r.mask)
+        out = layer.step(ins)
+        ctx.sync()
+        check_delta(out, want.poisoned(), S, f"density {dens}", slack=slack)
