@@ -291,6 +291,69 @@ __global__ __launch_bounds__(kMaskThreads) void mask_pass_kernel(MaskKernelArgs 
     }
 }
 
+// Mask pass for square windows from 5x5 on (any stride and padding): the input flags a chunk of outputs can see are a
+// contiguous run of the input mask -- whole rows of one or a few streams -- so the workgroup packs that run into bits in
+// LDS (16-byte loads, one round trip), and a window row of a pixel is one shifted word, masked by the columns that exist.
+// Byte by byte, the k*k dependent loads of a pixel took the 7x7 stride-2 stem of 8 256x256 streams 51 us (TBD), a 5x5
+// window on 60 K pixels 31 us (TBD for mask and list).
+constexpr int kSpanWords = 2048;                               // input flags a workgroup has room for, in words of 32
+__global__ __launch_bounds__(kMaskThreads) void mask_span_kernel(MaskKernelArgs a, FastDiv div_ow, FastDiv div_oh) {
+    __shared__ int s_red[kMaskThreads / kWave];
+    __shared__ uint32_t s_bits[kSpanWords];
+    const int in_px = a.n * a.h * a.w, out_px = (int)a.out_pixels;
+    auto row_of = [&](int p, int& n, int& oy, int& ox) {
+        const uint32_t t1 = fast_div((uint32_t)p, div_ow);
+        ox = p - (int)t1 * a.ow;
+        n = (int)fast_div(t1, div_oh);
+        oy = (int)t1 - n * a.oh;
+    };
+    const int c0 = blockIdx.x * kChunk, c1 = min(c0 + kChunk, out_px) - 1;
+    int n0, oy0, ox0, n1, oy1, ox1;
+    row_of(c0, n0, oy0, ox0);
+    row_of(c1, n1, oy1, ox1);
+    const int first_row = max(oy0 * a.stride - a.pad, 0), last_row = min(oy1 * a.stride - a.pad + a.k - 1, a.h - 1);
+    const int base = (n0 * a.h + first_row) * a.w & ~31;        // (the host has checked that the run fits, span_fits)
+    const int words = ((n1 * a.h + last_row + 1) * a.w - base + 31) / 32;
+    for (int w = threadIdx.x; w < words; w += kMaskThreads) s_bits[w] = self_mask_word(a.mask_in + base, w, in_px - base);
+    __syncthreads();
+    const int p0 = c0 + (int)threadIdx.x * kPxPerThread;
+    uint64_t word = 0;
+    if (p0 < out_px) {
+        int n, oy, ox;
+        row_of(p0, n, oy, ox);
+        for (int i = 0; i < kPxPerThread && p0 + i < out_px; ++i) {
+            const int iy0 = oy * a.stride - a.pad, ix0 = ox * a.stride - a.pad;
+            uint32_t cols = (1u << a.k) - 1u;                  // window columns inside the map
+            if (ix0 < 0) cols &= ~((1u << -ix0) - 1u);
+            if (ix0 + a.k > a.w) cols &= (1u << (a.w - ix0)) - 1u;
+            uint32_t any = 0;
+            const int y0 = max(iy0, 0), y1 = min(iy0 + a.k, a.h);
+            for (int iy = y0; iy < y1; ++iy) any |= self_bits32(s_bits, words, (n * a.h + iy) * a.w + ix0 - base) & cols;
+            bool f = any != 0;
+            if (a.mask_b && mask_b_flag(a.mask_b, p0 + i, a.b_stride, a.b_h, a.b_w, a.oh, a.ow)) f = true;
+            word |= (uint64_t)(f ? 1 : 0) << (8 * i);
+            if (++ox == a.ow) { ox = 0; if (++oy == a.oh) { oy = 0; ++n; } }
+        }
+        if (p0 + kPxPerThread <= out_px) *reinterpret_cast<uint64_t*>(a.mask_out + p0) = word;
+        else for (int i = 0; p0 + i < out_px; ++i) a.mask_out[p0 + i] = (uint8_t)((word >> (8 * i)) & 1);
+    }
+    const int total = block_sum(__popcll(word), s_red);
+    if (threadIdx.x == 0) {
+        a.chunk_counts[blockIdx.x] = total;
+        if (blockIdx.x == 0 && a.zero_count) *a.zero_count = 0;
+    }
+}
+// The longest run a chunk's windows can see, in rows of the input: the chunk's output rows (one more than fit, cut at both
+// ends) times the stride, the window, and at every border between streams the rows that no window starts in.
+static bool span_fits(const MaskKernelArgs& a) {
+    if (a.kw != a.k || a.pad_w != a.pad || a.up != 1 || a.k < 5 || a.k > 15) return false;
+    if (reinterpret_cast<uintptr_t>(a.mask_in) % 16 != 0 || a.out_pixels > INT32_MAX / 2 || (int64_t)a.n * a.h * a.w > INT32_MAX / 2) return false;
+    const int64_t out_rows = kChunk / a.ow + 2;
+    const int64_t borders = out_rows / a.oh + 1;
+    const int64_t rows = out_rows * a.stride + 2 * a.k + borders * (2 * a.k + a.stride);
+    return (rows < (int64_t)a.n * a.h ? rows : (int64_t)a.n * a.h) * a.w + 64 <= 32 * (int64_t)kSpanWords;
+}
+
 struct EmitArgs {
     const uint8_t* mask;
     const int32_t* chunk_counts;
@@ -537,7 +600,7 @@ static dcnn_status mask_compact_on(dcnn_ctx* ctx, const MaskPassArgs& m, const W
         return check_hip(ctx, hipGetLastError(), "mask_list_kernel launch");
     }
     // one launch for small maps; large maps keep the two passes
-    const bool fused = !m.emit_only && m.idx_out != nullptr && nchunks <= kFusedMaxChunks;
+    bool fused = !m.emit_only && m.idx_out != nullptr && nchunks <= kFusedMaxChunks;
     MaskKernelArgs a{};
     if (!m.emit_only) {
         a.mask_in = m.mask_in; a.mask_b = m.mask_b;
@@ -551,7 +614,13 @@ static dcnn_status mask_compact_on(dcnn_ctx* ctx, const MaskPassArgs& m, const W
         a.bilinear = m.bilinear;
         a.b_stride = m.b_stride; a.b_h = m.b_h; a.b_w = m.b_w;
         a.kw = m.kw > 0 ? m.kw : m.k; a.pad_w = m.kw > 0 ? m.pad_w : m.pad;
-        if (!fused) {
+        if (span_fits(a)) fused = false;                       // (window taps byte by byte cost more than a second launch)
+        if (!fused && span_fits(a)) {
+            hipLaunchKernelGGL(mask_span_kernel, dim3(nchunks), dim3(kMaskThreads), 0, ctx->stream, a, make_fastdiv((uint32_t)m.ow),
+                               make_fastdiv((uint32_t)m.oh));
+            st = check_hip(ctx, hipGetLastError(), "mask_span_kernel launch");
+            if (st != DCNN_OK) return st;
+        } else if (!fused) {
             hipLaunchKernelGGL(mask_pass_kernel, dim3(nchunks), dim3(kMaskThreads), 0, ctx->stream, a);
             st = check_hip(ctx, hipGetLastError(), "mask_pass_kernel launch");
             if (st != DCNN_OK) return st;

@@ -940,6 +940,26 @@ def test_mask_compact_on_words_of_flags(n, h, w, k, stride, pad, second):
     assert np.array_equal(to_np(idx)[:flat.size], flat)
 
 
+@pytest.mark.parametrize("n,h,w", [(1, 5, 9), (3, 37, 53), (40, 9, 7), (2, 96, 130), (1, 3, 9000), (1, 12, 8000)])
+@pytest.mark.parametrize("k,stride,pad", [(5, 1, 2), (7, 2, 3), (5, 2, 0), (7, 1, 6), (9, 1, 4)])
+def test_mask_compact_wide_windows(n, h, w, k, stride, pad):
+    """Windows from 5x5 on: chunks that start and end within rows, cross several streams, and (8000 wide) runs of input
+    flags that do not fit a workgroup's room."""
+    if h + 2 * pad < k or w + 2 * pad < k:
+        pytest.skip("window larger than the map")
+    rng = np.random.default_rng(n + h + w)
+    mask = (rng.random((n, h, w)) < 0.01).astype(np.uint8)
+    mask[:, -1, 0] = 1
+    want = orc.window_mask(mask, k, stride, pad)
+    ctx = pkg.Context(max(mask.size, want.size))
+    got, idx, count = ctx.mask_compact(torch.from_numpy(mask).cuda(), k, stride, pad)
+    ctx.sync()
+    assert np.array_equal(to_np(got), want)
+    flat = np.flatnonzero(want.reshape(-1))
+    assert int(to_np(count)[0]) == flat.size
+    assert np.array_equal(to_np(idx)[:flat.size], flat)
+
+
 @pytest.mark.parametrize("S,k,stride,cin,cout,nhw,res", [
     ("f16", 3, 1, 256, 512, (2, 8, 9), False),       # whole groups of K-steps, 16 channel blocks
     ("f16", 1, 1, 520, 776, (3, 7, 11), False),      # a K-step past the pixel's channels, a block of 8 channels
