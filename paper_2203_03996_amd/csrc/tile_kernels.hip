@@ -646,7 +646,9 @@ static dcnn_status launch_dwconv_t(dcnn_ctx* ctx, bool init, const ListArgs& l_i
     if (!init && vec && vpl <= 4 && c.k >= 1 && c.k <= 3 && map_bytes > 0 && map_bytes <= kWsMaxBytes && in_bytes <= kWsMaxBytes &&
         w_bytes <= 64 * 1024) {
         const int vpl_used = vpl <= 1 ? 1 : (vpl <= 2 ? 2 : 4);
-        const int ub = 4 / vpl_used;
+        // (nine taps per pixel and vector: half the iterations in flight, or the registers leave one wave per SIMD.  8 streams,
+        // 192 channels on 100 K pixels 31 -> 18.5 us, on 25 K 21.4 -> 19.3, 384 on 6 K 34 -> 24.6)
+        const int ub = c.k == 3 ? (vpl_used == 1 ? 2 : 1) : 4 / vpl_used;
         const TailShape shape = tail_shape(nvec, vpl_used, ub);
         const int sgrid = list_grid(ctx, l.max_count, kTileWaves * shape.run, l.self ? kSelfWgPerCu : 8);
         const size_t lds = tile_list_lds(l, w_bytes, kTileWaves * shape.run, sgrid, true);
@@ -654,7 +656,7 @@ static dcnn_status launch_dwconv_t(dcnn_ctx* ctx, bool init, const ListArgs& l_i
 #define DCNN_DW_SPARSE(VPL, UB, KS) hipLaunchKernelGGL((dwconv_sparse_kernel<T, VEC, VPL, UB, KS>), dim3(sgrid), dim3(kTileThreads), lds, ctx->stream, l, c, e, shape, ib, ip, mb, px)
 #define DCNN_DW_SPARSE_K(VPL, UB)                                                                                  \
     do {                                                                                                           \
-        if (c.k == 3) DCNN_DW_SPARSE(VPL, UB, 3);                                                                  \
+        if (c.k == 3) DCNN_DW_SPARSE(VPL, (VPL == 1 ? 2 : 1), 3);                                                  \
         else if (c.k == 2) DCNN_DW_SPARSE(VPL, UB, 2);                                                             \
         else DCNN_DW_SPARSE(VPL, UB, 1);                                                                           \
     } while (0)
