@@ -161,6 +161,23 @@ constexpr int64_t kSelfMaxPixels = 16384;
 inline size_t self_scratch_bytes(int64_t in_px, int64_t out_px) {
     return align_up(128 + 4 * (size_t)(2 * cdiv(in_px, 32) + cdiv(out_px, 32)) + 2 * (size_t)cdiv(out_px, 32), 16);
 }
+// How a list is cut into groups of entries and the groups are dealt out.  Kernels walk by these rules and launchers size the
+// room of lists built in place by them, so there is one of each.  Activation and depthwise kernels walk whole tiles -- every
+// part of a survivor word gets written -- and may own up to three groups of eight entries behind a list's last one.
+constexpr int kTileWaves = 4;                                  // waves per workgroup of the activation and depthwise kernels
+constexpr int kWideRun = 8;                                    // entries per workgroup and step of act_wide_kernel (a quarter tile)
+__host__ __device__ inline int64_t wide_groups(int64_t count) { return (count + kTile - 1) / kTile * (kTile / kWideRun); }
+__host__ __device__ inline int64_t run_groups(int64_t count, int run) {        // kTileWaves runs of `run` entries
+    return ((count + kTile - 1) / kTile * (kTile / run) + kTileWaves - 1) / kTileWaves;
+}
+// Groups begin, begin + step, ... below end are workgroup `block`'s: consecutive groups stay on one XCD and share its L2
+// (workgroup b runs on XCD b % 8; an XCD owns a contiguous range, its workgroups stride through it).
+struct WgTileRange { int64_t begin, end, step; };
+__host__ __device__ inline WgTileRange tile_range(int64_t groups, uint32_t block, uint32_t grid) {
+    const int64_t per = (groups + kXcd - 1) / kXcd, xcd = block % kXcd;
+    const int64_t end = (xcd + 1) * per;
+    return {xcd * per + block / kXcd, end < groups ? end : groups, grid / kXcd};
+}
 // entries of the groups that one workgroup of `grid` owns at most (tile ranges per XCD, or a plain stride over the grid)
 inline int64_t self_local_entries(int64_t out_px, int64_t entries_per_group, int grid, bool per_xcd) {
     const int64_t groups = cdiv(out_px, entries_per_group);

@@ -62,21 +62,8 @@ __device__ __forceinline__ int64_t list_count(const ListArgs& l) {
     return l.count ? (int64_t)(*l.count) : l.count_host;
 }
 
-// Work-list tiles are handed out so that consecutive tiles (neighbouring pixels) stay on one
-// XCD and share its L2: workgroup b runs on XCD b % 8; XCD x owns a contiguous range of
-// workgroup-tiles and its workgroups stride through that range.
-struct WgTileRange {
-    int64_t begin, end, step;
-};
-__device__ __forceinline__ WgTileRange wg_tile_range(int64_t n_wg_tiles) {
-    const int xcd = blockIdx.x % kXcd, slot = blockIdx.x / kXcd, nslots = gridDim.x / kXcd;
-    const int64_t per = (n_wg_tiles + kXcd - 1) / kXcd;
-    WgTileRange r;
-    r.begin = (int64_t)xcd * per + slot;
-    r.end = min((int64_t)(xcd + 1) * per, n_wg_tiles);
-    r.step = nslots;
-    return r;
-}
+// this workgroup's share of the work list's tiles
+__device__ __forceinline__ WgTileRange wg_tile_range(int64_t n_wg_tiles) { return tile_range(n_wg_tiles, blockIdx.x, gridDim.x); }
 
 __device__ __forceinline__ uint32_t fast_div(uint32_t n, const FastDiv& f) {
     return (__umulhi(n, f.m) + n) >> f.s;

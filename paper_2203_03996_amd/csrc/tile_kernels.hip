@@ -8,7 +8,6 @@
 
 namespace dcnn {
 
-constexpr int kTileWaves = 4;                       // waves (tiles) per workgroup
 constexpr int kTileThreads = kTileWaves * kWave;
 constexpr int kSelfWgPerCu = 4;                     // workgroups per compute unit that each build the list: more repeat the work more often
 
@@ -32,12 +31,13 @@ __device__ __forceinline__ const int32_t* tile_list_emit(const ListArgs& l, unsi
     if (l.self) self_emit<kTileThreads>(l, sb, (int)count, SelfSpan{(int)begin, (int)end, (int)step, entries}, px, nullptr);
     return px;
 }
-// Dynamic LDS of such a launch behind `used` bytes of the kernel's own, and where the pieces lie.
-static size_t tile_list_lds(ListArgs& l, size_t used, int64_t entries, int grid, bool per_xcd) {
+// Dynamic LDS of such a launch behind `used` bytes of the kernel's own, and where the pieces lie.  `groups`: groups of `entries`
+// list entries that the kernel walks when every pixel is listed, counted by the kernel's own rule.
+static size_t tile_list_lds(ListArgs& l, size_t used, int64_t groups, int64_t entries, int grid, bool per_xcd) {
     if (!l.self) return used;
     l.lds_scratch = (int)align_up(used, 16);
     l.lds_list = l.lds_scratch + (int)self_scratch_bytes(l.m_in_px, l.m_out_px);
-    l.lds_entries = (int)self_local_entries(l.m_out_px, entries, grid, per_xcd);
+    l.lds_entries = (int)self_local_entries(groups * entries, entries, grid, per_xcd);
     return (size_t)l.lds_list + (size_t)l.lds_entries * 4;
 }
 
@@ -58,8 +58,7 @@ __global__ __launch_bounds__(kTileThreads) void act_sparse_kernel(ListArgs l, Ac
     src.in = ws_rsrc(a.in_data, map_bytes);
     const int parts = kTile / shape.run;
     int survivors = 0;
-    const int64_t ntiles = (count + kTile - 1) / kTile;
-    const WgTileRange r = wg_tile_range((ntiles * parts + kTileWaves - 1) / kTileWaves);
+    const WgTileRange r = wg_tile_range(run_groups(count, shape.run));
     const int32_t* self_px = tile_list_emit(l, list_smem, sb, count, r.begin, r.end, r.step, kTileWaves * shape.run);
     for (int64_t wt = r.begin; wt < r.end; wt += r.step, self_px += kTileWaves * shape.run) {
         const int64_t unit = wt * kTileWaves + wave;
@@ -89,7 +88,6 @@ __global__ __launch_bounds__(kTileThreads) void act_sparse_kernel(ListArgs l, Ac
 // waves of a workgroup split the CHANNELS of a run's pixels instead (one vector per lane and pixel), request all
 // 8 pixels at once -- one round trip -- and agree on the per-pixel maximum through LDS.  Arithmetic, rounding and
 // decisions are those of sparse_tile_tail (Section 3.1, Eqs. 4-6).  Channels a multiple of 4 vectors.
-constexpr int kWideRun = 8;                                     // list entries per workgroup unit (a quarter tile)
 
 template <typename T, int V, int VPW>
 __global__ __launch_bounds__(kTileThreads) void act_wide_kernel(ListArgs l, ActArgs a, EpilogueArgs e, uint32_t map_bytes, uint32_t pixels) {
@@ -112,8 +110,7 @@ __global__ __launch_bounds__(kTileThreads) void act_wide_kernel(ListArgs l, ActA
     const bool stateful = e.act != DCNN_ACT_NONE;
     const bool has_res = e.res_data != nullptr;
     const float hi = act_hi(e.act);
-    const int64_t ntiles = (count + kTile - 1) / kTile;
-    const int64_t units = ntiles * (kTile / kWideRun);
+    const int64_t units = wide_groups(count);
     int survivors = 0;
     int parity = 0;
     const int32_t* self_px = tile_list_emit(l, list_smem, sb, count, blockIdx.x, units, gridDim.x, kWideRun);
@@ -314,11 +311,11 @@ static dcnn_status launch_act_t(dcnn_ctx* ctx, bool init, const ListArgs& l_in, 
     // wide pixels on maps of at most 64 K pixels: the channels of a pixel are split over the waves of a workgroup
     if (vec && nvec >= 2 * kWave && nvec % kTileWaves == 0 && nvec <= kWave * kTileWaves && map_bytes > 0 &&
         map_bytes <= kWsMaxBytes && l.max_count <= 65536) {
-        const int64_t units = cdiv(l.max_count, kWideRun);
+        const int64_t units = wide_groups(l.max_count);
         const int64_t cap = (int64_t)ctx->num_cu * 8;
         const int wgrid = (int)(units < cap ? units : cap);
         const uint32_t mb = (uint32_t)map_bytes, px = (uint32_t)l.max_count;
-        const size_t lds = tile_list_lds(l, 0, kWideRun, wgrid, false);
+        const size_t lds = tile_list_lds(l, 0, wide_groups(l.max_count), kWideRun, wgrid, false);
         hipLaunchKernelGGL((act_wide_kernel<T, VEC, 1>), dim3(wgrid), dim3(kTileThreads), lds, ctx->stream, l, a, e, mb, px);
         return check_hip(ctx, hipGetLastError(), "act_wide_kernel launch");
     }
@@ -328,7 +325,7 @@ static dcnn_status launch_act_t(dcnn_ctx* ctx, bool init, const ListArgs& l_in, 
         const TailShape shape = tail_shape(nvec, vpl_used, ub);
         const int sgrid = list_grid(ctx, l.max_count, kTileWaves * shape.run, l.self ? kSelfWgPerCu : 8);
         const uint32_t mb = (uint32_t)map_bytes, px = (uint32_t)l.max_count;
-        const size_t lds = tile_list_lds(l, 0, kTileWaves * shape.run, sgrid, true);
+        const size_t lds = tile_list_lds(l, 0, run_groups(l.max_count, shape.run), kTileWaves * shape.run, sgrid, true);
 #define DCNN_ACT_SPARSE(VPL, UB) hipLaunchKernelGGL((act_sparse_kernel<T, VEC, VPL, UB>), dim3(sgrid), dim3(kTileThreads), lds, ctx->stream, l, a, e, shape, mb, px)
         if (vpl_used == 1) DCNN_ACT_SPARSE(1, 4);
         else if (vpl_used == 2) DCNN_ACT_SPARSE(2, 4);
@@ -442,8 +439,7 @@ __global__ __launch_bounds__(kTileThreads) void dwconv_sparse_kernel(ListArgs l,
     src.w_lds = w_lds; src.C = e.c; src.w = c.w; src.row_bytes = (uint32_t)e.c * (uint32_t)sizeof(T);
     const int parts = kTile / shape.run;
     int survivors = 0;
-    const int64_t ntiles = (count + kTile - 1) / kTile;
-    const WgTileRange r = wg_tile_range((ntiles * parts + kTileWaves - 1) / kTileWaves);
+    const WgTileRange r = wg_tile_range(run_groups(count, shape.run));
     const int32_t* self_px = tile_list_emit(l, dw_smem, sb, count, r.begin, r.end, r.step, kTileWaves * shape.run);
     for (int64_t wt = r.begin; wt < r.end; wt += r.step, self_px += kTileWaves * shape.run) {
         const int64_t unit = wt * kTileWaves + wave;
@@ -651,7 +647,7 @@ static dcnn_status launch_dwconv_t(dcnn_ctx* ctx, bool init, const ListArgs& l_i
         const int ub = c.k == 3 ? (vpl_used == 1 ? 2 : 1) : 4 / vpl_used;
         const TailShape shape = tail_shape(nvec, vpl_used, ub);
         const int sgrid = list_grid(ctx, l.max_count, kTileWaves * shape.run, l.self ? kSelfWgPerCu : 8);
-        const size_t lds = tile_list_lds(l, w_bytes, kTileWaves * shape.run, sgrid, true);
+        const size_t lds = tile_list_lds(l, w_bytes, run_groups(l.max_count, shape.run), kTileWaves * shape.run, sgrid, true);
         const uint32_t ib = (uint32_t)in_bytes, ip = (uint32_t)in_pixels, mb = (uint32_t)map_bytes, px = (uint32_t)l.max_count;
 #define DCNN_DW_SPARSE(VPL, UB, KS) hipLaunchKernelGGL((dwconv_sparse_kernel<T, VEC, VPL, UB, KS>), dim3(sgrid), dim3(kTileThreads), lds, ctx->stream, l, c, e, shape, ib, ip, mb, px)
 #define DCNN_DW_SPARSE_K(VPL, UB)                                                                                  \
@@ -1060,7 +1056,7 @@ dcnn_status launch_upsample(dcnn_ctx* ctx, int dtype, const ListArgs& l_in, cons
     if (l.self) {
         const int64_t want = cdiv(l.max_count, kUpRun), cap = (int64_t)ctx->num_cu * kSelfWgPerCu;
         const int grid = (int)(want < cap ? want : cap);
-        const size_t lds = tile_list_lds(l, 0, kUpRun, grid, false);
+        const size_t lds = tile_list_lds(l, 0, cdiv(l.max_count, kUpRun), kUpRun, grid, false);
         const bool vec = a.c % (dtype == DCNN_F16 ? 8 : 4) == 0;
 #define DCNN_UP_SELF(T, V) hipLaunchKernelGGL((upsample_kernel<T, V>), dim3(grid), dim3(256), lds, ctx->stream, l, a)
         if (dtype == DCNN_F16) { if (vec) DCNN_UP_SELF(f16, 8); else DCNN_UP_SELF(f16, 1); }

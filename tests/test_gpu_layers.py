@@ -186,6 +186,30 @@ def test_add_act(S, act, shape):
             assert np.array_equal(to_np(layer.state_tensor(1)), ract.xT)
 
 
+@pytest.mark.parametrize("S,c", [("f16", 1024), ("f16", 2048), ("f32", 512), ("f32", 1024)])
+@pytest.mark.parametrize("nhw", [(1, 1, 1), (1, 5, 13), (1, 7, 12), (2, 8, 8), (1, 11, 13), (4, 22, 22)])
+def test_wide_add_act_builds_its_list_on_any_pixel_count(S, c, nhw):
+    """The tile count is rounded up to whole tiles while the map ends inside one: 1, 65, 84, 128, 143 and 1936 pixels end 1, 1,
+    20, 32, 15 and 16 entries into their last tile, listed in full, in part and not at all."""
+    rng = np.random.default_rng(c + nhw[1])
+    n, h, w = nhw
+    shape, eps = (n, h, w, c), 0.4
+    radd, ract = orc.Add(S), orc.ActTrunc("relu", eps, S)
+    ctx = pkg.Context(n * h * w)
+    layer = pkg.Layer(ctx, pkg.make_desc(pkg.ACT, DT[S], n, h, w, c, act=pkg.ACT_RELU, eps=eps, n_in=2, want_idx=0))
+    dense = [rng.normal(0, 1, shape).astype(NP_DTYPE[S]) for _ in range(2)]
+    ract.init(radd.init(*dense))
+    layer.init([torch.from_numpy(a).cuda() for a in dense])
+    for t, (d0, d1) in enumerate([(1.0, 1.0), (0.2, 0.1), (0.97, 0.5), (0.0, 0.0), (1.0, 0.0)]):
+        da, db = _rand_delta(rng, shape, d0, S, 0.15), _rand_delta(rng, shape, d1, S, 0.15)
+        want = ract.step(radd.step(da, db).poisoned()).poisoned()
+        out = layer.step([_upload(da), _upload(db)])
+        ctx.sync()
+        check_delta(out, want, S, f"frame {t}", exact_values=True)
+        assert np.array_equal(to_np(layer.state_tensor(0)), ract.xA), f"frame {t}"
+        assert np.array_equal(to_np(layer.state_tensor(1)), ract.xT), f"frame {t}"
+
+
 # ---- convolution: linear (values within tolerance; masks and lists bit-exact) -------------------
 CONV_CASES = [
     # S, k, stride, pad, cin, cout, (n,h,w)
