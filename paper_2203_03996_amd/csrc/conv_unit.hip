@@ -39,8 +39,6 @@ __global__ __launch_bounds__(kUnitMaxWaves* kWave) void conv_unit_kernel(ListArg
     constexpr int kNoTap = 31;
     constexpr int stage_row = kUnitStageRow(ES);
     extern __shared__ __align__(16) unsigned char smem[];
-    clear_ahead(e);
-
     const int lane = threadIdx.x % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int nwaves = blockDim.x / kWave;

@@ -189,9 +189,8 @@ static void carve(dcnn_layer* L, void* state) {
             // A convolution or activation that walks its input's own list and truncates needs an output mask that is 0
             // wherever it does not write.  Instead of a mask pass per step it alternates between two masks, and
             // its kernel clears the one of the next step while it runs (clear_ahead).
-            // So does a layer that builds its list in its own kernel (which of the layers with a list of their own do is
-            // decided when the layer is created; the memory is there for all that could).
-            if (act && (own ? !d.want_idx : d.kind != DCNN_DWCONV))
+            // (A layer whose kernel builds the list writes the zeros itself, self_list.h, and uses the first of them only.)
+            if (act && !own && d.kind != DCNN_DWCONV)
                 L->out_mask_alt = static_cast<uint8_t*>(cv.take((size_t)L->out_pixels));
         }
         if (own) {
@@ -565,7 +564,7 @@ dcnn_status dcnn_layer_step(dcnn_layer* L, const dcnn_delta* const* in, int32_t 
     v.n = d.n; v.h = L->oh; v.w = L->ow; v.c = L->oc; v.dtype = d.dtype;
     v.data = d.fuse_accum ? L->buf2 : L->out_data;
     // (a layer with two output masks: this step writes one, which is all zero, and clears the other for the next step)
-    const bool alternates = L->out_mask_alt && (!own || L->self);
+    const bool alternates = L->out_mask_alt && !L->self;
     uint8_t* const mask_cur = (alternates && L->mask_phase) ? L->out_mask_alt : L->out_mask;
     uint8_t* const mask_next = alternates ? (L->mask_phase ? L->out_mask : L->out_mask_alt) : nullptr;
     v.mask = L->alias_mask ? in[0]->mask : mask_cur;
@@ -624,13 +623,16 @@ dcnn_status dcnn_layer_step(dcnn_layer* L, const dcnn_delta* const* in, int32_t 
         l.div_iw = make_fastdiv((uint32_t)d.w); l.div_ih = make_fastdiv((uint32_t)d.h);
         l.div_up = make_fastdiv((uint32_t)l.m_up);
         if (!act && own) { l.mask_out = L->out_mask; l.idx_out = L->out_idx; l.count_out = L->out_count; }
-        else if (act) l.count_out = own ? L->list_count : L->out_count;       // the list's length, for the statistics
+        else if (act) {
+            l.mask_zero = mask_cur;
+            l.count_out = own ? L->list_count : L->out_count;       // the list's length, for the statistics
+        }
     } else if (own || L->self) {
         // (a layer that would build its list itself but has to have one in memory this time: its own output list serves,
         // nobody walks that)
         MaskPassArgs m{};
         m.mask_in = in[0]->mask; m.mask_b = n_in == 2 ? in[1]->mask : nullptr;
-        m.mask_out = alternates ? nullptr : L->out_mask;
+        m.mask_out = L->out_mask;
         m.idx_out = own ? L->list : L->out_idx; m.count_out = own ? L->list_count : L->out_count;
         m.n = d.n; m.h = d.h; m.w = d.w; m.oh = L->oh; m.ow = L->ow;
         m.k = 1; m.stride = 1; m.pad = 0; m.up = 1; m.emit_only = 0;

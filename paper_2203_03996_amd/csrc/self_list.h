@@ -7,8 +7,9 @@
 // 16-byte loads), forms the flagged output pixels as bits (a 3x3 window on whole words), takes the prefix sums of the
 // words' counts -- the position of every pixel in the ascending list -- and keeps the entries of its own tiles.  The
 // tiles are those of the stored list (same order, same partition), so results do not depend on which form is used.
-// What other kernels need is written by the workgroups in shares: the output mask and, where the caller asked for it,
-// the ascending list and its length.
+// What other kernels need is written by the workgroups in shares: the output mask (of a layer that truncates: its zeros at
+// the pixels that are not listed, so that a step depends on nothing an earlier one left) and, where the caller asked for it, the
+// ascending list and its length.
 #pragma once
 
 #include "device_utils.h"
@@ -336,6 +337,13 @@ __device__ __forceinline__ void self_emit(const ListArgs& l, const SelfBits& s, 
                 const uint32_t v = (f & 1u) | (f & 2u) << 7 | (f & 4u) << 14 | (f & 8u) << 21;
                 if (i * 4 + 4 <= l.m_out_px) *reinterpret_cast<uint32_t*>(l.mask_out + i * 4) = v;
                 else for (int k = 0; i * 4 + k < l.m_out_px; ++k) l.mask_out[i * 4 + k] = (uint8_t)((f >> k) & 1u);
+            }
+        }
+        if (l.mask_zero != nullptr) {
+            for (int i = (int)blockIdx.x * per * 8 + tid; i < w1 * 8; i += NT) {     // (a listed pixel's byte is its tile's business)
+                const uint32_t f = (s.obits[i / 8] >> (4 * (i % 8))) & 15u;
+                if (f == 0 && i * 4 + 4 <= l.m_out_px) *reinterpret_cast<uint32_t*>(l.mask_zero + i * 4) = 0u;
+                else for (int k = 0; k < 4 && i * 4 + k < l.m_out_px; ++k) if (!((f >> k) & 1u)) l.mask_zero[i * 4 + k] = 0;
             }
         }
         if (l.idx_out != nullptr) {

@@ -425,7 +425,6 @@ __global__ __launch_bounds__(kTileThreads) void dwconv_sparse_kernel(ListArgs l,
         for (int i = threadIdx.x; i < nv; i += kTileThreads) reinterpret_cast<Raw*>(w_lds)[i] = wsrc[i];
     }
     __syncthreads();
-    clear_ahead(e);
     SelfBits sb;
     const int64_t count = tile_list_count(l, dw_smem, sb);
     const int lane = threadIdx.x % kWave;

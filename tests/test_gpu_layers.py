@@ -1021,3 +1021,50 @@ def test_conv_per_channel_block(S, k, stride, cin, cout, nhw, res):
         out = layer.step(ins)
         ctx.sync()
         check_delta(out, want.poisoned(), S, f"density {dens}", slack=slack)
+
+
+@pytest.mark.parametrize("S,kind,k,stride,cin,cout,nhw", [
+    ("f16", "conv", 3, 1, 32, 32, (1, 20, 23)),          # resident weights
+    ("f16", "conv", 3, 2, 64, 128, (2, 21, 18)),
+    ("f16", "conv", 3, 1, 256, 256, (1, 14, 15)),        # streamed weights
+    ("f32", "conv", 5, 1, 12, 20, (1, 17, 16)),          # plain kernel
+    ("f16", "dwconv", 3, 1, 96, 96, (2, 13, 17)),
+    ("f16", "add", 1, 1, 64, 64, (1, 19, 31)),
+    ("f16", "add", 1, 1, 1024, 1024, (1, 11, 13)),
+])
+def test_a_captured_step_of_a_layer_with_its_own_list_replays(S, kind, k, stride, cin, cout, nhw):
+    """One step recorded into a graph and replayed on changing inputs: each replay leaves mask, values and buffers of the same
+    step of an eager layer -- in particular no flag of an earlier replay."""
+    n, h, w = nhw
+    rng = np.random.default_rng(cin + h)
+    dt, n_in = NP_DTYPE[S], 2 if kind == "add" else 1
+    code = {"conv": pkg.CONV, "dwconv": pkg.DWCONV, "add": pkg.ACT}[kind]
+    desc = pkg.make_desc(code, DT[S], n, h, w, cin, k=k, stride=stride, pad=k // 2, cout=cout, act=pkg.ACT_RELU, eps=0.3, n_in=n_in, want_idx=0)
+    wgt = None if kind == "add" else torch.from_numpy((rng.standard_normal((k, k, cin, cout) if kind == "conv" else (k, k, cin)) *
+                                                       np.sqrt(2.0 / (k * k * (cin if kind == "conv" else 1)))).astype(dt)).cuda()
+    dense = [torch.from_numpy(rng.standard_normal((n, h, w, cin)).astype(dt)).cuda() for _ in range(n_in)]
+    frames = [[_rand_delta(rng, (n, h, w, cin), dens, S, 0.4) for _ in range(n_in)] for dens in (0.02, 0.3, 1.0, 0.0, 0.03, 0.0, 0.5)]
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        ctx = pkg.Context(n * h * w)
+        eager, replayed = (pkg.Layer(ctx, desc, wgt) for _ in range(2))
+        fixed = [pkg.Delta(torch.zeros_like(d), torch.zeros((n, h, w), dtype=torch.uint8, device="cuda"), None, None) for d in dense]
+        for layer in (eager, replayed):
+            layer.init(dense)
+            layer.step(fixed)                                  # (also the first launch of every kernel)
+        ctx.sync()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            out = replayed.step(fixed)
+        for t, frame in enumerate(frames):
+            for f, d in zip(fixed, frame):
+                f.data.copy_(torch.from_numpy(d.data))
+                f.mask.copy_(torch.from_numpy(d.mask))
+            graph.replay()
+            want = eager.step([_upload(d) for d in frame])
+            ctx.sync()
+            mask = to_np(want.mask)
+            assert np.array_equal(to_np(out.mask), mask), f"replay {t}: mask"
+            assert np.array_equal(to_np(out.data)[mask == 1], to_np(want.data)[mask == 1]), f"replay {t}: delta"
+            for which in (0, 1):
+                assert np.array_equal(to_np(replayed.state_tensor(which)), to_np(eager.state_tensor(which))), f"replay {t}: buffer {which}"
