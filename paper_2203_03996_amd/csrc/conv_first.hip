@@ -283,12 +283,18 @@ __global__ __launch_bounds__(kFirstWaves* kWave, 2) void conv_first_kernel(ConvA
     }
 }
 
+// Input bytes of one stream that a launch must reach with 32-bit offsets.
+static uint64_t first_stream_bytes(size_t es, const ConvArgs& c) {
+    const uint64_t a = (uint64_t)c.h * c.w * c.cin * es, b = c.in2_data ? (uint64_t)c.h2 * c.w2 * c.cin2 * es : 0;
+    return a > b ? a : b;
+}
+
+// (nothing here depends on the number of streams, see launch_conv_first_t)
 bool conv_first_supported(int dtype, const ConvArgs& c, int cout, bool flat) {
     const size_t es = dtype_size(dtype);
     const int vec = dtype == DCNN_F16 ? 8 : 4;
     if (flat || cout % vec != 0 || ((size_t)c.cin * es) % 16 != 0) return false;
-    if ((uint64_t)c.n * c.h * c.w * c.cin * es > kWsMaxBytes) return false;
-    return c.in2_data == nullptr || (((size_t)c.cin2 * es) % 16 == 0 && (uint64_t)c.n * c.h2 * c.w2 * c.cin2 * es <= kWsMaxBytes);
+    return first_stream_bytes(es, c) <= kWsMaxBytes && (c.in2_data == nullptr || ((size_t)c.cin2 * es) % 16 == 0);
 }
 
 template <typename T>
@@ -328,8 +334,27 @@ static dcnn_status launch_conv_first_t(dcnn_ctx* ctx, const ConvArgs& c, const E
     return check_hip(ctx, hipGetLastError(), "conv_first_kernel launch");
 }
 
-dcnn_status launch_conv_first(dcnn_ctx* ctx, int dtype, const ConvArgs& c, const EpilogueArgs& e, const ConvPlan& p, const void* bias2) {
-    return dtype == DCNN_F16 ? launch_conv_first_t<f16>(ctx, c, e, p, bias2) : launch_conv_first_t<float>(ctx, c, e, p, bias2);
+dcnn_status launch_conv_first(dcnn_ctx* ctx, int dtype, const ConvArgs& c_all, const EpilogueArgs& e_all, const ConvPlan& p, const void* bias2) {
+    // Inputs past 2 GiB go through in slices of whole streams: the kernel that serves a layer, and with it the order of its
+    // sums, is the same however many streams there are.
+    const size_t es = dtype_size(dtype);
+    const uint64_t slice = kWsMaxBytes / first_stream_bytes(es, c_all);
+    auto at = [](const void* base, uint64_t bytes) -> const void* { return base ? static_cast<const char*>(base) + bytes : nullptr; };
+    auto at_mut = [](void* base, uint64_t bytes) -> void* { return base ? static_cast<char*>(base) + bytes : nullptr; };
+    for (int first = 0; first < c_all.n;) {
+        ConvArgs c = c_all;
+        EpilogueArgs e = e_all;
+        c.n = (uint64_t)(c_all.n - first) < slice ? c_all.n - first : (int)slice;
+        const uint64_t out = (uint64_t)first * c.oh * c.ow * e.c * es;
+        c.in_data = at(c.in_data, (uint64_t)first * c.h * c.w * c.cin * es);
+        c.in2_data = at(c.in2_data, (uint64_t)first * c.h2 * c.w2 * c.cin2 * es);
+        e.res_data = at(e.res_data, out);
+        e.xA = at_mut(e.xA, out); e.xT = at_mut(e.xT, out); e.out_data = at_mut(e.out_data, out);
+        const dcnn_status st = dtype == DCNN_F16 ? launch_conv_first_t<f16>(ctx, c, e, p, bias2) : launch_conv_first_t<float>(ctx, c, e, p, bias2);
+        if (st != DCNN_OK) return st;
+        first += c.n;
+    }
+    return DCNN_OK;
 }
 
 }  // namespace dcnn

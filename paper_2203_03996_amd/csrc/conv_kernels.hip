@@ -157,7 +157,7 @@ dcnn_status launch_conv(dcnn_ctx* ctx, int dtype, bool init, const ListArgs& l, 
     c.kch2 = c.in2_data ? (int)cdiv(c.cin2, dtype == DCNN_F16 ? 16 : 8) : 0;
     c.div_ow = make_fastdiv((uint32_t)c.ow);
     c.div_oh = make_fastdiv((uint32_t)c.oh);
-    // The dense first frame over 16-byte pixels and channel vectors (tensors below 2 GiB) splits over channels as well as
+    // The dense first frame over 16-byte pixels and channel vectors (a stream's input below 2 GiB) splits over channels as well as
     // pixels; everything else of a first frame stays with the plain kernel.
     if (init && p.w_bytes <= kWsMaxBytes && conv_first_supported(dtype, c, c.cout, p.flat)) return launch_conv_first(ctx, dtype, c, e, p, c.bias2);
     if (!init && conv_unit_supported(ctx, dtype, l, c, e, p)) return launch_conv_unit(ctx, dtype, l, c, e, p);

@@ -920,6 +920,30 @@ def test_first_frame_tiles(S, k, stride, cin, cout, nhw, mode):
     assert np.array_equal(alone[0], got[n - 1])
 
 
+def test_first_frame_of_a_batch_past_2_gib_has_the_bits_of_single_streams():
+    """3x3 64->16 on 112x112 with its K-steps split over four waves: 1400 streams hold 2.09 GiB of input (two launches); the first,
+    the one at the border of the launches and the last stream against the same streams alone."""
+    n, h, w, cin, cout = 1400, 112, 112, 64, 16
+    torch.manual_seed(5)
+    x = torch.randn((n, h, w, cin), dtype=torch.float16, device="cuda")
+    assert x.numel() * 2 > 2 ** 31
+    wgt = (torch.randn((3, 3, cin, cout), device="cuda") * 0.06).half()
+
+    def run(streams):
+        m = streams.shape[0]
+        ctx = pkg.Context(m * h * w)
+        layer = pkg.Layer(ctx, pkg.make_desc(pkg.CONV, pkg.F16, m, h, w, cin, k=3, pad=1, cout=cout, act=pkg.ACT_RELU, eps=0.05), wgt)
+        out = layer.init([streams])
+        ctx.sync()
+        return out, layer.state_tensor(0), layer
+
+    out, buf, _keep = run(x)
+    border = (2 ** 31 - 1) // (h * w * cin * 2)
+    for i in (0, border - 1, border, n - 1):
+        alone, alone_buf, _keep2 = run(x[i:i + 1].contiguous())
+        assert torch.equal(out[i], alone[0]) and torch.equal(buf[i], alone_buf[0]), f"stream {i}"
+
+
 @pytest.mark.parametrize("S", ["f32", "f16"])
 @pytest.mark.parametrize("k,stride,c,hw", [(3, 1, 16, (5, 7)), (3, 2, 200, (9, 6)), (2, 2, 8, (6, 6)), (1, 1, 24, (3, 1))])
 def test_depthwise_first_frame_pixel_groups(S, k, stride, c, hw):
