@@ -147,6 +147,8 @@ struct ListArgs {
     uint8_t* mask_out;           // what the kernel writes for others, each may be null: the flags of the list,
     int32_t* idx_out;            // the ascending list,
     int32_t* count_out;          // its length
+    int32_t* in_idx_out;         // the ascending list of the INPUT's flagged pixels and its length, on behalf of a producer that
+    int32_t* in_count_out;       //    leaves it to this kernel, or both null
     uint8_t* mask_zero;          // 0 at every pixel that is not listed (the kernel itself writes the decision at those that are)
     int lds_scratch, lds_list;   // byte offsets into the kernel's dynamic LDS (set by the launchers)
     int lds_entries;             // room for this many entries

@@ -15,7 +15,9 @@ struct dcnn_layer {
     bool alias_mask;            // output mask / index list are those of input 0
     bool has_bias;
     bool self = false;          // sparse steps build their work list in the layer's own kernel (self_list.h)
-    bool skip_list = false;     // input layer of a network in which nobody walks its list: only the mask is written
+    bool skip_list = false;     // input layer of a network whose list is written by a consumer's kernel (in_idx_out), not by its own
+    int32_t* in_idx_out = nullptr;      // such a consumer: where the input layer's list and its length go
+    int32_t* in_count_out = nullptr;
     bool has_bias2 = false;     // bias of the fused projection
     size_t state_bytes;
     // pieces of the caller-provided state memory

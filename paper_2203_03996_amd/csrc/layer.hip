@@ -182,6 +182,11 @@ static void carve(dcnn_layer* L, void* state) {
         // a stateless, mask-preserving layer (1x1 s1 conv without activation) forwards its input's
         // mask and index list; every other layer owns them
         L->alias_mask = !act && !own && (d.kind == DCNN_CONV || d.kind == DCNN_DWCONV);
+        if (L->alias_mask && L->out_pixels <= kSelfMaxPixels) {
+            // (where such a layer's kernel builds the list, nobody has handed it one: it has room for its own)
+            L->out_idx = static_cast<int32_t*>(cv.take((size_t)L->out_pixels * sizeof(int32_t)));
+            L->out_count = static_cast<int32_t*>(cv.take(kAlign));
+        }
         if (!L->alias_mask) {
             L->out_mask = static_cast<uint8_t*>(cv.take((size_t)L->out_pixels));
             L->out_idx = static_cast<int32_t*>(cv.take((size_t)L->out_pixels * sizeof(int32_t)));
@@ -229,6 +234,8 @@ int collect_clears(const dcnn_layer* L, bool with_flags, ClearPiece* out) {
         if (L->out_mask_alt) out[n++] = {L->out_mask_alt, L->out_pixels};
         out[n++] = {L->out_count, (kXtIoOffset + 4) * (int64_t)sizeof(int32_t)};   // the count, the statistics scratch and the x^T row counters behind it
         if (L->list_count && L->list_count != L->out_count) out[n++] = {L->list_count, (int64_t)sizeof(int32_t)};
+    } else if (L->out_count) {
+        out[n++] = {L->out_count, (kXtIoOffset + 4) * (int64_t)sizeof(int32_t)};
     }
     if (with_flags && L->xt_flags) out[n++] = {L->xt_flags, L->out_pixels};
     return n;
@@ -568,11 +575,12 @@ dcnn_status dcnn_layer_step(dcnn_layer* L, const dcnn_delta* const* in, int32_t 
     uint8_t* const mask_cur = (alternates && L->mask_phase) ? L->out_mask_alt : L->out_mask;
     uint8_t* const mask_next = alternates ? (L->mask_phase ? L->out_mask : L->out_mask_alt) : nullptr;
     v.mask = L->alias_mask ? in[0]->mask : mask_cur;
-    v.idx = L->alias_mask ? in[0]->idx : L->out_idx;
+    const bool alias_list = L->alias_mask && !L->self;
+    v.idx = alias_list ? in[0]->idx : L->out_idx;
     // A layer with an activation whose output list nobody walks (want_idx == 0) does not count its flagged outputs:
     // atomics on one counter are served one after the other (~2.4 ns each; a few thousand waves adding their share at
     // the end of a kernel cost 10-20 us), and nothing on a step's path needs the number.  Statistics count the mask.
-    v.count = L->alias_mask ? in[0]->count : ((act && !d.want_idx) ? nullptr : L->out_count);
+    v.count = alias_list ? in[0]->count : ((act && !d.want_idx) ? nullptr : L->out_count);
     L->last_in_count = in[0]->count;
     L->last_in2_count = n_in == 2 ? in[1]->count : nullptr;
     L->last_in_mask = in[0]->mask;
@@ -584,9 +592,8 @@ dcnn_status dcnn_layer_step(dcnn_layer* L, const dcnn_delta* const* in, int32_t 
         a.out_idx = L->out_idx; a.out_count = L->out_count; a.pixels = L->in_pixels;
         a.n = d.n; a.h = d.h; a.w = d.w; a.c = d.c; a.eps = d.eps; a.dilate_r = d.dilate_r;
         a.mask_only = L->skip_list ? 1 : 0;
-        if (L->skip_list) v.count = nullptr;
         L->last_in_count = nullptr;
-        L->last_work_count = L->skip_list ? nullptr : L->out_count;
+        L->last_work_count = L->out_count;
         // optional timing: the generation pass together with the list emission that belongs to it
         const bool timed_gen = L->events_used < L->events.size();
         if (timed_gen) {
@@ -622,10 +629,16 @@ dcnn_status dcnn_layer_step(dcnn_layer* L, const dcnn_delta* const* in, int32_t 
         l.div_ow = make_fastdiv((uint32_t)L->ow); l.div_oh = make_fastdiv((uint32_t)L->oh);
         l.div_iw = make_fastdiv((uint32_t)d.w); l.div_ih = make_fastdiv((uint32_t)d.h);
         l.div_up = make_fastdiv((uint32_t)l.m_up);
-        if (!act && own) { l.mask_out = L->out_mask; l.idx_out = L->out_idx; l.count_out = L->out_count; }
-        else if (act) {
+        l.in_idx_out = L->in_idx_out; l.in_count_out = L->in_count_out;
+        if (!act) {
+            l.mask_out = L->out_mask; l.idx_out = L->out_idx; l.count_out = L->out_count;
+        } else {
             l.mask_zero = mask_cur;
             l.count_out = own ? L->list_count : L->out_count;       // the list's length, for the statistics
+            if (!own && L->in_idx_out) {                           // (its list is the input's)
+                l.idx_out = L->in_idx_out; l.count_out = L->in_count_out;
+                l.in_idx_out = l.in_count_out = nullptr;
+            }
         }
     } else if (own || L->self) {
         // (a layer that would build its list itself but has to have one in memory this time: its own output list serves,
@@ -647,6 +660,13 @@ dcnn_status dcnn_layer_step(dcnn_layer* L, const dcnn_delta* const* in, int32_t 
         st = launch_mask_compact(ctx, m);
         if (st != DCNN_OK) return st;
         l.list = m.idx_out; l.count = m.count_out; l.taps = own ? L->taps : nullptr;
+        if (L->in_idx_out) {                                   // the input layer's list is this layer's to write
+            MaskPassArgs mi{};
+            mi.mask_in = in[0]->mask; mi.idx_out = L->in_idx_out; mi.count_out = L->in_count_out;
+            mi.n = d.n; mi.h = mi.oh = d.h; mi.w = mi.ow = d.w; mi.k = 1; mi.stride = 1; mi.up = 1;
+            st = launch_mask_compact(ctx, mi);
+            if (st != DCNN_OK) return st;
+        }
     } else {
         l.list = in[0]->idx; l.count = in[0]->count;
         if (act && !mask_next) {
@@ -780,8 +800,8 @@ dcnn_status dcnn_layer_output(const dcnn_layer* L, dcnn_delta* out_view) {
         dcnn_delta v{};
         v.n = L->d.n; v.h = L->oh; v.w = L->ow; v.c = L->oc; v.dtype = L->d.dtype;
         v.data = L->d.kind == DCNN_ACCUM ? L->buf0 : (L->d.fuse_accum ? L->buf2 : L->out_data);
-        v.mask = L->out_mask; v.idx = L->out_idx;
-        v.count = (has_act(L->d) && !L->d.want_idx) ? nullptr : L->out_count;
+        v.mask = L->out_mask; v.idx = L->alias_mask ? nullptr : L->out_idx;
+        v.count = (L->alias_mask || (has_act(L->d) && !L->d.want_idx)) ? nullptr : L->out_count;
         *out_view = v;
         return DCNN_OK;
     }
@@ -825,9 +845,7 @@ dcnn_status dcnn_layer_stats(dcnn_layer* L, dcnn_stats* s) {
     st = read_or_count(L->last_in_count, L->last_in_mask, s->pixels_in_total, &s->pixels_in);
     if (st == DCNN_OK) st = read_or_count(L->last_in2_count, L->last_in2_mask, s->pixels_in2_total, &s->pixels_in2);
     if (st == DCNN_OK) st = read(L->last_work_count, &s->pixels_work);
-    if (L->self && L->last_work_count == nullptr) s->pixels_work = s->pixels_in;   // a list nobody stored: the input's own
     if (st == DCNN_OK) st = read_or_count(L->view.count, L->view.mask, L->out_pixels, &s->pixels_out);
-    if (L->skip_list) s->pixels_work = s->pixels_out;
     s->kind = L->d.kind; s->act = L->d.act; s->n_in = L->d.n_in;
     s->c_in = L->d.c; s->c_out = L->oc;
     const bool window = L->d.kind == DCNN_CONV || L->d.kind == DCNN_DWCONV || L->d.kind == DCNN_MAXPOOL;

@@ -31,7 +31,7 @@ struct Planned {
     size_t state_off, state_bytes;
     dcnn_layer* layer;
     bool self = false;              // the layer's kernel builds its work list (layer_lists_itself)
-    bool skip_list = false;         // input layer whose list nobody walks
+    int list_writer = -1;           // input layer whose list nobody walks: the layer whose kernel writes it on the side
     int lane = 0;                   // which of the network's streams runs the layer (0: the context's own)
     hipEvent_t done = nullptr;      // recorded behind the layer when a layer on another lane consumes its output
 };
@@ -323,20 +323,21 @@ dcnn_status dcnn_net_finalize(dcnn_net* net, int32_t fuse, size_t* arena_bytes) 
     // which outputs need an index list: consumers that walk their input's list as it is
     for (auto& p : net->plan) p.d.want_idx = (fuse & 2) ? 1 : 0;
     // (from the back: a layer's own want_idx is final once its consumers have been seen.  On small maps a layer's kernel
-    // builds its list from the masks and needs nobody's; a stateless 1x1 convolution hands its input's list on to
-    // whoever walks it.)
+    // builds its list from the masks and needs nobody's, and has the input's flags at hand: it writes the input layer's
+    // list, which belongs to that layer's output whoever reads it, where a launch of its own would take 3-4 us.)
     for (size_t a = net->plan.size(); a-- > 0;) {
         Planned& p = net->plan[a];
         const dcnn_layer_desc& d = p.d;
         p.self = layer_lists_itself(ctx, d, true);
         if (p.in_nodes.empty()) {
-            p.skip_list = d.kind == DCNN_DELTAGEN && d.dilate_r == 0 && !d.want_idx;
+            if (d.kind == DCNN_DELTAGEN && d.dilate_r == 0 && !d.want_idx)
+                for (size_t q = a + 1; q < net->plan.size() && p.list_writer < 0; ++q)
+                    if (net->plan[q].self && net->layer_of_node[net->plan[q].in_nodes[0]] == (int)a) p.list_writer = (int)q;
             continue;
         }
         const bool walker_conv = is_conv(d) && d.kh == 1 && d.stride == 1 && d.n_in == 1;
         const bool walks_input_list = d.kind == DCNN_ACCUM || d.kind == DCNN_MAXPOOL || walker_conv || (d.kind == DCNN_ACT && d.n_in == 1);
-        const bool forwards_list = walker_conv && d.act == DCNN_ACT_NONE && d.want_idx;
-        if ((walks_input_list && !p.self) || forwards_list) net->plan[net->layer_of_node[p.in_nodes[0]]].d.want_idx = 1;
+        if (walks_input_list && !p.self) net->plan[net->layer_of_node[p.in_nodes[0]]].d.want_idx = 1;
     }
     size_t off = 0;
     for (auto& p : net->plan) {
@@ -438,8 +439,13 @@ dcnn_status dcnn_net_bind(dcnn_net* net, void* arena_dev, size_t arena_bytes) {
     for (auto& p : net->plan) {
         if (st != DCNN_OK) break;
         st = dcnn::layer_create(net->lane_ctx[p.lane], &p.d, p.w, p.b, p.w2, p.b2, static_cast<char*>(arena_dev) + p.state_off, p.state_bytes, p.self, &p.layer);
-        if (st == DCNN_OK) p.layer->skip_list = p.skip_list;
         if (st != DCNN_OK) st = lane_fail(net, p, st);
+    }
+    for (auto& p : net->plan) {
+        if (st != DCNN_OK || p.list_writer < 0) continue;
+        p.layer->skip_list = true;
+        dcnn_layer* const writer = net->plan[p.list_writer].layer;
+        writer->in_idx_out = p.layer->out_idx; writer->in_count_out = p.layer->out_count;
     }
     if (st == DCNN_OK) st = lanes_end(net);
     if (st != DCNN_OK) {
@@ -510,6 +516,8 @@ dcnn_status dcnn_net_step(dcnn_net* net, const void* frame_dev, void* out_dev) {
             for (int in : p.in_nodes) {
                 dcnn_status st = dcnn_layer_output(net->plan[net->layer_of_node[in]].layer, &views[n_in]);
                 if (st != DCNN_OK) return st;
+                // (a list written on the side is there when the step has ended, not before)
+                if (net->plan[net->layer_of_node[in]].list_writer >= 0) { views[n_in].idx = nullptr; views[n_in].count = nullptr; }
                 ins[n_in] = &views[n_in];
                 ++n_in;
             }

@@ -9,7 +9,7 @@
 // tiles are those of the stored list (same order, same partition), so results do not depend on which form is used.
 // What other kernels need is written by the workgroups in shares: the output mask (of a layer that truncates: its zeros at
 // the pixels that are not listed, so that a step depends on nothing an earlier one left) and, where the caller asked for it, the
-// ascending list and its length.
+// ascending list and its length, and those of the input.
 #pragma once
 
 #include "device_utils.h"
@@ -353,6 +353,25 @@ __device__ __forceinline__ void self_emit(const ListArgs& l, const SelfBits& s, 
             }
         }
         if (l.count_out != nullptr && blockIdx.x == 0 && tid == 0) *l.count_out = count;
+        if (l.in_idx_out != nullptr) {                         // (uniform for the grid)
+            // a run of words per workgroup: the flags before it are summed by all threads, those within it by each for itself
+            constexpr int NWV = NT / kWave;
+            const int share = (s.in_words + (int)gridDim.x - 1) / (int)gridDim.x;
+            const int w0 = min((int)blockIdx.x * share, s.in_words), w2 = min(w0 + share, s.in_words);
+            int part = 0;
+            for (int w = tid; w < w0; w += NT) part += __popc(s.ibits[w]);
+            part = self_scan(part);
+            if (tid % kWave == kWave - 1) s.red[tid / kWave] = part;
+            lds_block_sync();
+            int before = 0;
+            for (int i = 0; i < NWV; ++i) before += s.red[i];
+            for (int w = w0 + tid; w < w2; w += NT) {
+                int j = before;
+                for (int v = w0; v < w; ++v) j += __popc(s.ibits[v]);
+                for (uint32_t rest = s.ibits[w]; rest; rest &= rest - 1) l.in_idx_out[j++] = w * 32 + __builtin_ctz(rest);
+                if (w == s.in_words - 1) *l.in_count_out = j;
+            }
+        }
     }
     lds_block_sync();
 }

@@ -848,3 +848,32 @@ def test_lists_built_in_the_kernels_change_nothing(spec_fn, streams):
             for s0, s1 in zip(nets[0].stats(), nets[1].stats()):
                 for key in ("pixels_in", "pixels_in2", "pixels_work", "pixels_out"):
                     assert s0[key] == s1[key], f"frame {t}: {key} of a layer of kind {s0['kind']}: {s0[key]} and {s1[key]}"
+
+
+@pytest.mark.parametrize("spec_fn", [_small_hrnet, _small_resnet, lambda: wl.mobilenet_stack(eps=0.05, h=50, w=45, frames=4),
+                                     lambda: wl.bottleneck_block(eps=0.08, h=61, w=33, frames=4),
+                                     lambda: wl.bottleneck_block(eps=0.08, h=130, w=127, frames=4),
+                                     lambda: wl.single_conv_relu(eps=0.05), lambda: wl.tiny_mixed_net(eps=0.05)])
+@pytest.mark.parametrize("flags,counting", [(1, False), (5, False), (1, True), (0, False)])
+def test_layers_without_an_activation_hand_out_their_list(spec_fn, flags, counting):
+    """Whoever walks it: the input layer and every layer that does not truncate come with the ordered list of their mask and its
+    length, on maps whose consumers build their lists themselves (the largest one here is past that) as well as on others."""
+    spec = spec_fn()
+    wts = wl.make_weights(spec, 31)
+    vid = wl.make_batch(spec["video"], 31, 1).astype(NP_DTYPE[spec["dtype"]])
+    ctx = pkg.Context(max(h * w for h, w, _ in wl.node_shapes(spec)))
+    net = pkg.Net(ctx, spec, wts, 1, flags)
+    if counting:
+        net.set_counting(True)
+    net.init(torch.from_numpy(vid[0]).cuda())
+    for t in range(1, vid.shape[0]):
+        net.step(torch.from_numpy(vid[t]).cuda())
+        ctx.sync()
+        for i, s in enumerate(net.stats()):
+            if s["act"] != pkg.ACT_NONE or s["kind"] == pkg.ACCUM:
+                continue
+            view = net.layer_output(i)[1]
+            flat = np.flatnonzero(to_np(view.mask).reshape(-1))
+            assert view.count is not None and view.idx is not None, f"frame {t} layer {i} of kind {s['kind']}: no list"
+            assert int(to_np(view.count)[0]) == flat.size, f"frame {t} layer {i} of kind {s['kind']}: count"
+            assert np.array_equal(to_np(view.idx)[:flat.size], flat), f"frame {t} layer {i} of kind {s['kind']}: list"
