@@ -19,16 +19,20 @@ static int list_grid(const dcnn_ctx* ctx, int64_t max_count, int entries_per_wg,
 }
 
 // Work lists built by the kernel itself (self_list.h), for the kernels of kTileThreads threads: the length of the list, and
-// the entries of this workgroup's groups.
+// the entries of this workgroup's groups.  SELF is a variant of its own: with both ways in one kernel the walk of a stored list
+// took 0.4-1 us longer a launch (@).
+template <bool SELF>
 __device__ __forceinline__ int64_t tile_list_count(const ListArgs& l, unsigned char* smem, SelfBits& sb) {
-    if (!l.self) return list_count(l);
+    if constexpr (!SELF) return list_count(l);
     sb = self_carve(l, smem + l.lds_scratch);
     return self_build<kTileThreads>(l, sb, nullptr);
 }
+template <bool SELF>
 __device__ __forceinline__ const int32_t* tile_list_emit(const ListArgs& l, unsigned char* smem, const SelfBits& sb, int64_t count,
                                                          int64_t begin, int64_t end, int64_t step, int entries) {
+    if constexpr (!SELF) return nullptr;
     int32_t* px = reinterpret_cast<int32_t*>(smem + l.lds_list);
-    if (l.self) self_emit<kTileThreads>(l, sb, (int)count, SelfSpan{(int)begin, (int)end, (int)step, entries}, px, nullptr);
+    self_emit<kTileThreads>(l, sb, (int)count, SelfSpan{(int)begin, (int)end, (int)step, entries}, px, nullptr);
     return px;
 }
 // Dynamic LDS of such a launch behind `used` bytes of the kernel's own, and where the pieces lie.  `groups`: groups of `entries`
@@ -41,13 +45,13 @@ static size_t tile_list_lds(ListArgs& l, size_t used, int64_t groups, int64_t en
     return (size_t)l.lds_list + (size_t)l.lds_entries * 4;
 }
 
-template <typename T, int V, int VPL, int UB>
+template <typename T, int V, int VPL, int UB, bool SELF>
 __global__ __launch_bounds__(kTileThreads) void act_sparse_kernel(ListArgs l, ActArgs a, EpilogueArgs e, TailShape shape,
                                                                    uint32_t map_bytes, uint32_t pixels) {
     extern __shared__ __align__(16) unsigned char list_smem[];
     clear_ahead(e);
     SelfBits sb;
-    const int64_t count = tile_list_count(l, list_smem, sb);
+    const int64_t count = tile_list_count<SELF>(l, list_smem, sb);
     const int lane = threadIdx.x % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     TailRsrc rs;
@@ -59,7 +63,7 @@ __global__ __launch_bounds__(kTileThreads) void act_sparse_kernel(ListArgs l, Ac
     const int parts = kTile / shape.run;
     int survivors = 0;
     const WgTileRange r = wg_tile_range(run_groups(count, shape.run));
-    const int32_t* self_px = tile_list_emit(l, list_smem, sb, count, r.begin, r.end, r.step, kTileWaves * shape.run);
+    const int32_t* self_px = tile_list_emit<SELF>(l, list_smem, sb, count, r.begin, r.end, r.step, kTileWaves * shape.run);
     for (int64_t wt = r.begin; wt < r.end; wt += r.step, self_px += kTileWaves * shape.run) {
         const int64_t unit = wt * kTileWaves + wave;
         const int64_t tile = unit / parts;
@@ -67,7 +71,7 @@ __global__ __launch_bounds__(kTileThreads) void act_sparse_kernel(ListArgs l, Ac
         const int64_t base = tile * kTile;
         if (base >= count) continue;
         const int j = lane % kTile;
-        const int p_mine = (j / shape.run == part) ? (l.self ? self_px[wave * shape.run + j % shape.run] : list_pixel(l.list, base + j, count)) : -1;
+        const int p_mine = (j / shape.run == part) ? (SELF ? self_px[wave * shape.run + j % shape.run] : list_pixel(l.list, base + j, count)) : -1;
         const int p_off = p_mine >= 0 ? p_mine : (int)kOob;
         // a stream without a mask is flagged wherever the list points
         const int rflag = e.res_mask ? __builtin_amdgcn_raw_buffer_load_b8(rs_rmask, p_off, 0, 0) : 1;
@@ -89,7 +93,7 @@ __global__ __launch_bounds__(kTileThreads) void act_sparse_kernel(ListArgs l, Ac
 // 8 pixels at once -- one round trip -- and agree on the per-pixel maximum through LDS.  Arithmetic, rounding and
 // decisions are those of sparse_tile_tail (Section 3.1, Eqs. 4-6).  Channels a multiple of 4 vectors.
 
-template <typename T, int V, int VPW>
+template <typename T, int V, int VPW, bool SELF>
 __global__ __launch_bounds__(kTileThreads) void act_wide_kernel(ListArgs l, ActArgs a, EpilogueArgs e, uint32_t map_bytes, uint32_t pixels) {
     typedef typename RawOf<T, V>::type Raw;
     constexpr uint32_t ES = sizeof(T);
@@ -97,7 +101,7 @@ __global__ __launch_bounds__(kTileThreads) void act_wide_kernel(ListArgs l, ActA
     extern __shared__ __align__(16) unsigned char list_smem[];
     clear_ahead(e);
     SelfBits sb;
-    const int64_t count = tile_list_count(l, list_smem, sb);
+    const int64_t count = tile_list_count<SELF>(l, list_smem, sb);
     const int lane = threadIdx.x % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const __amdgpu_buffer_rsrc_t rs_in = ws_rsrc(a.in_data, map_bytes), rs_res = ws_rsrc(e.res_data, map_bytes);
@@ -113,13 +117,13 @@ __global__ __launch_bounds__(kTileThreads) void act_wide_kernel(ListArgs l, ActA
     const int64_t units = wide_groups(count);
     int survivors = 0;
     int parity = 0;
-    const int32_t* self_px = tile_list_emit(l, list_smem, sb, count, blockIdx.x, units, gridDim.x, kWideRun);
+    const int32_t* self_px = tile_list_emit<SELF>(l, list_smem, sb, count, blockIdx.x, units, gridDim.x, kWideRun);
     for (int64_t unit = blockIdx.x; unit < units; unit += gridDim.x, parity ^= 1, self_px += kWideRun) {
         const int64_t tile = unit / (kTile / kWideRun);
         const int part = (int)(unit - tile * (kTile / kWideRun));
         const int64_t base = tile * kTile + part * kWideRun;
         // entry lane % 8 of the run: pixel and the update flags of both streams (one round trip for the run)
-        const int p_mine = l.self ? self_px[lane % kWideRun] : list_pixel(l.list, base + lane % kWideRun, count);
+        const int p_mine = SELF ? self_px[lane % kWideRun] : list_pixel(l.list, base + lane % kWideRun, count);
         const int p_off = p_mine >= 0 ? p_mine : (int)kOob;
         const int rflag_mine = e.res_mask ? __builtin_amdgcn_raw_buffer_load_b8(rs_rmask, p_off, 0, 0) : 1;
         const int iflag_mine = a.in_mask ? __builtin_amdgcn_raw_buffer_load_b8(rs_imask, p_off, 0, 0) : 1;
@@ -316,7 +320,8 @@ static dcnn_status launch_act_t(dcnn_ctx* ctx, bool init, const ListArgs& l_in, 
         const int wgrid = (int)(units < cap ? units : cap);
         const uint32_t mb = (uint32_t)map_bytes, px = (uint32_t)l.max_count;
         const size_t lds = tile_list_lds(l, 0, wide_groups(l.max_count), kWideRun, wgrid, false);
-        hipLaunchKernelGGL((act_wide_kernel<T, VEC, 1>), dim3(wgrid), dim3(kTileThreads), lds, ctx->stream, l, a, e, mb, px);
+        if (l.self) hipLaunchKernelGGL((act_wide_kernel<T, VEC, 1, true>), dim3(wgrid), dim3(kTileThreads), lds, ctx->stream, l, a, e, mb, px);
+        else hipLaunchKernelGGL((act_wide_kernel<T, VEC, 1, false>), dim3(wgrid), dim3(kTileThreads), lds, ctx->stream, l, a, e, mb, px);
         return check_hip(ctx, hipGetLastError(), "act_wide_kernel launch");
     }
     if (vec && vpl <= 4 && map_bytes > 0 && map_bytes <= kWsMaxBytes) {
@@ -326,11 +331,13 @@ static dcnn_status launch_act_t(dcnn_ctx* ctx, bool init, const ListArgs& l_in, 
         const int sgrid = list_grid(ctx, l.max_count, kTileWaves * shape.run, l.self ? kSelfWgPerCu : 8);
         const uint32_t mb = (uint32_t)map_bytes, px = (uint32_t)l.max_count;
         const size_t lds = tile_list_lds(l, 0, run_groups(l.max_count, shape.run), kTileWaves * shape.run, sgrid, true);
-#define DCNN_ACT_SPARSE(VPL, UB) hipLaunchKernelGGL((act_sparse_kernel<T, VEC, VPL, UB>), dim3(sgrid), dim3(kTileThreads), lds, ctx->stream, l, a, e, shape, mb, px)
+#define DCNN_ACT_SPARSE_S(VPL, UB, S) hipLaunchKernelGGL((act_sparse_kernel<T, VEC, VPL, UB, S>), dim3(sgrid), dim3(kTileThreads), lds, ctx->stream, l, a, e, shape, mb, px)
+#define DCNN_ACT_SPARSE(VPL, UB) do { if (l.self) DCNN_ACT_SPARSE_S(VPL, UB, true); else DCNN_ACT_SPARSE_S(VPL, UB, false); } while (0)
         if (vpl_used == 1) DCNN_ACT_SPARSE(1, 4);
         else if (vpl_used == 2) DCNN_ACT_SPARSE(2, 4);
         else DCNN_ACT_SPARSE(4, 2);
 #undef DCNN_ACT_SPARSE
+#undef DCNN_ACT_SPARSE_S
         return check_hip(ctx, hipGetLastError(), "act_sparse_kernel launch");
     }
     if (l.self) return fail(ctx, DCNN_EUNSUPPORTED, "activation: this shape does not build its work list in place");
@@ -412,7 +419,7 @@ template <typename T, int V, int VPL, int UB, int KS> struct DwSrc {
     }
 };
 
-template <typename T, int V, int VPL, int UB, int KS>
+template <typename T, int V, int VPL, int UB, int KS, bool SELF>
 __global__ __launch_bounds__(kTileThreads) void dwconv_sparse_kernel(ListArgs l, ConvArgs c, EpilogueArgs e, TailShape shape,
                                                                       uint32_t in_bytes, uint32_t in_pixels, uint32_t map_bytes,
                                                                       uint32_t pixels) {
@@ -426,7 +433,7 @@ __global__ __launch_bounds__(kTileThreads) void dwconv_sparse_kernel(ListArgs l,
     }
     __syncthreads();
     SelfBits sb;
-    const int64_t count = tile_list_count(l, dw_smem, sb);
+    const int64_t count = tile_list_count<SELF>(l, dw_smem, sb);
     const int lane = threadIdx.x % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     TailRsrc rs;
@@ -439,7 +446,7 @@ __global__ __launch_bounds__(kTileThreads) void dwconv_sparse_kernel(ListArgs l,
     const int parts = kTile / shape.run;
     int survivors = 0;
     const WgTileRange r = wg_tile_range(run_groups(count, shape.run));
-    const int32_t* self_px = tile_list_emit(l, dw_smem, sb, count, r.begin, r.end, r.step, kTileWaves * shape.run);
+    const int32_t* self_px = tile_list_emit<SELF>(l, dw_smem, sb, count, r.begin, r.end, r.step, kTileWaves * shape.run);
     for (int64_t wt = r.begin; wt < r.end; wt += r.step, self_px += kTileWaves * shape.run) {
         const int64_t unit = wt * kTileWaves + wave;
         const int64_t tile = unit / parts;
@@ -447,7 +454,7 @@ __global__ __launch_bounds__(kTileThreads) void dwconv_sparse_kernel(ListArgs l,
         const int64_t base = tile * kTile;
         if (base >= count) continue;
         const int j = lane % kTile;
-        const int p_mine = (j / shape.run == part) ? (l.self ? self_px[wave * shape.run + j % shape.run] : list_pixel(l.list, base + j, count)) : -1;
+        const int p_mine = (j / shape.run == part) ? (SELF ? self_px[wave * shape.run + j % shape.run] : list_pixel(l.list, base + j, count)) : -1;
         const int rflag = e.res_mask ? __builtin_amdgcn_raw_buffer_load_b8(rs_rmask, p_mine >= 0 ? p_mine : (int)kOob, 0, 0) : 1;
         // tap word of this lane's entry: all flags of the window requested together
         uint32_t word = 0;
@@ -648,7 +655,8 @@ static dcnn_status launch_dwconv_t(dcnn_ctx* ctx, bool init, const ListArgs& l_i
         const int sgrid = list_grid(ctx, l.max_count, kTileWaves * shape.run, l.self ? kSelfWgPerCu : 8);
         const size_t lds = tile_list_lds(l, w_bytes, run_groups(l.max_count, shape.run), kTileWaves * shape.run, sgrid, true);
         const uint32_t ib = (uint32_t)in_bytes, ip = (uint32_t)in_pixels, mb = (uint32_t)map_bytes, px = (uint32_t)l.max_count;
-#define DCNN_DW_SPARSE(VPL, UB, KS) hipLaunchKernelGGL((dwconv_sparse_kernel<T, VEC, VPL, UB, KS>), dim3(sgrid), dim3(kTileThreads), lds, ctx->stream, l, c, e, shape, ib, ip, mb, px)
+#define DCNN_DW_SPARSE_S(VPL, UB, KS, S) hipLaunchKernelGGL((dwconv_sparse_kernel<T, VEC, VPL, UB, KS, S>), dim3(sgrid), dim3(kTileThreads), lds, ctx->stream, l, c, e, shape, ib, ip, mb, px)
+#define DCNN_DW_SPARSE(VPL, UB, KS) do { if (l.self) DCNN_DW_SPARSE_S(VPL, UB, KS, true); else DCNN_DW_SPARSE_S(VPL, UB, KS, false); } while (0)
 #define DCNN_DW_SPARSE_K(VPL, UB)                                                                                  \
     do {                                                                                                           \
         if (c.k == 3) DCNN_DW_SPARSE(VPL, (VPL == 1 ? 2 : 1), 3);                                                  \
@@ -660,6 +668,7 @@ static dcnn_status launch_dwconv_t(dcnn_ctx* ctx, bool init, const ListArgs& l_i
         else DCNN_DW_SPARSE_K(4, 1);
 #undef DCNN_DW_SPARSE_K
 #undef DCNN_DW_SPARSE
+#undef DCNN_DW_SPARSE_S
         return check_hip(ctx, hipGetLastError(), "dwconv_sparse_kernel launch");
     }
     if (l.self) return fail(ctx, DCNN_EUNSUPPORTED, "depthwise conv: this shape does not build its work list in place");
@@ -889,11 +898,11 @@ __global__ __launch_bounds__(256) void maxpool_commit_kernel(ListArgs l, PoolArg
 }
 
 constexpr int kUpRun = 32;
-template <typename T, int V>
+template <typename T, int V, bool SELF = false>
 __global__ __launch_bounds__(256) void upsample_kernel(ListArgs l, UpsampleArgs a) {
     extern __shared__ __align__(16) unsigned char list_smem[];
     SelfBits sb;
-    const int64_t count = tile_list_count(l, list_smem, sb);
+    const int64_t count = tile_list_count<SELF>(l, list_smem, sb);
     const int C = a.c;
     const int nvec = (C + V - 1) / V;
     const T* in = static_cast<const T*>(a.in_data);
@@ -901,15 +910,15 @@ __global__ __launch_bounds__(256) void upsample_kernel(ListArgs l, UpsampleArgs 
     const int ow = a.w * a.factor, oh = a.h * a.factor;
     // (a list built here: groups of kUpRun entries, strided over the grid; their pixels are in LDS)
     const int64_t groups = (count + kUpRun - 1) / kUpRun;
-    const int32_t* self_px = tile_list_emit(l, list_smem, sb, count, blockIdx.x, groups, gridDim.x, kUpRun);
+    const int32_t* self_px = tile_list_emit<SELF>(l, list_smem, sb, count, blockIdx.x, groups, gridDim.x, kUpRun);
     const int64_t mine = (int64_t)blockIdx.x < groups ? (groups - blockIdx.x + gridDim.x - 1) / gridDim.x * kUpRun : 0;
-    const int64_t total = (l.self ? mine : count) * nvec;
-    const int64_t first = l.self ? threadIdx.x : (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t stride = l.self ? blockDim.x : (int64_t)gridDim.x * blockDim.x;
+    const int64_t total = (SELF ? mine : count) * nvec;
+    const int64_t first = SELF ? threadIdx.x : (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t stride = SELF ? blockDim.x : (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = first; i < total; i += stride) {
         const int64_t j = i / nvec;
         const int vi = (int)(i - j * nvec);
-        const int64_t p = l.self ? (int64_t)self_px[j] : (l.list ? (int64_t)l.list[j] : j);
+        const int64_t p = SELF ? (int64_t)self_px[j] : (l.list ? (int64_t)l.list[j] : j);
         if (p < 0) continue;                                   // past the end of the list
         const int ox = (int)(p % ow);
         const int64_t t = p / ow;
@@ -1057,7 +1066,7 @@ dcnn_status launch_upsample(dcnn_ctx* ctx, int dtype, const ListArgs& l_in, cons
         const int grid = (int)(want < cap ? want : cap);
         const size_t lds = tile_list_lds(l, 0, cdiv(l.max_count, kUpRun), kUpRun, grid, false);
         const bool vec = a.c % (dtype == DCNN_F16 ? 8 : 4) == 0;
-#define DCNN_UP_SELF(T, V) hipLaunchKernelGGL((upsample_kernel<T, V>), dim3(grid), dim3(256), lds, ctx->stream, l, a)
+#define DCNN_UP_SELF(T, V) hipLaunchKernelGGL((upsample_kernel<T, V, true>), dim3(grid), dim3(256), lds, ctx->stream, l, a)
         if (dtype == DCNN_F16) { if (vec) DCNN_UP_SELF(f16, 8); else DCNN_UP_SELF(f16, 1); }
         else { if (vec) DCNN_UP_SELF(float, 4); else DCNN_UP_SELF(float, 1); }
 #undef DCNN_UP_SELF
