@@ -7,6 +7,8 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <type_traits>
+
 #include "../../include/deltacnn.h"
 
 namespace dcnn {
@@ -129,14 +131,16 @@ struct EpilogueArgs {
     int64_t clear_bytes;         // (the output mask of the layer's NEXT step, see dcnn_layer_step)
 };
 
-struct ListArgs {
+struct StoredList {
     const int32_t* list;         // nullptr: identity (entry j is pixel j)
     const int32_t* count;        // nullptr: use count_host
     int64_t count_host;
     int64_t max_count;           // upper bound used to size the grid
     const uint32_t* taps;        // optional, per entry: bit t set iff window tap t of the entry's pixel is in
                                  // bounds and flagged in the input mask (written with the list by the mask pass)
-    // The kernel builds the list itself from the masks (self_list.h); list, count and taps are then null.
+};
+// ... or built by the kernel itself from the masks (self_list.h); list, count and taps are then null.
+struct ListArgs : StoredList {
     int self;
     int want_taps;               // ... with the entries' tap words (bit 30: flagged in m_b)
     const uint8_t* m_in;         // input mask [n, m_h, m_w]
@@ -153,6 +157,9 @@ struct ListArgs {
     int lds_scratch, lds_list;   // byte offsets into the kernel's dynamic LDS (set by the launchers)
     int lds_entries;             // room for this many entries
 };
+// What a kernel takes: the five words of a stored list where it walks one.  (All of ListArgs on every launch, 250 bytes of
+// arguments more, cost 0.4 us a launch: activations of 5-11 us 5-8 % slower.)
+template <bool SELF> using ListParam = std::conditional_t<SELF, ListArgs, StoredList>;
 
 // ---- work lists built by the kernel itself (host side; self_list.h has the device side) ---------------------------
 constexpr int64_t kListMaxPixels = 65536;    // mask_list_kernel: input and output pixels (positions are kept in 16 bits)

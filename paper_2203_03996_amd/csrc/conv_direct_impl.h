@@ -31,7 +31,7 @@ constexpr int kDirectWaves = 4;
 // per tile (the two edges are different lanes).  A third of the gather traffic of a kernel that L2 bounds, and the
 // weight operands of a row's three taps are multiplied with the same gathered registers.
 template <typename T, int NB, int KS, int TI, int D, bool ROW, bool SELF>
-__device__ __forceinline__ void conv_direct_body(const ListArgs& l, const ConvArgs& c, const EpilogueArgs& e, int npass, int cs,
+__device__ __forceinline__ void conv_direct_body(const ListParam<SELF>& l, const ConvArgs& c, const EpilogueArgs& e, int npass, int cs,
                                                  int64_t count, unsigned char* smem, const SelfBits& sb) {
     typedef typename Mma<T>::Vec Vec;
     constexpr int V = Elem<T>::VEC;
@@ -45,12 +45,15 @@ __device__ __forceinline__ void conv_direct_body(const ListArgs& l, const ConvAr
     const int units_per_iter = NW / cs;                        // groups of TI tiles per workgroup iteration
     const int64_t ntiles = (count + kTile - 1) / kTile;
     const WgTileRange r = wg_tile_range((ntiles + units_per_iter * TI - 1) / (units_per_iter * TI));
-    const int32_t* self_px = reinterpret_cast<const int32_t*>(smem + l.lds_list);
-    const uint32_t* self_tap = reinterpret_cast<const uint32_t*>(smem + l.lds_list) + l.lds_entries;
+    const int32_t* self_px = nullptr;
+    const uint32_t* self_tap = nullptr;
     const int group = units_per_iter * TI * kTile;
-    if constexpr (SELF)
-        self_emit<kDirectWaves * kWave>(l, sb, (int)count, SelfSpan{(int)r.begin, (int)r.end, (int)r.step, group},
-                                        const_cast<int32_t*>(self_px), const_cast<uint32_t*>(self_tap));
+    if constexpr (SELF) {
+        int32_t* const px = reinterpret_cast<int32_t*>(smem + l.lds_list);
+        uint32_t* const tap = reinterpret_cast<uint32_t*>(px) + l.lds_entries;
+        self_emit<kDirectWaves * kWave>(l, sb, (int)count, SelfSpan{(int)r.begin, (int)r.end, (int)r.step, group}, px, tap);
+        self_px = px; self_tap = l.want_taps ? tap : nullptr;
+    }
     if (r.begin >= r.end) return;
 
     const int lane = threadIdx.x % kWave;
@@ -86,7 +89,7 @@ __device__ __forceinline__ void conv_direct_body(const ListArgs& l, const ConvAr
         return SELF ? self_px[round * group + (slot * TI + ti) * kTile + col] : list_pixel(l.list, tile_of(wt, ti) * kTile + col, count);
     };
     auto tap_word = [&](int64_t wt, int ti, int p32, int round) -> uint32_t {
-        if (SELF && l.want_taps) return self_tap[round * group + (slot * TI + ti) * kTile + col] & ((1u << (KS * KS)) - 1u);
+        if (SELF && self_tap != nullptr) return self_tap[round * group + (slot * TI + ti) * kTile + col] & ((1u << (KS * KS)) - 1u);
         if (l.taps == nullptr) return p32 >= 0 ? 1u : 0u;      // a 1x1 layer on its input's own list: its one tap
         const int64_t j = tile_of(wt, ti) * kTile + col;
         return (wt < r.end && j < count) ? (l.taps[j] & ((1u << (KS * KS)) - 1u)) : 0u;
@@ -293,7 +296,7 @@ __device__ __forceinline__ void conv_direct_body(const ListArgs& l, const ConvAr
 // Lists too short to keep the chip busy with TI tiles per wave run one tile per wave and a deeper ring instead
 // (more waves, more loads in flight); the length of the list is only known on the device.
 template <typename T, int NB, int KS, int TI, bool SELF>
-__global__ __launch_bounds__(kDirectWaves* kWave, 2) void conv_direct_kernel(ListArgs l, ConvArgs c, EpilogueArgs e, int npass, int cs,
+__global__ __launch_bounds__(kDirectWaves* kWave, 2) void conv_direct_kernel(ListParam<SELF> l, ConvArgs c, EpilogueArgs e, int npass, int cs,
                                                                              int blocked_min_tiles) {
     extern __shared__ __align__(16) unsigned char smem[];
     clear_ahead(e);

@@ -61,7 +61,7 @@ inline size_t conv_ws_lds_bytes(const ConvPlan& p, int dtype, int k, int cout, i
 // 2 dense accumulated output O of a final layer (O += emitted delta; the delta itself is not stored).
 // SELF: the kernel builds its work list (a compile-time variant: the code costs the others 3 % through their registers).
 template <typename T, int NB, int KS, int AUX, bool DUAL, bool SELF>
-__global__ __launch_bounds__(kWsWaves* kWave) void conv_ws_kernel(ListArgs l, ConvArgs c, EpilogueArgs e, int cs) {
+__global__ __launch_bounds__(kWsWaves* kWave) void conv_ws_kernel(ListParam<SELF> l, ConvArgs c, EpilogueArgs e, int cs) {
     typedef typename Mma<T>::Vec Vec;
     constexpr int V = Elem<T>::VEC;
     typedef typename RawOf<T, V>::type Raw;
@@ -80,8 +80,12 @@ __global__ __launch_bounds__(kWsWaves* kWave) void conv_ws_kernel(ListArgs l, Co
 
     const int tiles_per_iter = NP / cs;
     // (a list built here: its scratch memory is the staging area, which nothing uses yet; the entries follow everything else)
-    const int32_t* self_px = reinterpret_cast<const int32_t*>(smem + l.lds_list);
-    const uint32_t* self_tap = reinterpret_cast<const uint32_t*>(smem + l.lds_list) + l.lds_entries;
+    int32_t* self_px = nullptr;
+    uint32_t* self_tap = nullptr;
+    if constexpr (SELF) {
+        self_px = reinterpret_cast<int32_t*>(smem + l.lds_list);
+        self_tap = reinterpret_cast<uint32_t*>(self_px) + l.lds_entries;
+    }
     int64_t count;
     SelfBits sb;
     SelfAhead ahead;
@@ -135,7 +139,7 @@ __global__ __launch_bounds__(kWsWaves* kWave) void conv_ws_kernel(ListArgs l, Co
     const WgTileRange r = wg_tile_range((count + tiles_per_iter * kTile - 1) / (tiles_per_iter * kTile));
     if constexpr (SELF)
         self_emit<kWsWaves * kWave>(l, sb, (int)count, SelfSpan{(int)r.begin, (int)r.end, (int)r.step, tiles_per_iter * kTile},
-                                    const_cast<int32_t*>(self_px), const_cast<uint32_t*>(self_tap));
+                                    self_px, self_tap);
     if (r.begin >= r.end) return;                              // nothing for this workgroup: skip the weight load
     const int rounds = (int)((r.end - r.begin + r.step - 1) / r.step);
 
@@ -215,8 +219,11 @@ __global__ __launch_bounds__(kWsWaves* kWave) void conv_ws_kernel(ListArgs l, Co
         const int kgroups2 = DUAL ? (c.kch2 + GK - 1) / GK : 1;
         (void)rs_in2; (void)cin2_bytes; (void)origin2; (void)kgroups2;
         auto tap_word = [&](int rd, int p32) -> uint32_t {
-            if (SELF ? !l.want_taps : l.taps == nullptr) return p32 >= 0 ? 1u : 0u;
-            if (SELF) return rd < rounds ? self_tap[(rd * tiles_per_iter + slot) * kTile + col] : 0u;
+            if constexpr (SELF) {
+                if (!l.want_taps) return p32 >= 0 ? 1u : 0u;
+                return rd < rounds ? self_tap[(rd * tiles_per_iter + slot) * kTile + col] : 0u;
+            }
+            if (l.taps == nullptr) return p32 >= 0 ? 1u : 0u;
             const int64_t j = tile_of(rd) * kTile + col;
             return (rd < rounds && j < count) ? l.taps[j] : 0u;
         };

@@ -58,7 +58,7 @@ template <typename T> __device__ __forceinline__ float round_residue(float x) { 
 __device__ __forceinline__ float act_hi(int act) { return act == DCNN_ACT_RELU6 ? 6.0f : INFINITY; }
 __device__ __forceinline__ float act_clamp(float x, float hi) { return __builtin_amdgcn_fmed3f(x, 0.0f, hi); }
 
-__device__ __forceinline__ int64_t list_count(const ListArgs& l) {
+__device__ __forceinline__ int64_t list_count(const StoredList& l) {
     return l.count ? (int64_t)(*l.count) : l.count_host;
 }
 

@@ -651,7 +651,7 @@ dcnn_status launch_mask_compact(dcnn_ctx* ctx, const MaskPassArgs& m) {
 }
 
 // ---- statistics: x^T rows read / written by a step (see launch_xt_row_count) --------------------------
-__global__ __launch_bounds__(kMaskThreads) void xt_row_count_kernel(int phase, ListArgs l, const uint8_t* flags, uint8_t* before,
+__global__ __launch_bounds__(kMaskThreads) void xt_row_count_kernel(int phase, StoredList l, const uint8_t* flags, uint8_t* before,
                                                                     unsigned long long* io) {
     __shared__ int s_red[kMaskThreads / kWave];
     const int64_t count = list_count(l);

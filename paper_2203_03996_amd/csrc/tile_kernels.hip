@@ -20,20 +20,26 @@ static int list_grid(const dcnn_ctx* ctx, int64_t max_count, int entries_per_wg,
 
 // Work lists built by the kernel itself (self_list.h), for the kernels of kTileThreads threads: the length of the list, and
 // the entries of this workgroup's groups.  SELF is a variant of its own: with both ways in one kernel the walk of a stored list
-// took 0.4-1 us longer a launch (@).
+// took 0.4-1 us longer a launch.
 template <bool SELF>
-__device__ __forceinline__ int64_t tile_list_count(const ListArgs& l, unsigned char* smem, SelfBits& sb) {
-    if constexpr (!SELF) return list_count(l);
-    sb = self_carve(l, smem + l.lds_scratch);
-    return self_build<kTileThreads>(l, sb, nullptr);
+__device__ __forceinline__ int64_t tile_list_count(const ListParam<SELF>& l, unsigned char* smem, SelfBits& sb) {
+    if constexpr (SELF) {
+        sb = self_carve(l, smem + l.lds_scratch);
+        return self_build<kTileThreads>(l, sb, nullptr);
+    } else {
+        return list_count(l);
+    }
 }
 template <bool SELF>
-__device__ __forceinline__ const int32_t* tile_list_emit(const ListArgs& l, unsigned char* smem, const SelfBits& sb, int64_t count,
+__device__ __forceinline__ const int32_t* tile_list_emit(const ListParam<SELF>& l, unsigned char* smem, const SelfBits& sb, int64_t count,
                                                          int64_t begin, int64_t end, int64_t step, int entries) {
-    if constexpr (!SELF) return nullptr;
-    int32_t* px = reinterpret_cast<int32_t*>(smem + l.lds_list);
-    self_emit<kTileThreads>(l, sb, (int)count, SelfSpan{(int)begin, (int)end, (int)step, entries}, px, nullptr);
-    return px;
+    if constexpr (SELF) {
+        int32_t* px = reinterpret_cast<int32_t*>(smem + l.lds_list);
+        self_emit<kTileThreads>(l, sb, (int)count, SelfSpan{(int)begin, (int)end, (int)step, entries}, px, nullptr);
+        return px;
+    } else {
+        return nullptr;
+    }
 }
 // Dynamic LDS of such a launch behind `used` bytes of the kernel's own, and where the pieces lie.  `groups`: groups of `entries`
 // list entries that the kernel walks when every pixel is listed, counted by the kernel's own rule.
@@ -46,7 +52,7 @@ static size_t tile_list_lds(ListArgs& l, size_t used, int64_t groups, int64_t en
 }
 
 template <typename T, int V, int VPL, int UB, bool SELF>
-__global__ __launch_bounds__(kTileThreads) void act_sparse_kernel(ListArgs l, ActArgs a, EpilogueArgs e, TailShape shape,
+__global__ __launch_bounds__(kTileThreads) void act_sparse_kernel(ListParam<SELF> l, ActArgs a, EpilogueArgs e, TailShape shape,
                                                                    uint32_t map_bytes, uint32_t pixels) {
     extern __shared__ __align__(16) unsigned char list_smem[];
     clear_ahead(e);
@@ -94,7 +100,7 @@ __global__ __launch_bounds__(kTileThreads) void act_sparse_kernel(ListArgs l, Ac
 // decisions are those of sparse_tile_tail (Section 3.1, Eqs. 4-6).  Channels a multiple of 4 vectors.
 
 template <typename T, int V, int VPW, bool SELF>
-__global__ __launch_bounds__(kTileThreads) void act_wide_kernel(ListArgs l, ActArgs a, EpilogueArgs e, uint32_t map_bytes, uint32_t pixels) {
+__global__ __launch_bounds__(kTileThreads) void act_wide_kernel(ListParam<SELF> l, ActArgs a, EpilogueArgs e, uint32_t map_bytes, uint32_t pixels) {
     typedef typename RawOf<T, V>::type Raw;
     constexpr uint32_t ES = sizeof(T);
     __shared__ float s_max[2][kWideRun][kTileWaves];
@@ -231,7 +237,7 @@ __global__ __launch_bounds__(kTileThreads) void act_wide_kernel(ListArgs l, ActA
 
 // ---- activation + truncation (+ add) ----------------------------------------------------------
 template <typename T, int V, int VPL>
-__global__ __launch_bounds__(kTileThreads) void act_kernel(ListArgs l, ActArgs a, EpilogueArgs e) {
+__global__ __launch_bounds__(kTileThreads) void act_kernel(StoredList l, ActArgs a, EpilogueArgs e) {
     typedef typename RawOf<T, V>::type Raw;
     constexpr int UB = (V * VPL >= 16) ? 2 : 4;
     clear_ahead(e);
@@ -420,7 +426,7 @@ template <typename T, int V, int VPL, int UB, int KS> struct DwSrc {
 };
 
 template <typename T, int V, int VPL, int UB, int KS, bool SELF>
-__global__ __launch_bounds__(kTileThreads) void dwconv_sparse_kernel(ListArgs l, ConvArgs c, EpilogueArgs e, TailShape shape,
+__global__ __launch_bounds__(kTileThreads) void dwconv_sparse_kernel(ListParam<SELF> l, ConvArgs c, EpilogueArgs e, TailShape shape,
                                                                       uint32_t in_bytes, uint32_t in_pixels, uint32_t map_bytes,
                                                                       uint32_t pixels) {
     typedef typename RawOf<T, V>::type Raw;
@@ -492,7 +498,7 @@ __global__ __launch_bounds__(kTileThreads) void dwconv_sparse_kernel(ListArgs l,
 // Work list = flagged OUTPUT pixels.  Every tap's update flag is checked before its values are
 // read (unflagged memory is invalid), load and multiply are fused per pixel.
 template <typename T, int V, int VPL>
-__global__ __launch_bounds__(kTileThreads) void dwconv_kernel(ListArgs l, ConvArgs c, EpilogueArgs e, int init) {
+__global__ __launch_bounds__(kTileThreads) void dwconv_kernel(StoredList l, ConvArgs c, EpilogueArgs e, int init) {
     typedef typename RawOf<T, V>::type Raw;
     constexpr int UB = 2;
     const int64_t count = list_count(l);
@@ -782,7 +788,7 @@ __global__ __launch_bounds__(kDeltaGenThreads) void deltagen_kernel(DeltaGenArgs
 
 // Delta generation for a given list of pixels (the dilated input mask): delta <- frame - P, P <- frame.
 template <typename T, int V>
-__global__ __launch_bounds__(256) void deltagen_apply_kernel(ListArgs l, DeltaGenArgs a) {
+__global__ __launch_bounds__(256) void deltagen_apply_kernel(StoredList l, DeltaGenArgs a) {
     const int64_t count = list_count(l);
     const int C = a.c;
     const int nvec = (C + V - 1) / V;
@@ -806,7 +812,7 @@ __global__ __launch_bounds__(256) void deltagen_apply_kernel(ListArgs l, DeltaGe
 
 // ---- final accumulation, max pooling, upsampling ----------------------------------------------
 template <typename T, int V>
-__global__ __launch_bounds__(256) void accum_kernel(ListArgs l, AccumArgs a) {
+__global__ __launch_bounds__(256) void accum_kernel(StoredList l, AccumArgs a) {
     const int64_t count = list_count(l);
     const int C = a.c;
     const int nvec = (C + V - 1) / V;
@@ -829,7 +835,7 @@ __global__ __launch_bounds__(256) void accum_kernel(ListArgs l, AccumArgs a) {
 // Pooling output pass over the flagged OUTPUT pixels: dy = max_w(x^A (+ delta at flagged inputs)) - max_w(x^A).
 // x^A itself is brought up to date by the commit pass afterwards.
 template <typename T, int V>
-__global__ __launch_bounds__(256) void maxpool_out_kernel(ListArgs l, PoolArgs a, int init) {
+__global__ __launch_bounds__(256) void maxpool_out_kernel(StoredList l, PoolArgs a, int init) {
     const int64_t count = list_count(l);
     const int C = a.c;
     const int nvec = (C + V - 1) / V;
@@ -877,7 +883,7 @@ __global__ __launch_bounds__(256) void maxpool_out_kernel(ListArgs l, PoolArgs a
 }
 
 template <typename T, int V>
-__global__ __launch_bounds__(256) void maxpool_commit_kernel(ListArgs l, PoolArgs a) {
+__global__ __launch_bounds__(256) void maxpool_commit_kernel(StoredList l, PoolArgs a) {
     const int64_t count = list_count(l);
     const int C = a.c;
     const int nvec = (C + V - 1) / V;
@@ -899,7 +905,7 @@ __global__ __launch_bounds__(256) void maxpool_commit_kernel(ListArgs l, PoolArg
 
 constexpr int kUpRun = 32;
 template <typename T, int V, bool SELF = false>
-__global__ __launch_bounds__(256) void upsample_kernel(ListArgs l, UpsampleArgs a) {
+__global__ __launch_bounds__(256) void upsample_kernel(ListParam<SELF> l, UpsampleArgs a) {
     extern __shared__ __align__(16) unsigned char list_smem[];
     SelfBits sb;
     const int64_t count = tile_list_count<SELF>(l, list_smem, sb);
@@ -957,7 +963,7 @@ __global__ __launch_bounds__(256) void upsample_kernel(ListArgs l, UpsampleArgs 
 // stream's flagged pixels p = w, w + 4, ... in ascending order, the four partial sums are added in a fixed order:
 // the result does not depend on scheduling.
 template <typename T, int V>
-__global__ __launch_bounds__(256) void gavgpool_kernel(ListArgs l, GapArgs a) {
+__global__ __launch_bounds__(256) void gavgpool_kernel(StoredList l, GapArgs a) {
     __shared__ float s_part[3][kWave][V];
     const int64_t count = list_count(l);
     if ((int64_t)blockIdx.x >= count) return;                  // uniform for the block
@@ -996,7 +1002,7 @@ __global__ __launch_bounds__(256) void gavgpool_kernel(ListArgs l, GapArgs a) {
 // not flagged at p contributes zeros; its memory there is not read).  One element per thread: the channel
 // counts of the two inputs need not be multiples of the vector width.
 template <typename T>
-__global__ __launch_bounds__(256) void concat_kernel(ListArgs l, ConcatArgs a) {
+__global__ __launch_bounds__(256) void concat_kernel(StoredList l, ConcatArgs a) {
     const int64_t count = list_count(l);
     const int C = a.ca + a.cb;
     const T* xa = static_cast<const T*>(a.a_data);
