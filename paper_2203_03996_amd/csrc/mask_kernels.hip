@@ -568,10 +568,17 @@ __global__ __launch_bounds__(kListThreads) void mask_list_kernel(ListArgs l, uin
     }
 }
 
+// Where one launch is the faster one.  Every workgroup repeats the work on the whole map, so it grows with the map where the two
+// passes cost 7-10 us up to 64 K pixels.  us, two passes -> one launch: 3x3 on 16 K pixels 7.5 -> 4.6, on 64 K 7.6 -> 6.8.  A second
+// mask is a second round trip for all of it: 3x3 on 48 K 7.7 -> 6.9, but on 62 K 8.1 -> 9.3, an addition of two masks of 62 K 6.2 ->
+// 7.5 (kernel times).  Stride 2 tests the outputs one by one: 1x1 on 24 K input pixels 7.3 -> 7.4, on 32 K 7.3 -> 7.7, on 64 K
+// 7.5 -> 11.4; 3x3 on 24 K 9.3 -> 8.6, on 40 K 9.1 -> 10.0.
+constexpr int64_t kListMaxPixelsTwo = 49152, kListMaxPixelsStrided = 24576;
 static bool list_kernel_serves(const MaskPassArgs& m, int64_t in_px, int64_t out_px) {
     if (m.emit_only || m.idx_out == nullptr || m.kw > 0 || in_px > kListMaxPixels || out_px > kListMaxPixels) return false;
     if (m.up > 1) { if (m.bilinear || m.mask_b != nullptr) return false; }
     else if (m.stride > 2 || !((m.k == 1 && m.pad == 0) || (m.k == 3 && m.pad == 1))) return false;
+    if ((m.stride == 2 && in_px > kListMaxPixelsStrided) || (m.mask_b != nullptr && out_px > kListMaxPixelsTwo)) return false;
     if (m.b_stride > 0 && out_px > kSelfMaxPixels) return false;        // (sampled pixel by pixel by every workgroup)
     return (reinterpret_cast<uintptr_t>(m.mask_in) | reinterpret_cast<uintptr_t>(m.mask_b) | reinterpret_cast<uintptr_t>(m.mask_out)) % 16 == 0;
 }
@@ -614,7 +621,7 @@ static dcnn_status mask_compact_on(dcnn_ctx* ctx, const MaskPassArgs& m, const W
         a.bilinear = m.bilinear;
         a.b_stride = m.b_stride; a.b_h = m.b_h; a.b_w = m.b_w;
         a.kw = m.kw > 0 ? m.kw : m.k; a.pad_w = m.kw > 0 ? m.pad_w : m.pad;
-        if (span_fits(a)) fused = false;                       // (window taps byte by byte cost more than a second launch)
+        if (span_fits(a)) fused = false;                       // (byte by byte the windows of 512 pixels take 27 us at 5x5 and 71 at 9x9, in two launches 8.4 and 10.1)
         if (!fused && span_fits(a)) {
             hipLaunchKernelGGL(mask_span_kernel, dim3(nchunks), dim3(kMaskThreads), 0, ctx->stream, a, make_fastdiv((uint32_t)m.ow),
                                make_fastdiv((uint32_t)m.oh));
