@@ -322,7 +322,9 @@ static dcnn_status launch_act_t(dcnn_ctx* ctx, bool init, const ListArgs& l_in, 
     if (vec && nvec >= 2 * kWave && nvec % kTileWaves == 0 && nvec <= kWave * kTileWaves && map_bytes > 0 &&
         map_bytes <= kWsMaxBytes && l.max_count <= 65536) {
         const int64_t units = wide_groups(l.max_count);
-        const int64_t cap = (int64_t)ctx->num_cu * 8;
+        // (two fit a compute unit, and in place each builds the list: beyond that they built it again and again.  16 K pixels of 1024
+        // channels, 3 / 30 / 100 % listed: 32 / 66 / 100 us with eight, 15.5 / 50 / 80 on a stored list, now 13.5 / 49 / 76.)
+        const int64_t cap = (int64_t)ctx->num_cu * (l.self ? 2 : 8);
         const int wgrid = (int)(units < cap ? units : cap);
         const uint32_t mb = (uint32_t)map_bytes, px = (uint32_t)l.max_count;
         const size_t lds = tile_list_lds(l, 0, wide_groups(l.max_count), kWideRun, wgrid, false);
