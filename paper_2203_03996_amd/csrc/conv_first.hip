@@ -3,7 +3,8 @@
 // f(v); Fig. 2).  No pixel is decided on, so the output channels need not meet and the work splits freely over
 // pixels AND channels -- which is what the sparse kernels, whose tail wants the whole pixel, cannot do.
 //
-// A wave owns 64 pixels x 64 output channels (2 x 2 MFMA 32x32 blocks): four 16-byte operands per lane and K-step feed four
+// A wave owns 64 pixels x 64 output channels (2 x 2 MFMA 32x32 blocks; x 32 where the last tile would be half empty, see
+// launch_conv_first_t): four 16-byte operands per lane and K-step feed four
 // MFMAs, straight from global memory / L2 into registers, a ring of kFirstRing K-steps in flight.  With enough such
 // tiles the four waves of a workgroup take four pixel tiles of the same channels (they share the weights in the
 // vector cache); with too few -- the deep stages of a backbone: 512 pixels, K = 4608 -- they split the K-steps of ONE
@@ -16,7 +17,7 @@
 namespace dcnn {
 
 constexpr int kFirstWaves = 4;
-constexpr int kFirstPx = 64, kFirstCh = 64;                    // tile of a wave
+constexpr int kFirstPx = 64;                                   // tile of a wave: pixels; its channels are 32 * TC
 constexpr int kFirstRing = 4;                                  // K-steps whose operands are in registers or on their way
 
 struct FirstArgs {
@@ -29,27 +30,29 @@ struct FirstArgs {
     const void* bias2;             // bias of the projection
 };
 
-template <typename T> constexpr int first_stage_stride() { return kFirstCh * (int)sizeof(T) + kStagePad; }
+template <typename T> constexpr int first_stage_stride(int channels) { return channels * (int)sizeof(T) + kStagePad; }
 
-template <typename T, int SPLIT>
+template <typename T, int SPLIT, int TC>
 __global__ __launch_bounds__(kFirstWaves* kWave, 2) void conv_first_kernel(ConvArgs c, EpilogueArgs e, FirstArgs f) {
     typedef typename Mma<T>::Vec Vec;
     constexpr int V = Elem<T>::VEC;
     typedef typename RawOf<T, V>::type Raw;
     constexpr int ES = (int)sizeof(T);
-    constexpr int TP = kFirstPx / 32, TC = kFirstCh / 32, D = kFirstRing;
-    constexpr int stage_stride = first_stage_stride<T>();
+    constexpr int TP = kFirstPx / 32, kFirstCh = TC * 32, D = kFirstRing;
+    constexpr int stage_stride = first_stage_stride<T>(kFirstCh);
     static_assert(SPLIT == 1 || SPLIT == kFirstWaves, "one tile per wave or one tile per workgroup");
-    static_assert(TP * TC == kFirstWaves, "after a split every wave sums one block");
+    static_assert(SPLIT == 1 || TP * TC <= kFirstWaves, "after a split a wave sums one block");
     extern __shared__ __align__(16) unsigned char smem[];
 
-    // One tile per wave: units in launch order.  (A contiguous eighth per XCD, workgroup b running on XCD b % 8, keeps
-    // neighbours in one L2 but spreads the eight fronts over memory a power of two apart: 563 -> 530 us for the layer above
-    // without it.)  One tile per workgroup: the XCDs do take an eighth each, so that a weight slice is fetched by few L2s.
+    // One tile per wave: pixel groups in launch order, the channel groups of one behind each other on one XCD (workgroup b runs
+    // on XCD b % 8): they gather the same pixels and, where rows are no multiple of a cache line, write parts of the same lines
+    // (8 streams of 128x128, 1x1 256->320: 99 us with the channel groups on different XCDs, now 70).  (A contiguous eighth of the
+    // pixels per XCD spreads the eight fronts over memory a power of two apart: 563 -> 530 us for the layer above without it.)
+    // One tile per workgroup: the XCDs do take an eighth each, so that a weight slice is fetched by few L2s.
+    const int64_t in_xcd = blockIdx.x / kXcd, xcd = blockIdx.x % kXcd;
     const int64_t per = (f.units + kXcd - 1) / kXcd;
-    const int64_t in_xcd = blockIdx.x / kXcd;
-    const int64_t unit = SPLIT == 1 ? (int64_t)blockIdx.x : (int64_t)(blockIdx.x % kXcd) * per + in_xcd;
-    if (in_xcd >= per || unit >= f.units) return;              // uniform for the workgroup
+    const int64_t unit = SPLIT == 1 ? (in_xcd / f.cgroups * kXcd + xcd) * f.cgroups + in_xcd % f.cgroups : xcd * per + in_xcd;
+    if ((SPLIT != 1 && in_xcd >= per) || unit >= f.units) return;   // uniform for the workgroup
     const int lane = threadIdx.x % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int col = lane % 32, g = lane / 32;
@@ -206,20 +209,22 @@ __global__ __launch_bounds__(kFirstWaves* kWave, 2) void conv_first_kernel(ConvA
                         partial[((wave * (TP * TC) + i * TC + b) * 4 + q) * kWave + lane] = v;
                     }
             lds_block_sync();
-            f32x16 sum;
+            if (wave < TP * TC) {
+                f32x16 sum;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                f32x4 v = partial[(wave * 4 + q) * kWave + lane];
+                for (int q = 0; q < 4; ++q) {
+                    f32x4 v = partial[(wave * 4 + q) * kWave + lane];
 #pragma unroll
-                for (int o = 1; o < kFirstWaves; ++o) {
-                    const f32x4 u = partial[((o * (TP * TC) + wave) * 4 + q) * kWave + lane];
+                    for (int o = 1; o < kFirstWaves; ++o) {
+                        const f32x4 u = partial[((o * (TP * TC) + wave) * 4 + q) * kWave + lane];
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) v[k] += u[k];
+                        for (int k = 0; k < 4; ++k) v[k] += u[k];
+                    }
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) sum[4 * q + k] = v[k];
                 }
-#pragma unroll
-                for (int k = 0; k < 4; ++k) sum[4 * q + k] = v[k];
+                stage_block(sum, wave / TC, wave % TC, bias, add);
             }
-            stage_block(sum, wave / TC, wave % TC, bias, add);
             lds_block_sync();                                  // (the partial sums may be overwritten, the staged tile may be read)
         }
     };
@@ -234,7 +239,7 @@ __global__ __launch_bounds__(kFirstWaves* kWave, 2) void conv_first_kernel(ConvA
     }
     lds_wave_sync();
 
-    // tail: 64 channels of a pixel are NV vectors, neighbouring lanes hold neighbouring vectors
+    // tail: the tile's channels of a pixel are NV vectors, neighbouring lanes hold neighbouring vectors
     constexpr int NV = kFirstCh / V;
     constexpr int NLANES = SPLIT == 1 ? kWave : kFirstWaves * kWave;
     constexpr int PPI = NLANES / NV, NIT = kFirstPx / PPI;
@@ -289,38 +294,59 @@ static uint64_t first_stream_bytes(size_t es, const ConvArgs& c) {
     return a > b ? a : b;
 }
 
-// (nothing here depends on the number of streams, see launch_conv_first_t)
-bool conv_first_supported(int dtype, const ConvArgs& c, int cout, bool flat) {
+// The waves of a workgroup share a tile's K-steps where ONE stream has fewer tiles than the chip has compute units (256) and K
+// is long enough to be worth cutting.  The number of streams stays out of the rule on purpose: the order of the sum
+// must not depend on it (a stream gives the same bits alone and in a batch).  Measured against the sum in one chain over 80
+// shapes: the distance from the 64-bit result is the same in fp16 (rounding to storage) and half as large in fp32.
+static bool first_splits(const ConvArgs& c) {
+    return cdiv((int64_t)c.oh * c.ow, kFirstPx) * cdiv(c.cout, 64) < 256 && c.k * c.k * c.kch >= 8 * kFirstWaves;
+}
+// Tiles of 32 channels for layers of up to 32: the other half of a tile of 64 would be padding (fp32, 4 streams of 128x128, 32
+// channels: 5x5 128->32 240 us, now 154, plain kernel 178).
+static bool first_narrow(const ConvArgs& c) { return c.cout <= 32; }
+
+// (What decides between sums in one chain and split ones looks at one stream; kernels that sum in one chain give the same bits.)
+bool conv_first_supported(int dtype, const ConvArgs& c, const ConvPlan& p) {
     const size_t es = dtype_size(dtype);
     const int vec = dtype == DCNN_F16 ? 8 : 4;
-    if (flat || cout % vec != 0 || ((size_t)c.cin * es) % 16 != 0) return false;
-    return first_stream_bytes(es, c) <= kWsMaxBytes && (c.in2_data == nullptr || ((size_t)c.cin2 * es) % 16 == 0);
+    if (p.flat || p.w_bytes > kWsMaxBytes || c.cout % vec != 0 || ((size_t)c.cin * es) % 16 != 0) return false;
+    if (first_stream_bytes(es, c) > kWsMaxBytes || (c.in2_data != nullptr && ((size_t)c.cin2 * es) % 16 != 0)) return false;
+    const int64_t ctiles = first_narrow(c) ? 1 : cdiv(c.cout, 64), tiles = cdiv((int64_t)c.n * c.oh * c.ow, kFirstPx) * ctiles;
+    if (c.in2_data != nullptr || first_narrow(c) || first_splits(c) || tiles < 1024) return true;
+    // Matrix work bounds long sums over enough tiles to fill the chip, and there the plain kernel's plan is the better one where it
+    // pads the channels to fewer blocks than tiles of 64 do, or, on large maps, where the number of tiles leaves waves of a workgroup
+    // to gather for themselves: 8 streams of 128x128, fp16, 3x3 256->96 193 us against 152, 5x5 256->160 957 against 714 (but one
+    // stream of the former 48 against 73, 4 streams of 96x96 of the latter 241 against 364, and 3x3 64->96 54 against 58: short sums
+    // are bound by the gathers); fp32, whose K-steps take 16 times as long, 1x1 32->72 41 against 38 and on 96x96 18 against 21.
+    const bool uneven = ctiles > 2 && ctiles % 4 != 0;
+    const int long_sum = dtype == DCNN_F16 ? 64 : (tiles < 4096 ? 32 : 4);     // K-steps
+    if ((ctiles * 64 > p.cout_pad || (uneven && tiles >= 4096)) && c.k * c.k * c.kch >= long_sum) return false;
+    // Stores bound short sums on large maps, and whole rows are the better ones where the tiles' parts of a row share 64-byte pieces:
+    // 1x1 64->328 on the same maps 111 us against 77, 64->136 50 against 46 (but on 4 of 96x96 34 against 37 and 16 against 29,
+    // 256->328 100 against 150, and with whole pieces 64->160 30 against 46).
+    return c.k * c.k * c.kch > 8 || tiles < 4096 || ((size_t)c.cout * es) % 64 == 0 || !(uneven || ctiles > 4);
 }
 
 template <typename T>
 static dcnn_status launch_conv_first_t(dcnn_ctx* ctx, const ConvArgs& c, const EpilogueArgs& e, const ConvPlan& p, const void* bias2) {
     FirstArgs f{};
     f.nb = p.nb; f.ngroups = p.npass * p.cs;
-    const int ctiles = (int)cdiv(e.c, kFirstCh);
     f.pixels = (int64_t)c.n * c.oh * c.ow;
     f.bias2 = bias2;
     const int64_t ptiles = cdiv(f.pixels, kFirstPx);
-    // The waves of a workgroup share a tile's K-steps where ONE stream has fewer tiles than the chip has compute units and K
-    // is long enough to be worth cutting.  The number of streams stays out of the rule on purpose: the order of the sum
-    // must not depend on it (a stream gives the same bits alone and in a batch).
-    const bool split = cdiv((int64_t)c.oh * c.ow, kFirstPx) * ctiles < 256 && c.k * c.k * c.kch >= 8 * kFirstWaves;
-    f.wc = split ? 1 : (ctiles >= 4 ? 4 : ctiles);             // (three tiles: two side by side, then one)
-    if (f.wc == 3) f.wc = 2;
+    const bool split = first_splits(c), narrow = first_narrow(c);
+    const int ctiles = narrow ? 1 : (int)cdiv(e.c, 64);
+    f.wc = split ? 1 : (ctiles % 4 == 0 ? 4 : (ctiles % 2 == 0 ? 2 : 1));      // (no wave without channels)
     f.cgroups = (int)cdiv(ctiles, f.wc);
     f.units = (split ? ptiles : cdiv(ptiles, kFirstWaves / f.wc)) * f.cgroups;
-    const size_t stage = (size_t)kFirstPx * first_stage_stride<T>();
-    const size_t lds = split ? (size_t)kFirstWaves * 4 * 4 * kWave * 16 + stage : kFirstWaves * stage;
-    const int64_t grid = cdiv(f.units, kXcd) * kXcd;
+    const size_t stage = (size_t)kFirstPx * first_stage_stride<T>(narrow ? 32 : 64);
+    const size_t lds = split ? (size_t)kFirstWaves * (narrow ? 2 : 4) * 4 * kWave * 16 + stage : kFirstWaves * stage;
+    const int64_t grid = split ? cdiv(f.units, kXcd) * kXcd : cdiv(f.units / f.cgroups, kXcd) * kXcd * f.cgroups;
     if (grid > INT32_MAX) return fail(ctx, DCNN_ESHAPE, "first frame: %lld workgroups", (long long)grid);
     hipError_t err = hipSuccess;
-#define DCNN_FIRST_LAUNCH(SPLIT)                                                                                 \
+#define DCNN_FIRST_LAUNCH(SPLIT, TC)                                                                               \
     do {                                                                                                         \
-        auto kern = conv_first_kernel<T, SPLIT>;                                                                 \
+        auto kern = conv_first_kernel<T, SPLIT, TC>;                                                                 \
         static bool attr_set = false;                                                                            \
         if (!attr_set) {                                                                                         \
             err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes); \
@@ -328,7 +354,9 @@ static dcnn_status launch_conv_first_t(dcnn_ctx* ctx, const ConvArgs& c, const E
         }                                                                                                        \
         if (err == hipSuccess) hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kFirstWaves * kWave), lds, ctx->stream, c, e, f); \
     } while (0)
-    if (split) DCNN_FIRST_LAUNCH(kFirstWaves); else DCNN_FIRST_LAUNCH(1);
+    if (split) { if (narrow) DCNN_FIRST_LAUNCH(kFirstWaves, 1); else DCNN_FIRST_LAUNCH(kFirstWaves, 2); }
+    else if (narrow) DCNN_FIRST_LAUNCH(1, 1);
+    else DCNN_FIRST_LAUNCH(1, 2);
 #undef DCNN_FIRST_LAUNCH
     if (err != hipSuccess) return check_hip(ctx, err, "hipFuncSetAttribute(conv_first_kernel)");
     return check_hip(ctx, hipGetLastError(), "conv_first_kernel launch");

@@ -136,7 +136,7 @@ DCNN_DECL_ALL(f32)
 #undef DCNN_DECL_ALL
 #undef DCNN_DECL
 // conv_first.hip
-bool conv_first_supported(int dtype, const ConvArgs& c, int cout, bool flat);
+bool conv_first_supported(int dtype, const ConvArgs& c, const ConvPlan& p);
 // conv_unit.hip
 bool conv_unit_supported(const dcnn_ctx* ctx, int dtype, const ListArgs& l, const ConvArgs& c, const EpilogueArgs& e, const ConvPlan& p);
 dcnn_status launch_conv_unit(dcnn_ctx* ctx, int dtype, const ListArgs& l, const ConvArgs& c, const EpilogueArgs& e, const ConvPlan& p);
@@ -159,7 +159,7 @@ dcnn_status launch_conv(dcnn_ctx* ctx, int dtype, bool init, const ListArgs& l, 
     c.div_oh = make_fastdiv((uint32_t)c.oh);
     // The dense first frame over 16-byte pixels and channel vectors (a stream's input below 2 GiB) splits over channels as well as
     // pixels; everything else of a first frame stays with the plain kernel.
-    if (init && p.w_bytes <= kWsMaxBytes && conv_first_supported(dtype, c, c.cout, p.flat)) return launch_conv_first(ctx, dtype, c, e, p, c.bias2);
+    if (init && conv_first_supported(dtype, c, p)) return launch_conv_first(ctx, dtype, c, e, p, c.bias2);
     if (!init && conv_unit_supported(ctx, dtype, l, c, e, p)) return launch_conv_unit(ctx, dtype, l, c, e, p);
     if (init && c.in2_data) return fail(ctx, DCNN_EUNSUPPORTED, "first frame of a convolution with a fused projection: shape not covered");
 #define DCNN_CASE(NB) case NB: return dtype == DCNN_F16 ? launch_conv_f16_nb##NB(ctx, init, l, c, e, p) : launch_conv_f32_nb##NB(ctx, init, l, c, e, p);

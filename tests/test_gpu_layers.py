@@ -867,6 +867,11 @@ def test_error_paths():
     ("f32", 7, 2, 8, 12, (1, 21, 19), "plain"),          # wide window, 12 channels
     ("f16", 1, 1, 32, 256, (2, 12, 11), "projection"),   # second K loop, four channel tiles side by side
     ("f32", 1, 1, 16, 64, (1, 9, 31), "projection"),
+    ("f16", 1, 1, 24, 32, (2, 20, 21), "act"),           # tiles of 32 channels, whole and split sums, a projection
+    ("f32", 3, 1, 24, 20, (2, 11, 13), "residual"),
+    ("f16", 1, 1, 48, 24, (2, 9, 14), "projection"),
+    ("f16", 1, 1, 16, 320, (3, 17, 23), "act"),          # five channel tiles, one wave each, pixel groups no multiple of the XCDs
+    ("f16", 3, 1, 128, 72, (4, 92, 94), "act"),          # batch on the plain kernel, a single stream on tiles
 ])
 def test_first_frame_tiles(S, k, stride, cin, cout, nhw, mode):
     """The dense first frame at the edges of its tiles (64 pixels x 64 channels, with and without split K), and the same
