@@ -193,14 +193,30 @@ static int unit_waves(const dcnn_ctx* ctx, int64_t tiles, int blocks) {
     return w;
 }
 
-bool conv_unit_supported(const dcnn_ctx*, int dtype, const ListArgs& l, const ConvArgs& c, const EpilogueArgs& e, const ConvPlan& p) {
+// The length of a list is known on the device only, so the rule looks at the map's: units if every pixel is listed, K-steps of a
+// sum and passes over the channels.  A unit fetches its weights for 32 pixels, the register-blocked kernel and the streamed one for
+// more, so long sums over full lists of large maps are theirs.  us, other kernel -> units, all pixels / 30 % / 10 % listed:
+//   up to a wave per SIMD:   3x3 256->256 on 4096 pixels 41 -> 29 / 32 -> 20 / .., 1x1 1024->256 17.5 -> 15 / 17 -> 9 / ..
+//   beyond, one pass:        3x3 256->256 on 6272 43 -> 48, 1x1 1024->256 18 -> 24: no
+//   several passes, K <= 32: 1x1 256->1024 on 6272 34 -> 25 / 18 -> 10 / 17 -> 7, 512->2048 on 16 K 153 -> 160 / 79 -> 56 / 75 -> 9
+//                            (stride 2, whose lists cost more: 256->1024 on 4096 outputs 32 -> 33 / 21 -> 22 / 20 -> 19, 512->2048 57 -> 76: no)
+//   3x3, K <= 72:            128->512 on 8192 51 -> 52 / 44 -> 37 / 42 -> 24, on 16 K 84 -> 96: no
+//   longer:                  3x3 256->512 on 4096 43 -> 47, 1x1 1024->512 20 -> 24: no (at 10 % 34 -> 26 and 18 -> 13)
+static int64_t unit_limit(const dcnn_ctx* ctx, const ConvArgs& c, const ConvPlan& p) {
+    const int ksteps = c.k * c.k * c.kch;
+    if (p.npass > 1 && ksteps <= 32) return c.stride == 1 ? INT64_MAX : (int64_t)ctx->num_cu * 16;
+    if (p.npass > 1 && c.k == 3 && ksteps <= 72) return (int64_t)ctx->num_cu * 16;
+    return (int64_t)ctx->num_cu * 4;
+}
+
+bool conv_unit_supported(const dcnn_ctx* ctx, int dtype, const ListArgs& l, const ConvArgs& c, const EpilogueArgs& e, const ConvPlan& p) {
     const size_t es = dtype_size(dtype);
     const int vec = dtype == DCNN_F16 ? 8 : 4;
     if (!p.stream || p.flat || (c.k != 1 && c.k != 3) || e.c % vec != 0 || ((size_t)c.cin * es) % 16 != 0) return false;
     if (e.act != DCNN_ACT_NONE || c.in2_data != nullptr || e.accum_O != nullptr || e.xt_flags != nullptr) return false;
     if (!l.self && l.taps == nullptr && !(c.k == 1 && c.stride == 1 && l.list != nullptr)) return false;
     const int64_t out_px = (int64_t)c.n * c.oh * c.ow;
-    return out_px <= kUnitMaxPixels && (uint64_t)c.n * c.h * c.w * c.cin * es <= kWsMaxBytes && (uint64_t)out_px * e.c * es <= kWsMaxBytes &&
+    return out_px <= kUnitMaxPixels && cdiv(out_px, kTile) * cdiv(e.c, 32) <= unit_limit(ctx, c, p) && (uint64_t)c.n * c.h * c.w * c.cin * es <= kWsMaxBytes && (uint64_t)out_px * e.c * es <= kWsMaxBytes &&
            p.w_bytes <= kWsMaxBytes;
 }
 
