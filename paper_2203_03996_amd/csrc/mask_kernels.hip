@@ -314,7 +314,11 @@ __global__ __launch_bounds__(kMaskThreads) void mask_span_kernel(MaskKernelArgs 
     const int first_row = max(oy0 * a.stride - a.pad, 0), last_row = min(oy1 * a.stride - a.pad + a.k - 1, a.h - 1);
     const int base = (n0 * a.h + first_row) * a.w & ~31;        // (the host has checked that the run fits, span_fits)
     const int words = ((n1 * a.h + last_row + 1) * a.w - base + 31) / 32;
-    for (int w = threadIdx.x; w < words; w += kMaskThreads) s_bits[w] = self_mask_word(a.mask_in + base, w, in_px - base);
+    for (int w = threadIdx.x; w < min(words, (in_px - base) / 32); w += kMaskThreads) s_bits[w] = self_mask_word(a.mask_in + base, w);
+    if (words * 32 > in_px - base && threadIdx.x < kWave) {    // (the run ends with the mask, inside a word)
+        const uint32_t v = self_mask_tail(a.mask_in + base, in_px - base);
+        if (threadIdx.x == 0) s_bits[words - 1] = v;
+    }
     __syncthreads();
     const int p0 = c0 + (int)threadIdx.x * kPxPerThread;
     uint64_t word = 0;

@@ -26,34 +26,17 @@ __device__ __forceinline__ uint32_t self_pack(const uint4& a, const uint4& b) {
     return pack8((uint64_t)a.x | (uint64_t)a.y << 32) | pack8((uint64_t)a.z | (uint64_t)a.w << 32) << 8 |
            pack8((uint64_t)b.x | (uint64_t)b.y << 32) << 16 | pack8((uint64_t)b.z | (uint64_t)b.w << 32) << 24;
 }
-// flags of pixels 32*w .. 32*w+31 of a mask of `px` bytes (16-byte aligned)
-__device__ __forceinline__ uint32_t self_mask_word(const uint8_t* mask, int w, int px) {
-    const int p0 = w * 32;
-    if (p0 + 32 <= px)
-        return self_pack(*reinterpret_cast<const uint4*>(mask + p0), *reinterpret_cast<const uint4*>(mask + p0 + 16));
-    // The last word of a mask that ends inside one, without a read past it: whole dwords and up to three bytes, all requested
-    // together (positions past the end repeat the last ones).  Byte after byte, each load waited for, a map of 100 x 100 pixels
-    // cost every kernel that builds its list 4-5 us over one of 96 x 104 (add + ReLU, 64 channels: 14.8 us, now 12.4).
-    uint32_t bits = 0;
-    const int dwords = px / 4;
-    if (dwords > 0) {
-        uint32_t v[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] = reinterpret_cast<const uint32_t*>(mask)[min(p0 / 4 + i, dwords - 1)];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            uint32_t f = v[i] | v[i] >> 4;
-            f |= f >> 2; f |= f >> 1;
-            if (p0 / 4 + i < dwords) bits |= ((f & 0x01010101u) * 0x01020408u >> 24) << (4 * i);
-        }
-    }
-    uint8_t last[3];
-#pragma unroll
-    for (int i = 0; i < 3; ++i) last[i] = mask[min(dwords * 4 + i, px - 1)];
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-        if (dwords * 4 + i < px && last[i]) bits |= 1u << (dwords * 4 + i - p0);
-    return bits;
+// flags of pixels 32*w .. 32*w+31 of a mask (16-byte aligned) that holds them all
+__device__ __forceinline__ uint32_t self_mask_word(const uint8_t* mask, int w) {
+    return self_pack(*reinterpret_cast<const uint4*>(mask + w * 32), *reinterpret_cast<const uint4*>(mask + w * 32 + 16));
+}
+// The last word of a mask of `px` bytes that ends inside it: a byte per lane, by a whole wave, all lanes get the word.  (Byte after
+// byte by the lane whose word it is, each load waited for, a map of 100 x 100 pixels cost every kernel that builds its list 4-5 us
+// over one of 96 x 104: add + ReLU, 64 channels, 14.8 us, now 11.4.  With dwords and bytes requested together by that lane the
+// code alone cost all maps 0.4 us a launch.)
+__device__ __forceinline__ uint32_t self_mask_tail(const uint8_t* mask, int px) {
+    const int at = (px & ~31) + (int)(threadIdx.x % kWave);
+    return (uint32_t)__ballot(at < px && mask[min(at, px - 1)] != 0);
 }
 
 // 32 bits from bit position `pos` on; positions outside the array read some word of it (callers mask those bits)
@@ -112,6 +95,7 @@ __device__ __forceinline__ int self_scan(int v) {
     return self_dpp_add<0x143, 0xc>(v);     // row_bcast:31 into rows 2 and 3
 }
 
+constexpr int kSelfTail = 31;                                  // where SelfBits::red keeps the second mask's incomplete last word
 struct SelfBits {
     uint32_t* ibits;
     uint32_t* obits;
@@ -169,7 +153,7 @@ __device__ __forceinline__ uint32_t self_dilate_word(const ListArgs& l, const Se
 }
 
 // The input mask on its way: requested before the kernel does anything else that waits (two words per thread of a
-// workgroup of 1024; the last, incomplete word of a mask is read when it is needed).
+// workgroup of 1024; an incomplete last word is read in self_build).
 constexpr int kSelfAhead = 2;
 struct SelfAhead { uint4 a[kSelfAhead], b[kSelfAhead]; };
 __device__ __forceinline__ void self_request(const ListArgs& l, SelfAhead& v) {
@@ -194,21 +178,37 @@ __device__ __forceinline__ int self_build(const ListArgs& l, const SelfBits& s, 
     const bool win3 = l.m_k == 3 && l.m_stride == 1 && l.m_pad == 1 && l.m_up == 1;   // (up > 1 comes with k = 1)
     int nin = 0;
     static_assert(NT == 1024 || NT <= 512, "self_request assumes 1024 threads");
+    const bool b_words = l.m_b != nullptr && l.b_stride <= 0;  // the second mask has the output's shape
     int i = 0;
 #pragma unroll 2
-    for (int w = tid; w < s.in_words; w += NT, ++i) {
+    for (int w = tid; w < l.m_in_px / 32; w += NT, ++i) {
         uint32_t v;
-        if (ahead != nullptr && w * 32 + 32 <= l.m_in_px) v = i == 0 ? self_pack(ahead->a[0], ahead->b[0]) : self_pack(ahead->a[1], ahead->b[1]);
-        else v = self_mask_word(l.m_in, w, l.m_in_px);
+        if (ahead != nullptr) v = i == 0 ? self_pack(ahead->a[0], ahead->b[0]) : self_pack(ahead->a[1], ahead->b[1]);
+        else v = self_mask_word(l.m_in, w);
         s.ibits[w] = v;
         nin += __popc(v);
-        if (copy) s.obits[w] = v | ((l.m_b && l.b_stride <= 0) ? self_mask_word(l.m_b, w, l.m_out_px) : 0u);
+        if (copy) s.obits[w] = v | (b_words ? self_mask_word(l.m_b, w) : 0u);
+    }
+    if (wave == NWV - 1) {                                     // incomplete last words (the last wave has the fewest whole ones)
+        uint32_t b = 0;
+        if (b_words && l.m_out_px % 32 != 0) {
+            b = self_mask_tail(l.m_b, l.m_out_px);
+            if (lane == 0) s.red[kSelfTail] = (int)b;
+        }
+        if (l.m_in_px % 32 != 0) {
+            const uint32_t v = self_mask_tail(l.m_in, l.m_in_px);
+            if (lane == 0) {
+                s.ibits[s.in_words - 1] = v;
+                nin += __popc(v);
+                if (copy) s.obits[s.in_words - 1] = v | b;
+            }
+        }
     }
     lds_block_sync();
     if (win3) {
         for (int w = tid; w < s.out_words; w += NT) {
             uint32_t hit = self_dilate_word(l, s, w, l.div_ow, l.div_oh);      // (input and output maps have one shape)
-            if (l.m_b && l.b_stride <= 0) hit |= self_mask_word(l.m_b, w, l.m_out_px);
+            if (b_words) hit |= w * 32 + 32 <= l.m_out_px ? self_mask_word(l.m_b, w) : (uint32_t)s.red[kSelfTail];
             s.obits[w] = hit;
         }
     } else if (l.m_up > 1) {
