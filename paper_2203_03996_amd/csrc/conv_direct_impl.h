@@ -300,32 +300,32 @@ __global__ __launch_bounds__(kDirectWaves* kWave, 2) void conv_direct_kernel(Lis
                                                                              int blocked_min_tiles) {
     extern __shared__ __align__(16) unsigned char smem[];
     clear_ahead(e);
-    int64_t count;
-    SelfBits sb;
-    int nin = -1;                                              // flagged input pixels, if known
     if constexpr (SELF) {
-        sb = self_carve(l, smem + l.lds_scratch);
-        count = self_build<kDirectWaves * kWave>(l, sb, &nin);
-    } else {
-        count = list_count(l);
-        if (c.in_count) nin = *c.in_count;
-    }
-    if (count >= (int64_t)blocked_min_tiles * kTile) {
-        if constexpr (KS == 3 && NB <= 2) {
-            // Row gathers pay when most taps of the listed windows are flagged.  Every flagged input pixel is a tap
-            // of (up to) nine listed outputs, so flagged inputs / listed outputs IS the mean fraction of flagged taps
-            // per window.  Measured on 3x3 128->128, 256x256 maps, uniform-random masks: all taps flagged 0.40 ->
-            // 0.30 ms, half of them 0.231 -> 0.243 ms, a tenth 0.127 -> 0.156 ms; hence three quarters.
-            // (an input that comes without a count: the rule of the resident-weight kernel, most of the map listed)
-            const bool dense_taps = nin >= 0 ? (int64_t)nin * 4 >= count * 3 : count * 4 >= (int64_t)c.n * c.oh * c.ow * 3;
-            if (c.stride == 1 && c.pad == 1 && dense_taps) {
-                conv_direct_body<T, NB, KS, (TI > 3 ? 3 : TI), 2, true, SELF>(l, c, e, npass, cs, count, smem, sb);   // 3 tiles: two operand sets of 12 vectors fit beside 96 accumulators
-                return;
-            }
-        }
-        conv_direct_body<T, NB, KS, TI, 3, false, SELF>(l, c, e, npass, cs, count, smem, sb);
-    } else {
+        // (maps whose kernels build the list are too small for more than one tile per wave)
+        const SelfBits sb = self_carve(l, smem + l.lds_scratch);
+        const int64_t count = self_build<kDirectWaves * kWave>(l, sb);
         conv_direct_body<T, NB, KS, 1, (NB >= 4 ? 6 : 8), false, SELF>(l, c, e, npass, cs, count, smem, sb);
+    } else {
+        const SelfBits sb{};
+        const int64_t count = list_count(l);
+        if (count >= (int64_t)blocked_min_tiles * kTile) {
+            if constexpr (KS == 3 && NB <= 2) {
+                // Row gathers pay when most taps of the listed windows are flagged.  Every flagged input pixel is a tap
+                // of (up to) nine listed outputs, so flagged inputs / listed outputs IS the mean fraction of flagged taps
+                // per window.  Measured on 3x3 128->128, 256x256 maps, uniform-random masks: all taps flagged 0.40 ->
+                // 0.30 ms, half of them 0.231 -> 0.243 ms, a tenth 0.127 -> 0.156 ms; hence three quarters.
+                // (an input that comes without a count: the rule of the resident-weight kernel, most of the map listed)
+                const bool dense_taps = c.in_count ? (int64_t)*c.in_count * 4 >= count * 3
+                                                   : count * 4 >= (int64_t)c.n * c.oh * c.ow * 3;
+                if (c.stride == 1 && c.pad == 1 && dense_taps) {
+                    conv_direct_body<T, NB, KS, (TI > 3 ? 3 : TI), 2, true, SELF>(l, c, e, npass, cs, count, smem, sb);   // 3 tiles: two operand sets of 12 vectors fit beside 96 accumulators
+                    return;
+                }
+            }
+            conv_direct_body<T, NB, KS, TI, 3, false, SELF>(l, c, e, npass, cs, count, smem, sb);
+        } else {
+            conv_direct_body<T, NB, KS, 1, (NB >= 4 ? 6 : 8), false, SELF>(l, c, e, npass, cs, count, smem, sb);
+        }
     }
 }
 

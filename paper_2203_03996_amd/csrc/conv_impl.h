@@ -53,7 +53,7 @@ __global__ __launch_bounds__(WMODE == 2 ? 256 : DCNN_CONV_BOUNDS) void conv_mfma
     SelfBits sb;
     if (l.self) {
         sb = self_carve(l, smem + l.lds_scratch);
-        count = self_build<kThreads>(l, sb, nullptr);
+        count = self_build<kThreads>(l, sb);
     } else {
         count = list_count(l);
     }
@@ -559,14 +559,7 @@ static dcnn_status launch_conv_nb(dcnn_ctx* ctx, bool init, const ListArgs& l_in
         const int blocked_min_tiles = (int)((int64_t)ctx->num_cu * 4 * TI / p.cs);
         const int64_t b_cap = (int64_t)ctx->num_cu * 2;        // 4 waves of up to 256 registers: two workgroups per compute unit
         const int b_grid = (int)(cdiv(b_want < b_cap ? b_want : b_cap, kXcd) * kXcd);
-        // (the number of tiles per wave is chosen on the device: room for whichever groups give one workgroup the most entries)
-        int64_t b_group = 0, most = 0;
-        for (int ti = 1; ti <= TI; ++ti) {
-            const int64_t ge = (kDirectWaves / p.cs) * ti * kTile;
-            const int64_t ents = l.self ? self_local_entries(l.m_out_px, ge, b_grid, true) : 1;
-            if (ents > most) { most = ents; b_group = ge; }
-        }
-        const size_t b_all = place_list(b_lds, 0, b_group, b_grid);
+        const size_t b_all = place_list(b_lds, 0, (kDirectWaves / p.cs) * kTile, b_grid);
         if (b_all > kLdsBytes) return fail(ctx, DCNN_EUNSUPPORTED, "conv: a work list built in place does not fit LDS");
 #define DCNN_BLOCKED_LAUNCH(KS, SELF)                                                                            \
     do {                                                                                                         \

@@ -102,8 +102,7 @@ bool conv_self_fits(const dcnn_ctx* ctx, int dtype, int k, int cin, int cout, bo
     const size_t ws_w = p.w_bytes + (size_t)cdiv(cin2, dtype == DCNN_F16 ? 16 : 8) * 2 * p.cout_pad * 16;
     if (ws_lds != 0 && !fits(ws_lds, ws_w, (kWsProducers / p.cs) * kTile, cus)) return false;
     const size_t direct_lds = conv_stage_bytes(kDirectWaves, p.nb, dtype) + conv_xchg_bytes(kDirectWaves);
-    for (int ti = 1; ti <= 4; ++ti)
-        if (!fits(direct_lds, 0, (kDirectWaves / p.cs) * ti * kTile, 2 * cus)) return false;
+    if (!fits(direct_lds, 0, (kDirectWaves / p.cs) * kTile, 2 * cus)) return false;
     return fits(p.lds_bytes, p.stream ? 0 : p.w_bytes, (p.waves / p.cs) * kTile, cus);
 }
 

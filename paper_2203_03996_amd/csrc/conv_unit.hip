@@ -50,9 +50,9 @@ __global__ __launch_bounds__(kUnitMaxWaves* kWave) void conv_unit_kernel(ListArg
     if (l.self) {
         sb = self_carve(l, smem + l.lds_scratch);
         // (the workgroup's size is a launch parameter here: the list code is written for a fixed number of threads)
-        if (nwaves == 1) count = self_build<kWave>(l, sb, nullptr);
-        else if (nwaves == 2) count = self_build<2 * kWave>(l, sb, nullptr);
-        else count = self_build<4 * kWave>(l, sb, nullptr);
+        if (nwaves == 1) count = self_build<kWave>(l, sb);
+        else if (nwaves == 2) count = self_build<2 * kWave>(l, sb);
+        else count = self_build<4 * kWave>(l, sb);
         if (nwaves == 1) self_emit<kWave>(l, sb, count, SelfSpan{0, 0, 1, 1}, nullptr, nullptr);
         else if (nwaves == 2) self_emit<2 * kWave>(l, sb, count, SelfSpan{0, 0, 1, 1}, nullptr, nullptr);
         else self_emit<4 * kWave>(l, sb, count, SelfSpan{0, 0, 1, 1}, nullptr, nullptr);

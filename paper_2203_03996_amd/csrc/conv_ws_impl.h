@@ -134,7 +134,7 @@ __global__ __launch_bounds__(kWsWaves* kWave) void conv_ws_kernel(ListParam<SELF
     if constexpr (SELF) {
         // (fetching the weights together with the mask was measured: every workgroup then fetches them, also those that turn
         // out to have no tile, and a one-stream step went from 49.7 to 53.0 us)
-        count = self_build<kWsWaves * kWave>(l, sb, nullptr, &ahead);
+        count = self_build<kWsWaves * kWave>(l, sb, &ahead);
     }
     const WgTileRange r = wg_tile_range((count + tiles_per_iter * kTile - 1) / (tiles_per_iter * kTile));
     if constexpr (SELF)

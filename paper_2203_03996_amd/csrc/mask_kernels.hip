@@ -544,7 +544,7 @@ __global__ __launch_bounds__(kListThreads) void mask_list_kernel(ListArgs l, uin
     SelfAhead ahead;
     self_request(l, ahead);
     const SelfBits s = self_carve(l, smem);
-    const int count = self_build<kListThreads>(l, s, nullptr, &ahead);
+    const int count = self_build<kListThreads>(l, s, &ahead);
     if (blockIdx.x == 0 && threadIdx.x == 0) *l.count_out = count;
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
     const int w_end = min(((int)blockIdx.x + 1) * kListShare, s.out_words);

@@ -168,15 +168,14 @@ __device__ __forceinline__ void self_request(const ListArgs& l, SelfAhead& v) {
     }
 }
 
-// Phase 1: all flags and list positions.  Returns the length of the list; *in_count (if wanted): flagged input pixels.  Every thread
+// Phase 1: all flags and list positions.  Returns the length of the list.  Every thread
 // of the workgroup (NT of them) calls it; ends with a barrier.
 template <int NT>
-__device__ __forceinline__ int self_build(const ListArgs& l, const SelfBits& s, int* in_count, const SelfAhead* ahead = nullptr) {
+__device__ __forceinline__ int self_build(const ListArgs& l, const SelfBits& s, const SelfAhead* ahead = nullptr) {
     constexpr int NWV = NT / kWave;
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
     const bool copy = l.m_k == 1 && l.m_stride == 1 && l.m_up == 1;
     const bool win3 = l.m_k == 3 && l.m_stride == 1 && l.m_pad == 1 && l.m_up == 1;   // (up > 1 comes with k = 1)
-    int nin = 0;
     static_assert(NT == 1024 || NT <= 512, "self_request assumes 1024 threads");
     const bool b_words = l.m_b != nullptr && l.b_stride <= 0;  // the second mask has the output's shape
     int i = 0;
@@ -186,7 +185,6 @@ __device__ __forceinline__ int self_build(const ListArgs& l, const SelfBits& s, 
         if (ahead != nullptr) v = i == 0 ? self_pack(ahead->a[0], ahead->b[0]) : self_pack(ahead->a[1], ahead->b[1]);
         else v = self_mask_word(l.m_in, w);
         s.ibits[w] = v;
-        nin += __popc(v);
         if (copy) s.obits[w] = v | (b_words ? self_mask_word(l.m_b, w) : 0u);
     }
     if (wave == NWV - 1) {                                     // incomplete last words (the last wave has the fewest whole ones)
@@ -199,7 +197,6 @@ __device__ __forceinline__ int self_build(const ListArgs& l, const SelfBits& s, 
             const uint32_t v = self_mask_tail(l.m_in, l.m_in_px);
             if (lane == 0) {
                 s.ibits[s.in_words - 1] = v;
-                nin += __popc(v);
                 if (copy) s.obits[s.in_words - 1] = v | b;
             }
         }
@@ -287,10 +284,6 @@ __device__ __forceinline__ int self_build(const ListArgs& l, const SelfBits& s, 
     }
     const int inc = self_scan(mine);
     if (lane == kWave - 1) s.red[wave] = inc;
-    if (in_count != nullptr) {
-        const int sum_in = self_scan(nin);
-        if (lane == kWave - 1) s.red[16 + wave] = sum_in;
-    }
     lds_block_sync();
     // (at most 16 waves: their totals fit one row of lanes, every wave scans them again)
     const int waves = self_row_scan(lane < NWV ? s.red[lane] : 0);
@@ -301,7 +294,6 @@ __device__ __forceinline__ int self_build(const ListArgs& l, const SelfBits& s, 
         const int w = tid * W + i;
         if (w < s.out_words) { s.prefix[w] = (uint16_t)run; run += __popc(s.obits[w]); }
     }
-    if (in_count != nullptr) *in_count = __builtin_amdgcn_readlane(self_row_scan(lane < NWV ? s.red[16 + lane] : 0), NWV - 1);
     lds_block_sync();
     return total;
 }

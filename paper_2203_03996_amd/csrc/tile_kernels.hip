@@ -25,7 +25,7 @@ template <bool SELF>
 __device__ __forceinline__ int64_t tile_list_count(const ListParam<SELF>& l, unsigned char* smem, SelfBits& sb) {
     if constexpr (SELF) {
         sb = self_carve(l, smem + l.lds_scratch);
-        return self_build<kTileThreads>(l, sb, nullptr);
+        return self_build<kTileThreads>(l, sb);
     } else {
         return list_count(l);
     }
