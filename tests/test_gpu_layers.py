@@ -163,7 +163,7 @@ def test_add_act(S, act, shape):
     eps = 0.4
     radd, ract = orc.Add(S), orc.ActTrunc(act, eps, S)
     ctx = pkg.Context(n * h * w)
-    layer = pkg.Layer(ctx, pkg.make_desc(pkg.ACT, DT[S], n, h, w, c, act=pkg.ACT_RELU if act == "relu" else pkg.ACT_NONE, eps=eps, n_in=2))
+    layer = pkg.Layer(ctx, pkg.make_desc(pkg.ACT, DT[S], n, h, w, c, act=pkg.ACT_CODES[act], eps=eps, n_in=2))
     a0 = rng.normal(0, 1, shape).astype(NP_DTYPE[S])
     b0 = rng.normal(0, 1, shape).astype(NP_DTYPE[S])
     r0 = radd.init(a0, b0)
@@ -1097,3 +1097,97 @@ def test_a_captured_step_of_a_layer_with_its_own_list_replays(S, kind, k, stride
             assert np.array_equal(to_np(out.data)[mask == 1], to_np(want.data)[mask == 1]), f"replay {t}: delta"
             for which in (0, 1):
                 assert np.array_equal(to_np(replayed.state_tensor(which)), to_np(eager.state_tensor(which))), f"replay {t}: buffer {which}"
+
+
+def _off_alignment(delta):
+    """The same update with its mask 8 bytes off a 16-byte border: such a layer takes a list from memory."""
+    room = torch.zeros(delta.mask.numel() + 16, dtype=torch.uint8, device="cuda")
+    mask = room[8:8 + delta.mask.numel()].view(delta.mask.shape)
+    mask.copy_(delta.mask)
+    return pkg.Delta(delta.data, mask, delta.idx, delta.count)
+
+
+@pytest.mark.parametrize("S,kind,k,stride,cin,cout,act", [
+    ("f16", "conv", 3, 1, 64, 64, "relu"), ("f16", "conv", 1, 2, 48, 32, "relu6"), ("f16", "conv", 3, 2, 256, 128, "relu"),
+    ("f16", "conv", 3, 1, 256, 512, "none"), ("f16", "conv", 1, 2, 512, 1032, "none"), ("f16", "conv", 3, 1, 128, 128, "none"),
+    ("f32", "conv", 5, 1, 12, 20, "relu"), ("f32", "conv", 7, 2, 8, 16, "none"), ("f16", "conv", 3, 1, 20, 27, "relu"),
+    ("f16", "residual", 3, 1, 64, 64, "relu"), ("f16", "projection", 1, 1, 64, 256, "relu"), ("f16", "projection", 3, 2, 64, 64, "relu"),
+    ("f16", "dwconv", 3, 1, 96, 96, "relu6"), ("f32", "dwconv", 3, 2, 200, 200, "relu"), ("f16", "dwconv", 2, 2, 32, 32, "none"),
+    ("f16", "add", 1, 1, 64, 64, "relu"), ("f16", "add", 1, 1, 1024, 1024, "relu"), ("f32", "add", 1, 1, 1024, 1024, "none"), ("f32", "add", 1, 1, 20, 20, "none"),
+    ("f16", "upsample", 2, 1, 40, 40, "none"), ("f32", "upsample", 4, 1, 6, 6, "none"),
+])
+@pytest.mark.parametrize("nhw", [(1, 5, 13), (3, 12, 14), (1, 40, 51)])
+def test_lists_built_in_the_kernel_and_stored_ones_give_the_same_bits(S, kind, k, stride, cin, cout, act, nhw):
+    """Every kind of layer that can build its list, on maps that end 1, 24 and 24 pixels into a word of flags (and other places
+    after a stride), against the same layer on a list in memory; the second layer changes between the two."""
+    n, h, w = nhw
+    rng = np.random.default_rng(cin + cout + h)
+    dt = NP_DTYPE[S]
+    code = {"conv": pkg.CONV, "residual": pkg.CONV, "projection": pkg.CONV, "dwconv": pkg.DWCONV, "add": pkg.ACT, "upsample": pkg.UPSAMPLE}[kind]
+    pad = 0 if kind == "dwconv" and k == 2 else k // 2
+    oh, ow = (h * k, w * k) if kind == "upsample" else ((h + 2 * pad - k) // stride + 1, (w + 2 * pad - k) // stride + 1)
+    ins = [(n, h, w, cin)]
+    proj = None
+    if kind == "residual":
+        ins.append((n, oh, ow, cout))
+    elif kind == "add":
+        ins.append(ins[0])
+    elif kind == "projection":
+        ps = stride
+        proj = (24, (oh - 1) * ps + 1, (ow - 1) * ps + 1, ps)
+        ins.append((n, proj[1], proj[2], 24))
+    desc = pkg.make_desc(code, DT[S], n, h, w, cin, k=1 if kind == "upsample" else k, stride=stride, pad=0 if kind == "upsample" else pad, cout=cout,
+                         act=pkg.ACT_CODES[act], eps=0.3, n_in=len(ins), factor=k if kind == "upsample" else 1, want_idx=0, proj=proj)
+    wgt = None
+    if code == pkg.CONV:
+        parts = [rng.standard_normal((k, k, cin, cout)).reshape(-1) * np.sqrt(2.0 / (k * k * cin))]
+        if proj:
+            parts.append(rng.standard_normal(24 * cout) * np.sqrt(2.0 / 24))
+        wgt = torch.from_numpy(np.concatenate(parts).astype(dt)).cuda()
+    elif code == pkg.DWCONV:
+        wgt = torch.from_numpy((rng.standard_normal((k, k, cin)) * 0.5).astype(dt)).cuda()
+    ctx = pkg.Context(max(a * b * c for a, b, c, _ in ins + [(n, oh, ow, cout)]))
+    inside, stored = (pkg.Layer(ctx, desc, wgt) for _ in range(2))
+    dense = [torch.from_numpy(rng.standard_normal(shape).astype(dt)).cuda() for shape in ins]
+    for layer in (inside, stored):
+        layer.init(dense)
+    for t, dens in enumerate((0.05, 1.0, 0.4, 0.0, 0.02, 0.9)):
+        deltas = [_upload(_rand_delta(rng, shape, dens if i == 0 else dens * 0.7, S, 0.4)) for i, shape in enumerate(ins)]
+        a = inside.step(deltas)
+        b = stored.step([_off_alignment(d) for d in deltas] if t != 2 else deltas)
+        ctx.sync()
+        mask = to_np(b.mask)
+        assert np.array_equal(to_np(a.mask), mask), f"step {t}: mask"
+        assert np.array_equal(to_np(a.data)[mask == 1], to_np(b.data)[mask == 1]), f"step {t}: values"
+        assert (a.count is None) == (b.count is None)
+        if a.count is not None:
+            flat = np.flatnonzero(mask.reshape(-1))
+            for view in (a, b):
+                assert int(to_np(view.count)[0]) == flat.size and np.array_equal(to_np(view.idx)[:flat.size], flat), f"step {t}: list"
+        for which in ((0, 1) if act != "none" else ()):
+            assert np.array_equal(to_np(inside.state_tensor(which)), to_np(stored.state_tensor(which))), f"step {t}: buffer {which}"
+        sa, sb = inside.stats(), stored.stats()
+        assert all(sa[key] == sb[key] for key in ("pixels_in", "pixels_in2", "pixels_work", "pixels_out")), f"step {t}: statistics"
+
+
+@pytest.mark.parametrize("k,stride", [(1, 1), (3, 1), (3, 2), (1, 2), (7, 2)])
+@pytest.mark.parametrize("at", [4, 8])
+def test_mask_compact_of_unaligned_masks(k, stride, at):
+    """Masks that do not start on a 16-byte border go through the two passes."""
+    rng = np.random.default_rng(k + at)
+    mask = (rng.random((2, 45, 67)) < 0.05).astype(np.uint8)
+    want = orc.window_mask(mask, k, stride, k // 2)
+    mask_b = (rng.random(want.shape) < 0.02).astype(np.uint8)
+    want = want | mask_b
+    views = []
+    for m in (mask, mask_b):
+        room = torch.zeros(m.size + 32, dtype=torch.uint8, device="cuda")
+        v = room[at:at + m.size].view(m.shape)
+        v.copy_(torch.from_numpy(m))
+        views.append(v)
+    ctx = pkg.Context(mask.size)
+    got, idx, count = ctx.mask_compact(views[0], k, stride, k // 2, views[1])
+    ctx.sync()
+    assert np.array_equal(to_np(got), want)
+    flat = np.flatnonzero(want.reshape(-1))
+    assert int(to_np(count)[0]) == flat.size and np.array_equal(to_np(idx)[:flat.size], flat)

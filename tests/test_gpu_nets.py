@@ -818,8 +818,10 @@ def test_frames_of_the_wrong_shape_are_refused_before_any_launch():
                                      lambda: wl.tiny_mixed_net(eps=0.05, dtype="f16"), lambda: wl.tiny_mixed_net(eps=0.05)])
 @pytest.mark.parametrize("streams", [1, 3])
 def test_lists_built_in_the_kernels_change_nothing(spec_fn, streams):
-    """Small maps: with every layer's list in memory (flag bit 1) and with the lists built by the layers' own kernels the dense
-    output, the stored frame, every x^A and every mask are the same bits, frame after frame and after a reset."""
+    """Small maps: with the lists of layers with an activation in memory (flag bit 1 asks for their outputs' lists, which are compacted
+    from a stored one) and with those too built by the layers' own kernels the dense output, the stored frame, every x^A and
+    every mask are the same bits, frame after frame and after a reset.  (Layers without an activation build theirs in both;
+    test_gpu_layers.py holds every kind of layer against stored lists.)"""
     spec = spec_fn()
     S, seed = spec["dtype"], 77
     wts = wl.make_weights(spec, seed)
