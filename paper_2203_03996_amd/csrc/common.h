@@ -75,7 +75,6 @@ struct MaskPassArgs {
     int n, h, w, oh, ow, k, stride, pad;
     int up;                      // > 1: nearest upsampling of the input mask by this factor (k = 1)
     int bilinear;                // with up > 1: bilinear upsampling instead (sources that carry weight)
-    int32_t* zero_count;         // optional counter the pass resets to 0 (survivor count of the layer)
     int emit_only;               // 1: mask_in is final and its flags have been counted: counts_per_chunk numbers per chunk of
     const int32_t* counts;       //    pixels, in `counts`
     int counts_per_chunk;

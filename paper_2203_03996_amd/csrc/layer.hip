@@ -649,7 +649,6 @@ dcnn_status dcnn_layer_step(dcnn_layer* L, const dcnn_delta* const* in, int32_t 
         m.idx_out = own ? L->list : L->out_idx; m.count_out = own ? L->list_count : L->out_count;
         m.n = d.n; m.h = d.h; m.w = d.w; m.oh = L->oh; m.ow = L->ow;
         m.k = 1; m.stride = 1; m.pad = 0; m.up = 1; m.emit_only = 0;
-        m.zero_count = nullptr;
         if (d.kind == DCNN_CONV || d.kind == DCNN_DWCONV || d.kind == DCNN_MAXPOOL) { m.k = d.kh; m.stride = d.stride; m.pad = d.pad; }
         if (d.kind == DCNN_UPSAMPLE || d.kind == DCNN_UPSAMPLE_BILINEAR) { m.up = d.factor; m.bilinear = d.kind == DCNN_UPSAMPLE_BILINEAR; }
         if (d.kind == DCNN_GAVGPOOL) { m.k = d.h; m.kw = d.w; m.pad_w = 0; }   // one window over the whole map
@@ -674,8 +673,7 @@ dcnn_status dcnn_layer_step(dcnn_layer* L, const dcnn_delta* const* in, int32_t 
             MaskPassArgs m{};
             m.mask_in = in[0]->mask; m.mask_out = L->out_mask; m.idx_out = nullptr;
             m.n = d.n; m.h = d.h; m.w = d.w; m.oh = L->oh; m.ow = L->ow; m.k = 1; m.stride = 1; m.pad = 0; m.up = 1;
-            m.zero_count = nullptr;
-            st = launch_mask_compact(ctx, m);
+                st = launch_mask_compact(ctx, m);
             if (st != DCNN_OK) return st;
         }
     }

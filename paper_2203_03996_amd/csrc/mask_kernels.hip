@@ -168,7 +168,6 @@ struct MaskKernelArgs {
     const uint8_t* mask_b;
     uint8_t* mask_out;
     int32_t* chunk_counts;
-    int32_t* zero_count;
     int64_t out_pixels;
     int n, h, w, oh, ow, k, stride, pad, up;
     int bilinear;                 // with up > 1: sources of a bilinear upsampling instead of the nearest pixel
@@ -285,10 +284,7 @@ __global__ __launch_bounds__(kMaskThreads) void mask_pass_kernel(MaskKernelArgs 
     const int64_t p0 = (int64_t)blockIdx.x * kChunk + (int64_t)threadIdx.x * kPxPerThread;
     const uint64_t word = mask_word<true>(a, p0);
     const int total = block_sum(__popcll(word), s_red);
-    if (threadIdx.x == 0) {
-        a.chunk_counts[blockIdx.x] = total;
-        if (blockIdx.x == 0 && a.zero_count) *a.zero_count = 0;
-    }
+    if (threadIdx.x == 0) a.chunk_counts[blockIdx.x] = total;
 }
 
 // Mask pass for square windows from 5x5 on (any stride and padding): the input flags a chunk of outputs can see are a
@@ -342,10 +338,7 @@ __global__ __launch_bounds__(kMaskThreads) void mask_span_kernel(MaskKernelArgs 
         else for (int i = 0; p0 + i < out_px; ++i) a.mask_out[p0 + i] = (uint8_t)((word >> (8 * i)) & 1);
     }
     const int total = block_sum(__popcll(word), s_red);
-    if (threadIdx.x == 0) {
-        a.chunk_counts[blockIdx.x] = total;
-        if (blockIdx.x == 0 && a.zero_count) *a.zero_count = 0;
-    }
+    if (threadIdx.x == 0) a.chunk_counts[blockIdx.x] = total;
 }
 // The longest run a chunk's windows can see, in rows of the input: the chunk's output rows (one more than fit, cut at both
 // ends) times the stride, the window, and at every border between streams the rows that no window starts in.
@@ -526,10 +519,7 @@ __global__ __launch_bounds__(kMaskThreads) void mask_emit_kernel(MaskKernelArgs 
     const int prefix = block_sum(part, s_red);
     int total;
     const int loc = block_exclusive_scan(__popcll(word), s_red, &total);
-    if (threadIdx.x == 0) {
-        if (chunk == 0 && a.zero_count) *a.zero_count = 0;
-        if (last) *e.count_out = prefix + total;
-    }
+    if (threadIdx.x == 0 && last) *e.count_out = prefix + total;
     if (total != 0) emit_entries(e, p0, word, prefix + loc, er);
 }
 
@@ -617,7 +607,6 @@ static dcnn_status mask_compact_on(dcnn_ctx* ctx, const MaskPassArgs& m, const W
         a.mask_in = m.mask_in; a.mask_b = m.mask_b;
         a.mask_out = m.mask_out ? m.mask_out : ws.scratch_mask;
         a.chunk_counts = ws.chunk_counts;
-        a.zero_count = m.zero_count;
         a.out_pixels = out_pixels;
         a.n = m.n; a.h = m.h; a.w = m.w; a.oh = m.oh; a.ow = m.ow;
         a.k = m.k; a.stride = m.stride; a.pad = m.pad;

@@ -1,5 +1,5 @@
 // The activation + truncation tail of the sparse steps that reach memory through buffer descriptors, shared by the
-// activation, depthwise and per-block convolution kernels.
+// activation and depthwise kernels.
 #pragma once
 
 #include "device_utils.h"
