@@ -233,9 +233,10 @@ bool conv_proj_supported(const dcnn_ctx* ctx, int dtype, int k, int cin, int cin
                          int64_t in2_elems, int64_t out_elems);
 // Maps on which layers with streamed weights run one wave per (tile, channel block) (conv_unit.hip).
 constexpr int64_t kUnitMaxPixels = 16384;
-// Can the sparse steps of this convolution build their work list in the kernel?  (LDS room in every kernel that may serve them.)
-bool conv_self_fits(const dcnn_ctx* ctx, int dtype, int k, int cin, int cout, bool fused, int cin2, int64_t in_px, int64_t out_px,
-                    bool want_taps);
+// Can the sparse steps of this convolution build their work list in the kernel, and is it the better way?  (LDS room in every kernel
+// that may serve them.)
+bool conv_self_fits(const dcnn_ctx* ctx, int dtype, int k, int stride, int cin, int cout, bool fused, int cin2, int64_t in_px,
+                    int64_t out_px, bool want_taps);
 size_t conv_proj_weight_bytes(int dtype, int k, int cin, int cin2, int cout);
 // Packs the projection's [cin2][cout] weights in the column grouping of the main convolution's plan.
 dcnn_status launch_pack_weights_proj(dcnn_ctx* ctx, int dtype, const void* w2, void* wpacked2, int k, int cin, int cin2,

@@ -86,10 +86,14 @@ bool conv_proj_supported(const dcnn_ctx* ctx, int dtype, int k, int cin, int cin
     return (uint64_t)in_elems <= lim && (uint64_t)in2_elems <= lim && (uint64_t)out_elems <= lim;
 }
 
-bool conv_self_fits(const dcnn_ctx* ctx, int dtype, int k, int cin, int cout, bool fused, int cin2, int64_t in_px, int64_t out_px,
-                    bool want_taps) {
+bool conv_self_fits(const dcnn_ctx* ctx, int dtype, int k, int stride, int cin, int cout, bool fused, int cin2, int64_t in_px,
+                    int64_t out_px, bool want_taps) {
     const ConvPlan p = conv_plan(dtype, k, cin, cout, fused);
     if (!p.ok) return false;
+    // A strided 1x1 window tests its outputs one by one, and the kernels of streamed weights have 256 threads for it.  1x1 stride 2
+    // 256->256, a tenth of the input flagged, list in place against a stored one: on 2 K input pixels 8.8 us and 9.3, on 4 K 11.3 and
+    // 9.7, on 6 K 14.8 and 10.0, on 16 K 17.6 and 11.8.
+    if (p.stream && k == 1 && stride == 2 && in_px >= 4096) return false;
     const size_t scratch = self_scratch_bytes(in_px, out_px);
     const int64_t cus = ctx->num_cu;
     auto fits = [&](size_t own, size_t shared, int64_t group, int64_t grid_cap) {
