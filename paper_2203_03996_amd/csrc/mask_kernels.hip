@@ -567,10 +567,13 @@ __global__ __launch_bounds__(kListThreads) void mask_list_kernel(ListArgs l, uin
 // mask is a second round trip for all of it: 3x3 on 48 K 7.7 -> 6.9, but on 62 K 8.1 -> 9.3, an addition of two masks of 62 K 6.2 ->
 // 7.5 (kernel times).  Stride 2 tests the outputs one by one: 1x1 on 24 K input pixels 7.3 -> 7.4, on 32 K 7.3 -> 7.7, on 64 K
 // 7.5 -> 11.4; 3x3 on 24 K 9.3 -> 8.6, on 40 K 9.1 -> 10.0.
-constexpr int64_t kListMaxPixelsTwo = 49152, kListMaxPixelsStrided = 24576;
+// Upsampled flags: an input row is expanded once for each of its output rows, so the limit is on input pixels x factor.  The whole
+// layer (32 channels, f16, us), two passes -> one launch: 2x from 10 K 10.3 -> 9.7, 11 K 10.2 -> 10.7, 14 K 10.3 -> 11.9, 16 K
+// 10.3 -> 12.3; 3x from 6 K 10.2 -> 10.3, 7 K 10.3 -> 10.9; 4x from 3 K 10.3 -> 8.8, 4 K 10.4 -> 9.5.
+constexpr int64_t kListMaxPixelsTwo = 49152, kListMaxPixelsStrided = 24576, kListMaxUpFlags = 20480;
 static bool list_kernel_serves(const MaskPassArgs& m, int64_t in_px, int64_t out_px) {
     if (m.emit_only || m.idx_out == nullptr || m.kw > 0 || in_px > kListMaxPixels || out_px > kListMaxPixels) return false;
-    if (m.up > 1) { if (m.bilinear || m.mask_b != nullptr) return false; }
+    if (m.up > 1) { if (m.bilinear || m.mask_b != nullptr || in_px * m.up > kListMaxUpFlags) return false; }
     else if (m.stride > 2 || !((m.k == 1 && m.pad == 0) || (m.k == 3 && m.pad == 1))) return false;
     if ((m.stride == 2 && in_px > kListMaxPixelsStrided) || (m.mask_b != nullptr && out_px > kListMaxPixelsTwo)) return false;
     if (m.b_stride > 0 && out_px > kSelfMaxPixels) return false;        // (sampled pixel by pixel by every workgroup)

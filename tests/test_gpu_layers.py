@@ -731,6 +731,25 @@ def test_upsample(S, factor):
         check_delta(out, want, S, f"upsample frame {t}", exact_values=True)
 
 
+@pytest.mark.parametrize("n,h,w,factor", [(1, 100, 102, 2), (1, 101, 102, 2), (2, 70, 81, 2), (1, 66, 103, 3), (1, 67, 103, 3), (1, 64, 64, 4)])
+def test_upsampled_mask_on_both_sides_of_the_one_launch_list(n, h, w, factor):
+    """Input pixels x factor just below and above 20 K: the list in one launch and in two passes, values and mask bit for bit."""
+    S, shape = "f16", (n, h, w, 8)
+    rng = np.random.default_rng(h * factor)
+    ref = orc.Upsample(factor, S)
+    ctx = pkg.Context(n * h * w * factor * factor)
+    layer = pkg.Layer(ctx, pkg.make_desc(pkg.UPSAMPLE, DT[S], n, h, w, 8, factor=factor))
+    x0 = rng.normal(0, 1, shape).astype(NP_DTYPE[S])
+    layer.init([torch.from_numpy(x0).cuda()])
+    ref.init(x0)
+    for t, dens in enumerate([0.3, 0.0, 1.0, 0.05]):
+        d = _rand_delta(rng, shape, dens, S)
+        want = ref.step(d).poisoned()
+        out = layer.step([_upload(d)])
+        ctx.sync()
+        check_delta(out, want, S, f"upsample x{factor} frame {t}", exact_values=True)
+
+
 @pytest.mark.parametrize("S", ["f32", "f16"])
 @pytest.mark.parametrize("factor,c", [(2, 32), (3, 5), (4, 16)])
 def test_upsample_bilinear(S, factor, c):
