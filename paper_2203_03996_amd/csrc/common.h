@@ -187,6 +187,15 @@ __host__ __device__ inline WgTileRange tile_range(int64_t groups, uint32_t block
     const int64_t end = (xcd + 1) * per;
     return {xcd * per + block / kXcd, end < groups ? end : groups, grid / kXcd};
 }
+// Tiles per round of a workgroup of the wave-specialised convolution that has room for `slots` of them: as few as go round the grid
+// once.  The vector memory path of one compute unit is what a short list waits for (64-72 clocks per load instruction, ~50 of them
+// per 3x3 tile of 64 channels): with always eight tiles to a workgroup a list of 4000 entries ran on 16 of 256 compute units.  Spread:
+// fp32 3x3 32->32 + ReLU on 64x64 27.6 -> 21.8 us with its input layer, the bottleneck block on one 128x128 stream 53.1 -> 47.5,
+// a four-resolution network on 8 streams 1399 -> 1325; lists that fill the chip anyway (64 streams) the same.
+__host__ __device__ inline int ws_slots(uint32_t tiles, uint32_t grid, int slots) {
+    const int each = (int)((tiles + grid - 1) / grid);
+    return each < 1 ? 1 : (each < slots ? each : slots);
+}
 // entries of the groups that one workgroup of `grid` owns at most (tile ranges per XCD, or a plain stride over the grid)
 inline int64_t self_local_entries(int64_t out_px, int64_t entries_per_group, int grid, bool per_xcd) {
     const int64_t groups = cdiv(out_px, entries_per_group);

@@ -508,7 +508,7 @@ static dcnn_status launch_conv_nb(dcnn_ctx* ctx, bool init, const ListArgs& l_in
         return fail(ctx, DCNN_EUNSUPPORTED, "conv %dx%d %d->%d: x^T row flags are kept by the wave-specialised kernel only", c.k, c.k,
                     c.cin, c.cout);
     if (ws_ok) {
-        const int64_t ws_want = cdiv(l.max_count > 0 ? l.max_count : 1, (kWsProducers / p.cs) * kTile);
+        const int64_t ws_want = max_tiles;
         const int64_t ws_cap = ctx->num_cu;                    // 16 waves of up to 128 registers fill a compute unit
         const int ws_grid = (int)(cdiv(ws_want < ws_cap ? ws_want : ws_cap, kXcd) * kXcd);
         const size_t ws_w_bytes = p.w_bytes + (dual ? (size_t)c.kch2 * 2 * p.cout_pad * 16 : 0);

@@ -10,6 +10,8 @@
 //   consumers (waves 8-15)  pick the tile of the PREVIOUS round up from LDS, apply residual /
 //                           activation / truncation (Section 3.1, Eqs. 4-6), and write state, output
 //                           delta, update mask and survivor word with coalesced 16-byte accesses.
+// A workgroup has room for 8/cs tiles per round and takes fewer when the list is short, so that it reaches every
+// compute unit (ws_slots); the waves of the slots left empty help with the weights and leave.
 // The result tiles are double-buffered and handed over per tile slot through two LDS counters (tiles staged /
 // tiles consumed), so a slot's producers and consumers wait for each other only, never for the whole workgroup.
 // Each role needs at most 128 registers: four waves per SIMD, and while the consumers wait for
@@ -78,7 +80,6 @@ __global__ __launch_bounds__(kWsWaves* kWave) void conv_ws_kernel(ListParam<SELF
     extern __shared__ __align__(16) unsigned char smem[];
     clear_ahead(e);
 
-    const int tiles_per_iter = NP / cs;
     // (a list built here: its scratch memory is the staging area, which nothing uses yet; the entries follow everything else)
     int32_t* self_px = nullptr;
     uint32_t* self_tap = nullptr;
@@ -136,17 +137,23 @@ __global__ __launch_bounds__(kWsWaves* kWave) void conv_ws_kernel(ListParam<SELF
         // out to have no tile, and a one-stream step went from 49.7 to 53.0 us)
         count = self_build<kWsWaves * kWave>(l, sb, &ahead);
     }
-    const WgTileRange r = wg_tile_range((count + tiles_per_iter * kTile - 1) / (tiles_per_iter * kTile));
+    const uint32_t ntiles = (uint32_t)((count + kTile - 1) / kTile);
+    const int tiles_per_iter = ws_slots(ntiles, gridDim.x, NP / cs);
+    const WgTileRange r = wg_tile_range((ntiles + tiles_per_iter - 1) / (uint32_t)tiles_per_iter);
     if constexpr (SELF)
         self_emit<kWsWaves * kWave>(l, sb, (int)count, SelfSpan{(int)r.begin, (int)r.end, (int)r.step, tiles_per_iter * kTile},
                                     self_px, self_tap);
     if (r.begin >= r.end) return;                              // nothing for this workgroup: skip the weight load
-    const int rounds = (int)((r.end - r.begin + r.step - 1) / r.step);
+    const int rounds = (int)((uint32_t)(r.end - r.begin + r.step - 1) / (uint32_t)r.step);
 
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
     const bool producer = wave < NP;
     const int ww = producer ? wave : wave - NP;
     const int slot = ww / cs, part = ww % cs;                  // which tile of the round; channel slice / pixel slice
+    if (slot >= tiles_per_iter) {                              // a short list: this slot stays empty, its waves help with the weights
+        load_weights();
+        return;
+    }
     // Hand-over of result tiles.  A tile slot is the business of its cs producers and cs consumers only, so instead of
     // a workgroup barrier per round (every wave waiting for the slowest of sixteen, round after round) each slot keeps
     // two counters in LDS: `staged` (bumped by a producer once its slice of a tile is in the staging buffer) and

@@ -1210,3 +1210,44 @@ def test_mask_compact_of_unaligned_masks(k, stride, at):
     assert np.array_equal(to_np(got), want)
     flat = np.flatnonzero(want.reshape(-1))
     assert int(to_np(count)[0]) == flat.size and np.array_equal(to_np(idx)[:flat.size], flat)
+
+
+@pytest.mark.parametrize("S,k,cin,cout,res", [("f16", 1, 16, 32, False), ("f16", 3, 16, 128, True), ("f32", 1, 16, 64, False)])
+@pytest.mark.parametrize("tiles", [1, 256, 257, 511, 513, 769, 1100])
+def test_tiles_of_short_lists_over_the_whole_chip(S, k, cin, cout, res, tiles):
+    """Lists of a tile or two per compute unit and of one more or less (the last one ends inside a tile): a workgroup takes one
+    tile per round, two, three, or as many as it has room for, and every entry is worked on once."""
+    n, h, w = 2, 136, 132
+    rng = np.random.default_rng(tiles + cout)
+    dt, eps = NP_DTYPE[S], 0.3
+    ctx, layer, rconv = _conv_layers(S, k, 1, k // 2, cin, cout, (n, h, w), rng, act=pkg.ACT_RELU, eps=eps, n_in=2 if res else 1)
+    radd, ract = orc.Add(S), orc.ActTrunc("relu", eps, S)
+    x0 = rng.normal(0, 1, (n, h, w, cin)).astype(dt)
+    s0 = rng.normal(0, 1, (n, h, w, cout)).astype(dt)
+    y0 = rconv.init(x0)
+    ract.init(radd.init(y0, s0) if res else y0)
+    layer.init([torch.from_numpy(a).cuda() for a in ([x0, s0] if res else [x0])])
+    layer.state_tensor(0).copy_(torch.from_numpy(ract.xA).cuda())
+    d = _rand_delta(rng, (n, h, w, cin), 0.0, S, 0.5)
+    if k == 1:
+        d.mask.reshape(-1)[rng.permutation(n * h * w)[:32 * tiles - 5]] = 1
+    else:                                                      # whole rows: (rows + 2) * w outputs are listed
+        rows = max(1, (32 * tiles) // w - 2)
+        d.mask.reshape(n * h, w)[:min(rows, h - 1)] = 1
+        d.mask.reshape(n * h, w)[h + 1:h + 1 + max(0, rows - h - 1)] = 1
+    d = ODelta(np.where(d.mask[..., None] == 1, rng.normal(0, 0.5, d.data.shape), np.nan).astype(dt), d.mask)
+    mid = rconv.step(d).poisoned()
+    sl = sum_slack(rconv, d.zero_filled()) + ulp(mid.data, S)
+    ins = [_upload(d)]
+    if res:
+        ds = _rand_delta(rng, (n, h, w, cout), 0.001, S, 0.5)
+        mid = radd.step(mid, ds).poisoned()
+        sl = sl + ulp(mid.data, S)
+        ins.append(_upload(ds))
+    want = ract.step(mid).poisoned()
+    out = layer.step(ins)
+    ctx.sync()
+    check_delta(out, want, S, f"{tiles} tiles", allow_mask_diff=_near_tie(ract, eps, sl), slack=sl)
+    agree = to_np(out.mask) == want.mask
+    for which, ref in ((0, ract.xA), (1, ract.xT)):
+        assert rel_err(to_np(layer.state_tensor(which))[agree], ref[agree], slack=sl[agree]) <= TOL[S]
