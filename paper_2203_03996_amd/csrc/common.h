@@ -155,6 +155,10 @@ struct ListArgs : StoredList {
     uint8_t* mask_zero;          // 0 at every pixel that is not listed (the kernel itself writes the decision at those that are)
     int lds_scratch, lds_list;   // byte offsets into the kernel's dynamic LDS (set by the launchers)
     int lds_entries;             // room for this many entries
+    // Kernels whose workgroups compact blocks of pixels of their own (local_build) instead of cutting up the map's list:
+    int writers;                 // the first workgroups of the grid write what belongs to the whole map
+    int local_shift;             // a block is 1 << local_shift pixels
+    int local_slots;             // pixels per workgroup: its blocks, whole
 };
 // What a kernel takes: the five words of a stored list where it walks one.  (All of ListArgs on every launch, 250 bytes of
 // arguments more, cost 0.4 us a launch: activations of 5-11 us 5-8 % slower.)
@@ -201,6 +205,25 @@ inline int64_t self_local_entries(int64_t out_px, int64_t entries_per_group, int
     const int64_t groups = cdiv(out_px, entries_per_group);
     const int64_t mine = per_xcd ? cdiv(cdiv(groups, kXcd), grid / kXcd) : cdiv(groups, grid);
     return (mine < 1 ? 1 : mine) * entries_per_group;
+}
+
+// Blocks that workgroups compact for themselves (local_build in self_list.h).  Workgroups of one launch: the writers of what
+// belongs to the whole map, then the owners of pixels.
+constexpr int kLocalHeader = 64;                               // bytes of counts ahead of a workgroup's entries
+inline int local_writers(const ListArgs& l) {
+    if (l.idx_out == nullptr && l.in_idx_out == nullptr) return l.count_out != nullptr ? 1 : 0;
+    const int64_t px = l.m_in_px > l.m_out_px ? l.m_in_px : l.m_out_px, w = cdiv(px, 8192);
+    return (int)(w < 8 ? w : 8);
+}
+struct LocalShape { int owners, slots, entries; };             // workgroups with pixels, pixels of each, room for entries
+// `group`: entries that a workgroup walks per iteration; owners_cap: workgroups that are worth having
+inline LocalShape local_shape(int64_t out_px, int local_shift, int64_t owners_cap, int group) {
+    const int64_t blocks = cdiv(out_px, 1 << local_shift);
+    LocalShape s;
+    s.owners = (int)(blocks < owners_cap ? blocks : owners_cap);
+    s.slots = (int)cdiv(blocks, s.owners) << local_shift;
+    s.entries = (int)(cdiv(s.slots, group) * group);
+    return s;
 }
 
 // Statistics (never on a timed path): x^T rows a convolution that keeps row flags reads and writes in one step.

@@ -32,7 +32,7 @@ constexpr int kDirectWaves = 4;
 // weight operands of a row's three taps are multiplied with the same gathered registers.
 template <typename T, int NB, int KS, int TI, int D, bool ROW, bool SELF>
 __device__ __forceinline__ void conv_direct_body(const ListParam<SELF>& l, const ConvArgs& c, const EpilogueArgs& e, int npass, int cs,
-                                                 int64_t count, unsigned char* smem, const SelfBits& sb) {
+                                                 int64_t count, unsigned char* smem, const int32_t* self_px, const uint32_t* self_tap) {
     typedef typename Mma<T>::Vec Vec;
     constexpr int V = Elem<T>::VEC;
     typedef typename RawOf<T, V>::type Raw;
@@ -44,16 +44,9 @@ __device__ __forceinline__ void conv_direct_body(const ListParam<SELF>& l, const
 
     const int units_per_iter = NW / cs;                        // groups of TI tiles per workgroup iteration
     const int64_t ntiles = (count + kTile - 1) / kTile;
-    const WgTileRange r = wg_tile_range((ntiles + units_per_iter * TI - 1) / (units_per_iter * TI));
-    const int32_t* self_px = nullptr;
-    const uint32_t* self_tap = nullptr;
+    const int64_t groups = (ntiles + units_per_iter * TI - 1) / (units_per_iter * TI);
+    const WgTileRange r = SELF ? WgTileRange{0, groups, 1} : wg_tile_range(groups);
     const int group = units_per_iter * TI * kTile;
-    if constexpr (SELF) {
-        int32_t* const px = reinterpret_cast<int32_t*>(smem + l.lds_list);
-        uint32_t* const tap = reinterpret_cast<uint32_t*>(px) + l.lds_entries;
-        self_emit<kDirectWaves * kWave>(l, sb, (int)count, SelfSpan{(int)r.begin, (int)r.end, (int)r.step, group}, px, tap);
-        self_px = px; self_tap = l.want_taps ? tap : nullptr;
-    }
     if (r.begin >= r.end) return;
 
     const int lane = threadIdx.x % kWave;
@@ -83,7 +76,7 @@ __device__ __forceinline__ void conv_direct_body(const ListParam<SELF>& l, const
         return ((int)n * c.h + oy * c.stride - c.pad) * c.w + ox * c.stride - c.pad;
     };
     auto tile_of = [&](int64_t wt, int ti) { return (wt * units_per_iter + slot) * TI + ti; };
-    // (a list built here: round wt is group (wt - begin) / step of this workgroup's entries)
+    // (entries of blocks compacted here: round wt is their wt-th group)
     auto entry = [&](int64_t wt, int ti, int round) {
         if (wt >= r.end) return -1;
         return SELF ? self_px[round * group + (slot * TI + ti) * kTile + col] : list_pixel(l.list, tile_of(wt, ti) * kTile + col, count);
@@ -301,12 +294,16 @@ __global__ __launch_bounds__(kDirectWaves* kWave, 2) void conv_direct_kernel(Lis
     extern __shared__ __align__(16) unsigned char smem[];
     clear_ahead(e);
     if constexpr (SELF) {
-        // (maps whose kernels build the list are too small for more than one tile per wave)
-        const SelfBits sb = self_carve(l, smem + l.lds_scratch);
-        const int64_t count = self_build<kDirectWaves * kWave>(l, sb);
-        conv_direct_body<T, NB, KS, 1, (NB >= 4 ? 6 : 8), false, SELF>(l, c, e, npass, cs, count, smem, sb);
+        if ((int)blockIdx.x < l.writers) {
+            local_write<kDirectWaves * kWave>(l, smem + l.lds_scratch);
+            return;
+        }
+        // (maps whose blocks the kernel compacts itself are too small for more than one tile per wave)
+        int32_t* px;
+        uint32_t* tap;
+        const int count = local_build<kDirectWaves * kWave>(l, smem + l.lds_list, px, tap);
+        conv_direct_body<T, NB, KS, 1, (NB >= 4 ? 6 : 8), false, SELF>(l, c, e, npass, cs, count, smem, px, l.want_taps ? tap : nullptr);
     } else {
-        const SelfBits sb{};
         const int64_t count = list_count(l);
         if (count >= (int64_t)blocked_min_tiles * kTile) {
             if constexpr (KS == 3 && NB <= 2) {
@@ -318,13 +315,13 @@ __global__ __launch_bounds__(kDirectWaves* kWave, 2) void conv_direct_kernel(Lis
                 const bool dense_taps = c.in_count ? (int64_t)*c.in_count * 4 >= count * 3
                                                    : count * 4 >= (int64_t)c.n * c.oh * c.ow * 3;
                 if (c.stride == 1 && c.pad == 1 && dense_taps) {
-                    conv_direct_body<T, NB, KS, (TI > 3 ? 3 : TI), 2, true, SELF>(l, c, e, npass, cs, count, smem, sb);   // 3 tiles: two operand sets of 12 vectors fit beside 96 accumulators
+                    conv_direct_body<T, NB, KS, (TI > 3 ? 3 : TI), 2, true, SELF>(l, c, e, npass, cs, count, smem, nullptr, nullptr);   // 3 tiles: two operand sets of 12 vectors fit beside 96 accumulators
                     return;
                 }
             }
-            conv_direct_body<T, NB, KS, TI, 3, false, SELF>(l, c, e, npass, cs, count, smem, sb);
+            conv_direct_body<T, NB, KS, TI, 3, false, SELF>(l, c, e, npass, cs, count, smem, nullptr, nullptr);
         } else {
-            conv_direct_body<T, NB, KS, 1, (NB >= 4 ? 6 : 8), false, SELF>(l, c, e, npass, cs, count, smem, sb);
+            conv_direct_body<T, NB, KS, 1, (NB >= 4 ? 6 : 8), false, SELF>(l, c, e, npass, cs, count, smem, nullptr, nullptr);
         }
     }
 }

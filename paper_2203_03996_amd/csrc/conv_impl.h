@@ -461,7 +461,7 @@ static dcnn_status launch_conv_nb(dcnn_ctx* ctx, bool init, const ListArgs& l_in
     const int ini = init ? 1 : 0;
     hipError_t err = hipSuccess;
     bool launched = false;
-    // A list built by the kernel: its scratch memory shares the space from `shared` on (staging, not in use yet), its entries
+    // A list built by the plain kernel: its scratch memory shares the space from `shared` on (staging, not in use yet), its entries
     // follow.  Returns the LDS size; the caller has made sure that it fits (conv_self_fits).
     auto place_list = [&](size_t total, size_t shared, int64_t group, int g) -> size_t {
         if (!l.self) return total;
@@ -471,6 +471,21 @@ static dcnn_status launch_conv_nb(dcnn_ctx* ctx, bool init, const ListArgs& l_in
         l.lds_list = (int)at;
         l.lds_entries = (int)self_local_entries(l.m_out_px, group, g, true);
         return at + (size_t)l.lds_entries * (l.want_taps ? 8 : 4);
+    };
+    // Blocks that the workgroups of the other kernels compact themselves: their entries follow everything else, a writer's flags share
+    // the space from `shared` on.
+    auto place_local = [&](size_t total, size_t shared, int group, int64_t cap_wgs, int* g) -> size_t {
+        if (!l.self) return total;
+        l.writers = local_writers(l);
+        const LocalShape s = local_shape(l.m_out_px, kLocalTileShift, cap_wgs - l.writers, group);
+        l.local_shift = kLocalTileShift;
+        l.local_slots = s.slots;
+        l.lds_entries = s.entries;
+        l.lds_scratch = (int)shared;
+        l.lds_list = (int)align_up(total, 16);
+        *g = s.owners + l.writers;
+        const size_t all = (size_t)l.lds_list + kLocalHeader + (size_t)s.entries * 8, scratch_end = shared + self_scratch_bytes(l.m_in_px, l.m_out_px);
+        return all > scratch_end ? all : scratch_end;
     };
     const size_t shared_weights = p.stream || direct ? 0 : p.w_bytes;
     const size_t plain_lds = place_list(lds_bytes, shared_weights, tiles_per_iter * kTile, grid);
@@ -510,9 +525,9 @@ static dcnn_status launch_conv_nb(dcnn_ctx* ctx, bool init, const ListArgs& l_in
     if (ws_ok) {
         const int64_t ws_want = max_tiles;
         const int64_t ws_cap = ctx->num_cu;                    // 16 waves of up to 128 registers fill a compute unit
-        const int ws_grid = (int)(cdiv(ws_want < ws_cap ? ws_want : ws_cap, kXcd) * kXcd);
+        int ws_grid = (int)(cdiv(ws_want < ws_cap ? ws_want : ws_cap, kXcd) * kXcd);
         const size_t ws_w_bytes = p.w_bytes + (dual ? (size_t)c.kch2 * 2 * p.cout_pad * 16 : 0);
-        const size_t ws_all = place_list(ws_lds, ws_w_bytes, (kWsProducers / p.cs) * kTile, ws_grid);
+        const size_t ws_all = place_local(ws_lds, ws_w_bytes, (kWsProducers / p.cs) * kTile, ws_cap, &ws_grid);
         if (ws_all > kLdsBytes) return fail(ctx, DCNN_EUNSUPPORTED, "conv: a work list built in place does not fit LDS");
 #define DCNN_WS_LAUNCH(KS, AUX, DUAL)                                                                            \
     do {                                                                                                         \
@@ -558,8 +573,8 @@ static dcnn_status launch_conv_nb(dcnn_ctx* ctx, bool init, const ListArgs& l_in
         // TI tiles per wave once that still gives every SIMD of the chip a wave (the list's length is read on the device)
         const int blocked_min_tiles = (int)((int64_t)ctx->num_cu * 4 * TI / p.cs);
         const int64_t b_cap = (int64_t)ctx->num_cu * 2;        // 4 waves of up to 256 registers: two workgroups per compute unit
-        const int b_grid = (int)(cdiv(b_want < b_cap ? b_want : b_cap, kXcd) * kXcd);
-        const size_t b_all = place_list(b_lds, 0, (kDirectWaves / p.cs) * kTile, b_grid);
+        int b_grid = (int)(cdiv(b_want < b_cap ? b_want : b_cap, kXcd) * kXcd);
+        const size_t b_all = place_local(b_lds, 0, (kDirectWaves / p.cs) * kTile, b_cap, &b_grid);
         if (b_all > kLdsBytes) return fail(ctx, DCNN_EUNSUPPORTED, "conv: a work list built in place does not fit LDS");
 #define DCNN_BLOCKED_LAUNCH(KS, SELF)                                                                            \
     do {                                                                                                         \

@@ -96,17 +96,21 @@ bool conv_self_fits(const dcnn_ctx* ctx, int dtype, int k, int stride, int cin, 
     if (p.stream && k == 1 && stride == 2 && in_px >= 4096) return false;
     const size_t scratch = self_scratch_bytes(in_px, out_px);
     const int64_t cus = ctx->num_cu;
-    auto fits = [&](size_t own, size_t shared, int64_t group, int64_t grid_cap, bool tile_grid = false) {
-        const int64_t want = cdiv(out_px, tile_grid ? kTile : group);
+    auto fits = [&](size_t own, size_t shared, int64_t group, int64_t grid_cap) {
+        const int64_t want = cdiv(out_px, group);
         const int grid = (int)(cdiv(want < grid_cap ? want : grid_cap, kXcd) * kXcd);
         const size_t at = align_up(own > shared + scratch ? own : shared + scratch, 16);
         return at + (size_t)self_local_entries(out_px, group, grid, true) * (want_taps ? 8 : 4) <= kLdsBytes;
     };
+    auto local_fits = [&](size_t own, size_t shared, int group, int64_t cap) {
+        const LocalShape s = local_shape(out_px, kLocalTileShift, cap - 8, group);
+        return align_up(own, 16) + kLocalHeader + (size_t)s.entries * 8 <= kLdsBytes && shared + scratch <= kLdsBytes;
+    };
     const size_t ws_lds = conv_ws_lds_bytes(p, dtype, k, cout, cin2);
     const size_t ws_w = p.w_bytes + (size_t)cdiv(cin2, dtype == DCNN_F16 ? 16 : 8) * 2 * p.cout_pad * 16;
-    if (ws_lds != 0 && !fits(ws_lds, ws_w, (kWsProducers / p.cs) * kTile, cus, true)) return false;
+    if (ws_lds != 0 && !local_fits(ws_lds, ws_w, (kWsProducers / p.cs) * kTile, cus)) return false;
     const size_t direct_lds = conv_stage_bytes(kDirectWaves, p.nb, dtype) + conv_xchg_bytes(kDirectWaves);
-    if (!fits(direct_lds, 0, (kDirectWaves / p.cs) * kTile, 2 * cus)) return false;
+    if (!local_fits(direct_lds, 0, (kDirectWaves / p.cs) * kTile, 2 * cus)) return false;
     return fits(p.lds_bytes, p.stream ? 0 : p.w_bytes, (p.waves / p.cs) * kTile, cus);
 }
 

@@ -7,6 +7,7 @@
 namespace dcnn {
 
 constexpr int kStagePad = 16;                       // bytes added to a staging row against bank conflicts
+constexpr int kLocalTileShift = 5;                  // blocks that a convolution's workgroups compact: as many pixels as a tile has
 constexpr int kGroup = 4;                           // K-steps per streamed weight slice
 constexpr size_t kLdsBytes = 160 * 1024;            // LDS of one gfx950 compute unit; the context refuses less
 

@@ -23,6 +23,7 @@ struct UnitArgs {
     int nb;                        // column blocks per packed channel group (the layer's plan)
     int blocks;                    // 32-channel blocks of the output
     int groups;                    // groups of one block per wave of the workgroup
+    int waves;                     // waves with a block (a workgroup that writes lists has more)
     uint32_t map_bytes, out_pixels;
 };
 
@@ -41,25 +42,24 @@ __global__ __launch_bounds__(kUnitMaxWaves* kWave) void conv_unit_kernel(ListArg
     extern __shared__ __align__(16) unsigned char smem[];
     const int lane = threadIdx.x % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int nwaves = blockDim.x / kWave;
+    const int nwaves = a.waves;
     const int col = lane % 32, g = lane / 32;
     unsigned char* stage = smem + (size_t)wave * kTile * stage_row;
 
-    int count;
-    SelfBits sb;
+    int count = 0, ntiles, first = blockIdx.x;
     if (l.self) {
-        sb = self_carve(l, smem + l.lds_scratch);
-        // (the workgroup's size is a launch parameter here: the list code is written for a fixed number of threads)
-        if (nwaves == 1) count = self_build<kWave>(l, sb);
-        else if (nwaves == 2) count = self_build<2 * kWave>(l, sb);
-        else count = self_build<4 * kWave>(l, sb);
-        if (nwaves == 1) self_emit<kWave>(l, sb, count, SelfSpan{0, 0, 1, 1}, nullptr, nullptr);
-        else if (nwaves == 2) self_emit<2 * kWave>(l, sb, count, SelfSpan{0, 0, 1, 1}, nullptr, nullptr);
-        else self_emit<4 * kWave>(l, sb, count, SelfSpan{0, 0, 1, 1}, nullptr, nullptr);
+        // tiles of 32 consecutive pixels as they lie, the listed ones taking part: nothing to build
+        if (first < l.writers) {
+            local_write<kUnitMaxWaves * kWave>(l, smem);
+            return;
+        }
+        if (wave >= nwaves) return;
+        first -= l.writers;
+        ntiles = (l.m_out_px + kTile - 1) / kTile;
     } else {
         count = (int)list_count(l);
+        ntiles = (count + kTile - 1) / kTile;
     }
-    const int ntiles = (count + kTile - 1) / kTile;
     const int kch = c.kch, ksteps = KS * KS * kch, cols = a.nb * 32;
     const int cin_bytes = c.cin * ES;
     const __amdgpu_buffer_rsrc_t rs_in = ws_rsrc(c.in_data, (uint64_t)c.n * c.h * c.w * cin_bytes);
@@ -70,23 +70,24 @@ __global__ __launch_bounds__(kUnitMaxWaves* kWave) void conv_unit_kernel(ListArg
     const uint32_t wstride = (uint32_t)(2 * cols * 16);        // weights of one K-step
     const uint32_t row_bytes = (uint32_t)e.c * ES;
 
-    for (int u = blockIdx.x; u < ntiles * a.groups; u += gridDim.x) {
+    for (int u = first; u < ntiles * a.groups; u += (int)gridDim.x - (l.self ? l.writers : 0)) {
         const int tile = u / a.groups;
         const int cb = (u - tile * a.groups) * nwaves + wave;  // this wave's channel block
         const bool cb_on = cb < a.blocks;
         const int j = tile * kTile + col;
-        int p = -1;
+        int p = -1, rflag = 1;
         uint32_t taps = 0;
-        if (j < count) {
-            if (l.self) {
-                p = self_select(sb, j);
-                taps = l.want_taps ? self_taps(l, sb.ibits, sb.in_words, p) : 1u;
-            } else {
-                p = l.list ? l.list[j] : j;
-                taps = l.taps ? l.taps[j] & ((1u << (KS * KS)) - 1u) : 1u;
-            }
+        if (l.self) {
+            taps = local_taps(l, j, j < l.m_out_px);
+            if (cb == 0 && g == 0 && j < l.m_out_px) local_mask(l, j, taps != 0);
+            if (taps != 0) p = j;
+            rflag = (taps & kLocalSecond) != 0;
+            if (__ballot(taps != 0) == 0) continue;
+        } else if (j < count) {
+            p = l.list ? l.list[j] : j;
+            taps = l.taps ? l.taps[j] & ((1u << (KS * KS)) - 1u) : 1u;
         }
-        const int rflag = e.res_mask ? __builtin_amdgcn_raw_buffer_load_b8(rs_rmask, p >= 0 ? p : (int)kOob, 0, 0) : 1;
+        if (!l.self && e.res_mask) rflag = __builtin_amdgcn_raw_buffer_load_b8(rs_rmask, p >= 0 ? p : (int)kOob, 0, 0);
         uint32_t base;                                         // this lane's 16 bytes of tap (0,0), K-step 0
         {
             const uint32_t pu = p >= 0 ? (uint32_t)p : 0u;
@@ -232,11 +233,18 @@ static dcnn_status launch_conv_unit_t(dcnn_ctx* ctx, const ListArgs& l_in, const
     a.groups = (int)cdiv(a.blocks, waves);
     a.map_bytes = (uint32_t)((uint64_t)out_px * e.c * sizeof(T));
     a.out_pixels = (uint32_t)out_px;
+    a.waves = waves;
     const int64_t want = tiles * a.groups, cap = (int64_t)ctx->num_cu * 8;
-    const int grid = (int)(cdiv(want < cap ? want : cap, kXcd) * kXcd);
+    int grid = (int)(cdiv(want < cap ? want : cap, kXcd) * kXcd);
     size_t lds = unit_stage_bytes(waves, dtype);
-    if (l.self) { l.lds_scratch = (int)lds; lds += self_scratch_bytes(l.m_in_px, l.m_out_px); }
-    const dim3 g(grid), b(waves * kWave);
+    if (l.self) {
+        // (multiples of 8 keep a channel group on its XCD; writers form the flags of the whole map: four waves)
+        l.writers = (int)cdiv(local_writers(l), kXcd) * kXcd;
+        grid += l.writers;
+        const size_t scratch = self_scratch_bytes(l.m_in_px, l.m_out_px);
+        if (scratch > lds) lds = scratch;
+    }
+    const dim3 g(grid), b((l.self ? kUnitMaxWaves : waves) * kWave);
     if (c.k == 1) hipLaunchKernelGGL((conv_unit_kernel<T, 1>), g, b, lds, ctx->stream, l, c, e, a);
     else hipLaunchKernelGGL((conv_unit_kernel<T, 3>), g, b, lds, ctx->stream, l, c, e, a);
     return check_hip(ctx, hipGetLastError(), "conv_unit_kernel launch");

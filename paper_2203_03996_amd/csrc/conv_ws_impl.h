@@ -80,19 +80,15 @@ __global__ __launch_bounds__(kWsWaves* kWave) void conv_ws_kernel(ListParam<SELF
     extern __shared__ __align__(16) unsigned char smem[];
     clear_ahead(e);
 
-    // (a list built here: its scratch memory is the staging area, which nothing uses yet; the entries follow everything else)
+    // (the pixels of this workgroup's own blocks: entries behind everything else; a writer's flags lie in the staging area)
     int32_t* self_px = nullptr;
     uint32_t* self_tap = nullptr;
-    if constexpr (SELF) {
-        self_px = reinterpret_cast<int32_t*>(smem + l.lds_list);
-        self_tap = reinterpret_cast<uint32_t*>(self_px) + l.lds_entries;
-    }
     int64_t count;
-    SelfBits sb;
-    SelfAhead ahead;
     if constexpr (SELF) {
-        sb = self_carve(l, smem + l.lds_scratch);
-        self_request(l, ahead);
+        if ((int)blockIdx.x < l.writers) {
+            local_write<kWsWaves * kWave>(l, smem + l.lds_scratch);
+            return;
+        }
     } else {
         count = list_count(l);
     }
@@ -132,17 +128,13 @@ __global__ __launch_bounds__(kWsWaves* kWave) void conv_ws_kernel(ListParam<SELF
         lds_block_sync();
     };
 
-    if constexpr (SELF) {
-        // (fetching the weights together with the mask was measured: every workgroup then fetches them, also those that turn
-        // out to have no tile, and a one-stream step went from 49.7 to 53.0 us)
-        count = self_build<kWsWaves * kWave>(l, sb, &ahead);
-    }
+    // (fetching the weights together with the flags was measured: every workgroup then fetches them, also those that turn out to
+    // have no tile, and a one-stream step went from 49.7 to 53.0 us)
+    if constexpr (SELF) count = local_build<kWsWaves * kWave>(l, smem + l.lds_list, self_px, self_tap);
     const uint32_t ntiles = (uint32_t)((count + kTile - 1) / kTile);
-    const int tiles_per_iter = ws_slots(ntiles, gridDim.x, NP / cs);
-    const WgTileRange r = wg_tile_range((ntiles + tiles_per_iter - 1) / (uint32_t)tiles_per_iter);
-    if constexpr (SELF)
-        self_emit<kWsWaves * kWave>(l, sb, (int)count, SelfSpan{(int)r.begin, (int)r.end, (int)r.step, tiles_per_iter * kTile},
-                                    self_px, self_tap);
+    const int tiles_per_iter = SELF ? min(max((int)ntiles, 1), NP / cs) : ws_slots(ntiles, gridDim.x, NP / cs);
+    const uint32_t groups = (ntiles + tiles_per_iter - 1) / (uint32_t)tiles_per_iter;
+    const WgTileRange r = SELF ? WgTileRange{0, (int64_t)groups, 1} : wg_tile_range(groups);
     if (r.begin >= r.end) return;                              // nothing for this workgroup: skip the weight load
     const int rounds = (int)((uint32_t)(r.end - r.begin + r.step - 1) / (uint32_t)r.step);
 
@@ -195,8 +187,10 @@ __global__ __launch_bounds__(kWsWaves* kWave) void conv_ws_kernel(ListParam<SELF
         const bool k_exact2 = kch * 32 == cin_bytes;           // no K-step at all does
         // (one gather per window row pays when most of the map is listed -- the dense mode and high update densities:
         // 4.6 % of the step with everything listed, 1 % at 50 % density; on short lists the tap-by-tap ring with its
-        // third set in flight is 1 % ahead)
-        const bool row_shift = KS == 3 && !DUAL && NB <= 2 && c.stride == 1 && c.pad == 1 && count * 4 >= (int64_t)c.n * c.oh * c.ow * 3;
+        // third set in flight is 1 % ahead.  Not on maps whose blocks may be compacted in place: there the pixel to the left need not be
+        // the entry before, and sums have one order whichever way the tiles came about.)
+        const int64_t out_px = (int64_t)c.n * c.oh * c.ow;
+        const bool row_shift = !SELF && KS == 3 && !DUAL && NB <= 2 && c.stride == 1 && c.pad == 1 && out_px > kListMaxPixels && count * 4 >= out_px * 3;
         (void)k_exact2; (void)row_shift;
         constexpr int kNoTap = 31;                             // cursor sentinel: no tap has this number
         // Which window taps of a list entry are in bounds and flagged comes with the work list (one

@@ -2,14 +2,17 @@
 //
 // On maps of up to kSelfMaxPixels pixels the mask pass, the list emission and the compaction of survivors cost more than
 // what they serve: each is a launch of its own with two or three dependent round trips to memory (4-6 us; a layer of a
-// network of small maps took 12-20 us, half of it spent on lists).  A mask of 16 K pixels is 2 KB of bits, though,
-// so every workgroup of the layer's own kernel can hold ALL flags in LDS: it reads the input mask (one round trip of
-// 16-byte loads), forms the flagged output pixels as bits (a 3x3 window on whole words), takes the prefix sums of the
-// words' counts -- the position of every pixel in the ascending list -- and keeps the entries of its own tiles.  The
-// tiles are those of the stored list (same order, same partition), so results do not depend on which form is used.
-// What other kernels need is written by the workgroups in shares: the output mask (of a layer that truncates: its zeros at
-// the pixels that are not listed, so that a step depends on nothing an earlier one left) and, where the caller asked for it, the
-// ascending list and its length, and those of the input.
+// network of small maps took 12-20 us, half of it spent on lists).  Two ways out, both with the entries' results unchanged:
+//   local_build  a workgroup compacts blocks of pixels of its own.  Most kernels.
+//   self_build   a mask of 16 K pixels is 2 KB of bits, so a workgroup can hold ALL flags in LDS: it reads the input mask
+//                (one round trip of 16-byte loads), forms the flagged output pixels as bits (a 3x3 window on whole words) and
+//                takes the prefix sums of the words' counts -- the position of every pixel in the ascending list.  The plain
+//                convolution kernel, which keeps the entries of its own tiles; the list kernel (mask_kernels.hip); and the
+//                few workgroups that write what belongs to the whole map beside the first way.
+// Every workgroup of a layer's kernel went the second way once: 3-5 us of the 11-18 that such a kernel took.  Step, all of
+// them -> blocks: bottleneck block on one 128x128 stream 47.5 -> 41.1 us, 3x3 fp32 32->32 + ReLU on 64x64 21.7 -> 19.7, 8 streams
+// of a ResNet-50-shaped network 1450 -> 1250, HRNet-shaped 1306 -> 1126, MobileNet-shaped 512 -> 413 (half of the last from
+// runs of one batch, tail_shape).
 #pragma once
 
 #include "device_utils.h"
@@ -386,6 +389,134 @@ __device__ __forceinline__ void self_emit(const ListArgs& l, const SelfBits& s, 
         }
     }
     lds_block_sync();
+}
+
+// ---- blocks of pixels that a workgroup compacts for itself ----------------------------------------------------------------
+// A kernel does not need the map's list to know its work, only some cut of it.  Here the map is cut into blocks of 8 .. 32
+// pixels that are dealt to the workgroups in turn; a workgroup tests the windows of its own pixels (a byte per tap and lane,
+// one round trip), packs the flagged ones together in LDS and walks those.  No workgroup repeats another's work and none
+// waits for a scan of the map.  What belongs to the whole map -- the ascending list, its length, the input's list -- is
+// written by `writers` workgroups at the front of the grid that form all flags, beside the others and not ahead of them.
+// An output pixel's sums do not depend on its neighbours in a tile, so results are those of the stored list.
+
+// Window taps of output pixel p (windows up to 3x3), bit ky*k+kx, and bit 30: the second mask's flag.  All loads go out together.
+constexpr uint32_t kLocalSecond = 1u << 30;
+__device__ __forceinline__ uint32_t local_taps(const ListArgs& l, int p, bool live) {
+    const uint32_t pu = live ? (uint32_t)p : 0u;
+    const uint32_t t1 = fast_div(pu, l.div_ow);
+    const int ox = (int)pu - (int)t1 * l.m_ow;
+    const int n = (int)fast_div(t1, l.div_oh);
+    const int oy = (int)t1 - n * l.m_oh;
+    uint8_t fb = 0;
+    if (l.m_b != nullptr) fb = l.m_b[l.b_stride > 0 ? ((int64_t)n * l.b_h + oy * l.b_stride) * l.b_w + ox * l.b_stride : (int64_t)pu];
+    uint32_t taps = 0;
+    if (l.m_k == 1) {
+        const int iy = l.m_up > 1 ? (int)fast_div((uint32_t)oy, l.div_up) : oy * l.m_stride;
+        const int ix = l.m_up > 1 ? (int)fast_div((uint32_t)ox, l.div_up) : ox * l.m_stride;
+        taps = l.m_in[(n * l.m_h + iy) * l.m_w + ix] ? 1u : 0u;
+    } else {
+        const int iy0 = oy * l.m_stride - l.m_pad, ix0 = ox * l.m_stride - l.m_pad;
+        uint8_t f[9];
+        bool in[9];
+#pragma unroll
+        for (int t = 0; t < 9; ++t) {
+            const int iy = iy0 + t / 3, ix = ix0 + t % 3;
+            in[t] = t / 3 < l.m_k && t % 3 < l.m_k && (unsigned)iy < (unsigned)l.m_h && (unsigned)ix < (unsigned)l.m_w;
+            f[t] = l.m_in[in[t] ? (n * l.m_h + iy) * l.m_w + ix : 0];
+        }
+#pragma unroll
+        for (int t = 0; t < 9; ++t)
+            if (in[t] && f[t]) taps |= 1u << ((t / 3) * l.m_k + t % 3);
+    }
+    if (fb) taps |= kLocalSecond;
+    return live ? taps : 0u;
+}
+// The flags of a workgroup's own pixels that others read: the output mask, or its zeros where nothing is listed.
+__device__ __forceinline__ void local_mask(const ListArgs& l, int p, bool listed) {
+    if (l.mask_out != nullptr) l.mask_out[p] = listed ? 1 : 0;
+    if (l.mask_zero != nullptr && !listed) l.mask_zero[p] = 0;
+}
+// The flagged pixels of this workgroup's blocks -> px and tap words in LDS, padded with -1 / 0 to l.lds_entries; returns their
+// number.  Every thread of the workgroup (NT of them) calls it; ends with a barrier.
+template <int NT>
+__device__ __forceinline__ int local_build(const ListArgs& l, unsigned char* at, int32_t*& px, uint32_t*& taps) {
+    constexpr int NWV = NT / kWave;
+    int* red = reinterpret_cast<int*>(at);                     // 64 bytes
+    px = reinterpret_cast<int32_t*>(at + 64);
+    taps = reinterpret_cast<uint32_t*>(px + l.lds_entries);
+    const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+    const int owner = (int)blockIdx.x - l.writers, owners = (int)gridDim.x - l.writers;
+    int count = 0;
+    for (int s0 = 0; s0 < l.local_slots; s0 += NT) {
+        const int slot = s0 + tid;
+        const int p = ((owner + (slot >> l.local_shift) * owners) << l.local_shift) + (slot & ((1 << l.local_shift) - 1));
+        const bool live = slot < l.local_slots && p < l.m_out_px;
+        uint32_t t = 0;
+        if (s0 + wave * kWave < l.local_slots) t = local_taps(l, p, live);
+        const uint64_t hit = __ballot(t != 0);
+        if (live) local_mask(l, p, t != 0);
+        if (s0 > 0) lds_block_sync();                          // (the counts of the step before have been read)
+        if (lane == 0) red[wave] = __popcll(hit);
+        lds_block_sync();
+        int before = count;
+#pragma unroll
+        for (int i = 0; i < NWV; ++i) {
+            const int c = red[i];
+            if (i < wave) before += c;
+            count += c;
+        }
+        if (t != 0) {
+            const int j = before + __popcll(hit & ((1ull << lane) - 1ull));
+            px[j] = p;
+            taps[j] = t;
+        }
+    }
+    for (int j = count + tid; j < l.lds_entries; j += NT) { px[j] = -1; taps[j] = 0; }
+    lds_block_sync();
+    return count;
+}
+// What belongs to the whole map, by writer blockIdx.x of l.writers.
+template <int NT>
+__device__ __forceinline__ void local_write(const ListArgs& l, unsigned char* scratch) {
+    const SelfBits s = self_carve(l, scratch);
+    const int count = self_build<NT>(l, s);
+    const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+    const int share = blockIdx.x;
+    if (l.count_out != nullptr && share == 0 && tid == 0) *l.count_out = count;
+    if (l.idx_out != nullptr) {
+        // two words of flags per wave and step, a pixel per lane
+        const int per = (s.out_words + l.writers - 1) / l.writers, w_end = min((share + 1) * per, s.out_words);
+        for (int w0 = share * per + 2 * wave; w0 < w_end; w0 += 2 * NT / kWave) {
+            const int w = w0 + lane / 32;
+            if (w >= w_end) continue;
+            const uint32_t bits = s.obits[w];
+            if ((bits >> (lane & 31)) & 1u) l.idx_out[(int)s.prefix[w] + __popc(bits & ((1u << (lane & 31)) - 1u))] = w * 32 + (lane & 31);
+        }
+    }
+    if (l.in_idx_out != nullptr && share == 0) {
+        // consecutive words per thread, a scan over threads
+        constexpr int NWV = NT / kWave;
+        const int W = (s.in_words + NT - 1) / NT;
+        int mine = 0;
+        for (int i = 0; i < W; ++i)
+            if (tid * W + i < s.in_words) mine += __popc(s.ibits[tid * W + i]);
+        const int inc = self_scan(mine);
+        lds_block_sync();                                      // (self_build's sums have been read)
+        if (lane == kWave - 1) s.red[wave] = inc;
+        lds_block_sync();
+        int j = inc - mine, total = 0;
+        for (int i = 0; i < NWV; ++i) {
+            const int c = s.red[i];
+            if (i < wave) j += c;
+            total += c;
+        }
+        for (int i = 0; i < W; ++i) {
+            const int w = tid * W + i;
+            if (w < s.in_words)
+                for (uint32_t rest = s.ibits[w]; rest; rest &= rest - 1) l.in_idx_out[j++] = w * 32 + __builtin_ctz(rest);
+        }
+        if (tid == 0) *l.in_count_out = total;
+    }
 }
 
 }  // namespace dcnn

@@ -120,16 +120,18 @@ __device__ __forceinline__ uint32_t sparse_tile_tail(const EpilogueArgs& e, cons
 // How the entries of a tile are spread over waves and batches for a pixel of `nvec` vectors.
 struct TailShape {
     int lp;        // lanes per pixel
-    int run;       // consecutive tile entries per wave (8, 16 or 32)
+    int run;       // consecutive tile entries per wave (1 .. 32)
     int nbatch;    // batches of UB iterations per wave
 };
-inline TailShape tail_shape(int nvec, int vpl, int ub) {
+// A run is one batch: a second one starts behind the first one's stores, 3-4 us later.  (min_run = 8 where survivor words are
+// wanted, which waves fill by the byte.)
+inline TailShape tail_shape(int nvec, int vpl, int ub, int min_run) {
     TailShape s;
     int lp = 1;
     while (lp < (int)cdiv(nvec, vpl)) lp <<= 1;
     s.lp = lp < 2 ? 2 : (lp > kWave ? kWave : lp);
     const int per_batch = ub * (kWave / s.lp);                 // entries one batch covers
-    s.run = per_batch < 8 ? 8 : (per_batch > kTile ? kTile : per_batch);
+    s.run = per_batch < min_run ? min_run : (per_batch > kTile ? kTile : per_batch);
     s.nbatch = (int)cdiv(s.run, per_batch);
     return s;
 }

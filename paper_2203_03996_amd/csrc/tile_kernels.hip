@@ -9,7 +9,6 @@
 namespace dcnn {
 
 constexpr int kTileThreads = kTileWaves * kWave;
-constexpr int kSelfWgPerCu = 4;                     // workgroups per compute unit that each build the list: more repeat the work more often
 
 static int list_grid(const dcnn_ctx* ctx, int64_t max_count, int entries_per_wg, int wg_per_cu) {
     int64_t want = cdiv(max_count > 0 ? max_count : 1, entries_per_wg);
@@ -18,37 +17,40 @@ static int list_grid(const dcnn_ctx* ctx, int64_t max_count, int entries_per_wg,
     return (int)(cdiv(g, kXcd) * kXcd);
 }
 
-// Work lists built by the kernel itself (self_list.h), for the kernels of kTileThreads threads: the length of the list, and
-// the entries of this workgroup's groups.  SELF is a variant of its own: with both ways in one kernel the walk of a stored list
-// took 0.4-1 us longer a launch.
+// Blocks of pixels that the workgroup compacts itself (local_build), for the kernels of kTileThreads threads.  SELF is a variant of
+// its own: with both ways in one kernel the walk of a stored list took 0.4-1 us longer a launch.  tile_list_done: a writer, which
+// has no pixels.
 template <bool SELF>
-__device__ __forceinline__ int64_t tile_list_count(const ListParam<SELF>& l, unsigned char* smem, SelfBits& sb) {
+__device__ __forceinline__ bool tile_list_done(const ListParam<SELF>& l, unsigned char* smem) {
     if constexpr (SELF) {
-        sb = self_carve(l, smem + l.lds_scratch);
-        return self_build<kTileThreads>(l, sb);
-    } else {
-        return list_count(l);
+        if ((int)blockIdx.x < l.writers) {
+            local_write<kTileThreads>(l, smem);
+            return true;
+        }
     }
+    return false;
 }
+struct LocalList { int32_t* px; uint32_t* taps; };
 template <bool SELF>
-__device__ __forceinline__ const int32_t* tile_list_emit(const ListParam<SELF>& l, unsigned char* smem, const SelfBits& sb, int64_t count,
-                                                         int64_t begin, int64_t end, int64_t step, int entries) {
-    if constexpr (SELF) {
-        int32_t* px = reinterpret_cast<int32_t*>(smem + l.lds_list);
-        self_emit<kTileThreads>(l, sb, (int)count, SelfSpan{(int)begin, (int)end, (int)step, entries}, px, nullptr);
-        return px;
-    } else {
-        return nullptr;
-    }
+__device__ __forceinline__ int64_t tile_list_count(const ListParam<SELF>& l, unsigned char* smem, LocalList& own) {
+    if constexpr (SELF) return local_build<kTileThreads>(l, smem + l.lds_list, own.px, own.taps);
+    else return list_count(l);
 }
-// Dynamic LDS of such a launch behind `used` bytes of the kernel's own, and where the pieces lie.  `groups`: groups of `entries`
-// list entries that the kernel walks when every pixel is listed, counted by the kernel's own rule.
-static size_t tile_list_lds(ListArgs& l, size_t used, int64_t groups, int64_t entries, int grid, bool per_xcd) {
-    if (!l.self) return used;
-    l.lds_scratch = (int)align_up(used, 16);
-    l.lds_list = l.lds_scratch + (int)self_scratch_bytes(l.m_in_px, l.m_out_px);
-    l.lds_entries = (int)self_local_entries(groups * entries, entries, grid, per_xcd);
-    return (size_t)l.lds_list + (size_t)l.lds_entries * 4;
+// Blocks, grid and dynamic LDS of such a launch behind `used` bytes of the kernel's own (a writer uses the space from 0 on).  A
+// block is what the workgroup walks in one iteration, `group` entries if all are listed, or more on maps that would
+// have more than 2048 of them (16 K pixels in blocks of 8).
+static size_t tile_list_place(ListArgs& l, size_t used, int group, int* grid) {
+    int shift = 3;
+    while (shift < 5 && ((1 << shift) < group || cdiv(l.m_out_px, 1 << shift) > 2048)) ++shift;
+    const LocalShape s = local_shape(l.m_out_px, shift, INT32_MAX, group);
+    l.writers = local_writers(l);
+    l.local_shift = shift;
+    l.local_slots = s.slots;
+    l.lds_entries = s.entries;
+    l.lds_list = (int)align_up(used, 16);
+    *grid = s.owners + l.writers;
+    const size_t all = (size_t)l.lds_list + kLocalHeader + (size_t)s.entries * 8, scratch = self_scratch_bytes(l.m_in_px, l.m_out_px);
+    return all > scratch ? all : scratch;
 }
 
 template <typename T, int V, int VPL, int UB, bool SELF>
@@ -56,8 +58,9 @@ __global__ __launch_bounds__(kTileThreads) void act_sparse_kernel(ListParam<SELF
                                                                    uint32_t map_bytes, uint32_t pixels) {
     extern __shared__ __align__(16) unsigned char list_smem[];
     clear_ahead(e);
-    SelfBits sb;
-    const int64_t count = tile_list_count<SELF>(l, list_smem, sb);
+    if (tile_list_done<SELF>(l, list_smem)) return;
+    LocalList own{};
+    const int64_t count = tile_list_count<SELF>(l, list_smem, own);
     const int lane = threadIdx.x % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     TailRsrc rs;
@@ -68,20 +71,30 @@ __global__ __launch_bounds__(kTileThreads) void act_sparse_kernel(ListParam<SELF
     src.in = ws_rsrc(a.in_data, map_bytes);
     const int parts = kTile / shape.run;
     int survivors = 0;
-    const WgTileRange r = wg_tile_range(run_groups(count, shape.run));
-    const int32_t* self_px = tile_list_emit<SELF>(l, list_smem, sb, count, r.begin, r.end, r.step, kTileWaves * shape.run);
-    for (int64_t wt = r.begin; wt < r.end; wt += r.step, self_px += kTileWaves * shape.run) {
+    const int64_t groups = SELF ? (count + kTileWaves * shape.run - 1) / (kTileWaves * shape.run) : run_groups(count, shape.run);
+    const WgTileRange r = SELF ? WgTileRange{0, groups, 1} : wg_tile_range(groups);
+    for (int64_t wt = r.begin; wt < r.end; wt += r.step) {
         const int64_t unit = wt * kTileWaves + wave;
         const int64_t tile = unit / parts;
         const int part = (int)(unit - tile * parts);
         const int64_t base = tile * kTile;
-        if (base >= count) continue;
+        if ((SELF ? unit * shape.run : base) >= count) continue;
         const int j = lane % kTile;
-        const int p_mine = (j / shape.run == part) ? (SELF ? self_px[wave * shape.run + j % shape.run] : list_pixel(l.list, base + j, count)) : -1;
-        const int p_off = p_mine >= 0 ? p_mine : (int)kOob;
-        // a stream without a mask is flagged wherever the list points
-        const int rflag = e.res_mask ? __builtin_amdgcn_raw_buffer_load_b8(rs_rmask, p_off, 0, 0) : 1;
-        src.flag_mine = a.in_mask ? __builtin_amdgcn_raw_buffer_load_b8(rs_imask, p_off, 0, 0) : 1;
+        const bool mine = j / shape.run == part;
+        int p_mine = -1, rflag = 1;
+        if constexpr (SELF) {
+            const int at = (int)unit * shape.run + j % shape.run;
+            const uint32_t word = mine ? own.taps[at] : 0u;
+            if (mine) p_mine = own.px[at];
+            rflag = (word & kLocalSecond) != 0;
+            src.flag_mine = (int)(word & 1u);
+        } else {
+            if (mine) p_mine = list_pixel(l.list, base + j, count);
+            const int p_off = p_mine >= 0 ? p_mine : (int)kOob;
+            // a stream without a mask is flagged wherever the list points
+            if (e.res_mask) rflag = __builtin_amdgcn_raw_buffer_load_b8(rs_rmask, p_off, 0, 0);
+            src.flag_mine = a.in_mask ? __builtin_amdgcn_raw_buffer_load_b8(rs_imask, p_off, 0, 0) : 1;
+        }
         const uint32_t bits = sparse_tile_tail<T, V, VPL, UB>(e, rs, src, shape.lp, p_mine, rflag, part * shape.run,
                                                               (part + 1) * shape.run, shape.nbatch, lane);
         if (e.surv) { if (lane == 0) store_survivors(e.surv, tile, part, parts, bits); }
@@ -106,8 +119,9 @@ __global__ __launch_bounds__(kTileThreads) void act_wide_kernel(ListParam<SELF> 
     __shared__ float s_max[2][kWideRun][kTileWaves];
     extern __shared__ __align__(16) unsigned char list_smem[];
     clear_ahead(e);
-    SelfBits sb;
-    const int64_t count = tile_list_count<SELF>(l, list_smem, sb);
+    if (tile_list_done<SELF>(l, list_smem)) return;
+    LocalList own{};
+    const int64_t count = tile_list_count<SELF>(l, list_smem, own);
     const int lane = threadIdx.x % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const __amdgpu_buffer_rsrc_t rs_in = ws_rsrc(a.in_data, map_bytes), rs_res = ws_rsrc(e.res_data, map_bytes);
@@ -120,19 +134,26 @@ __global__ __launch_bounds__(kTileThreads) void act_wide_kernel(ListParam<SELF> 
     const bool stateful = e.act != DCNN_ACT_NONE;
     const bool has_res = e.res_data != nullptr;
     const float hi = act_hi(e.act);
-    const int64_t units = wide_groups(count);
+    const int64_t units = SELF ? (count + kWideRun - 1) / kWideRun : wide_groups(count);
     int survivors = 0;
     int parity = 0;
-    const int32_t* self_px = tile_list_emit<SELF>(l, list_smem, sb, count, blockIdx.x, units, gridDim.x, kWideRun);
-    for (int64_t unit = blockIdx.x; unit < units; unit += gridDim.x, parity ^= 1, self_px += kWideRun) {
+    for (int64_t unit = SELF ? 0 : blockIdx.x; unit < units; unit += SELF ? 1 : gridDim.x, parity ^= 1) {
         const int64_t tile = unit / (kTile / kWideRun);
         const int part = (int)(unit - tile * (kTile / kWideRun));
         const int64_t base = tile * kTile + part * kWideRun;
         // entry lane % 8 of the run: pixel and the update flags of both streams (one round trip for the run)
-        const int p_mine = SELF ? self_px[lane % kWideRun] : list_pixel(l.list, base + lane % kWideRun, count);
-        const int p_off = p_mine >= 0 ? p_mine : (int)kOob;
-        const int rflag_mine = e.res_mask ? __builtin_amdgcn_raw_buffer_load_b8(rs_rmask, p_off, 0, 0) : 1;
-        const int iflag_mine = a.in_mask ? __builtin_amdgcn_raw_buffer_load_b8(rs_imask, p_off, 0, 0) : 1;
+        int p_mine, rflag_mine = 1, iflag_mine = 1;
+        if constexpr (SELF) {
+            const int at = (int)unit * kWideRun + lane % kWideRun;
+            p_mine = own.px[at];
+            rflag_mine = (own.taps[at] & kLocalSecond) != 0;
+            iflag_mine = (int)(own.taps[at] & 1u);
+        } else {
+            p_mine = list_pixel(l.list, base + lane % kWideRun, count);
+            const int p_off = p_mine >= 0 ? p_mine : (int)kOob;
+            if (e.res_mask) rflag_mine = __builtin_amdgcn_raw_buffer_load_b8(rs_rmask, p_off, 0, 0);
+            if (a.in_mask) iflag_mine = __builtin_amdgcn_raw_buffer_load_b8(rs_imask, p_off, 0, 0);
+        }
         int pix[kWideRun];
         uint32_t off[kWideRun][VPW];
         Raw rd[kWideRun][VPW], rr[kWideRun][VPW], ra[kWideRun][VPW], rt[kWideRun][VPW];
@@ -322,12 +343,10 @@ static dcnn_status launch_act_t(dcnn_ctx* ctx, bool init, const ListArgs& l_in, 
     if (vec && nvec >= 2 * kWave && nvec % kTileWaves == 0 && nvec <= kWave * kTileWaves && map_bytes > 0 &&
         map_bytes <= kWsMaxBytes && l.max_count <= 65536) {
         const int64_t units = wide_groups(l.max_count);
-        // (two fit a compute unit, and in place each builds the list: beyond that they built it again and again.  16 K pixels of 1024
-        // channels, 3 / 30 / 100 % listed: 32 / 66 / 100 us with eight, 15.5 / 50 / 80 on a stored list, now 13.5 / 49 / 76.)
-        const int64_t cap = (int64_t)ctx->num_cu * (l.self ? 2 : 8);
-        const int wgrid = (int)(units < cap ? units : cap);
+        const int64_t cap = (int64_t)ctx->num_cu * 8;
+        int wgrid = (int)(units < cap ? units : cap);
         const uint32_t mb = (uint32_t)map_bytes, px = (uint32_t)l.max_count;
-        const size_t lds = tile_list_lds(l, 0, wide_groups(l.max_count), kWideRun, wgrid, false);
+        const size_t lds = l.self ? tile_list_place(l, 0, kWideRun, &wgrid) : 0;
         if (l.self) hipLaunchKernelGGL((act_wide_kernel<T, VEC, 1, true>), dim3(wgrid), dim3(kTileThreads), lds, ctx->stream, l, a, e, mb, px);
         else hipLaunchKernelGGL((act_wide_kernel<T, VEC, 1, false>), dim3(wgrid), dim3(kTileThreads), lds, ctx->stream, l, a, e, mb, px);
         return check_hip(ctx, hipGetLastError(), "act_wide_kernel launch");
@@ -335,10 +354,10 @@ static dcnn_status launch_act_t(dcnn_ctx* ctx, bool init, const ListArgs& l_in, 
     if (vec && vpl <= 4 && map_bytes > 0 && map_bytes <= kWsMaxBytes) {
         const int vpl_used = vpl <= 1 ? 1 : (vpl <= 2 ? 2 : 4);
         const int ub = vpl_used == 4 ? 2 : 4;
-        const TailShape shape = tail_shape(nvec, vpl_used, ub);
-        const int sgrid = list_grid(ctx, l.max_count, kTileWaves * shape.run, l.self ? kSelfWgPerCu : 8);
+        const TailShape shape = tail_shape(nvec, vpl_used, ub, e.surv ? 8 : 1);
+        int sgrid = list_grid(ctx, l.max_count, kTileWaves * shape.run, 8);
         const uint32_t mb = (uint32_t)map_bytes, px = (uint32_t)l.max_count;
-        const size_t lds = tile_list_lds(l, 0, run_groups(l.max_count, shape.run), kTileWaves * shape.run, sgrid, true);
+        const size_t lds = l.self ? tile_list_place(l, 0, kTileWaves * shape.run, &sgrid) : 0;
 #define DCNN_ACT_SPARSE_S(VPL, UB, S) hipLaunchKernelGGL((act_sparse_kernel<T, VEC, VPL, UB, S>), dim3(sgrid), dim3(kTileThreads), lds, ctx->stream, l, a, e, shape, mb, px)
 #define DCNN_ACT_SPARSE(VPL, UB) do { if (l.self) DCNN_ACT_SPARSE_S(VPL, UB, true); else DCNN_ACT_SPARSE_S(VPL, UB, false); } while (0)
         if (vpl_used == 1) DCNN_ACT_SPARSE(1, 4);
@@ -375,7 +394,7 @@ bool dwconv_self_fits(int dtype, int k, int channels, int64_t in_px, int64_t out
     const size_t es = dtype_size(dtype), w_bytes = (size_t)k * k * channels * es;
     return k >= 1 && k <= 3 && channels % vec == 0 && cdiv(channels / vec, kWave) <= 4 &&
            (uint64_t)(in_px > out_px ? in_px : out_px) * channels * es <= kWsMaxBytes &&
-           w_bytes + self_scratch_bytes(in_px, out_px) + 8 * 1024 <= 64 * 1024;
+           w_bytes + 8 * 1024 <= 64 * 1024 && self_scratch_bytes(in_px, out_px) <= 64 * 1024;
 }
 
 dcnn_status launch_act(dcnn_ctx* ctx, int dtype, bool init, const ListArgs& l, const ActArgs& a, const EpilogueArgs& e) {
@@ -434,14 +453,20 @@ __global__ __launch_bounds__(kTileThreads) void dwconv_sparse_kernel(ListParam<S
     typedef typename RawOf<T, V>::type Raw;
     extern __shared__ __align__(16) unsigned char dw_smem[];
     T* w_lds = reinterpret_cast<T*>(dw_smem);
+    if (tile_list_done<SELF>(l, dw_smem)) return;
+    LocalList own{};
+    int64_t count = 0;
+    if constexpr (SELF) {
+        count = tile_list_count<SELF>(l, dw_smem, own);
+        if (count == 0) return;                                // (nothing listed among this workgroup's pixels: no weights)
+    }
     {
         const Raw* wsrc = static_cast<const Raw*>(c.wpacked);      // [k][k][C], unpacked
         const int nv = KS * KS * e.c / V;
         for (int i = threadIdx.x; i < nv; i += kTileThreads) reinterpret_cast<Raw*>(w_lds)[i] = wsrc[i];
     }
     __syncthreads();
-    SelfBits sb;
-    const int64_t count = tile_list_count<SELF>(l, dw_smem, sb);
+    if constexpr (!SELF) count = list_count(l);
     const int lane = threadIdx.x % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     TailRsrc rs;
@@ -453,17 +478,26 @@ __global__ __launch_bounds__(kTileThreads) void dwconv_sparse_kernel(ListParam<S
     src.w_lds = w_lds; src.C = e.c; src.w = c.w; src.row_bytes = (uint32_t)e.c * (uint32_t)sizeof(T);
     const int parts = kTile / shape.run;
     int survivors = 0;
-    const WgTileRange r = wg_tile_range(run_groups(count, shape.run));
-    const int32_t* self_px = tile_list_emit<SELF>(l, dw_smem, sb, count, r.begin, r.end, r.step, kTileWaves * shape.run);
-    for (int64_t wt = r.begin; wt < r.end; wt += r.step, self_px += kTileWaves * shape.run) {
+    const int64_t groups = SELF ? (count + kTileWaves * shape.run - 1) / (kTileWaves * shape.run) : run_groups(count, shape.run);
+    const WgTileRange r = SELF ? WgTileRange{0, groups, 1} : wg_tile_range(groups);
+    for (int64_t wt = r.begin; wt < r.end; wt += r.step) {
         const int64_t unit = wt * kTileWaves + wave;
         const int64_t tile = unit / parts;
         const int part = (int)(unit - tile * parts);
         const int64_t base = tile * kTile;
-        if (base >= count) continue;
+        if ((SELF ? unit * shape.run : base) >= count) continue;
         const int j = lane % kTile;
-        const int p_mine = (j / shape.run == part) ? (SELF ? self_px[wave * shape.run + j % shape.run] : list_pixel(l.list, base + j, count)) : -1;
-        const int rflag = e.res_mask ? __builtin_amdgcn_raw_buffer_load_b8(rs_rmask, p_mine >= 0 ? p_mine : (int)kOob, 0, 0) : 1;
+        const bool mine = j / shape.run == part;
+        int p_mine = -1, rflag = 1;
+        uint32_t own_word = 0;
+        if constexpr (SELF) {
+            const int at = (int)unit * shape.run + j % shape.run;
+            if (mine) { p_mine = own.px[at]; own_word = own.taps[at]; }
+            rflag = (own_word & kLocalSecond) != 0;
+        } else {
+            if (mine) p_mine = list_pixel(l.list, base + j, count);
+            if (e.res_mask) rflag = __builtin_amdgcn_raw_buffer_load_b8(rs_rmask, p_mine >= 0 ? p_mine : (int)kOob, 0, 0);
+        }
         // tap word of this lane's entry: all flags of the window requested together
         uint32_t word = 0;
         int q_first = 0;
@@ -474,6 +508,9 @@ __global__ __launch_bounds__(kTileThreads) void dwconv_sparse_kernel(ListParam<S
             const int oy = t % c.oh, n = t / c.oh;
             const int iy0 = oy * c.stride - c.pad, ix0 = ox * c.stride - c.pad;
             q_first = (n * c.h + iy0) * c.w + ix0;
+            if constexpr (SELF) {
+                word = own_word & ((1u << (KS * KS)) - 1u);
+            } else {
             uint32_t f[KS * KS];
 #pragma unroll
             for (int t2 = 0; t2 < KS * KS; ++t2) {
@@ -485,6 +522,7 @@ __global__ __launch_bounds__(kTileThreads) void dwconv_sparse_kernel(ListParam<S
             }
 #pragma unroll
             for (int t2 = 0; t2 < KS * KS; ++t2) word |= f[t2] ? (1u << t2) : 0u;
+            }
         }
         src.word_mine = (int)word; src.q_mine = q_first;
         const uint32_t bits = sparse_tile_tail<T, V, VPL, UB>(e, rs, src, shape.lp, p_mine, rflag, part * shape.run,
@@ -659,9 +697,9 @@ static dcnn_status launch_dwconv_t(dcnn_ctx* ctx, bool init, const ListArgs& l_i
         // (nine taps per pixel and vector: half the iterations in flight, or the registers leave one wave per SIMD.  8 streams,
         // 192 channels on 100 K pixels 31 -> 18.5 us, on 25 K 21.4 -> 19.3, 384 on 6 K 34 -> 24.6)
         const int ub = c.k == 3 ? (vpl_used == 1 ? 2 : 1) : 4 / vpl_used;
-        const TailShape shape = tail_shape(nvec, vpl_used, ub);
-        const int sgrid = list_grid(ctx, l.max_count, kTileWaves * shape.run, l.self ? kSelfWgPerCu : 8);
-        const size_t lds = tile_list_lds(l, w_bytes, run_groups(l.max_count, shape.run), kTileWaves * shape.run, sgrid, true);
+        const TailShape shape = tail_shape(nvec, vpl_used, ub, e.surv ? 8 : 1);
+        int sgrid = list_grid(ctx, l.max_count, kTileWaves * shape.run, 8);
+        const size_t lds = l.self ? tile_list_place(l, w_bytes, kTileWaves * shape.run, &sgrid) : w_bytes;
         const uint32_t ib = (uint32_t)in_bytes, ip = (uint32_t)in_pixels, mb = (uint32_t)map_bytes, px = (uint32_t)l.max_count;
 #define DCNN_DW_SPARSE_S(VPL, UB, KS, S) hipLaunchKernelGGL((dwconv_sparse_kernel<T, VEC, VPL, UB, KS, S>), dim3(sgrid), dim3(kTileThreads), lds, ctx->stream, l, c, e, shape, ib, ip, mb, px)
 #define DCNN_DW_SPARSE(VPL, UB, KS) do { if (l.self) DCNN_DW_SPARSE_S(VPL, UB, KS, true); else DCNN_DW_SPARSE_S(VPL, UB, KS, false); } while (0)
@@ -909,24 +947,21 @@ constexpr int kUpRun = 32;
 template <typename T, int V, bool SELF = false>
 __global__ __launch_bounds__(256) void upsample_kernel(ListParam<SELF> l, UpsampleArgs a) {
     extern __shared__ __align__(16) unsigned char list_smem[];
-    SelfBits sb;
-    const int64_t count = tile_list_count<SELF>(l, list_smem, sb);
+    if (tile_list_done<SELF>(l, list_smem)) return;
+    LocalList own{};
+    const int64_t count = tile_list_count<SELF>(l, list_smem, own);
     const int C = a.c;
     const int nvec = (C + V - 1) / V;
     const T* in = static_cast<const T*>(a.in_data);
     T* out = static_cast<T*>(a.out_data);
     const int ow = a.w * a.factor, oh = a.h * a.factor;
     if constexpr (SELF) {
-        // nearest, on a list built here: groups of kUpRun entries, strided over the grid, their pixels in LDS.  Indexes fit 32 bits
-        // and the map's divisors are known (2x, 256 channels, all of 768 output pixels: 9.7 us with 64-bit divisions, now 8.3).
+        // nearest, the pixels of this workgroup's block.  Indexes fit 32 bits and the map's divisors are known (2x, 256 channels, all of
+        // 768 output pixels: 9.7 us with 64-bit divisions, now 8.3).
         typedef typename RawOf<T, V>::type Raw;
-        const int groups = ((int)count + kUpRun - 1) / kUpRun;
-        const int32_t* px = tile_list_emit<SELF>(l, list_smem, sb, count, blockIdx.x, groups, gridDim.x, kUpRun);
-        const int mine = (int)blockIdx.x < groups ? (groups - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x * kUpRun : 0;
-        for (uint32_t i = threadIdx.x; i < (uint32_t)mine * (uint32_t)nvec; i += blockDim.x) {
+        for (uint32_t i = threadIdx.x; i < (uint32_t)count * (uint32_t)nvec; i += blockDim.x) {
             const uint32_t j = i / (uint32_t)nvec, vi = i - j * (uint32_t)nvec;
-            const int p = px[j];
-            if (p < 0) continue;                               // past the end of the list
+            const int p = own.px[j];
             const uint32_t t1 = fast_div((uint32_t)p, l.div_ow), n = fast_div(t1, l.div_oh);
             const uint32_t ix = fast_div((uint32_t)p - t1 * (uint32_t)ow, l.div_up), iy = fast_div(t1 - n * (uint32_t)oh, l.div_up);
             const int64_t q = ((int64_t)n * a.h + iy) * a.w + ix;
@@ -1081,9 +1116,8 @@ dcnn_status launch_maxpool_commit(dcnn_ctx* ctx, int dtype, const ListArgs& l, c
 dcnn_status launch_upsample(dcnn_ctx* ctx, int dtype, const ListArgs& l_in, const UpsampleArgs& a) {
     ListArgs l = l_in;
     if (l.self) {
-        const int64_t want = cdiv(l.max_count, kUpRun), cap = (int64_t)ctx->num_cu * kSelfWgPerCu;
-        const int grid = (int)(want < cap ? want : cap);
-        const size_t lds = tile_list_lds(l, 0, cdiv(l.max_count, kUpRun), kUpRun, grid, false);
+        int grid = 0;
+        const size_t lds = tile_list_place(l, 0, kUpRun, &grid);
         const bool vec = a.c % (dtype == DCNN_F16 ? 8 : 4) == 0;
 #define DCNN_UP_SELF(T, V) hipLaunchKernelGGL((upsample_kernel<T, V, true>), dim3(grid), dim3(256), lds, ctx->stream, l, a)
         if (dtype == DCNN_F16) { if (vec) DCNN_UP_SELF(f16, 8); else DCNN_UP_SELF(f16, 1); }
