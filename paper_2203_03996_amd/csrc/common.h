@@ -123,6 +123,7 @@ struct EpilogueArgs {
                                  // few thousand of them at the end of a kernel cost 10-20 us (see dcnn_layer_step)
     uint8_t* xt_flags;           // optional, per output pixel: 0 = the pixel's x^T row is all zero bits in memory and is
                                  // not read; 1 = it may hold values.  Kept up to date by the wave-specialised kernel only.
+                                 // First frame: rows whose flag is 0 are not cleared again (null: every row is).
     void* accum_O;               // fused final accumulation: dense output O (output shape); the emitted delta is
                                  // added to it and not stored (sparse steps of layers with an activation only)
     int carry;                   // 1: an update leaves the rounding residue of x^A in x^T (s - round(s)) instead of 0
@@ -171,6 +172,7 @@ constexpr int64_t kListMaxPixels = 65536;    // mask_list_kernel: input and outp
 // four-resolution network: activation on 55 K pixels 16.1 us against 15.6 in two launches, on 13.8 K 11.8 against 19.6;
 // upsampling 20.0 against 11.5 and 9.0 against 15.1; a 1x1 layer on 32 K pixels of 256 channels 19.8 against 16.4.)
 constexpr int64_t kSelfMaxPixels = 16384;
+constexpr int64_t kLocalMaxPixels = kListMaxPixels;
 inline size_t self_scratch_bytes(int64_t in_px, int64_t out_px) {
     return align_up(128 + 4 * (size_t)(2 * cdiv(in_px, 32) + cdiv(out_px, 32)) + 2 * (size_t)cdiv(out_px, 32), 16);
 }

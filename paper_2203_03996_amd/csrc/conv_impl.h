@@ -477,8 +477,8 @@ static dcnn_status launch_conv_nb(dcnn_ctx* ctx, bool init, const ListArgs& l_in
     auto place_local = [&](size_t total, size_t shared, int group, int64_t cap_wgs, int* g) -> size_t {
         if (!l.self) return total;
         l.writers = local_writers(l);
-        const LocalShape s = local_shape(l.m_out_px, kLocalTileShift, cap_wgs - l.writers, group);
-        l.local_shift = kLocalTileShift;
+        l.local_shift = conv_local_shift(l.m_out_px, cap_wgs);
+        const LocalShape s = local_shape(l.m_out_px, l.local_shift, cap_wgs - l.writers, group);
         l.local_slots = s.slots;
         l.lds_entries = s.entries;
         l.lds_scratch = (int)shared;

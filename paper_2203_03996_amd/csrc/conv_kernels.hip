@@ -90,10 +90,6 @@ bool conv_self_fits(const dcnn_ctx* ctx, int dtype, int k, int stride, int cin, 
                     int64_t out_px, bool want_taps) {
     const ConvPlan p = conv_plan(dtype, k, cin, cout, fused);
     if (!p.ok) return false;
-    // A strided 1x1 window tests its outputs one by one, and the kernels of streamed weights have 256 threads for it.  1x1 stride 2
-    // 256->256, a tenth of the input flagged, list in place against a stored one: on 2 K input pixels 8.8 us and 9.3, on 4 K 11.3 and
-    // 9.7, on 6 K 14.8 and 10.0, on 16 K 17.6 and 11.8.
-    if (p.stream && k == 1 && stride == 2 && in_px >= 4096) return false;
     const size_t scratch = self_scratch_bytes(in_px, out_px);
     const int64_t cus = ctx->num_cu;
     auto fits = [&](size_t own, size_t shared, int64_t group, int64_t grid_cap) {
@@ -103,12 +99,15 @@ bool conv_self_fits(const dcnn_ctx* ctx, int dtype, int k, int stride, int cin, 
         return at + (size_t)self_local_entries(out_px, group, grid, true) * (want_taps ? 8 : 4) <= kLdsBytes;
     };
     auto local_fits = [&](size_t own, size_t shared, int group, int64_t cap) {
-        const LocalShape s = local_shape(out_px, kLocalTileShift, cap - 8, group);
+        const LocalShape s = local_shape(out_px, conv_local_shift(out_px, cap), cap - 8, group);
         return align_up(own, 16) + kLocalHeader + (size_t)s.entries * 8 <= kLdsBytes && shared + scratch <= kLdsBytes;
     };
     const size_t ws_lds = conv_ws_lds_bytes(p, dtype, k, cout, cin2);
     const size_t ws_w = p.w_bytes + (size_t)cdiv(cin2, dtype == DCNN_F16 ? 16 : 8) * 2 * p.cout_pad * 16;
-    if (ws_lds != 0 && !local_fits(ws_lds, ws_w, (kWsProducers / p.cs) * kTile, cus)) return false;
+    const bool ws = ws_lds != 0 && ((size_t)cin * dtype_size(dtype)) % 16 == 0;
+    if (ws && !local_fits(ws_lds, ws_w, (kWsProducers / p.cs) * kTile, cus)) return false;
+    if (out_px > kSelfMaxPixels) return ws;
+    if (in_px > kSelfMaxPixels) return ws || (p.stream && ((size_t)cin * dtype_size(dtype)) % 16 == 0 && cout % (dtype == DCNN_F16 ? 8 : 4) == 0 && (k == 1 || k == 3));
     const size_t direct_lds = conv_stage_bytes(kDirectWaves, p.nb, dtype) + conv_xchg_bytes(kDirectWaves);
     if (!local_fits(direct_lds, 0, (kDirectWaves / p.cs) * kTile, 2 * cus)) return false;
     return fits(p.lds_bytes, p.stream ? 0 : p.w_bytes, (p.waves / p.cs) * kTile, cus);

@@ -7,7 +7,9 @@
 namespace dcnn {
 
 constexpr int kStagePad = 16;                       // bytes added to a staging row against bank conflicts
-constexpr int kLocalTileShift = 5;                  // blocks that a convolution's workgroups compact: as many pixels as a tile has
+// Blocks that a convolution's workgroups compact: as many pixels as a tile has; 8 where a workgroup gets several, so that listed
+// regions spread evenly.
+inline int conv_local_shift(int64_t out_px, int64_t owners) { return cdiv(out_px, kTile) <= owners - 8 ? 5 : 3; }
 constexpr int kGroup = 4;                           // K-steps per streamed weight slice
 constexpr size_t kLdsBytes = 160 * 1024;            // LDS of one gfx950 compute unit; the context refuses less
 

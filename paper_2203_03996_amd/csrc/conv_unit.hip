@@ -12,6 +12,7 @@
 // a tail done by the last of a tile to arrive were built: the device-scope release and acquire that it takes cost
 // ~15 us a layer, 3x3 256->256 44 us against 32 in one workgroup.)
 #include "conv_plan.h"
+#include "conv_ws_impl.h"
 #include "self_list.h"
 
 namespace dcnn {
@@ -213,7 +214,7 @@ static int64_t unit_limit(const dcnn_ctx* ctx, const ConvArgs& c, const ConvPlan
 bool conv_unit_supported(const dcnn_ctx* ctx, int dtype, const ListArgs& l, const ConvArgs& c, const EpilogueArgs& e, const ConvPlan& p) {
     const size_t es = dtype_size(dtype);
     const int vec = dtype == DCNN_F16 ? 8 : 4;
-    if (!p.stream || p.flat || (c.k != 1 && c.k != 3) || e.c % vec != 0 || ((size_t)c.cin * es) % 16 != 0) return false;
+    if ((!p.stream && conv_ws_lds_bytes(p, dtype, c.k, e.c) != 0) || p.flat || (c.k != 1 && c.k != 3) || e.c % vec != 0 || ((size_t)c.cin * es) % 16 != 0) return false;
     if (e.act != DCNN_ACT_NONE || c.in2_data != nullptr || e.accum_O != nullptr || e.xt_flags != nullptr) return false;
     if (!l.self && l.taps == nullptr && !(c.k == 1 && c.stride == 1 && l.list != nullptr)) return false;
     const int64_t out_px = (int64_t)c.n * c.oh * c.ow;

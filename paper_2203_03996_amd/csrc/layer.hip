@@ -67,7 +67,7 @@ bool layer_lists_itself(const dcnn_ctx* ctx, const dcnn_layer_desc& d, bool walk
     int oh, ow, oc;
     if (out_shape(d, &oh, &ow, &oc) != DCNN_OK) return false;
     const int64_t in_px = (int64_t)d.n * d.h * d.w, out_px = (int64_t)d.n * oh * ow;
-    if (in_px > kSelfMaxPixels || out_px > kSelfMaxPixels) return false;
+    if (in_px > kLocalMaxPixels || out_px > kLocalMaxPixels) return false;
     // windows that work on whole words of flags (1x1, 3x3 with padding 1); any other is tested pixel by pixel and is
     // worth it on small maps only (with an activation, 5x5 32->32: in place on 576 pixels 24 us and on 2400 27, stored on 2600 30;
     // 7x7 8->8: in place on 1024 37, stored on 2025 44)
@@ -80,7 +80,7 @@ bool layer_lists_itself(const dcnn_ctx* ctx, const dcnn_layer_desc& d, bool walk
             return window() && conv_self_fits(ctx, d.dtype, d.kh, d.stride, d.c, oc, act, d.proj_c, in_px, out_px, own && (d.kh == 1 || d.kh == 3));
         case DCNN_DWCONV: return own && window() && dwconv_self_fits(d.dtype, d.kh, oc, in_px, out_px);
         case DCNN_ACT: return act_self_fits(d.dtype, oc, out_px);
-        case DCNN_UPSAMPLE: return d.factor > 1;
+        case DCNN_UPSAMPLE: return d.factor > 1 && out_px <= kSelfMaxPixels;
         default: return false;
     }
 }
@@ -183,7 +183,7 @@ static void carve(dcnn_layer* L, void* state) {
         // a stateless, mask-preserving layer (1x1 s1 conv without activation) forwards its input's
         // mask and index list; every other layer owns them
         L->alias_mask = !act && !own && (d.kind == DCNN_CONV || d.kind == DCNN_DWCONV);
-        if (L->alias_mask && L->out_pixels <= kSelfMaxPixels) {
+        if (L->alias_mask && L->out_pixels <= kLocalMaxPixels) {
             // (where such a layer's kernel builds the list, nobody has handed it one: it has room for its own)
             L->out_idx = static_cast<int32_t*>(cv.take((size_t)L->out_pixels * sizeof(int32_t)));
             L->out_count = static_cast<int32_t*>(cv.take(kAlign));

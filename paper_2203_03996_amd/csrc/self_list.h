@@ -479,9 +479,35 @@ __device__ __forceinline__ int local_build(const ListArgs& l, unsigned char* at,
 template <int NT>
 __device__ __forceinline__ void local_write(const ListArgs& l, unsigned char* scratch) {
     const SelfBits s = self_carve(l, scratch);
-    const int count = self_build<NT>(l, s);
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
     const int share = blockIdx.x;
+    if (l.idx_out == nullptr && l.in_idx_out == nullptr && l.m_k == 1 && l.m_stride == 1 && l.m_up == 1 && l.b_stride <= 0) {
+        // only the length is wanted and the flags are the masks': their sum, eight words a thread in flight
+        constexpr int NWV = NT / kWave;
+        const int whole = l.m_out_px / 32;
+        int sum = 0;
+#pragma unroll 8
+        for (int w = tid; w < whole; w += NT) {
+            uint32_t v = self_mask_word(l.m_in, w);
+            if (l.m_b != nullptr) v |= self_mask_word(l.m_b, w);
+            sum += __popc(v);
+        }
+        if (wave == NWV - 1 && l.m_out_px % 32 != 0) {
+            uint32_t v = self_mask_tail(l.m_in, l.m_out_px);
+            if (l.m_b != nullptr) v |= self_mask_tail(l.m_b, l.m_out_px);
+            if (lane == 0) sum += __popc(v);
+        }
+        sum = self_scan(sum);
+        if (lane == kWave - 1) s.red[wave] = sum;
+        lds_block_sync();
+        if (share == 0 && tid == 0 && l.count_out != nullptr) {
+            int total = 0;
+            for (int i = 0; i < NWV; ++i) total += s.red[i];
+            *l.count_out = total;
+        }
+        return;
+    }
+    const int count = self_build<NT>(l, s);
     if (l.count_out != nullptr && share == 0 && tid == 0) *l.count_out = count;
     if (l.idx_out != nullptr) {
         // two words of flags per wave and step, a pixel per lane

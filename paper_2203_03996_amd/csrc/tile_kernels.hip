@@ -37,11 +37,11 @@ __device__ __forceinline__ int64_t tile_list_count(const ListParam<SELF>& l, uns
     else return list_count(l);
 }
 // Blocks, grid and dynamic LDS of such a launch behind `used` bytes of the kernel's own (a writer uses the space from 0 on).  A
-// block is what the workgroup walks in one iteration, `group` entries if all are listed, or more on maps that would
-// have more than 2048 of them (16 K pixels in blocks of 8).
+// block is what the workgroup walks in one iteration, `group` entries if all are listed, or more on maps that would have more than
+// 1024 of them: four workgroups fit a compute unit.
 static size_t tile_list_place(ListArgs& l, size_t used, int group, int* grid) {
     int shift = 3;
-    while (shift < 5 && ((1 << shift) < group || cdiv(l.m_out_px, 1 << shift) > 2048)) ++shift;
+    while (shift < 6 && ((1 << shift) < (group < 32 ? group : 32) || cdiv(l.m_out_px, 1 << shift) > 1024)) ++shift;
     const LocalShape s = local_shape(l.m_out_px, shift, INT32_MAX, group);
     l.writers = local_writers(l);
     l.local_shift = shift;

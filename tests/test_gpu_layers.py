@@ -1251,3 +1251,50 @@ def test_tiles_of_short_lists_over_the_whole_chip(S, k, cin, cout, res, tiles):
     agree = to_np(out.mask) == want.mask
     for which, ref in ((0, ract.xA), (1, ract.xT)):
         assert rel_err(to_np(layer.state_tensor(which))[agree], ref[agree], slack=sl[agree]) <= TOL[S]
+
+
+@pytest.mark.parametrize("S,kind,k,stride,cin,cout,act,nhw", [
+    # one block of 32 pixels per workgroup, and one more than there are workgroups (blocks of 8, several each)
+    ("f16", "conv", 3, 1, 32, 32, "relu", (1, 88, 90)), ("f16", "conv", 3, 1, 32, 32, "relu", (1, 91, 91)),
+    # the largest map of each kind, ends inside a block and inside a word of flags
+    ("f16", "residual", 3, 1, 32, 32, "relu", (5, 113, 115)), ("f16", "conv", 3, 2, 32, 32, "relu6", (4, 127, 129)), ("f32", "projection", 1, 2, 32, 32, "relu", (4, 61, 63)),
+    ("f16", "add", 1, 1, 16, 16, "relu", (4, 127, 129)), ("f32", "add", 1, 1, 12, 12, "none", (2, 181, 181)), ("f16", "dwconv", 3, 1, 16, 16, "relu6", (4, 127, 129)),
+    ("f16", "dwconv", 3, 2, 24, 24, "none", (4, 127, 128)), ("f16", "add", 1, 1, 512, 512, "relu", (1, 127, 129)), ("f16", "upsample", 2, 1, 16, 16, "none", (1, 63, 65)),
+    # streamed weights and units: the largest outputs, and inputs beyond those that list themselves
+    ("f16", "conv", 3, 2, 128, 128, "relu", (4, 127, 127)), ("f16", "conv", 1, 2, 256, 512, "none", (2, 127, 127)), ("f16", "conv", 1, 1, 384, 96, "none", (3, 45, 47)),
+])
+def test_blocks_of_larger_maps_give_the_bits_of_a_stored_list(S, kind, k, stride, cin, cout, act, nhw):
+    """The same comparison where a workgroup compacts several blocks of pixels, up to the largest maps that take that way."""
+    test_lists_built_in_the_kernel_and_stored_ones_give_the_same_bits(S, kind, k, stride, cin, cout, act, nhw)
+
+
+@pytest.mark.parametrize("S,k,cin,cout,hw,act,residue", [("f16", 1, 64, 64, (40, 51), "relu", 0), ("f32", 3, 32, 32, (23, 29), "relu6", 1),
+                                                         ("f16", 3, 128, 64, (9, 7), "relu", 0), ("f16", 1, 32, 24, (33, 65), "relu", 1)])
+def test_second_first_frame_clears_every_truncated_row(S, k, cin, cout, hw, act, residue):
+    """A first frame after sparse steps (some of which leave values in x^T) gives the state of a layer that never saw them: the rows
+    that hold values are cleared, and the steps behind it are the same."""
+    rng = np.random.default_rng(cin + cout)
+    dt, n, (h, w) = NP_DTYPE[S], 2, hw
+    desc = pkg.make_desc(pkg.CONV, DT[S], n, h, w, cin, k=k, stride=1, pad=k // 2, cout=cout, act=pkg.ACT_CODES[act], eps=0.6, want_idx=0, xT_residue=residue)
+    wgt = torch.from_numpy((rng.standard_normal((k, k, cin, cout)) * np.sqrt(2.0 / (k * k * cin))).astype(dt)).cuda()
+    ctx = pkg.Context(n * h * w)
+    used, fresh, looked_at = (pkg.Layer(ctx, desc, wgt) for _ in range(3))
+    first, again = (torch.from_numpy(rng.standard_normal((n, h, w, cin)).astype(dt)).cuda() for _ in range(2))
+    deltas = [_upload(_rand_delta(rng, (n, h, w, cin), dens, S, 0.2)) for dens in (0.3, 0.05, 0.6, 0.2)]
+    for layer in (used, looked_at):
+        layer.init([first])
+        for d in deltas[:2]:
+            layer.step([d])
+    assert torch.count_nonzero(looked_at.state_tensor(1)) > 0
+    looked_at.state_tensor(1).fill_(1.0)                       # whoever has the buffer may write it
+    dense = [layer.init([again]) for layer in (used, fresh, looked_at)]
+    assert all(torch.equal(y, dense[1]) for y in dense) or dense[0] is None
+    for d in deltas[2:]:
+        views = [layer.step([d]) for layer in (used, fresh, looked_at)]
+        ctx.sync()
+        mask = to_np(views[1].mask)
+        for v in views:
+            assert np.array_equal(to_np(v.mask), mask) and np.array_equal(to_np(v.data)[mask == 1], to_np(views[1].data)[mask == 1])
+    used.init([first])
+    ctx.sync()
+    assert torch.count_nonzero(used.state_tensor(1)) == 0
