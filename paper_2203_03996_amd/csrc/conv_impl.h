@@ -27,13 +27,40 @@
 
 namespace dcnn {
 
+// 16 bytes of a pixel's channels from `ch` on, rows of any length from a vector on: one load at the row's own alignment, which the
+// last vector of a row ends with and is then moved down, so nothing outside the row is read.
+template <typename T>
+__device__ __forceinline__ typename Mma<T>::Vec row_vector(const T* ptr, bool ok, int ch, int cin, const T* zeros) {
+    typedef typename Mma<T>::Vec Vec;
+    constexpr int KP = Mma<T>::KPACK;
+    const int past = max(ch + KP - cin, 0);                    // elements behind the row's end
+    const T* at = ok ? ptr - past : zeros;
+    u32x4 w;
+    __builtin_memcpy(&w, at, 16);
+    if constexpr (sizeof(T) == 2) {
+        if (past & 4) { w[0] = w[2]; w[1] = w[3]; w[2] = w[3] = 0u; }
+        if (past & 2) { w[0] = w[1]; w[1] = w[2]; w[2] = w[3]; w[3] = 0u; }
+        if (past & 1) {
+            w[0] = __builtin_amdgcn_alignbit(w[1], w[0], 16); w[1] = __builtin_amdgcn_alignbit(w[2], w[1], 16);
+            w[2] = __builtin_amdgcn_alignbit(w[3], w[2], 16); w[3] >>= 16;
+        }
+    } else {
+        if (past & 2) { w[0] = w[2]; w[1] = w[3]; w[2] = w[3] = 0u; }
+        if (past & 1) { w[0] = w[1]; w[1] = w[2]; w[2] = w[3]; w[3] = 0u; }
+    }
+    return __builtin_bit_cast(Vec, w);
+}
+// How the plain kernel reads its input: rows of 16-byte aligned pixels, rows of any length, or value by value -- a flat (tap,
+// channel) dimension, or pixels narrower than a vector.  A kernel each: code that is not there is not fetched.
+enum { kRowsAny = 0, kRowsAligned = 1, kValues = 2 };
+
 #ifndef DCNN_CONV_BOUNDS
 #define DCNN_CONV_BOUNDS 512
 #endif
 // WMODE: where the weight operands come from -- 0 resident in LDS, 1 streamed through LDS in slices (8 waves in
 // lockstep), 2 loaded straight from global memory / L2 by each wave together with its gathers, several K-steps in
 // flight (short work lists on layers whose weights do not fit LDS; 4 waves of up to 512 registers).
-template <typename T, int NB, int V, bool ALIGNED, int WMODE, int KS>
+template <typename T, int NB, int V, int ROWS, int WMODE, int KS>
 __global__ __launch_bounds__(WMODE == 2 ? 256 : DCNN_CONV_BOUNDS) void conv_mfma_kernel(ListArgs l, ConvArgs c, EpilogueArgs e, int init,
                                                                  int npass, int cs, int pass_split) {
     typedef typename Mma<T>::Vec Vec;
@@ -41,26 +68,38 @@ __global__ __launch_bounds__(WMODE == 2 ? 256 : DCNN_CONV_BOUNDS) void conv_mfma
     constexpr int KP = Mma<T>::KPACK;
     constexpr int COLS = NB * 32;
     constexpr int GK = 4;                                      // K-steps whose gathers are in flight together
-    constexpr bool STREAM = WMODE == 1;
+    constexpr bool STREAM = WMODE == 1, ALIGNED = ROWS == kRowsAligned;
+    static_assert(ROWS != kValues || WMODE == 0, "value by value: resident weights");
     extern __shared__ __align__(16) unsigned char smem[];
     clear_ahead(e);
 
     const int nwaves = blockDim.x / kWave, nthreads = blockDim.x;
-    const int tiles_per_iter = nwaves / cs;
     constexpr int kThreads = WMODE == 2 ? 256 : DCNN_CONV_BOUNDS;   // (the launcher's block size)
-    const int32_t* self_px = reinterpret_cast<const int32_t*>(smem + l.lds_list);
+    const bool local = l.local_slots > 0;                      // blocks compacted here (windows up to 3x3), else a list of the map
+    int32_t* self_px = reinterpret_cast<int32_t*>(smem + l.lds_list);
+    uint32_t* self_tap = nullptr;
     int64_t count;
     SelfBits sb;
-    if (l.self) {
+    if (local) {
+        if ((int)blockIdx.x < l.writers) {
+            if (blockIdx.y == 0) local_write<kThreads>(l, smem + l.lds_scratch);
+            return;
+        }
+        count = local_build<kThreads>(l, smem + l.lds_list, self_px, self_tap);
+    } else if (l.self) {
         sb = self_carve(l, smem + l.lds_scratch);
         count = self_build<kThreads>(l, sb);
     } else {
         count = list_count(l);
     }
-    const WgTileRange r = wg_tile_range((count + tiles_per_iter * kTile - 1) / (tiles_per_iter * kTile));
-    if (l.self)
-        self_emit<kThreads>(l, sb, (int)count, SelfSpan{(int)r.begin, (int)r.end, (int)r.step, tiles_per_iter * kTile},
-                            const_cast<int32_t*>(self_px), nullptr);
+    // (streamed slices want all waves; otherwise a short list is spread over the grid, as in the wave-specialised kernel: 3x3 13->19 of
+    // 64x64 pixels ran on 16 compute units)
+    const uint32_t ntiles = (uint32_t)((count + kTile - 1) / kTile);
+    const int tiles_per_iter = WMODE != 0 ? nwaves / cs : local ? min(max((int)ntiles, 1), nwaves / cs) : ws_slots(ntiles, gridDim.x, nwaves / cs);
+    const int64_t groups = (count + tiles_per_iter * kTile - 1) / (tiles_per_iter * kTile);
+    const WgTileRange r = local ? WgTileRange{0, groups, 1} : wg_tile_range(groups);
+    if (l.self && !local)
+        self_emit<kThreads>(l, sb, (int)count, SelfSpan{(int)r.begin, (int)r.end, (int)r.step, tiles_per_iter * kTile}, self_px, nullptr);
     if (r.begin >= r.end) return;                              // nothing for this workgroup: skip the weight load
 
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
@@ -70,7 +109,7 @@ __global__ __launch_bounds__(WMODE == 2 ? 256 : DCNN_CONV_BOUNDS) void conv_mfma
     const int taps = ksz * ksz, kch = c.kch;
     // flat K (stems with very few channels, unaligned kernels only): the K loop sees ONE tap of kch K-steps whose
     // elements are (tap, channel) pairs; which window tap an element belongs to is looked up per element
-    const bool flat = !ALIGNED && c.flat != 0;
+    const bool flat = ROWS == kValues && c.flat != 0;
     const int ktaps = flat ? 1 : taps;
     const int ksteps = ktaps * kch;
     const bool full_tail = npass == 1;
@@ -90,16 +129,15 @@ __global__ __launch_bounds__(WMODE == 2 ? 256 : DCNN_CONV_BOUNDS) void conv_mfma
                                              (size_t)2 * nwaves * kTile * sizeof(float));
     if constexpr (WMODE == 0) {
         for (int i = threadIdx.x; i < w_vecs; i += nthreads) w_lds[i] = wglob[i];
-        if constexpr (!ALIGNED) {
-            if (flat) {
-                for (int j = threadIdx.x; j < taps * c.cin; j += nthreads) {
-                    const int tap = j / c.cin, ch = j - tap * c.cin;
-                    const int dy = tap / ksz, dx = tap - dy * ksz;
-                    flat_lut[j] = make_int2((dy * c.w + dx) * c.cin + ch, tap);
-                }
+        if constexpr (ROWS == kValues) {
+            for (int j = threadIdx.x; j < (flat ? taps : 1) * c.cin; j += nthreads) {
+                const int tap = j / c.cin, ch = j - tap * c.cin;
+                const int dy = tap / ksz, dx = tap - dy * ksz;
+                flat_lut[j] = make_int2((dy * c.w + dx) * c.cin + ch, tap);
             }
         }
         lds_block_sync();
+        if (slot >= tiles_per_iter) return;                    // (a slot that stays empty has helped with the weights)
     }
 
     // First frame: the bias joins the fp32 sum BEFORE its one rounding to the storage type (a convolution with
@@ -146,6 +184,13 @@ __global__ __launch_bounds__(WMODE == 2 ? 256 : DCNN_CONV_BOUNDS) void conv_mfma
         return l.self ? self_px[(round * tiles_per_iter + slot) * kTile + col]
                       : list_pixel(l.list, (wt_ * tiles_per_iter + slot) * kTile + col, count);
     };
+    // which taps an entry needs, where that came with it (windows up to 3x3)
+    const bool words = local || l.taps != nullptr;
+    auto tap_word = [&](int64_t wt_, int round) -> uint32_t {
+        const int64_t j = (wt_ * tiles_per_iter + slot) * kTile + col;
+        if (local) return self_tap[(round * tiles_per_iter + slot) * kTile + col] & 0x1ffu;
+        return j < count ? l.taps[j] & 0x1ffu : 0u;
+    };
     TileGeom g_next = geometry(entry(r.begin, 0));
     int p32_next2 = entry(r.begin + r.step, 1);
     int round = 0;
@@ -165,6 +210,8 @@ __global__ __launch_bounds__(WMODE == 2 ? 256 : DCNN_CONV_BOUNDS) void conv_mfma
 #pragma unroll
             for (int t = 0; t < KS * KS; ++t)
                 if (flag_next[t]) tapbits |= 1ull << t;
+        } else if (words) {
+            tapbits = tap_word(wt, round);
         } else {
             for (int t = 0, dy = 0, dx = 0; t < taps; ++t) {
                 bool ok = valid && (unsigned)(iy0 + dy) < (unsigned)c.h && (unsigned)(ix0 + dx) < (unsigned)c.w;
@@ -191,25 +238,25 @@ __global__ __launch_bounds__(WMODE == 2 ? 256 : DCNN_CONV_BOUNDS) void conv_mfma
         // 16 bytes of input channels per K-step for this lane's pixel; lanes that do not need the tap
         // (or whose channels are padding) read the zero page instead: no branches, no invalid reads
         auto gather_group = [&](const Cursor& cu, Vec (&x)[GK]) {
-            if constexpr (!ALIGNED) {
-                if (flat) {
-                    const T* first = in + (int64_t)q00 * c.cin;   // element of tap (0,0), channel 0; only used with a flagged tap
-                    const int nflat = taps * c.cin;
+            if constexpr (ROWS == kValues) {
+                // element of tap (0,0) -- or of the cursor's tap --, channel 0; only used with a flagged tap
+                const T* first = in + (int64_t)(flat ? q00 : q00 + cu.dy * c.w + cu.dx) * c.cin;
+                const int nflat = flat ? taps * c.cin : c.cin;
+                const uint64_t tb = flat ? tapbits : tapbits >> min(cu.t, 63);
 #pragma unroll
-                    for (int u = 0; u < GK; ++u) {
-                        Vec v;
+                for (int u = 0; u < GK; ++u) {
+                    Vec v;
 #pragma unroll
-                        for (int i = 0; i < KP; ++i) {
-                            const int j = (2 * (cu.kc0 + u) + g) * KP + i;
-                            const bool inside = cu.t < ktaps && cu.kc0 + u < kch && j < nflat;
-                            const int2 lt = flat_lut[inside ? j : 0];
-                            const bool ok = inside && ((tapbits >> lt.y) & 1);
-                            v[i] = ok ? first[lt.x] : (T)0.0f;
-                        }
-                        x[u] = v;
+                    for (int i = 0; i < KP; ++i) {
+                        const int j = (2 * (cu.kc0 + u) + g) * KP + i;
+                        const bool inside = cu.t < ktaps && cu.kc0 + u < kch && j < nflat;
+                        const int2 lt = flat_lut[inside ? j : 0];
+                        const bool ok = inside && ((tb >> lt.y) & 1);
+                        v[i] = ok ? first[lt.x] : (T)0.0f;
                     }
-                    return;
+                    x[u] = v;
                 }
+                return;
             }
             const bool tap_ok = cu.t < taps && ((tapbits >> cu.t) & 1);
             const T* src = in + (int64_t)(q00 + cu.dy * c.w + cu.dx) * c.cin;
@@ -221,10 +268,7 @@ __global__ __launch_bounds__(WMODE == 2 ? 256 : DCNN_CONV_BOUNDS) void conv_mfma
                 if constexpr (ALIGNED) {
                     x[u] = *reinterpret_cast<const Vec*>(ptr);
                 } else {
-                    Vec v;
-#pragma unroll
-                    for (int i = 0; i < KP; ++i) v[i] = (ok && ch + i < c.cin) ? ptr[i] : (T)0.0f;
-                    x[u] = v;
+                    x[u] = row_vector<T>(ptr, ok, ch, c.cin, zeros);
                 }
             }
         };
@@ -408,7 +452,7 @@ __global__ __launch_bounds__(WMODE == 2 ? 256 : DCNN_CONV_BOUNDS) void conv_mfma
             };
             const MaxExchange mx{xchg, cs, part};
             uint32_t bits;
-            const bool exchange = cs > 1 && full_tail && e.act != DCNN_ACT_NONE && !init;
+            const bool exchange = V > 1 && cs > 1 && full_tail && e.act != DCNN_ACT_NONE && !init;   // (one value per lane comes with one wave per tile)
             if constexpr (PREFETCH_TAIL) {
                 if (exchange) bits = tail_finish<T, V, NIT, true>(e, false, lane, dx, ch0, nch, mx, tl);
                 else bits = tail_finish<T, V, NIT, false>(e, init != 0, lane, dx, ch0, nch, mx, tl);
@@ -443,12 +487,15 @@ static dcnn_status launch_conv_nb(dcnn_ctx* ctx, bool init, const ListArgs& l_in
     const size_t lds_bytes = direct ? conv_stage_bytes(kDirectWaves, NB, sizeof(T) == 2 ? DCNN_F16 : DCNN_F32) + conv_xchg_bytes(kDirectWaves)
                                     : p.lds_bytes;
     const int tiles_per_iter = waves / p.cs;
-    int64_t want = cdiv(l.max_count > 0 ? l.max_count : 1, tiles_per_iter * kTile);
+    const bool resident = !p.stream && !direct;
+    int64_t want = cdiv(max_tiles, tiles_per_iter);
+    // (resident weights: a workgroup per compute unit before one gets a second tile)
+    if (resident && want < ctx->num_cu) want = max_tiles < ctx->num_cu ? max_tiles : ctx->num_cu;
     int64_t per_cu = (int64_t)(kLdsBytes / lds_bytes);
     per_cu = per_cu < 1 ? 1 : (per_cu > 4 ? 4 : per_cu);
     if (direct) per_cu = 2;
     int64_t cap = (int64_t)ctx->num_cu * per_cu;
-    const int grid = (int)(cdiv(want < cap ? want : cap, kXcd) * kXcd);
+    int grid = (int)(cdiv(want < cap ? want : cap, kXcd) * kXcd);
     // several passes and fewer workgroups than the chip holds: spread the passes over grid.y
     int ysplit = 1;
     if (p.npass > 1 && grid < cap) {
@@ -488,7 +535,10 @@ static dcnn_status launch_conv_nb(dcnn_ctx* ctx, bool init, const ListArgs& l_in
         return all > scratch_end ? all : scratch_end;
     };
     const size_t shared_weights = p.stream || direct ? 0 : p.w_bytes;
-    const size_t plain_lds = place_list(lds_bytes, shared_weights, tiles_per_iter * kTile, grid);
+    const bool values = !aligned && (p.flat || c.cin < VEC);
+    const size_t own_lds = lds_bytes + (values && !p.flat ? conv_flat_lut_bytes() : 0);
+    const size_t plain_lds = c.k <= 3 ? place_local(own_lds, shared_weights, tiles_per_iter * kTile, cap, &grid)
+                                      : place_list(own_lds, shared_weights, tiles_per_iter * kTile, grid);
 #define DCNN_CONV_LAUNCH(V, AL, WM, KS)                                                                          \
     do {                                                                                                         \
         auto kern = conv_mfma_kernel<T, NB, V, AL, WM, KS>;                                                      \
@@ -600,19 +650,22 @@ static dcnn_status launch_conv_nb(dcnn_ctx* ctx, bool init, const ListArgs& l_in
     // channels) is specialised on the window size; odd shapes take the generic-window kernels
     if (vec_out && aligned) {
         if (direct) {
-            if (c.k == 1) DCNN_CONV_LAUNCH(VEC, true, 2, 1);
-            else if (c.k == 3) DCNN_CONV_LAUNCH(VEC, true, 2, 3);
-            else DCNN_CONV_LAUNCH(VEC, true, 2, 0);
+            if (c.k == 1) DCNN_CONV_LAUNCH(VEC, kRowsAligned, 2, 1);
+            else if (c.k == 3) DCNN_CONV_LAUNCH(VEC, kRowsAligned, 2, 3);
+            else DCNN_CONV_LAUNCH(VEC, kRowsAligned, 2, 0);
         }
-        else if (p.stream) DCNN_CONV_LAUNCH(VEC, true, 1, 0);
-        else if (c.k == 1) DCNN_CONV_LAUNCH(VEC, true, 0, 1);
-        else if (c.k == 3) DCNN_CONV_LAUNCH(VEC, true, 0, 3);
-        else DCNN_CONV_LAUNCH(VEC, true, 0, 0);
-    } else if (vec_out && !p.stream) {
-        DCNN_CONV_LAUNCH(VEC, false, 0, 0);
-    } else if (!vec_out && !p.stream) {
+        else if (p.stream) DCNN_CONV_LAUNCH(VEC, kRowsAligned, 1, 0);
+        else if (c.k == 1) DCNN_CONV_LAUNCH(VEC, kRowsAligned, 0, 1);
+        else if (c.k == 3) DCNN_CONV_LAUNCH(VEC, kRowsAligned, 0, 3);
+        else DCNN_CONV_LAUNCH(VEC, kRowsAligned, 0, 0);
+    } else if (!p.stream) {
+        if (vec_out) { if (values) DCNN_CONV_LAUNCH(VEC, kValues, 0, 0); else DCNN_CONV_LAUNCH(VEC, kRowsAny, 0, 0); }
         if constexpr (NB <= 2) {
-            if (aligned) DCNN_CONV_LAUNCH(1, true, 0, 0); else DCNN_CONV_LAUNCH(1, false, 0, 0);
+            if (!vec_out) {
+                if (aligned) DCNN_CONV_LAUNCH(1, kRowsAligned, 0, 0);
+                else if (values) DCNN_CONV_LAUNCH(1, kValues, 0, 0);
+                else DCNN_CONV_LAUNCH(1, kRowsAny, 0, 0);
+            }
         }
     }
 #undef DCNN_CONV_LAUNCH

@@ -107,10 +107,10 @@ bool conv_self_fits(const dcnn_ctx* ctx, int dtype, int k, int stride, int cin, 
     const bool ws = ws_lds != 0 && ((size_t)cin * dtype_size(dtype)) % 16 == 0;
     if (ws && !local_fits(ws_lds, ws_w, (kWsProducers / p.cs) * kTile, cus)) return false;
     if (out_px > kSelfMaxPixels) return ws;
-    if (in_px > kSelfMaxPixels) return ws || (p.stream && ((size_t)cin * dtype_size(dtype)) % 16 == 0 && cout % (dtype == DCNN_F16 ? 8 : 4) == 0 && (k == 1 || k == 3));
-    const size_t direct_lds = conv_stage_bytes(kDirectWaves, p.nb, dtype) + conv_xchg_bytes(kDirectWaves);
-    if (!local_fits(direct_lds, 0, (kDirectWaves / p.cs) * kTile, 2 * cus)) return false;
-    return fits(p.lds_bytes, p.stream ? 0 : p.w_bytes, (p.waves / p.cs) * kTile, cus);
+    const size_t shared = p.stream ? 0 : p.w_bytes, plain = p.lds_bytes + (cin < (dtype == DCNN_F16 ? 8 : 4) && !p.flat ? conv_flat_lut_bytes() : 0);
+    const int group = (p.waves / p.cs) * kTile;
+    if (k <= 3) return local_fits(plain, shared, group, cus) && local_fits(plain, shared, group, 4 * cus);
+    return in_px <= kSelfMaxPixels && fits(p.lds_bytes, shared, group, cus);
 }
 
 size_t conv_proj_weight_bytes(int dtype, int k, int cin, int cin2, int cout) {
