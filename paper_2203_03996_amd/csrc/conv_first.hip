@@ -32,7 +32,7 @@ struct FirstArgs {
 
 template <typename T> constexpr int first_stage_stride(int channels) { return channels * (int)sizeof(T) + kStagePad; }
 
-template <typename T, int SPLIT, int TC>
+template <typename T, int SPLIT, int TC, bool XT>
 __global__ __launch_bounds__(kFirstWaves* kWave, 2) void conv_first_kernel(ConvArgs c, EpilogueArgs e, FirstArgs f) {
     typedef typename Mma<T>::Vec Vec;
     constexpr int V = Elem<T>::VEC;
@@ -64,6 +64,10 @@ __global__ __launch_bounds__(kFirstWaves* kWave, 2) void conv_first_kernel(ConvA
     const int ch0 = ct * kFirstCh;
     if (SPLIT == 1 && (px0 >= f.pixels || ch0 >= e.c)) return;   // (no workgroup barrier below in this case)
     const int cols = f.nb * 32;
+    // x^T row flags of the tile's pixels, one per lane: rows that hold zeros already are not written again
+    static_assert(kFirstPx == kWave, "a pixel's flag per lane");
+    int xt_row = 1;
+    if constexpr (XT) xt_row = e.xt_flags[px0 + lane < f.pixels ? px0 + lane : px0];
 
     // the lane's pixels: origin of their windows
     struct Px { int iy0, ix0; uint32_t base, base2; bool on; };
@@ -254,22 +258,24 @@ __global__ __launch_bounds__(kFirstWaves* kWave, 2) void conv_first_kernel(ConvA
     T* xA = static_cast<T*>(e.xA);
     T* xT = static_cast<T*>(e.xT);
     T* out = static_cast<T*>(e.out_data);
-    if (ch >= e.c) return;                                     // (channels are a multiple of V)
+    const bool ch_on = ch < e.c;                               // (channels are a multiple of V; the flags are handed on by all lanes)
     constexpr int HB = NIT < 8 ? NIT : 8;                      // residual rows requested together
 #pragma unroll
     for (int it0 = 0; it0 < NIT; it0 += HB) {
         Raw rr[HB];
+        int xt_on[HB];
 #pragma unroll
         for (int h = 0; h < HB; ++h) {
             const int64_t p = px0 + (it0 + h) * PPI + grp;
+            xt_on[h] = XT ? __shfl(xt_row, (it0 + h) * PPI + grp, kWave) : 1;
             rr[h] = raw_zero<T, V>();
-            if (res != nullptr && p < f.pixels) rr[h] = raw_load<T, V>(res + p * e.c + ch);
+            if (res != nullptr && p < f.pixels && ch_on) rr[h] = raw_load<T, V>(res + p * e.c + ch);
         }
 #pragma unroll
         for (int h = 0; h < HB; ++h) {
             const int row = (it0 + h) * PPI + grp;
             const int64_t p = px0 + row;
-            if (p >= f.pixels) continue;
+            if (p >= f.pixels || !ch_on) continue;
             const Raw d0 = raw_load<T, V>(reinterpret_cast<const T*>(stage + (size_t)row * stage_stride) + sub * V);
             Raw o_a = d0;
             if (res != nullptr) {
@@ -281,7 +287,7 @@ __global__ __launch_bounds__(kFirstWaves* kWave, 2) void conv_first_kernel(ConvA
             const int64_t off = p * e.c + ch;
             if (stateful) {
                 __builtin_nontemporal_store(o_a, reinterpret_cast<Raw*>(xA + off));
-                if (xT != nullptr) __builtin_nontemporal_store(raw_zero<T, V>(), reinterpret_cast<Raw*>(xT + off));
+                if (xT != nullptr && xt_on[h]) __builtin_nontemporal_store(raw_zero<T, V>(), reinterpret_cast<Raw*>(xT + off));
             }
             raw_store<T, V>(out + off, o_y);
         }
@@ -344,9 +350,9 @@ static dcnn_status launch_conv_first_t(dcnn_ctx* ctx, const ConvArgs& c, const E
     const int64_t grid = split ? cdiv(f.units, kXcd) * kXcd : cdiv(f.units / f.cgroups, kXcd) * kXcd * f.cgroups;
     if (grid > INT32_MAX) return fail(ctx, DCNN_ESHAPE, "first frame: %lld workgroups", (long long)grid);
     hipError_t err = hipSuccess;
-#define DCNN_FIRST_LAUNCH(SPLIT, TC)                                                                               \
+#define DCNN_FIRST_LAUNCH_X(SPLIT, TC, XT)                                                                               \
     do {                                                                                                         \
-        auto kern = conv_first_kernel<T, SPLIT, TC>;                                                                 \
+        auto kern = conv_first_kernel<T, SPLIT, TC, XT>;                                                                 \
         static bool attr_set = false;                                                                            \
         if (!attr_set) {                                                                                         \
             err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes); \
@@ -354,10 +360,12 @@ static dcnn_status launch_conv_first_t(dcnn_ctx* ctx, const ConvArgs& c, const E
         }                                                                                                        \
         if (err == hipSuccess) hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kFirstWaves * kWave), lds, ctx->stream, c, e, f); \
     } while (0)
+#define DCNN_FIRST_LAUNCH(SPLIT, TC) do { if (e.xt_flags) DCNN_FIRST_LAUNCH_X(SPLIT, TC, true); else DCNN_FIRST_LAUNCH_X(SPLIT, TC, false); } while (0)
     if (split) { if (narrow) DCNN_FIRST_LAUNCH(kFirstWaves, 1); else DCNN_FIRST_LAUNCH(kFirstWaves, 2); }
     else if (narrow) DCNN_FIRST_LAUNCH(1, 1);
     else DCNN_FIRST_LAUNCH(1, 2);
 #undef DCNN_FIRST_LAUNCH
+#undef DCNN_FIRST_LAUNCH_X
     if (err != hipSuccess) return check_hip(ctx, err, "hipFuncSetAttribute(conv_first_kernel)");
     return check_hip(ctx, hipGetLastError(), "conv_first_kernel launch");
 }
@@ -378,6 +386,7 @@ dcnn_status launch_conv_first(dcnn_ctx* ctx, int dtype, const ConvArgs& c_all, c
         c.in2_data = at(c.in2_data, (uint64_t)first * c.h2 * c.w2 * c.cin2 * es);
         e.res_data = at(e.res_data, out);
         e.xA = at_mut(e.xA, out); e.xT = at_mut(e.xT, out); e.out_data = at_mut(e.out_data, out);
+        if (e.xt_flags) e.xt_flags += (int64_t)first * c.oh * c.ow;
         const dcnn_status st = dtype == DCNN_F16 ? launch_conv_first_t<f16>(ctx, c, e, p, bias2) : launch_conv_first_t<float>(ctx, c, e, p, bias2);
         if (st != DCNN_OK) return st;
         first += c.n;

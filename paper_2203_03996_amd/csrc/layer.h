@@ -37,6 +37,12 @@ struct dcnn_layer {
                                         // sparse steps run on the wave-specialised kernel); nullptr: none
     bool counting = false, counted = false;   // statistics mode (dcnn_layer_set_counting); the last step was counted
     mutable bool xt_flags_stale = false;  // the state memory was handed out: the flags are rebuilt from x^T before the next step
+    // The row flags describe x^T as it lies in memory: a first frame has gone through and nobody outside can write x^T, so the next
+    // first frame clears the rows that hold values only.  From 64 MB of x^T on: there the stores count (64 streams of 128x128, 64 to 256
+    // channels, 134-537 MB a layer: first frame 906 -> 844 us when no row holds any), below it reading the flags and a clearing launch of
+    // their own do (layers of 4-16 MB, ResNet-50-shaped: 947 -> 959 us).
+    bool xt_flags_hold = false;
+    mutable bool xt_shared = false;       // x^T was handed out once (dcnn_layer_state): whoever has it may write it at any time
     void* wpacked;
     void* bias;
     void* wpacked2;                     // fused projection: weights in the main plan's column grouping
@@ -68,6 +74,10 @@ dcnn_status layer_init(dcnn_layer* L, const void* const* dense_in, int32_t n_in,
 // The pieces of the layer's state that are zero before its first sparse step: masks, counts, x^T row flags.
 constexpr int kMaxLayerClears = 5;
 int collect_clears(const dcnn_layer* L, bool with_flags, ClearPiece* out);
+constexpr size_t kXtSparseClear = 64ull << 20;
+inline bool clears_rows_by_flag(const dcnn_layer* L) { return L->xt_flags && !L->xt_shared && L->buf1_bytes >= kXtSparseClear; }
+// The row flags alone, of a layer whose first frame reads them: a network clears them behind its first frame.
+int collect_flag_clear(const dcnn_layer* L, ClearPiece* out);
 // Host-side bookkeeping that goes with cleared pieces.
 void sparse_output_cleared(dcnn_layer* L);
 }  // namespace dcnn

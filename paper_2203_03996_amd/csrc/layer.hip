@@ -238,8 +238,14 @@ int collect_clears(const dcnn_layer* L, bool with_flags, ClearPiece* out) {
     } else if (L->out_count) {
         out[n++] = {L->out_count, (kXtIoOffset + 4) * (int64_t)sizeof(int32_t)};
     }
-    if (with_flags && L->xt_flags) out[n++] = {L->xt_flags, L->out_pixels};
+    if (L->xt_flags && (with_flags || !clears_rows_by_flag(L))) out[n++] = {L->xt_flags, L->out_pixels};
     return n;
+}
+
+int collect_flag_clear(const dcnn_layer* L, ClearPiece* out) {
+    if (!clears_rows_by_flag(L)) return 0;
+    *out = {L->xt_flags, L->out_pixels};
+    return 1;
 }
 
 void sparse_output_cleared(dcnn_layer* L) { L->mask_phase = 0; }
@@ -487,6 +493,8 @@ dcnn_status dcnn::layer_init(dcnn_layer* L, const void* const* dense_in, int32_t
             e.c = L->oc; e.act = d.act; e.eps = d.eps; e.bias = L->has_bias ? L->bias : nullptr;
             e.res_data = (d.n_in == 2 && !has_proj(d)) ? dense_in[1] : nullptr; e.res_mask = nullptr;
             e.xA = L->buf0; e.xT = L->buf1; e.out_data = dense_out; e.out_mask = nullptr; e.surv = nullptr;
+            e.xt_flags = L->xt_flags_hold && clears_rows_by_flag(L) ? L->xt_flags : nullptr;
+            L->xt_flags_hold = false;                             // (until this frame has been issued whole)
             st = launch_conv(ctx, d.dtype, true, full_list(L->out_pixels), c, e);
             if (st == DCNN_OK && d.fuse_accum && dense_out != L->buf2) st = launch_copy(ctx, L->buf2, dense_out, L->buf2_bytes);
             break;
@@ -534,6 +542,7 @@ dcnn_status dcnn::layer_init(dcnn_layer* L, const void* const* dense_in, int32_t
     if (st != DCNN_OK) return st;
     if (clear) st = clear_sparse_output(L, true);
     if (st != DCNN_OK) return st;
+    L->xt_flags_hold = L->xt_flags != nullptr;
     L->xt_flags_stale = false;                                // the first frame leaves x^T all zero, and its row flags clear
     L->inited = true;
     L->last_in_count = nullptr;
@@ -811,7 +820,7 @@ dcnn_status dcnn_layer_output(const dcnn_layer* L, dcnn_delta* out_view) {
 dcnn_status dcnn_layer_state(const dcnn_layer* L, int32_t which, void** ptr_dev, size_t* bytes) {
     if (!L || !ptr_dev || !bytes) return DCNN_EINVAL;
     if (which == 0 && L->buf0) { *ptr_dev = L->buf0; *bytes = L->buf0_bytes; return DCNN_OK; }
-    if (which == 1 && L->buf1) { L->xt_flags_stale = true; *ptr_dev = L->buf1; *bytes = L->buf1_bytes; return DCNN_OK; }
+    if (which == 1 && L->buf1) { L->xt_flags_stale = L->xt_shared = true; *ptr_dev = L->buf1; *bytes = L->buf1_bytes; return DCNN_OK; }
     if (which == 2 && L->buf2) { *ptr_dev = L->buf2; *bytes = L->buf2_bytes; return DCNN_OK; }
     return fail(L->ctx, DCNN_EINVAL, "layer_state: the layer has no buffer %d", which);
 }

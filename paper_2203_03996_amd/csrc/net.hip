@@ -127,8 +127,9 @@ dcnn_status lanes_end(dcnn_net* net) {
     return DCNN_OK;
 }
 
-// Clears what is zero before the first sparse step in every layer, on the caller's stream (every lane starts behind it).
-dcnn_status clear_layers(dcnn_net* net, bool with_flags) {
+// Clears pieces of every layer, on the caller's stream: `collect(layer, out)` names up to kMaxLayerClears of them.
+template <class Collect>
+dcnn_status clear_pieces(dcnn_net* net, Collect collect) {
     ClearPiece pieces[kClearPieces];
     int n = 0;
     for (auto& p : net->plan) {
@@ -137,11 +138,18 @@ dcnn_status clear_layers(dcnn_net* net, bool with_flags) {
             if (st != DCNN_OK) return st;
             n = 0;
         }
-        n += collect_clears(p.layer, with_flags, pieces + n);
-        sparse_output_cleared(p.layer);
+        n += collect(p.layer, pieces + n);
     }
-    return launch_clear(net->ctx, pieces, n);
+    return n > 0 ? launch_clear(net->ctx, pieces, n) : DCNN_OK;
 }
+// What is zero before the first sparse step (every lane starts behind it), but for the row flags of x^T: a first frame reads them.
+dcnn_status clear_layers(dcnn_net* net) {
+    return clear_pieces(net, [](dcnn_layer* L, ClearPiece* out) {
+        sparse_output_cleared(L);
+        return collect_clears(L, false, out);
+    });
+}
+dcnn_status clear_flags(dcnn_net* net) { return clear_pieces(net, [](dcnn_layer* L, ClearPiece* out) { return collect_flag_clear(L, out); }); }
 
 }  // namespace
 
@@ -336,6 +344,11 @@ dcnn_status dcnn_net_finalize(dcnn_net* net, int32_t fuse, size_t* arena_bytes) 
             continue;
         }
         const bool walker_conv = is_conv(d) && d.kh == 1 && d.stride == 1 && d.n_in == 1;
+        // (a stored list that is there anyway is the better one on larger maps: a layer that does not truncate writes its own.  8 streams,
+        // 1x1 48->288 on 25 K pixels: 14.6 us on it, 20 on blocks)
+        if (p.self && walker_conv && (int64_t)d.n * d.h * d.w > kSelfMaxPixels &&
+            net->plan[net->layer_of_node[p.in_nodes[0]]].d.act == DCNN_ACT_NONE && net->plan[net->layer_of_node[p.in_nodes[0]]].d.kind != DCNN_DELTAGEN)
+            p.self = false;
         const bool walks_input_list = d.kind == DCNN_ACCUM || d.kind == DCNN_MAXPOOL || walker_conv || (d.kind == DCNN_ACT && d.n_in == 1);
         if (walks_input_list && !p.self) net->plan[net->layer_of_node[p.in_nodes[0]]].d.want_idx = 1;
     }
@@ -344,11 +357,6 @@ dcnn_status dcnn_net_finalize(dcnn_net* net, int32_t fuse, size_t* arena_bytes) 
         dcnn_layer_sizes sz;
         dcnn_status st = dcnn_layer_query(&p.d, &sz);
         if (st != DCNN_OK) return fail(ctx, st, "net_finalize: layer for node %d is invalid", p.out_node);
-        // (a stored list that is there anyway is the better one on larger maps: a layer that does not truncate writes its own.  8 streams,
-        // 1x1 48->288 on 25 K pixels: 14.6 us on it, 20 on blocks)
-        if (p.self && walker_conv && (int64_t)d.n * d.h * d.w > kSelfMaxPixels &&
-            net->plan[net->layer_of_node[p.in_nodes[0]]].d.act == DCNN_ACT_NONE && net->plan[net->layer_of_node[p.in_nodes[0]]].d.kind != DCNN_DELTAGEN)
-            p.self = false;
         p.state_off = off;
         p.state_bytes = sz.state_bytes;
         off += align_up(sz.state_bytes);
@@ -470,7 +478,7 @@ dcnn_status dcnn_net_init(dcnn_net* net, const void* frame_dev, void* out_dev) {
     // during the dense first frame every layer writes its dense output into its own (dense-shaped)
     // delta buffer, which the consumers read; afterwards those buffers hold sparse updates again.  (The input layer's
     // consumers read the frame itself, and a layer with a folded output layer writes O.)
-    dcnn_status st = clear_layers(net, true);
+    dcnn_status st = clear_layers(net);
     if (st == DCNN_OK) st = lanes_begin(net);
     if (st != DCNN_OK) return st;
     const bool frame_direct = reinterpret_cast<uintptr_t>(frame_dev) % 16 == 0;
@@ -495,7 +503,11 @@ dcnn_status dcnn_net_init(dcnn_net* net, const void* frame_dev, void* out_dev) {
         if (st != DCNN_OK) return st;
     }
     st = lanes_end(net);
-    if (st != DCNN_OK) return st;
+    if (st == DCNN_OK) st = clear_flags(net);
+    if (st != DCNN_OK) {
+        for (auto& p : net->plan) p.layer->xt_flags_hold = false;
+        return st;
+    }
     net->inited = true;
     return DCNN_OK;
 }
@@ -548,7 +560,7 @@ dcnn_status dcnn_net_reset(dcnn_net* net) {
     if (!net->bound) return fail(net->ctx, DCNN_ESTATE, "net_reset: bind an arena first");
     for (auto& p : net->plan) p.layer->inited = false;
     net->inited = false;
-    return clear_layers(net, false);
+    return clear_layers(net);
 }
 
 dcnn_status dcnn_net_output(const dcnn_net* net, dcnn_delta* out_view) {

@@ -1269,7 +1269,9 @@ def test_blocks_of_larger_maps_give_the_bits_of_a_stored_list(S, kind, k, stride
 
 
 @pytest.mark.parametrize("S,k,cin,cout,hw,act,residue", [("f16", 1, 64, 64, (40, 51), "relu", 0), ("f32", 3, 32, 32, (23, 29), "relu6", 1),
-                                                         ("f16", 3, 128, 64, (9, 7), "relu", 0), ("f16", 1, 32, 24, (33, 65), "relu", 1)])
+                                                         ("f16", 3, 128, 64, (9, 7), "relu", 0), ("f16", 1, 32, 24, (33, 65), "relu", 1),
+                                                         # 64 MB of x^T and more: cleared by row
+                                                         ("f16", 1, 16, 256, (257, 257), "relu", 0), ("f32", 3, 16, 64, (363, 363), "relu6", 1)])
 def test_second_first_frame_clears_every_truncated_row(S, k, cin, cout, hw, act, residue):
     """A first frame after sparse steps (some of which leave values in x^T) gives the state of a layer that never saw them: the rows
     that hold values are cleared, and the steps behind it are the same."""
