@@ -62,7 +62,7 @@ enum { kRowsAny = 0, kRowsAligned = 1, kValues = 2 };
 // flight (short work lists on layers whose weights do not fit LDS; 4 waves of up to 512 registers).
 template <typename T, int NB, int V, int ROWS, int WMODE, int KS>
 __global__ __launch_bounds__(WMODE == 2 ? 256 : DCNN_CONV_BOUNDS) void conv_mfma_kernel(ListArgs l, ConvArgs c, EpilogueArgs e, int init,
-                                                                 int npass, int cs, int pass_split) {
+                                                                 int npass, int cs, int pass_split, int spread) {
     typedef typename Mma<T>::Vec Vec;
     typedef typename RawOf<T, V>::type Raw;
     constexpr int KP = Mma<T>::KPACK;
@@ -75,7 +75,10 @@ __global__ __launch_bounds__(WMODE == 2 ? 256 : DCNN_CONV_BOUNDS) void conv_mfma
 
     const int nwaves = blockDim.x / kWave, nthreads = blockDim.x;
     constexpr int kThreads = WMODE == 2 ? 256 : DCNN_CONV_BOUNDS;   // (the launcher's block size)
-    const bool local = l.local_slots > 0;                      // blocks compacted here (windows up to 3x3), else a list of the map
+    // 1x1 and 3x3 windows compact blocks here, others build the map's list (the kernels that never see a window of the former are
+    // without that code)
+    constexpr bool kWindow13 = !(ROWS == kRowsAligned && V > 1 && KS == 0);
+    const bool local = kWindow13 && l.local_slots > 0;
     int32_t* self_px = reinterpret_cast<int32_t*>(smem + l.lds_list);
     uint32_t* self_tap = nullptr;
     int64_t count;
@@ -93,9 +96,10 @@ __global__ __launch_bounds__(WMODE == 2 ? 256 : DCNN_CONV_BOUNDS) void conv_mfma
         count = list_count(l);
     }
     // (streamed slices want all waves; otherwise a short list is spread over the grid, as in the wave-specialised kernel: 3x3 13->19 of
-    // 64x64 pixels ran on 16 compute units)
+    // 64x64 pixels ran on 16 compute units.  `spread`: the compute units, or fewer workgroups: one of this size fills a unit's registers, and spread over two per
+    // unit the 7x7 stem of a ResNet-50-shaped network took 58 us, not 35)
     const uint32_t ntiles = (uint32_t)((count + kTile - 1) / kTile);
-    const int tiles_per_iter = WMODE != 0 ? nwaves / cs : local ? min(max((int)ntiles, 1), nwaves / cs) : ws_slots(ntiles, gridDim.x, nwaves / cs);
+    const int tiles_per_iter = WMODE != 0 ? nwaves / cs : local ? min(max((int)ntiles, 1), nwaves / cs) : ws_slots(ntiles, spread, nwaves / cs);
     const int64_t groups = (count + tiles_per_iter * kTile - 1) / (tiles_per_iter * kTile);
     const WgTileRange r = local ? WgTileRange{0, groups, 1} : wg_tile_range(groups);
     if (l.self && !local)
@@ -185,7 +189,7 @@ __global__ __launch_bounds__(WMODE == 2 ? 256 : DCNN_CONV_BOUNDS) void conv_mfma
                       : list_pixel(l.list, (wt_ * tiles_per_iter + slot) * kTile + col, count);
     };
     // which taps an entry needs, where that came with it (windows up to 3x3)
-    const bool words = local || l.taps != nullptr;
+    const bool words = kWindow13 && (local || l.taps != nullptr);
     auto tap_word = [&](int64_t wt_, int round) -> uint32_t {
         const int64_t j = (wt_ * tiles_per_iter + slot) * kTile + col;
         if (local) return self_tap[(round * tiles_per_iter + slot) * kTile + col] & 0x1ffu;
@@ -243,6 +247,7 @@ __global__ __launch_bounds__(WMODE == 2 ? 256 : DCNN_CONV_BOUNDS) void conv_mfma
                 const T* first = in + (int64_t)(flat ? q00 : q00 + cu.dy * c.w + cu.dx) * c.cin;
                 const int nflat = flat ? taps * c.cin : c.cin;
                 const uint64_t tb = flat ? tapbits : tapbits >> min(cu.t, 63);
+                const int64_t to_zeros = ((int64_t)reinterpret_cast<intptr_t>(zeros) - (int64_t)reinterpret_cast<intptr_t>(first)) / (int64_t)sizeof(T);
 #pragma unroll
                 for (int u = 0; u < GK; ++u) {
                     Vec v;
@@ -252,7 +257,9 @@ __global__ __launch_bounds__(WMODE == 2 ? 256 : DCNN_CONV_BOUNDS) void conv_mfma
                         const bool inside = cu.t < ktaps && cu.kc0 + u < kch && j < nflat;
                         const int2 lt = flat_lut[inside ? j : 0];
                         const bool ok = inside && ((tb >> lt.y) & 1);
-                        v[i] = ok ? first[lt.x] : (T)0.0f;
+                        int64_t at = ok ? (int64_t)lt.x : to_zeros;
+                        asm volatile("" : "+v"(at));               // one load at a computed place, not a load behind a branch
+                        v[i] = first[at];
                     }
                     x[u] = v;
                 }
@@ -537,8 +544,9 @@ static dcnn_status launch_conv_nb(dcnn_ctx* ctx, bool init, const ListArgs& l_in
     const size_t shared_weights = p.stream || direct ? 0 : p.w_bytes;
     const bool values = !aligned && (p.flat || c.cin < VEC);
     const size_t own_lds = lds_bytes + (values && !p.flat ? conv_flat_lut_bytes() : 0);
-    const size_t plain_lds = c.k <= 3 ? place_local(own_lds, shared_weights, tiles_per_iter * kTile, cap, &grid)
+    const size_t plain_lds = c.k == 1 || c.k == 3 ? place_local(own_lds, shared_weights, tiles_per_iter * kTile, cap, &grid)
                                       : place_list(own_lds, shared_weights, tiles_per_iter * kTile, grid);
+    const int spread = grid < ctx->num_cu ? grid : ctx->num_cu;
 #define DCNN_CONV_LAUNCH(V, AL, WM, KS)                                                                          \
     do {                                                                                                         \
         auto kern = conv_mfma_kernel<T, NB, V, AL, WM, KS>;                                                      \
@@ -549,7 +557,7 @@ static dcnn_status launch_conv_nb(dcnn_ctx* ctx, bool init, const ListArgs& l_in
             attr_set = (err == hipSuccess);                                                                      \
         }                                                                                                        \
         if (err == hipSuccess)                                                                                   \
-            hipLaunchKernelGGL(kern, dim3(grid, grid_y), dim3(waves * kWave), plain_lds, ctx->stream, l, c, e, ini, p.npass, p.cs, pass_split); \
+            hipLaunchKernelGGL(kern, dim3(grid, grid_y), dim3(waves * kWave), plain_lds, ctx->stream, l, c, e, ini, p.npass, p.cs, pass_split, spread); \
         launched = true;                                                                                         \
     } while (0)
     // resident weights, vector-aligned channels, one pass, sparse step: the wave-specialised kernel

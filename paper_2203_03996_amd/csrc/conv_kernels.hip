@@ -109,7 +109,7 @@ bool conv_self_fits(const dcnn_ctx* ctx, int dtype, int k, int stride, int cin, 
     if (out_px > kSelfMaxPixels) return ws;
     const size_t shared = p.stream ? 0 : p.w_bytes, plain = p.lds_bytes + (cin < (dtype == DCNN_F16 ? 8 : 4) && !p.flat ? conv_flat_lut_bytes() : 0);
     const int group = (p.waves / p.cs) * kTile;
-    if (k <= 3) return local_fits(plain, shared, group, cus) && local_fits(plain, shared, group, 4 * cus);
+    if (k == 1 || k == 3) return local_fits(plain, shared, group, cus) && local_fits(plain, shared, group, 4 * cus);
     return in_px <= kSelfMaxPixels && fits(p.lds_bytes, shared, group, cus);
 }
 
