@@ -134,10 +134,12 @@ __global__ __launch_bounds__(WMODE == 2 ? 256 : DCNN_CONV_BOUNDS) void conv_mfma
     if constexpr (WMODE == 0) {
         for (int i = threadIdx.x; i < w_vecs; i += nthreads) w_lds[i] = wglob[i];
         if constexpr (ROWS == kValues) {
-            for (int j = threadIdx.x; j < (flat ? taps : 1) * c.cin; j += nthreads) {
-                const int tap = j / c.cin, ch = j - tap * c.cin;
-                const int dy = tap / ksz, dx = tap - dy * ksz;
-                flat_lut[j] = make_int2((dy * c.w + dx) * c.cin + ch, tap);
+            if (flat) {
+                for (int j = threadIdx.x; j < taps * c.cin; j += nthreads) {
+                    const int tap = j / c.cin, ch = j - tap * c.cin;
+                    const int dy = tap / ksz, dx = tap - dy * ksz;
+                    flat_lut[j] = make_int2((dy * c.w + dx) * c.cin + ch, tap);
+                }
             }
         }
         lds_block_sync();
@@ -255,7 +257,8 @@ __global__ __launch_bounds__(WMODE == 2 ? 256 : DCNN_CONV_BOUNDS) void conv_mfma
                     for (int i = 0; i < KP; ++i) {
                         const int j = (2 * (cu.kc0 + u) + g) * KP + i;
                         const bool inside = cu.t < ktaps && cu.kc0 + u < kch && j < nflat;
-                        const int2 lt = flat_lut[inside ? j : 0];
+                        int2 lt = make_int2(j, 0);             // (one tap's channels lie as they are: no table, and no room for one)
+                        if (flat) lt = flat_lut[inside ? j : 0];
                         const bool ok = inside && ((tb >> lt.y) & 1);
                         int64_t at = ok ? (int64_t)lt.x : to_zeros;
                         asm volatile("" : "+v"(at));               // one load at a computed place, not a load behind a branch
@@ -543,9 +546,8 @@ static dcnn_status launch_conv_nb(dcnn_ctx* ctx, bool init, const ListArgs& l_in
     };
     const size_t shared_weights = p.stream || direct ? 0 : p.w_bytes;
     const bool values = !aligned && (p.flat || c.cin < VEC);
-    const size_t own_lds = lds_bytes + (values && !p.flat ? conv_flat_lut_bytes() : 0);
-    const size_t plain_lds = c.k == 1 || c.k == 3 ? place_local(own_lds, shared_weights, tiles_per_iter * kTile, cap, &grid)
-                                      : place_list(own_lds, shared_weights, tiles_per_iter * kTile, grid);
+    const size_t plain_lds = c.k == 1 || c.k == 3 ? place_local(lds_bytes, shared_weights, tiles_per_iter * kTile, cap, &grid)
+                                      : place_list(lds_bytes, shared_weights, tiles_per_iter * kTile, grid);
     const int spread = grid < ctx->num_cu ? grid : ctx->num_cu;
 #define DCNN_CONV_LAUNCH(V, AL, WM, KS)                                                                          \
     do {                                                                                                         \

@@ -107,9 +107,9 @@ bool conv_self_fits(const dcnn_ctx* ctx, int dtype, int k, int stride, int cin, 
     const bool ws = ws_lds != 0 && ((size_t)cin * dtype_size(dtype)) % 16 == 0;
     if (ws && !local_fits(ws_lds, ws_w, (kWsProducers / p.cs) * kTile, cus)) return false;
     if (out_px > kSelfMaxPixels) return ws;
-    const size_t shared = p.stream ? 0 : p.w_bytes, plain = p.lds_bytes + (cin < (dtype == DCNN_F16 ? 8 : 4) && !p.flat ? conv_flat_lut_bytes() : 0);
+    const size_t shared = p.stream ? 0 : p.w_bytes;
     const int group = (p.waves / p.cs) * kTile;
-    if (k == 1 || k == 3) return local_fits(plain, shared, group, cus) && local_fits(plain, shared, group, 4 * cus);
+    if (k == 1 || k == 3) return local_fits(p.lds_bytes, shared, group, cus) && local_fits(p.lds_bytes, shared, group, 4 * cus);
     return in_px <= kSelfMaxPixels && fits(p.lds_bytes, shared, group, cus);
 }
 

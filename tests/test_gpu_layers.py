@@ -1300,3 +1300,17 @@ def test_second_first_frame_clears_every_truncated_row(S, k, cin, cout, hw, act,
     used.init([first])
     ctx.sync()
     assert torch.count_nonzero(used.state_tensor(1)) == 0
+
+
+@pytest.mark.parametrize("S,k,stride,cin,cout,nhw", [
+    # pixels narrower than a vector whose resident weights leave less than 2 KB of LDS
+    ("f16", 1, 1, 4, 3904, (1, 6, 7)), ("f16", 1, 1, 7, 3336, (1, 5, 5)), ("f32", 1, 1, 3, 3872, (1, 6, 7)), ("f32", 1, 1, 2, 1800, (2, 5, 9)),
+    # narrow pixels and a window too large for one flat K dimension
+    ("f16", 7, 1, 7, 40, (1, 15, 15)), ("f16", 7, 2, 6, 19, (2, 13, 11)),
+    # odd channel counts above a vector: rows end inside one, at every place in it
+    ("f16", 3, 1, 13, 19, (1, 14, 15)), ("f16", 1, 1, 9, 40, (2, 9, 8)), ("f16", 5, 2, 18, 24, (1, 16, 17)), ("f16", 3, 1, 43, 64, (1, 9, 30)),
+    ("f16", 3, 2, 92, 16, (1, 21, 20)), ("f32", 3, 1, 7, 12, (1, 17, 16)), ("f32", 1, 1, 5, 33, (1, 12, 11)), ("f32", 7, 1, 6, 8, (1, 11, 13)),
+])
+def test_conv_on_rows_that_are_no_whole_vectors(S, k, stride, cin, cout, nhw):
+    """The gathers of the plain kernel: value by value (with and without a flat K dimension) and one load at the row's own alignment."""
+    test_conv_linear(S, k, stride, k // 2, cin, cout, nhw)
