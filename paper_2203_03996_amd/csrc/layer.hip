@@ -257,6 +257,14 @@ static dcnn_status clear_sparse_output(dcnn_layer* L, bool with_flags) {
     return launch_clear(L->ctx, pieces, n);
 }
 
+// Is work on this stream being recorded into a graph?  (A stream that cannot tell is taken to be.)
+static bool stream_records(hipStream_t stream) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
 static ListArgs full_list(int64_t pixels) {
     ListArgs l{};
     l.list = nullptr; l.count = nullptr; l.count_host = pixels; l.max_count = pixels;
@@ -474,6 +482,7 @@ dcnn_status dcnn::layer_init(dcnn_layer* L, const void* const* dense_in, int32_t
     if (!dense_out && d.kind != DCNN_ACCUM) return fail(ctx, DCNN_EINVAL, "init: dense output is null");
     const size_t es = dtype_size(d.dtype);
     dcnn_status st = DCNN_OK;
+    bool recording = false;
     switch (d.kind) {
         case DCNN_DELTAGEN:
             st = launch_copy(ctx, L->buf0, dense_in[0], L->buf0_bytes);
@@ -493,8 +502,11 @@ dcnn_status dcnn::layer_init(dcnn_layer* L, const void* const* dense_in, int32_t
             e.c = L->oc; e.act = d.act; e.eps = d.eps; e.bias = L->has_bias ? L->bias : nullptr;
             e.res_data = (d.n_in == 2 && !has_proj(d)) ? dense_in[1] : nullptr; e.res_mask = nullptr;
             e.xA = L->buf0; e.xT = L->buf1; e.out_data = dense_out; e.out_mask = nullptr; e.surv = nullptr;
-            e.xt_flags = L->xt_flags_hold && clears_rows_by_flag(L) ? L->xt_flags : nullptr;
-            L->xt_flags_hold = false;                             // (until this frame has been issued whole)
+            // (A frame that is recorded runs later, any number of times or never, on an x^T that may have been handed out since: it
+            // clears every row and says nothing about what the memory holds now.)
+            recording = clears_rows_by_flag(L) && stream_records(ctx->stream);
+            e.xt_flags = L->xt_flags_hold && clears_rows_by_flag(L) && !recording ? L->xt_flags : nullptr;
+            if (!recording) L->xt_flags_hold = false;             // (until this frame has been issued whole)
             st = launch_conv(ctx, d.dtype, true, full_list(L->out_pixels), c, e);
             if (st == DCNN_OK && d.fuse_accum && dense_out != L->buf2) st = launch_copy(ctx, L->buf2, dense_out, L->buf2_bytes);
             break;
@@ -542,7 +554,7 @@ dcnn_status dcnn::layer_init(dcnn_layer* L, const void* const* dense_in, int32_t
     if (st != DCNN_OK) return st;
     if (clear) st = clear_sparse_output(L, true);
     if (st != DCNN_OK) return st;
-    L->xt_flags_hold = L->xt_flags != nullptr;
+    if (!recording) L->xt_flags_hold = L->xt_flags != nullptr;
     L->xt_flags_stale = false;                                // the first frame leaves x^T all zero, and its row flags clear
     L->inited = true;
     L->last_in_count = nullptr;

@@ -1314,3 +1314,37 @@ def test_second_first_frame_clears_every_truncated_row(S, k, cin, cout, hw, act,
 def test_conv_on_rows_that_are_no_whole_vectors(S, k, stride, cin, cout, nhw):
     """The gathers of the plain kernel: value by value (with and without a flat K dimension) and one load at the row's own alignment."""
     test_conv_linear(S, k, stride, k // 2, cin, cout, nhw)
+
+
+def test_first_frames_into_a_graph_leave_nothing_to_rely_on():
+    """A first frame on 64 MB of x^T or more skips the rows that hold zeros already.  One that is recorded has not run: neither a
+    later first frame nor its own replays may take the rows to be zero because of it."""
+    rng = np.random.default_rng(3)
+    n, h, w, cin, cout = 2, 257, 257, 16, 256
+    desc = pkg.make_desc(pkg.CONV, DT["f16"], n, h, w, cin, k=1, cout=cout, act=pkg.ACT_RELU, eps=0.6, want_idx=0)
+    wgt = torch.from_numpy(rng.standard_normal((1, 1, cin, cout)).astype(np.float16)).cuda()
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        ctx = pkg.Context(n * h * w)
+        twin, layer = (pkg.Layer(ctx, desc, wgt) for _ in range(2))
+        at = twin.state_tensor(1).data_ptr() - twin.state.data_ptr()
+        x_t = layer.state[at:at + n * h * w * cout * 2]
+        x_t.fill_(0x3c)                                            # memory as it comes
+        frame = torch.from_numpy(rng.standard_normal((n, h, w, cin)).astype(np.float16)).cuda()
+        out = torch.empty((n, h, w, cout), dtype=torch.float16, device="cuda")
+        stream.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            layer.init([frame], out)
+        layer.init([frame], out)
+        stream.synchronize()
+        assert torch.count_nonzero(x_t) == 0, "first frame behind a recorded one"
+        again = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(again, stream=stream):
+            layer.init([frame], out)
+        for g in (graph, again):
+            layer.state_tensor(1).fill_(1.0)                       # whoever has the buffer may write it
+            stream.synchronize()
+            g.replay()
+            stream.synchronize()
+            assert torch.count_nonzero(x_t) == 0, "replayed first frame"
