@@ -184,14 +184,13 @@ __global__ __launch_bounds__(kWsWaves* kWave) void conv_ws_kernel(ListParam<SELF
         const int cin_bytes = c.cin * ES;
         const int kgroups = (kch + GK - 1) / GK;               // groups of GK K-steps per tap
         const bool k_exact = kgroups * GK * 32 == cin_bytes;   // no K-step of a group reaches past the pixel's channels
-        const bool k_exact2 = kch * 32 == cin_bytes;           // no K-step at all does
-        // (one gather per window row pays when most of the map is listed -- the dense mode and high update densities:
-        // 4.6 % of the step with everything listed, 1 % at 50 % density; on short lists the tap-by-tap ring with its
-        // third set in flight is 1 % ahead.  Not on maps whose blocks may be compacted in place: there the pixel to the left need not be
-        // the entry before, and sums have one order whichever way the tiles came about.)
-        const int64_t out_px = (int64_t)c.n * c.oh * c.ow;
-        const bool row_shift = !SELF && KS == 3 && !DUAL && NB <= 2 && c.stride == 1 && c.pad == 1 && out_px > kListMaxPixels && count * 4 >= out_px * 3;
-        (void)k_exact2; (void)row_shift;
+        // One gather per window row pays when most of the map is listed -- the dense mode and high update densities: 3x3 64->64 on 64
+        // streams of 128x128, everything listed, 176 us against 222; on short lists the tap-by-tap ring with its third set in
+        // flight is 1 % ahead.  Not beside blocks compacted in place: their steps of 12-14 us take 0.6 us longer with this code in
+        // the kernel, for 26 -> 23 us with everything listed on 64 K pixels.
+        constexpr bool ROWS = KS == 3 && !DUAL && NB <= 2;
+        const bool row_shift = ROWS && !SELF && c.stride == 1 && c.pad == 1 && count * 4 >= (int64_t)c.n * c.oh * c.ow * 3;
+        (void)row_shift;
         constexpr int kNoTap = 31;                             // cursor sentinel: no tap has this number
         // Which window taps of a list entry are in bounds and flagged comes with the work list (one
         // word per entry); a 1x1 layer that walks its input's own list has exactly its one tap.
@@ -262,9 +261,22 @@ __global__ __launch_bounds__(kWsWaves* kWave) void conv_ws_kernel(ListParam<SELF
                 // lane of the wave needs is skipped altogether.  With a projection, its K groups follow
                 // as "tap" kTapProj of the same sequence, so its gathers are in flight while the last
                 // main group is multiplied.  t == kNoTap once the pairs run out.
-                struct Cursor { uint32_t rest; int t, kg; };
+                // 3x3 windows go row by row, group by group and tap by tap, the order of the row gathers below, so that sums do not
+                // depend on which of the two a tile took (up to a group of K-steps that is tap by tap).
+                struct Cursor { uint32_t rest; int t, kg; uint32_t all, row; };   // (all, row: taps of the cursor's row, and those still to come for this group)
                 auto first_tap = [](uint32_t m) { return m ? __builtin_ctz(m) : kNoTap; };
+                auto row_of = [&](uint32_t m) { return kgroups == 1 ? m : m & (m & 7u ? 7u : (m & 070u ? 070u : 0700u)); };   // (one group: all taps are a row)
+                auto start = [&]() { return Cursor{wave_taps, first_tap(wave_taps), 0, row_of(wave_taps), row_of(wave_taps)}; };
                 auto advance = [&](Cursor& cu) {
+                    if constexpr (ROWS) {
+                        cu.row &= cu.row - 1;
+                        if (cu.row == 0) {
+                            if (++cu.kg >= kgroups) { cu.kg = 0; cu.rest &= ~cu.all; cu.all = row_of(cu.rest); }
+                            cu.row = cu.all;
+                        }
+                        cu.t = first_tap(cu.row);
+                        return;
+                    }
                     if (++cu.kg >= ((DUAL && cu.t == kTapProj) ? kgroups2 : kgroups)) {
                         cu.kg = 0;
                         cu.rest &= cu.rest - 1;
@@ -342,99 +354,99 @@ __global__ __launch_bounds__(kWsWaves* kWave) void conv_ws_kernel(ListParam<SELF
                 // s is multiplied.  The loop body is straight-line code (groups past the end of the
                 // sequence multiply zeros), so every wait counts exactly the loads issued after it.
                 bool rows_done = false;
-                if constexpr (KS == 3 && !DUAL && NB <= 2) {
+                if constexpr (ROWS && !SELF) {
+                    // ---- 3x3, stride 1, padding 1: one gather per window ROW instead of one per tap ---------------
+                    // The list holds every pixel with a flagged tap, so if this lane's left tap (dy, 0) is flagged, the pixel to
+                    // its left is listed too and, in an ascending list, is the entry just before it: the lane below holds
+                    // that very input pixel as ITS centre tap (dy, 1).  The left and right taps of a row are therefore the
+                    // centre column moved by one lane; lanes whose neighbour sits in another tile or row fetch theirs.  One
+                    // vector per lane is left for that: a tile with an entry that has neither neighbour takes the ring.  A
+                    // third of the gathers, and of the cache lines the vector memory pipeline has to look up -- which is
+                    // what bounds this kernel.  A lane whose tap is not flagged (or out of bounds) takes zeros, whatever its
+                    // neighbour holds.
+                    bool from_l = false, from_r = false;
                     if (row_shift) {
-                        // ---- 3x3, stride 1, padding 1: one gather per window ROW instead of one per tap ---------------
-                        // The list is ascending and holds every pixel with a flagged tap, so if this lane's left tap
-                        // (dy, 0) is flagged, the pixel to its left is listed too and is the entry just before it: the
-                        // lane below holds that very input pixel as ITS centre tap (dy, 1).  The left and right taps of
-                        // a row are therefore the centre column moved by one lane; only the first and the last column
-                        // of the tile (whose neighbours sit in other tiles) fetch theirs.  A third of the gathers, and
-                        // of the cache lines the vector memory pipeline has to look up -- which is what bounds this
-                        // kernel.  A lane whose tap is not flagged (or out of bounds) takes zeros, whatever its
-                        // neighbour holds.
-                        constexpr int RG = 2;                          // K-steps per row group
-                        const int rgroups = (kch + RG - 1) / RG;
+                        from_l = col > 0 && __shfl_up(p32_cur, 1, kWave) == p32_cur - 1;
+                        from_r = col < kTile - 1 && __shfl_down(p32_cur, 1, kWave) == p32_cur + 1;
+                    }
+                    if (row_shift && __ballot(p32_cur >= 0 && !from_l && !from_r) == 0) {
                         uint32_t rows = 0;
 #pragma unroll
                         for (int dy = 0; dy < 3; ++dy)
                             if ((wave_taps >> (3 * dy)) & 7u) rows |= 1u << dy;
-                        struct RCur { uint32_t rest; int dy, kg; };
+                        struct RCur { uint32_t rest; int dy, kg; };    // dy == 3: past the end, zeros
                         auto rfirst = [](uint32_t m) { return m ? __builtin_ctz(m) : 3; };
                         auto radvance = [&](RCur& cu) {
-                            if (++cu.kg >= rgroups) { cu.kg = 0; cu.rest &= cu.rest - 1; cu.dy = rfirst(cu.rest); }
+                            if (++cu.kg >= kgroups) { cu.kg = 0; cu.rest &= cu.rest - 1; cu.dy = rfirst(cu.rest); }
                         };
-                        const bool first_col = col == 0, last_col = col == kTile - 1;
-                        struct RSet { Vec xc[RG], xl[RG], xr[RG]; };
-                        auto gather_row = [&](const RCur& cu, RSet& st) {
+                        // One register set: the vectors of K-step u are requested for the next group as soon as the last tap has
+                        // used those of this one (a second set does not fit beside 64 accumulators).
+                        Vec xc[GK], xe[GK];
+                        struct Off { uint32_t c, e; int kg; };
+                        auto offsets = [&](const RCur& cu) {
                             const bool live = cu.dy < 3;
                             const int dy = live ? cu.dy : 0;
                             const uint32_t three = live ? (tapbits >> (3 * dy)) & 7u : 0u;
-                            const uint32_t row0 = base00 + (uint32_t)(dy * c.w * cin_bytes + cu.kg * (RG * 32));
-                            const uint32_t offc = (three & 2u) ? row0 + (uint32_t)cin_bytes : kOob;
-                            const uint32_t offl = (first_col && (three & 1u)) ? row0 : kOob;
-                            const uint32_t offr = (last_col && (three & 4u)) ? row0 + 2u * (uint32_t)cin_bytes : kOob;
-#pragma unroll
-                            for (int u = 0; u < RG; ++u) {
-                                const bool pad = !k_exact2 && (2 * (cu.kg * RG + u) + g) * 16 >= cin_bytes;
-                                st.xc[u] = ws_load16<Vec>(rs_in, pad ? kOob : offc + (uint32_t)u * 32u);
-                                st.xl[u] = ws_load16<Vec>(rs_in, pad ? kOob : offl + (uint32_t)u * 32u);
-                                st.xr[u] = ws_load16<Vec>(rs_in, pad ? kOob : offr + (uint32_t)u * 32u);
-                            }
-                            __builtin_amdgcn_sched_barrier(0);
+                            const uint32_t row0 = base00 + (uint32_t)(dy * c.w * cin_bytes + cu.kg * (GK * 32));
+                            Off o{(three & 2u) ? row0 + (uint32_t)cin_bytes : kOob,
+                                  (!from_l && (three & 1u)) ? row0 : (!from_r && (three & 4u)) ? row0 + 2u * (uint32_t)cin_bytes : kOob, cu.kg};
+                            asm volatile("" : "+v"(o.c));          // one load at a computed offset, not a load per case
+                            asm volatile("" : "+v"(o.e));
+                            return o;
                         };
-                        // the centre column moved by one lane: lane l takes lane l-1 (from_below) or l+1
-                        auto shifted = [&](const Vec& v, bool from_below, bool take, const Vec& other) -> Vec {
-                            const u32x4 w = __builtin_bit_cast(u32x4, v), o = __builtin_bit_cast(u32x4, other);
+                        auto request_step = [&](const Off& o, int u) {
+                            const bool pad = !k_exact && (2 * (o.kg * GK + u) + g) * 16 >= cin_bytes;
+                            xc[u] = ws_load16<Vec>(rs_in, pad ? kOob : o.c + (uint32_t)u * 32u);
+                            xe[u] = ws_load16<Vec>(rs_in, pad ? kOob : o.e + (uint32_t)u * 32u);
+                        };
+                        // the centre column moved by one lane: lane l takes lane l-1 (from_below) or l+1, a lane without that
+                        // neighbour what it fetched
+                        auto moved = [&](const Vec& v, bool from_below, bool take, bool fetched, const Vec& ev) -> Vec {
+                            const u32x4 w = __builtin_bit_cast(u32x4, v), o = __builtin_bit_cast(u32x4, ev);
                             u32x4 r;
 #pragma unroll
                             for (int i = 0; i < 4; ++i) {
                                 const int sft = from_below ? __builtin_amdgcn_update_dpp(0, (int)w[i], 0x138, 0xf, 0xf, true)    // wave_shr:1
                                                            : __builtin_amdgcn_update_dpp(0, (int)w[i], 0x130, 0xf, 0xf, true);   // wave_shl:1
-                                r[i] = take ? (uint32_t)sft : o[i];
+                                r[i] = take ? (fetched ? o[i] : (uint32_t)sft) : 0u;
                             }
                             return __builtin_bit_cast(Vec, r);
                         };
-                        auto mma_row = [&](const RCur& cu, const RSet& st) {
-                            const int dy = cu.dy < 3 ? cu.dy : 0;
-                            const uint32_t three = cu.dy < 3 ? (tapbits >> (3 * dy)) & 7u : 0u;
-                            const bool take_l = !first_col && (three & 1u), take_r = !last_col && (three & 4u);
-                            const uint32_t wave_three = cu.dy < 3 ? (wave_taps >> (3 * dy)) & 7u : 0u;
+                        RCur rc{rows, rfirst(rows), 0};
+                        Off o = offsets(rc);
 #pragma unroll
-                            for (int u = 0; u < RG; ++u) {
-                                const int kc = cu.kg * RG + u;
-                                if (kc >= kch) continue;
-                                const Vec xl = shifted(st.xc[u], true, take_l, st.xl[u]);
-                                const Vec xr = shifted(st.xc[u], false, take_r, st.xr[u]);
+                        for (int u = 0; u < GK; ++u) request_step(o, u);
+                        while (rc.dy < 3) {
+                            const uint32_t three = (tapbits >> (3 * rc.dy)) & 7u, wave_three = (wave_taps >> (3 * rc.dy)) & 7u;
+                            const Vec* wrow = wbase + (size_t)(3 * rc.dy * kch + rc.kg * GK) * 2 * COLS;
+                            const int steps = kch - rc.kg * GK;
+                            radvance(rc);
+                            o = offsets(rc);
 #pragma unroll
-                                for (int dx = 0; dx < 3; ++dx) {
-                                    if (!((wave_three >> dx) & 1u)) continue;
-                                    const Vec* wrow = wbase + (size_t)((3 * dy + dx) * kch + kc) * 2 * COLS;
-                                    Vec wv[NB];
+                            for (int dx = 0; dx < 3; ++dx) {
+                                const bool any = (wave_three >> dx) & 1u;
+                                const Vec* wtap = wrow + (size_t)(dx * kch) * 2 * COLS;
 #pragma unroll
-                                    for (int b = 0; b < NB; ++b) wv[b] = wrow[b * 32];
+                                for (int u = 0; u < GK; ++u) {
+                                    if (any && u < steps) {
+                                        const Vec x = dx == 0 ? moved(xc[u], true, three & 1u, !from_l, xe[u])
+                                                    : dx == 1 ? xc[u] : moved(xc[u], false, three & 4u, !from_r, xe[u]);
 #pragma unroll
-                                    for (int b = 0; b < NB; ++b) Mma<T>::run(acc[b], wv[b], dx == 0 ? xl : (dx == 1 ? st.xc[u] : xr));
+                                        for (int b = 0; b < NB; ++b) Mma<T>::run(acc[b], wtap[(size_t)u * 2 * COLS + b * 32], x);
+                                    }
+                                    if (dx == 2) {
+                                        request_step(o, u);
+                                        __builtin_amdgcn_sched_barrier(0);
+                                    }
                                 }
                             }
-                            __builtin_amdgcn_sched_barrier(0);
-                        };
-                        RSet ra, rb;
-                        RCur rg{rows, rfirst(rows), 0};
-                        RCur rm = rg;
-                        gather_row(rg, ra); radvance(rg);
-                        while (rm.dy < 3) {
-                            gather_row(rg, rb); radvance(rg);
-                            mma_row(rm, ra); radvance(rm);
-                            gather_row(rg, ra); radvance(rg);
-                            mma_row(rm, rb); radvance(rm);
                         }
                         rows_done = true;
                     }
                 }
                 if (!rows_done) {
                 Vec x[NSETS][GK];
-                Cursor cg{wave_taps, first_tap(wave_taps), 0};     // gathers run ahead of the matrix work
+                Cursor cg = start();                               // gathers run ahead of the matrix work
                 Cursor cm = cg;
 #pragma unroll
                 for (int i = 0; i < NSETS - 1; ++i) { gather_group(cg, x[i]); advance(cg); }

@@ -311,10 +311,37 @@ def test_conv3x3_row_gathers_on_structured_masks(pattern, nhw):
     data = rng.normal(0, 1, (n, h, w, cin)).astype(NP_DTYPE[S])
     d = ODelta(data, mask).poisoned()
     want = ref.step(d).poisoned()
-    out = layer.step([_upload(d)])
+    out = layer.step([_off_alignment(_upload(d))])       # (a list from memory: blocks compacted in place are gathered tap by tap)
     ctx.sync()
     assert want.count * 4 >= n * h * w * 3, "the pattern must list at least three quarters of the map"
     check_delta(out, want, S, f"row gathers, {pattern}", slack=sum_slack(ref, d.zero_filled()))
+
+
+@pytest.mark.parametrize("S,cin,cout", [("f16", 64, 64), ("f16", 136, 24), ("f16", 24, 64), ("f32", 20, 40)])
+def test_conv3x3_of_a_stream_has_the_same_bits_alone_and_in_a_batch(S, cin, cout):
+    """One stream of 7 K pixels compacts blocks in place and gathers tap by tap; ten of them take a list from memory and, with most
+    of the map listed, one gather per window row.  One to five groups of K-steps, the last one whole or not."""
+    rng = np.random.default_rng(cin)
+    n, h, w = 10, 89, 83
+    dt = NP_DTYPE[S]
+    wgt = torch.from_numpy((rng.standard_normal((3, 3, cin, cout)) * np.sqrt(2.0 / (9 * cin))).astype(dt)).cuda()
+    layers = []
+    for streams in (1, n):
+        ctx = pkg.Context(streams * h * w)
+        desc = pkg.make_desc(pkg.CONV, DT[S], streams, h, w, cin, k=3, stride=1, pad=1, cout=cout, act=pkg.ACT_RELU, eps=0.3, want_idx=0)
+        layers.append((ctx, pkg.Layer(ctx, desc, wgt)))
+    first = torch.from_numpy(rng.standard_normal((n, h, w, cin)).astype(dt)).cuda()
+    for (ctx, layer), frame in zip(layers, (first[3:4].contiguous(), first)):
+        layer.init([frame])
+    for dens in (1.0, 0.5, 0.03, 0.95):
+        d = _rand_delta(rng, (n, h, w, cin), dens, S, 0.4)
+        alone = layers[0][1].step([_upload(ODelta(d.data[3:4].copy(), d.mask[3:4].copy()))])
+        batch = layers[1][1].step([_upload(d)])
+        for ctx, _ in layers:
+            ctx.sync()
+        mask = to_np(alone.mask)[0]
+        assert np.array_equal(to_np(batch.mask)[3], mask), f"density {dens}: mask"
+        assert np.array_equal(to_np(batch.data)[3][mask == 1], to_np(alone.data)[0][mask == 1]), f"density {dens}: values"
 
 
 @pytest.mark.parametrize("pattern", ["all", "holes", "sevenths"])
