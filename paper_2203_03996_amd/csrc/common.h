@@ -158,8 +158,10 @@ struct ListArgs : StoredList {
     int lds_entries;             // room for this many entries
     // Kernels whose workgroups compact blocks of pixels of their own (local_build) instead of cutting up the map's list:
     int writers;                 // the first workgroups of the grid write what belongs to the whole map
-    int local_shift;             // a block is 1 << local_shift pixels
-    int local_slots;             // pixels per workgroup: its blocks, whole
+    union { int local_shift;     // a block is 1 << local_shift pixels
+            int run_even; };     // or, where workgroups share runs of pixels (local_run): how (run_share)
+    union { int local_slots;     // pixels per workgroup: its blocks, whole
+            int run_parts; };    // or the workgroups that share a run
 };
 // What a kernel takes: the five words of a stored list where it walks one.  (All of ListArgs on every launch, 250 bytes of
 // arguments more, cost 0.4 us a launch: activations of 5-11 us 5-8 % slower.)
@@ -230,6 +232,33 @@ inline LocalShape local_shape(int64_t out_px, int local_shift, int64_t owners_ca
     s.slots = (int)cdiv(blocks, s.owners) << local_shift;
     s.entries = (int)(cdiv(s.slots, group) * group);
     return s;
+}
+
+// Runs of consecutive pixels that `parts` workgroups compact, each for itself, and divide among themselves (local_run in self_list.h).
+constexpr int kRunPixels = 256, kRunTiles = kRunPixels / kTile;
+constexpr int kRunLds = kLocalHeader + kRunPixels * 8;
+// as many workgroups as a run has tiles, or fewer (a power of two) where `chip` of them are there as it is; `rest`: workgroups per tile
+inline int run_parts(int64_t out_px, int64_t rest, int64_t chip) {
+    const int64_t want = cdiv(chip, cdiv(out_px, kRunPixels) * rest);
+    int parts = 1;
+    while (parts < want && parts < kRunTiles) parts *= 2;
+    return parts;
+}
+// Workgroup `item` of the owners' -> run and part.  A scattered update lists a part or two of each run, a clustered one all parts of
+// some: first parts lie ahead of second ones, and each lot is turned against the one before, so that either way the workgroups with
+// work are spread over XCDs and compute units (not turned, a clustered 3x3 256->256 on 4096 pixels had two on some units and none on
+// others).
+struct RunPart { int run, part; };
+__host__ __device__ inline RunPart run_part(int item, int runs, int parts) {
+    const int part = item / runs, run = item - part * runs - part * runs / parts;
+    return {run < 0 ? run + runs : run, part};
+}
+// A workgroup's share of a run's entries: whole tiles, or (`even`) the same number for each, 16 at least -- a tile takes as long
+// as its pixels' lines do, so where every part has a SIMD to itself full tiles on some of them are the slower way.
+__host__ __device__ inline int run_share(int count, int parts, int even) {
+    if (!even) return ((count + kTile - 1) / kTile + parts - 1) / parts * kTile;
+    const int each = (count + parts - 1) / parts;
+    return each > kTile / 2 ? each : kTile / 2;
 }
 
 // Statistics (never on a timed path): x^T rows a convolution that keeps row flags reads and writes in one step.

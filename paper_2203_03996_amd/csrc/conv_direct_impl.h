@@ -46,7 +46,6 @@ __device__ __forceinline__ void conv_direct_body(const ListParam<SELF>& l, const
     const int64_t ntiles = (count + kTile - 1) / kTile;
     const int64_t groups = (ntiles + units_per_iter * TI - 1) / (units_per_iter * TI);
     const WgTileRange r = SELF ? WgTileRange{0, groups, 1} : wg_tile_range(groups);
-    const int group = units_per_iter * TI * kTile;
     if (r.begin >= r.end) return;
 
     const int lane = threadIdx.x % kWave;
@@ -76,28 +75,28 @@ __device__ __forceinline__ void conv_direct_body(const ListParam<SELF>& l, const
         return ((int)n * c.h + oy * c.stride - c.pad) * c.w + ox * c.stride - c.pad;
     };
     auto tile_of = [&](int64_t wt, int ti) { return (wt * units_per_iter + slot) * TI + ti; };
-    // (entries of blocks compacted here: round wt is their wt-th group)
-    auto entry = [&](int64_t wt, int ti, int round) {
+    auto entry = [&](int64_t wt, int ti) {
+        const int64_t j = tile_of(wt, ti) * kTile + col;
         if (wt >= r.end) return -1;
-        return SELF ? self_px[round * group + (slot * TI + ti) * kTile + col] : list_pixel(l.list, tile_of(wt, ti) * kTile + col, count);
+        if constexpr (SELF) return j < count ? self_px[j] : -1;   // (what lies behind belongs to the run's next workgroup)
+        return list_pixel(l.list, j, count);
     };
-    auto tap_word = [&](int64_t wt, int ti, int p32, int round) -> uint32_t {
-        if (SELF && self_tap != nullptr) return self_tap[round * group + (slot * TI + ti) * kTile + col] & ((1u << (KS * KS)) - 1u);
+    auto tap_word = [&](int64_t wt, int ti, int p32) -> uint32_t {
+        if (SELF && self_tap != nullptr) return p32 >= 0 ? self_tap[tile_of(wt, ti) * kTile + col] & ((1u << (KS * KS)) - 1u) : 0u;
         if (l.taps == nullptr) return p32 >= 0 ? 1u : 0u;      // a 1x1 layer on its input's own list: its one tap
         const int64_t j = tile_of(wt, ti) * kTile + col;
         return (wt < r.end && j < count) ? (l.taps[j] & ((1u << (KS * KS)) - 1u)) : 0u;
     };
 
     int survivors = 0;
-    int round = 0;
-    for (int64_t wt = r.begin; wt < r.end; wt += r.step, ++round) {
+    for (int64_t wt = r.begin; wt < r.end; wt += r.step) {
         int p32[TI];
         uint32_t tb[TI], base00[TI];
         uint32_t any = 0;
 #pragma unroll
         for (int ti = 0; ti < TI; ++ti) {
-            p32[ti] = entry(wt, ti, round);
-            tb[ti] = tap_word(wt, ti, p32[ti], round);
+            p32[ti] = entry(wt, ti);
+            tb[ti] = tap_word(wt, ti, p32[ti]);
             base00[ti] = (uint32_t)origin(p32[ti]) * (uint32_t)cin_bytes + (uint32_t)g * 16u;
             any |= tb[ti];
         }
@@ -298,11 +297,19 @@ __global__ __launch_bounds__(kDirectWaves* kWave, 2) void conv_direct_kernel(Lis
             local_write<kDirectWaves * kWave>(l, smem + l.lds_scratch);
             return;
         }
-        // (maps whose blocks the kernel compacts itself are too small for more than one tile per wave)
-        int32_t* px;
-        uint32_t* tap;
-        const int count = local_build<kDirectWaves * kWave>(l, smem + l.lds_list, px, tap);
-        conv_direct_body<T, NB, KS, 1, (NB >= 4 ? 6 : 8), false, SELF>(l, c, e, npass, cs, count, smem, px, l.want_taps ? tap : nullptr);
+        // Maps whose lists are built here are too small for more than one tile per wave.  The layer's weights are fetched for every
+        // tile, so tiles are filled from a run of pixels (local_run) and each workgroup of the run takes its share of them.  2 / 10 /
+        // 30 % of the pixels flagged at random, a workgroup per 32 pixels as they lie -> runs: 3x3 128->128 + ReLU on 128x128 pixels
+        // 19.3 / 21.2 / 22.4 -> 17.7 / 20.5 / 21.4 us, 256->256 on 8 streams of 28x28 24.2 / 25.5 / 26.1 -> 23.3 / 24.5 / 25.4.
+        static_assert(kDirectWaves * kWave == kRunPixels, "a pixel per thread");
+        const RunPart rp = run_part((int)blockIdx.x - l.writers, (l.m_out_px + kRunPixels - 1) / kRunPixels, l.run_parts);
+        const int32_t* px;
+        const uint32_t* tap;
+        const int all = local_run(l, smem + l.lds_list, rp.run, rp.part == 0, px, tap);
+        const int share = run_share(all, l.run_parts, l.run_even), from = rp.part * share;
+        const int count = min(all - from, share);              // (none where the run lists fewer)
+        if (count <= 0) return;
+        conv_direct_body<T, NB, KS, 1, (NB >= 4 ? 6 : 8), false, SELF>(l, c, e, npass, cs, count, smem, px + from, l.want_taps ? tap + from : nullptr);
     } else {
         const int64_t count = list_count(l);
         if (count >= (int64_t)blocked_min_tiles * kTile) {

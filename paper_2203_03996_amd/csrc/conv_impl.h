@@ -634,7 +634,18 @@ static dcnn_status launch_conv_nb(dcnn_ctx* ctx, bool init, const ListArgs& l_in
         const int blocked_min_tiles = (int)((int64_t)ctx->num_cu * 4 * TI / p.cs);
         const int64_t b_cap = (int64_t)ctx->num_cu * 2;        // 4 waves of up to 256 registers: two workgroups per compute unit
         int b_grid = (int)(cdiv(b_want < b_cap ? b_want : b_cap, kXcd) * kXcd);
-        const size_t b_all = place_local(b_lds, 0, (kDirectWaves / p.cs) * kTile, b_cap, &b_grid);
+        size_t b_all = b_lds;
+        if (l.self) {
+            l.writers = local_writers(l);
+            l.run_parts = run_parts(l.m_out_px, 1, b_cap);
+            l.run_even = 1;
+            b_grid = (int)cdiv(l.m_out_px, kRunPixels) * l.run_parts + l.writers;
+            l.lds_scratch = 0;
+            l.lds_list = (int)align_up(b_lds, 16);
+            const size_t scratch = self_scratch_bytes(l.m_in_px, l.m_out_px);
+            b_all = (size_t)l.lds_list + kRunLds;
+            if (scratch > b_all) b_all = scratch;
+        }
         if (b_all > kLdsBytes) return fail(ctx, DCNN_EUNSUPPORTED, "conv: a work list built in place does not fit LDS");
 #define DCNN_BLOCKED_LAUNCH(KS, SELF)                                                                            \
     do {                                                                                                         \

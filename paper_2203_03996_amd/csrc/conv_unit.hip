@@ -6,7 +6,12 @@
 // each pulling 0.9 MB, took 54 us.  Here the work is cut as fine as it goes without splitting a sum -- the order of
 // every sum is that of the other kernels, so a stream gives the same bits whichever kernel its batch size selects --
 // and spread over the chip: unit u = (tile u / G, channel group u % G), and since workgroup b runs on XCD b % 8, a group's
-// weights are fetched into the L2 of one XCD only (of 8 / G, for fewer than 8 groups).
+// weights are fetched into the L2 of one XCD only (of 8 / G, for fewer than 8 groups).  A layer that compacts blocks in place does so
+// by runs of 256 pixels (local_run): tiles of 32 pixels as they lie hold a few listed ones each when flags are scattered and cost their
+// weights all the same.  One layer between an input and an output layer, f16, us, 2 / 10 / 30 % of the pixels flagged at random, tiles as they lie ->
+// runs: 1x1 512->2048 on 16 K pixels 91 / 119 / 138 -> 52 / 63 / 105, 256->1024 on 6272 26 / 30 / 33 -> 20 / 24 / 30; the layer alone, 3x3 128->512 on
+// 8192 21 / 28 / 32 -> 15 / 24 / 31.  3x3 256->256 on 4096 12.6 / 14.7 / 15.9 -> 11.4 / 15.3 / 16.2, with a quarter of it in one region 11.6 -> 14.0:
+// there every tile has a SIMD to itself.
 //
 // Layers without an activation only: a decision needs all channels of a pixel.  (Groups that leave their sums in memory and
 // a tail done by the last of a tile to arrive were built: the device-scope release and acquire that it takes cost
@@ -47,20 +52,34 @@ __global__ __launch_bounds__(kUnitMaxWaves* kWave) void conv_unit_kernel(ListArg
     const int col = lane % 32, g = lane / 32;
     unsigned char* stage = smem + (size_t)wave * kTile * stage_row;
 
-    int count = 0, ntiles, first = blockIdx.x;
+    // Units of this workgroup: u = first, first + step, ... below end.  Where blocks are compacted here they are the tiles of its share
+    // of a run's entries, `tile_px` each, for one group of channels.
+    int count, first = blockIdx.x, step = gridDim.x, tile_px = kTile;
+    const int32_t* run_px = nullptr;
+    const uint32_t* run_taps = nullptr;
     if (l.self) {
-        // tiles of 32 consecutive pixels as they lie, the listed ones taking part: nothing to build
+        static_assert(kUnitMaxWaves * kWave == kRunPixels, "a pixel per thread");
         if (first < l.writers) {
             local_write<kUnitMaxWaves * kWave>(l, smem);
             return;
         }
-        if (wave >= nwaves) return;
         first -= l.writers;
-        ntiles = (l.m_out_px + kTile - 1) / kTile;
+        const int group = first % a.groups;
+        const RunPart rp = run_part(first / a.groups, (l.m_out_px + kRunPixels - 1) / kRunPixels, l.run_parts);
+        const int all = local_run(l, smem + l.lds_list, rp.run, group == 0 && rp.part == 0, run_px, run_taps);
+        const int share = run_share(all, l.run_parts, l.run_even), from = rp.part * share;
+        count = min(all - from, share);
+        if (wave >= nwaves || count <= 0) return;
+        run_px += from;
+        run_taps += from;
+        const int tiles = (count + kTile - 1) / kTile;
+        tile_px = (count + tiles - 1) / tiles;
+        first = group;
+        step = a.groups;
     } else {
         count = (int)list_count(l);
-        ntiles = (count + kTile - 1) / kTile;
     }
+    const int end = (count + kTile - 1) / kTile * a.groups;
     const int kch = c.kch, ksteps = KS * KS * kch, cols = a.nb * 32;
     const int cin_bytes = c.cin * ES;
     const __amdgpu_buffer_rsrc_t rs_in = ws_rsrc(c.in_data, (uint64_t)c.n * c.h * c.w * cin_bytes);
@@ -71,22 +90,22 @@ __global__ __launch_bounds__(kUnitMaxWaves* kWave) void conv_unit_kernel(ListArg
     const uint32_t wstride = (uint32_t)(2 * cols * 16);        // weights of one K-step
     const uint32_t row_bytes = (uint32_t)e.c * ES;
 
-    for (int u = first; u < ntiles * a.groups; u += (int)gridDim.x - (l.self ? l.writers : 0)) {
+    for (int u = first; u < end; u += step) {
         const int tile = u / a.groups;
         const int cb = (u - tile * a.groups) * nwaves + wave;  // this wave's channel block
         const bool cb_on = cb < a.blocks;
-        const int j = tile * kTile + col;
+        const int j = tile * tile_px + col;
         int p = -1, rflag = 1;
         uint32_t taps = 0;
-        if (l.self) {
-            taps = local_taps(l, j, j < l.m_out_px);
-            if (cb == 0 && g == 0 && j < l.m_out_px) local_mask(l, j, taps != 0);
-            if (taps != 0) p = j;
-            rflag = (taps & kLocalSecond) != 0;
-            if (__ballot(taps != 0) == 0) continue;
-        } else if (j < count) {
-            p = l.list ? l.list[j] : j;
-            taps = l.taps ? l.taps[j] & ((1u << (KS * KS)) - 1u) : 1u;
+        if (col < tile_px && j < count) {
+            if (l.self) {
+                p = run_px[j];
+                taps = run_taps[j];
+                rflag = (taps & kLocalSecond) != 0;
+            } else {
+                p = l.list ? l.list[j] : j;
+                taps = l.taps ? l.taps[j] & ((1u << (KS * KS)) - 1u) : 1u;
+            }
         }
         if (!l.self && e.res_mask) rflag = __builtin_amdgcn_raw_buffer_load_b8(rs_rmask, p >= 0 ? p : (int)kOob, 0, 0);
         uint32_t base;                                         // this lane's 16 bytes of tap (0,0), K-step 0
@@ -197,7 +216,7 @@ static int unit_waves(const dcnn_ctx* ctx, int64_t tiles, int blocks) {
 
 // The length of a list is known on the device only, so the rule looks at the map's: units if every pixel is listed, K-steps of a
 // sum and passes over the channels.  A unit fetches its weights for 32 pixels, the register-blocked kernel and the streamed one for
-// more, so long sums over full lists of large maps are theirs.  us, other kernel -> units, all pixels / 30 % / 10 % listed:
+// more, so long sums over full lists of large maps are theirs.  Kernels on lists in memory, whose tiles are full, us, other kernel -> units, all pixels / 30 % / 10 % listed:
 //   up to a wave per SIMD:   3x3 256->256 on 4096 pixels 41 -> 29 / 32 -> 20 / .., 1x1 1024->256 17.5 -> 15 / 17 -> 9 / ..
 //   beyond, one pass:        3x3 256->256 on 6272 43 -> 48, 1x1 1024->256 18 -> 24: no
 //   several passes, K <= 32: 1x1 256->1024 on 6272 34 -> 25 / 18 -> 10 / 17 -> 7, 512->2048 on 16 K 153 -> 160 / 79 -> 56 / 75 -> 9
@@ -239,9 +258,14 @@ static dcnn_status launch_conv_unit_t(dcnn_ctx* ctx, const ListArgs& l_in, const
     int grid = (int)(cdiv(want < cap ? want : cap, kXcd) * kXcd);
     size_t lds = unit_stage_bytes(waves, dtype);
     if (l.self) {
-        // (multiples of 8 keep a channel group on its XCD; writers form the flags of the whole map: four waves)
+        // (multiples of 8 keep a channel group on its XCD; writers form the flags of the whole map: four waves.  LDS: entries behind
+        // the staging rows; a writer uses the space from 0 on)
         l.writers = (int)cdiv(local_writers(l), kXcd) * kXcd;
-        grid += l.writers;
+        l.run_parts = run_parts(out_px, a.groups, 4 * (int64_t)ctx->num_cu);
+        l.run_even = cdiv(out_px, kRunPixels) * l.run_parts * a.groups * waves <= 4 * (int64_t)ctx->num_cu;
+        l.lds_list = (int)align_up(lds, 16);
+        lds = (size_t)l.lds_list + kRunLds;
+        grid = (int)(cdiv(out_px, kRunPixels) * l.run_parts * a.groups) + l.writers;
         const size_t scratch = self_scratch_bytes(l.m_in_px, l.m_out_px);
         if (scratch > lds) lds = scratch;
     }

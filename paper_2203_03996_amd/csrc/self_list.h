@@ -475,6 +475,39 @@ __device__ __forceinline__ int local_build(const ListArgs& l, unsigned char* at,
     lds_block_sync();
     return count;
 }
+// The flagged pixels of run `run` (kRunPixels consecutive pixels, one per thread) -> px and tap words in LDS; returns their number.
+// For kernels in which a tile costs its weights: every workgroup of the run's has the same entries and takes its own share of them.
+// A run's tiles hold as many listed pixels as there are, where tiles of pixels as they lie each hold a few when flags are scattered.
+__device__ __forceinline__ int local_run(const ListArgs& l, unsigned char* at, int run, bool write_masks, const int32_t*& px_out,
+                                         const uint32_t*& taps_out) {
+    constexpr int NWV = kRunPixels / kWave;
+    int* red = reinterpret_cast<int*>(at);
+    int32_t* px = reinterpret_cast<int32_t*>(at + kLocalHeader);
+    uint32_t* taps = reinterpret_cast<uint32_t*>(px + kRunPixels);
+    px_out = px; taps_out = taps;
+    const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+    const int p = run * kRunPixels + tid;
+    const bool live = p < l.m_out_px;
+    const uint32_t t = local_taps(l, p, live);
+    const uint64_t hit = __ballot(t != 0);
+    if (write_masks && live) local_mask(l, p, t != 0);
+    if (lane == 0) red[wave] = __popcll(hit);
+    lds_block_sync();
+    int before = 0, count = 0;
+#pragma unroll
+    for (int i = 0; i < NWV; ++i) {
+        const int c = red[i];
+        if (i < wave) before += c;
+        count += c;
+    }
+    if (t != 0) {
+        const int j = before + __popcll(hit & ((1ull << lane) - 1ull));
+        px[j] = p;
+        taps[j] = t;
+    }
+    lds_block_sync();
+    return count;
+}
 // What belongs to the whole map, by writer blockIdx.x of l.writers.
 template <int NT>
 __device__ __forceinline__ void local_write(const ListArgs& l, unsigned char* scratch) {

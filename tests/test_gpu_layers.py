@@ -1295,6 +1295,14 @@ def test_blocks_of_larger_maps_give_the_bits_of_a_stored_list(S, kind, k, stride
     test_lists_built_in_the_kernel_and_stored_ones_give_the_same_bits(S, kind, k, stride, cin, cout, act, nhw)
 
 
+@pytest.mark.parametrize("S,k,stride,cin,cout,act", [("f16", 3, 1, 256, 256, "none"), ("f16", 3, 1, 128, 512, "none"), ("f16", 1, 2, 256, 1040, "none"), ("f16", 3, 1, 256, 256, "relu")])
+@pytest.mark.parametrize("nhw", [(1, 15, 17), (1, 16, 16), (1, 1, 257), (2, 16, 24), (8, 32, 32)])
+def test_runs_of_pixels_give_the_bits_of_a_stored_list(S, k, stride, cin, cout, act, nhw):
+    """The same comparison for kernels whose workgroups share runs of 256 pixels: a pixel less and more than a run, runs that list a
+    part of a tile, a few tiles and all of them, one workgroup for each tile of a run and one for several."""
+    test_lists_built_in_the_kernel_and_stored_ones_give_the_same_bits(S, "conv", k, stride, cin, cout, act, nhw)
+
+
 @pytest.mark.parametrize("S,k,cin,cout,hw,act,residue", [("f16", 1, 64, 64, (40, 51), "relu", 0), ("f32", 3, 32, 32, (23, 29), "relu6", 1),
                                                          ("f16", 3, 128, 64, (9, 7), "relu", 0), ("f16", 1, 32, 24, (33, 65), "relu", 1),
                                                          # 64 MB of x^T and more: cleared by row

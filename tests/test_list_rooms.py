@@ -48,12 +48,50 @@ int main() {
 }
 """
 
+RUNS = r"""
+#include "common.h"
+#include <vector>
+using namespace dcnn;
+int main() {
+    int bad = 0;
+    for (int cus : {256, 32})
+        for (int rest : {1, 2, 3, 8, 16, 32})
+            for (int px = 1; px <= (int)kSelfMaxPixels; px += px < 1500 ? 1 : 251) {
+                const int runs = (int)cdiv(px, kRunPixels), parts = run_parts(px, rest, 4 * (int64_t)cus);
+                std::vector<int> seen(runs * parts);
+                for (int item = 0; item < runs * parts; ++item) {
+                    const RunPart rp = run_part(item, runs, parts);
+                    if (rp.run < 0 || rp.run >= runs || rp.part < 0 || rp.part >= parts || seen[rp.run * parts + rp.part]++) ++bad;
+                }
+                if (kRunTiles % parts != 0) ++bad;
+            }
+    for (int parts = 1; parts <= kRunTiles; parts *= 2)
+        for (int even = 0; even < 2; ++even)
+            for (int count = 0; count <= kRunPixels; ++count) {
+                const int share = run_share(count, parts, even);
+                if (share * parts < count || (!even && share % kTile != 0) || (count > 0 && share < 1)) ++bad;
+                if (parts == kRunTiles && share > kTile) ++bad;         // a tile each
+            }
+    if (bad) printf("%d\n", bad);
+    return bad ? 1 : 0;
+}
+"""
+
+
+def test_every_run_and_share_has_one_workgroup(tmp_path):
+    """Runs of pixels that several workgroups divide: each (run, part) belongs to one workgroup, and the shares hold all entries."""
+    _run(tmp_path, RUNS)
+
 
 def test_every_workgroups_entries_fit(tmp_path):
+    _run(tmp_path, PROGRAM)
+
+
+def _run(tmp_path, program):
     if not os.path.exists(HIPCC):
         pytest.skip("no hipcc")
     src, exe = tmp_path / "rooms.cpp", tmp_path / "rooms"
-    src.write_text(PROGRAM)
+    src.write_text(program)
     inc = os.path.join(ROOT, "paper_2203_03996_amd", "csrc")
     r = subprocess.run([HIPCC, "-x", "hip", "--offload-host-only", "-O1", "-std=c++17", f"-I{inc}", str(src), "-o", str(exe)],
                        capture_output=True, text=True)
