@@ -50,9 +50,11 @@ __device__ __forceinline__ typename Mma<T>::Vec row_vector(const T* ptr, bool ok
     }
     return __builtin_bit_cast(Vec, w);
 }
-// How the plain kernel reads its input: rows of 16-byte aligned pixels, rows of any length, or value by value -- a flat (tap,
-// channel) dimension, or pixels narrower than a vector.  A kernel each: code that is not there is not fetched.
-enum { kRowsAny = 0, kRowsAligned = 1, kValues = 2 };
+// How the plain kernel reads its input: rows of 16-byte aligned pixels, rows of any length, or value by value -- pixels narrower than
+// a vector, or a flat (tap, channel) dimension, whose elements are looked up in a table.  A kernel each: code that is not there is
+// not fetched, and one load of a vector's eight does not wait for the last one's look-up behind a branch (with the last two in one
+// kernel the first frame of a ResNet-50-shaped network took 962-978 us, not 948).
+enum { kRowsAny = 0, kRowsAligned = 1, kValues = 2, kFlat = 3 };
 
 #ifndef DCNN_CONV_BOUNDS
 #define DCNN_CONV_BOUNDS 512
@@ -69,7 +71,8 @@ __global__ __launch_bounds__(WMODE == 2 ? 256 : DCNN_CONV_BOUNDS) void conv_mfma
     constexpr int COLS = NB * 32;
     constexpr int GK = 4;                                      // K-steps whose gathers are in flight together
     constexpr bool STREAM = WMODE == 1, ALIGNED = ROWS == kRowsAligned;
-    static_assert(ROWS != kValues || WMODE == 0, "value by value: resident weights");
+    constexpr bool VALUES = ROWS == kValues || ROWS == kFlat;
+    static_assert(!VALUES || WMODE == 0, "value by value: resident weights");
     extern __shared__ __align__(16) unsigned char smem[];
     clear_ahead(e);
 
@@ -113,7 +116,7 @@ __global__ __launch_bounds__(WMODE == 2 ? 256 : DCNN_CONV_BOUNDS) void conv_mfma
     const int taps = ksz * ksz, kch = c.kch;
     // flat K (stems with very few channels, unaligned kernels only): the K loop sees ONE tap of kch K-steps whose
     // elements are (tap, channel) pairs; which window tap an element belongs to is looked up per element
-    const bool flat = ROWS == kValues && c.flat != 0;
+    constexpr bool flat = ROWS == kFlat;
     const int ktaps = flat ? 1 : taps;
     const int ksteps = ktaps * kch;
     const bool full_tail = npass == 1;
@@ -133,13 +136,11 @@ __global__ __launch_bounds__(WMODE == 2 ? 256 : DCNN_CONV_BOUNDS) void conv_mfma
                                              (size_t)2 * nwaves * kTile * sizeof(float));
     if constexpr (WMODE == 0) {
         for (int i = threadIdx.x; i < w_vecs; i += nthreads) w_lds[i] = wglob[i];
-        if constexpr (ROWS == kValues) {
-            if (flat) {
-                for (int j = threadIdx.x; j < taps * c.cin; j += nthreads) {
-                    const int tap = j / c.cin, ch = j - tap * c.cin;
-                    const int dy = tap / ksz, dx = tap - dy * ksz;
-                    flat_lut[j] = make_int2((dy * c.w + dx) * c.cin + ch, tap);
-                }
+        if constexpr (flat) {
+            for (int j = threadIdx.x; j < taps * c.cin; j += nthreads) {
+                const int tap = j / c.cin, ch = j - tap * c.cin;
+                const int dy = tap / ksz, dx = tap - dy * ksz;
+                flat_lut[j] = make_int2((dy * c.w + dx) * c.cin + ch, tap);
             }
         }
         lds_block_sync();
@@ -244,7 +245,7 @@ __global__ __launch_bounds__(WMODE == 2 ? 256 : DCNN_CONV_BOUNDS) void conv_mfma
         // 16 bytes of input channels per K-step for this lane's pixel; lanes that do not need the tap
         // (or whose channels are padding) read the zero page instead: no branches, no invalid reads
         auto gather_group = [&](const Cursor& cu, Vec (&x)[GK]) {
-            if constexpr (ROWS == kValues) {
+            if constexpr (VALUES) {
                 // element of tap (0,0) -- or of the cursor's tap --, channel 0; only used with a flagged tap
                 const T* first = in + (int64_t)(flat ? q00 : q00 + cu.dy * c.w + cu.dx) * c.cin;
                 const int nflat = flat ? taps * c.cin : c.cin;
@@ -258,7 +259,7 @@ __global__ __launch_bounds__(WMODE == 2 ? 256 : DCNN_CONV_BOUNDS) void conv_mfma
                         const int j = (2 * (cu.kc0 + u) + g) * KP + i;
                         const bool inside = cu.t < ktaps && cu.kc0 + u < kch && j < nflat;
                         int2 lt = make_int2(j, 0);             // (one tap's channels lie as they are: no table, and no room for one)
-                        if (flat) lt = flat_lut[inside ? j : 0];
+                        if constexpr (flat) lt = flat_lut[inside ? j : 0];
                         const bool ok = inside && ((tb >> lt.y) & 1);
                         int64_t at = ok ? (int64_t)lt.x : to_zeros;
                         asm volatile("" : "+v"(at));               // one load at a computed place, not a load behind a branch
@@ -545,7 +546,7 @@ static dcnn_status launch_conv_nb(dcnn_ctx* ctx, bool init, const ListArgs& l_in
         return all > scratch_end ? all : scratch_end;
     };
     const size_t shared_weights = p.stream || direct ? 0 : p.w_bytes;
-    const bool values = !aligned && (p.flat || c.cin < VEC);
+    const bool values = !aligned && c.cin < VEC;
     const size_t plain_lds = c.k == 1 || c.k == 3 ? place_local(lds_bytes, shared_weights, tiles_per_iter * kTile, cap, &grid)
                                       : place_list(lds_bytes, shared_weights, tiles_per_iter * kTile, grid);
     const int spread = grid < ctx->num_cu ? grid : ctx->num_cu;
@@ -680,10 +681,15 @@ static dcnn_status launch_conv_nb(dcnn_ctx* ctx, bool init, const ListArgs& l_in
         else if (c.k == 3) DCNN_CONV_LAUNCH(VEC, kRowsAligned, 0, 3);
         else DCNN_CONV_LAUNCH(VEC, kRowsAligned, 0, 0);
     } else if (!p.stream) {
-        if (vec_out) { if (values) DCNN_CONV_LAUNCH(VEC, kValues, 0, 0); else DCNN_CONV_LAUNCH(VEC, kRowsAny, 0, 0); }
+        if (vec_out) {
+            if (p.flat) DCNN_CONV_LAUNCH(VEC, kFlat, 0, 0);
+            else if (values) DCNN_CONV_LAUNCH(VEC, kValues, 0, 0);
+            else DCNN_CONV_LAUNCH(VEC, kRowsAny, 0, 0);
+        }
         if constexpr (NB <= 2) {
             if (!vec_out) {
                 if (aligned) DCNN_CONV_LAUNCH(1, kRowsAligned, 0, 0);
+                else if (p.flat) DCNN_CONV_LAUNCH(1, kFlat, 0, 0);
                 else if (values) DCNN_CONV_LAUNCH(1, kValues, 0, 0);
                 else DCNN_CONV_LAUNCH(1, kRowsAny, 0, 0);
             }
