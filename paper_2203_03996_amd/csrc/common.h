@@ -178,6 +178,7 @@ constexpr int64_t kSelfMaxPixels = 16384;
 // the writers' 16-bit positions reach.  Steps with this limit at 16 K pixels -> here, 8 streams: HRNet-shaped 1126 -> 1012 us,
 // ResNet-50-shaped 1250 -> 1213.  Nearest upsampling stays at 16 K: its writers expand the flags, 18 us on 55 K pixels against 11 on a
 // stored list.
+constexpr int64_t kLocalMaxSampled = 49152;  // outputs whose second mask is sampled (layer_lists_itself)
 constexpr int64_t kLocalMaxPixels = kListMaxPixels;
 inline size_t self_scratch_bytes(int64_t in_px, int64_t out_px) {
     return align_up(128 + 4 * (size_t)(2 * cdiv(in_px, 32) + cdiv(out_px, 32)) + 2 * (size_t)cdiv(out_px, 32), 16);

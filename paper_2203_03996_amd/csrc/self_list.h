@@ -269,12 +269,24 @@ __device__ __forceinline__ int self_build(const ListArgs& l, const SelfBits& s, 
         }
     }
     if (l.m_b && l.b_stride > 0) {                             // a second mask of another size: sampled pixel by pixel
+        // (eight loads of a lane in flight: a 3x3 layer on 61 K pixels whose length was counted here 36 -> 32 us, most of it this)
         lds_block_sync();
-        for (int base = wave * kWave; base < l.m_out_px; base += NT) {
-            const int p = base + lane;
-            const uint64_t bits = __ballot(p < l.m_out_px && self_b_flag(l, p));
-            if (lane == 0) s.obits[base / 32] |= (uint32_t)bits;
-            if (lane == 1 && base / 32 + 1 < s.out_words) s.obits[base / 32 + 1] |= (uint32_t)(bits >> 32);
+        constexpr int B = 8;
+        for (int base0 = wave * kWave; base0 < l.m_out_px; base0 += B * NT) {
+            bool f[B];
+#pragma unroll
+            for (int u = 0; u < B; ++u) {
+                const int p = base0 + u * NT + lane;
+                const bool flag = self_b_flag(l, p < l.m_out_px ? p : 0);
+                f[u] = p < l.m_out_px && flag;
+            }
+#pragma unroll
+            for (int u = 0; u < B; ++u) {
+                const int base = base0 + u * NT;
+                const uint64_t bits = __ballot(f[u]);
+                if (lane == 0 && base / 32 < s.out_words) s.obits[base / 32] |= (uint32_t)bits;
+                if (lane == 1 && base / 32 + 1 < s.out_words) s.obits[base / 32 + 1] |= (uint32_t)(bits >> 32);
+            }
         }
     }
     lds_block_sync();

@@ -1169,7 +1169,7 @@ def test_lists_built_in_the_kernel_and_stored_ones_give_the_same_bits(S, kind, k
     n, h, w = nhw
     rng = np.random.default_rng(cin + cout + h)
     dt = NP_DTYPE[S]
-    code = {"conv": pkg.CONV, "residual": pkg.CONV, "projection": pkg.CONV, "dwconv": pkg.DWCONV, "add": pkg.ACT, "upsample": pkg.UPSAMPLE}[kind]
+    code = {"conv": pkg.CONV, "residual": pkg.CONV, "projection": pkg.CONV, "strided projection": pkg.CONV, "dwconv": pkg.DWCONV, "add": pkg.ACT, "upsample": pkg.UPSAMPLE}[kind]
     pad = 0 if kind == "dwconv" and k == 2 else k // 2
     oh, ow = (h * k, w * k) if kind == "upsample" else ((h + 2 * pad - k) // stride + 1, (w + 2 * pad - k) // stride + 1)
     ins = [(n, h, w, cin)]
@@ -1178,8 +1178,8 @@ def test_lists_built_in_the_kernel_and_stored_ones_give_the_same_bits(S, kind, k
         ins.append((n, oh, ow, cout))
     elif kind == "add":
         ins.append(ins[0])
-    elif kind == "projection":
-        ps = stride
+    elif kind in ("projection", "strided projection"):
+        ps = 2 if kind == "strided projection" else stride
         proj = (24, (oh - 1) * ps + 1, (ow - 1) * ps + 1, ps)
         ins.append((n, proj[1], proj[2], 24))
     desc = pkg.make_desc(code, DT[S], n, h, w, cin, k=1 if kind == "upsample" else k, stride=stride, pad=0 if kind == "upsample" else pad, cout=cout,
@@ -1286,6 +1286,7 @@ def test_tiles_of_short_lists_over_the_whole_chip(S, k, cin, cout, res, tiles):
     # the largest map of each kind, ends inside a block and inside a word of flags
     ("f16", "residual", 3, 1, 32, 32, "relu", (5, 113, 115)), ("f16", "conv", 3, 2, 32, 32, "relu6", (4, 127, 129)), ("f32", "projection", 1, 2, 32, 32, "relu", (4, 61, 63)),
     ("f16", "add", 1, 1, 16, 16, "relu", (4, 127, 129)), ("f32", "add", 1, 1, 12, 12, "none", (2, 181, 181)), ("f16", "dwconv", 3, 1, 16, 16, "relu6", (4, 127, 129)),
+    ("f16", "strided projection", 1, 1, 16, 32, "relu", (3, 127, 129)), ("f16", "strided projection", 3, 1, 32, 16, "relu", (3, 91, 91)),
     ("f16", "dwconv", 3, 2, 24, 24, "none", (4, 127, 128)), ("f16", "add", 1, 1, 512, 512, "relu", (1, 127, 129)), ("f16", "upsample", 2, 1, 16, 16, "none", (1, 63, 65)),
     # streamed weights and units: the largest outputs, and inputs beyond those that list themselves
     ("f16", "conv", 3, 2, 128, 128, "relu", (4, 127, 127)), ("f16", "conv", 1, 2, 256, 512, "none", (2, 127, 127)), ("f16", "conv", 1, 1, 384, 96, "none", (3, 45, 47)),
