@@ -220,7 +220,8 @@ inline int64_t self_local_entries(int64_t out_px, int64_t entries_per_group, int
 // belongs to the whole map, then the owners of pixels.
 constexpr int kLocalHeader = 64;                               // bytes of counts ahead of a workgroup's entries
 inline int local_writers(const ListArgs& l) {
-    if (l.idx_out == nullptr && l.in_idx_out == nullptr) return l.count_out != nullptr ? 1 : 0;
+    // (only the ascending list is shared out; the input's list and the lengths are the first one's)
+    if (l.idx_out == nullptr) return l.count_out != nullptr || l.in_idx_out != nullptr ? 1 : 0;
     const int64_t px = l.m_in_px > l.m_out_px ? l.m_in_px : l.m_out_px, w = cdiv(px, 8192);
     return (int)(w < 8 ? w : 8);
 }

@@ -526,6 +526,7 @@ __device__ __forceinline__ void local_write(const ListArgs& l, unsigned char* sc
     const SelfBits s = self_carve(l, scratch);
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
     const int share = blockIdx.x;
+    if (l.idx_out == nullptr && share > 0) return;             // (a launcher's multiple of eight)
     if (l.idx_out == nullptr && l.in_idx_out == nullptr && l.m_k == 1 && l.m_stride == 1 && l.m_up == 1 && l.b_stride <= 0) {
         // only the length is wanted and the flags are the masks': their sum, eight words a thread in flight
         constexpr int NWV = NT / kWave;
