@@ -169,17 +169,16 @@ template <bool SELF> using ListParam = std::conditional_t<SELF, ListArgs, Stored
 
 // ---- work lists built by the kernel itself (host side; self_list.h has the device side) ---------------------------
 constexpr int64_t kListMaxPixels = 65536;    // mask_list_kernel: input and output pixels (positions are kept in 16 bits)
-// Layers whose own kernel builds the list: every workgroup repeats the work, which costs it 3-4 us up to 16 K pixels and 5-8
-// beyond, against ~6 us for a launch of mask_list_kernel and ~5 for a compaction of survivors.  (8 streams of a
-// four-resolution network: activation on 55 K pixels 16.1 us against 15.6 in two launches, on 13.8 K 11.8 against 19.6;
-// upsampling 20.0 against 11.5 and 9.0 against 15.1; a 1x1 layer on 32 K pixels of 256 channels 19.8 against 16.4.)
+// Layers in whose kernel some workgroup forms all of the map's flags on the way: plain convolutions of windows other than 1x1 and 3x3,
+// upsampling (its writers), and kernels that fetch the weights for every tile (register-blocked, units, plain).  Forming them costs
+// 3-4 us up to 16 K pixels and 5-8 beyond, against ~6 us for a launch of mask_list_kernel.
 constexpr int64_t kSelfMaxPixels = 16384;
 // Layers whose workgroups compact blocks of their own (local_build; activations, depthwise and wave-specialised convolutions): as far as
 // the writers' 16-bit positions reach.  Steps with this limit at 16 K pixels -> here, 8 streams: HRNet-shaped 1126 -> 1012 us,
 // ResNet-50-shaped 1250 -> 1213.  Nearest upsampling stays at 16 K: its writers expand the flags, 18 us on 55 K pixels against 11 on a
 // stored list.
-constexpr int64_t kLocalMaxSampled = 49152;  // outputs whose second mask is sampled (layer_lists_itself)
 constexpr int64_t kLocalMaxPixels = kListMaxPixels;
+constexpr int64_t kLocalMaxSampled = 49152;  // outputs whose second mask is sampled (layer_lists_itself)
 inline size_t self_scratch_bytes(int64_t in_px, int64_t out_px) {
     return align_up(128 + 4 * (size_t)(2 * cdiv(in_px, 32) + cdiv(out_px, 32)) + 2 * (size_t)cdiv(out_px, 32), 16);
 }
@@ -209,10 +208,10 @@ __host__ __device__ inline int ws_slots(uint32_t tiles, uint32_t grid, int slots
     const int each = (int)((tiles + grid - 1) / grid);
     return each < 1 ? 1 : (each < slots ? each : slots);
 }
-// entries of the groups that one workgroup of `grid` owns at most (tile ranges per XCD, or a plain stride over the grid)
-inline int64_t self_local_entries(int64_t out_px, int64_t entries_per_group, int grid, bool per_xcd) {
+// entries of the groups that one workgroup of `grid` owns at most (tile_range)
+inline int64_t self_local_entries(int64_t out_px, int64_t entries_per_group, int grid) {
     const int64_t groups = cdiv(out_px, entries_per_group);
-    const int64_t mine = per_xcd ? cdiv(cdiv(groups, kXcd), grid / kXcd) : cdiv(groups, grid);
+    const int64_t mine = cdiv(cdiv(groups, kXcd), grid / kXcd);
     return (mine < 1 ? 1 : mine) * entries_per_group;
 }
 
@@ -234,6 +233,14 @@ inline LocalShape local_shape(int64_t out_px, int local_shift, int64_t owners_ca
     s.slots = (int)cdiv(blocks, s.owners) << local_shift;
     s.entries = (int)(cdiv(s.slots, group) * group);
     return s;
+}
+
+// Activation, depthwise and upsampling kernels: a block per workgroup, of as many pixels as it walks in one iteration (`group`
+// entries), 32 at most -- or 64 on maps that would have more than 1024 blocks, of which four fit a compute unit.
+inline int tile_local_shift(int64_t out_px, int group) {
+    int shift = 3;
+    while (shift < 6 && ((1 << shift) < (group < 32 ? group : 32) || cdiv(out_px, 1 << shift) > 1024)) ++shift;
+    return shift;
 }
 
 // Runs of consecutive pixels that `parts` workgroups compact, each for itself, and divide among themselves (local_run in self_list.h).
@@ -304,8 +311,8 @@ bool conv_proj_supported(const dcnn_ctx* ctx, int dtype, int k, int cin, int cin
 constexpr int64_t kUnitMaxPixels = 16384;
 // Can the sparse steps of this convolution build their work list in the kernel, and is it the better way?  (LDS room in every kernel
 // that may serve them.)
-bool conv_self_fits(const dcnn_ctx* ctx, int dtype, int k, int stride, int cin, int cout, bool fused, int cin2, int64_t in_px,
-                    int64_t out_px, bool want_taps);
+bool conv_self_fits(const dcnn_ctx* ctx, int dtype, int k, int cin, int cout, bool fused, int cin2, int64_t in_px,
+                    int64_t out_px);
 size_t conv_proj_weight_bytes(int dtype, int k, int cin, int cin2, int cout);
 // Packs the projection's [cin2][cout] weights in the column grouping of the main convolution's plan.
 dcnn_status launch_pack_weights_proj(dcnn_ctx* ctx, int dtype, const void* w2, void* wpacked2, int k, int cin, int cin2,

@@ -106,7 +106,7 @@ __global__ __launch_bounds__(WMODE == 2 ? 256 : DCNN_CONV_BOUNDS) void conv_mfma
     const int64_t groups = (count + tiles_per_iter * kTile - 1) / (tiles_per_iter * kTile);
     const WgTileRange r = local ? WgTileRange{0, groups, 1} : wg_tile_range(groups);
     if (l.self && !local)
-        self_emit<kThreads>(l, sb, (int)count, SelfSpan{(int)r.begin, (int)r.end, (int)r.step, tiles_per_iter * kTile}, self_px, nullptr);
+        self_emit<kThreads>(l, sb, (int)count, SelfSpan{(int)r.begin, (int)r.end, (int)r.step, tiles_per_iter * kTile}, self_px);
     if (r.begin >= r.end) return;                              // nothing for this workgroup: skip the weight load
 
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
@@ -527,8 +527,8 @@ static dcnn_status launch_conv_nb(dcnn_ctx* ctx, bool init, const ListArgs& l_in
         const size_t at = align_up(total > scratch_end ? total : scratch_end, 16);
         l.lds_scratch = (int)shared;
         l.lds_list = (int)at;
-        l.lds_entries = (int)self_local_entries(l.m_out_px, group, g, true);
-        return at + (size_t)l.lds_entries * (l.want_taps ? 8 : 4);
+        l.lds_entries = (int)self_local_entries(l.m_out_px, group, g);
+        return at + (size_t)l.lds_entries * 4;
     };
     // Blocks that the workgroups of the other kernels compact themselves: their entries follow everything else, a writer's flags share
     // the space from `shared` on.

@@ -86,8 +86,8 @@ bool conv_proj_supported(const dcnn_ctx* ctx, int dtype, int k, int cin, int cin
     return (uint64_t)in_elems <= lim && (uint64_t)in2_elems <= lim && (uint64_t)out_elems <= lim;
 }
 
-bool conv_self_fits(const dcnn_ctx* ctx, int dtype, int k, int stride, int cin, int cout, bool fused, int cin2, int64_t in_px,
-                    int64_t out_px, bool want_taps) {
+bool conv_self_fits(const dcnn_ctx* ctx, int dtype, int k, int cin, int cout, bool fused, int cin2, int64_t in_px,
+                    int64_t out_px) {
     const ConvPlan p = conv_plan(dtype, k, cin, cout, fused);
     if (!p.ok) return false;
     const size_t scratch = self_scratch_bytes(in_px, out_px);
@@ -96,7 +96,7 @@ bool conv_self_fits(const dcnn_ctx* ctx, int dtype, int k, int stride, int cin, 
         const int64_t want = cdiv(out_px, group);
         const int grid = (int)(cdiv(want < grid_cap ? want : grid_cap, kXcd) * kXcd);
         const size_t at = align_up(own > shared + scratch ? own : shared + scratch, 16);
-        return at + (size_t)self_local_entries(out_px, group, grid, true) * (want_taps ? 8 : 4) <= kLdsBytes;
+        return at + (size_t)self_local_entries(out_px, group, grid) * 4 <= kLdsBytes;
     };
     auto local_fits = [&](size_t own, size_t shared, int group, int64_t cap) {
         const LocalShape s = local_shape(out_px, conv_local_shift(out_px, cap), cap - 8, group);

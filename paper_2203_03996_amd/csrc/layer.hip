@@ -81,7 +81,7 @@ bool layer_lists_itself(const dcnn_ctx* ctx, const dcnn_layer_desc& d, bool walk
     if (sampled && out_px > kLocalMaxSampled) return false;
     switch (d.kind) {
         case DCNN_CONV:
-            return window() && conv_self_fits(ctx, d.dtype, d.kh, d.stride, d.c, oc, act, d.proj_c, in_px, out_px, own && (d.kh == 1 || d.kh == 3));
+            return window() && conv_self_fits(ctx, d.dtype, d.kh, d.c, oc, act, d.proj_c, in_px, out_px);
         case DCNN_DWCONV: return own && window() && dwconv_self_fits(d.dtype, d.kh, oc, in_px, out_px);
         case DCNN_ACT: return act_self_fits(d.dtype, oc, out_px);
         case DCNN_UPSAMPLE: return d.factor > 1 && out_px <= kSelfMaxPixels;

@@ -1,14 +1,16 @@
 // Work lists that a kernel builds for itself, on small maps.
 //
-// On maps of up to kSelfMaxPixels pixels the mask pass, the list emission and the compaction of survivors cost more than
+// On maps of up to 64 K pixels the mask pass, the list emission and the compaction of survivors cost more than
 // what they serve: each is a launch of its own with two or three dependent round trips to memory (4-6 us; a layer of a
-// network of small maps took 12-20 us, half of it spent on lists).  Two ways out, both with the entries' results unchanged:
-//   local_build  a workgroup compacts blocks of pixels of its own.  Most kernels.
+// network of small maps took 12-20 us, half of it spent on lists).  Ways out, all with the entries' results unchanged:
+//   local_build  a workgroup compacts blocks of pixels of its own.  Most kernels, up to kLocalMaxPixels or kSelfMaxPixels.
+//   local_run    several workgroups compact the same run of pixels and divide its entries.  Kernels in which every tile fetches
+//                the layer's weights: register-blocked convolution, units.
 //   self_build   a mask of 16 K pixels is 2 KB of bits, so a workgroup can hold ALL flags in LDS: it reads the input mask
 //                (one round trip of 16-byte loads), forms the flagged output pixels as bits (a 3x3 window on whole words) and
 //                takes the prefix sums of the words' counts -- the position of every pixel in the ascending list.  The plain
-//                convolution kernel, which keeps the entries of its own tiles; the list kernel (mask_kernels.hip); and the
-//                few workgroups that write what belongs to the whole map beside the first way.
+//                convolution kernel on windows other than 1x1 and 3x3, which keeps the entries of its own tiles; the list kernel
+//                (mask_kernels.hip); and the few workgroups that write what belongs to the whole map beside the other ways.
 // Every workgroup of a layer's kernel went the second way once: 3-5 us of the 11-18 that such a kernel took.  Step, all of
 // them -> blocks: bottleneck block on one 128x128 stream 47.5 -> 41.1 us, 3x3 fp32 32->32 + ReLU on 64x64 21.7 -> 19.7, 8 streams
 // of a ResNet-50-shaped network 1450 -> 1250, HRNet-shaped 1306 -> 1126, MobileNet-shaped 512 -> 413 (half of the last from
@@ -331,10 +333,10 @@ __device__ __forceinline__ int self_select(const SelfBits& s, int j) {
     return w * 32 + at;
 }
 
-// Phase 2: the entries of this workgroup's groups -> px (and tap words) in LDS, group after group; the shared outputs.
+// Phase 2: the entries of this workgroup's groups -> px in LDS, group after group; the shared outputs.
 // Ends with a barrier, after which the scratch memory of phase 1 is free.
 template <int NT>
-__device__ __forceinline__ void self_emit(const ListArgs& l, const SelfBits& s, int count, SelfSpan span, int32_t* px, uint32_t* taps) {
+__device__ __forceinline__ void self_emit(const ListArgs& l, const SelfBits& s, int count, SelfSpan span, int32_t* px) {
     const int tid = threadIdx.x;
     const int groups = span.begin < span.end ? (span.end - span.begin + span.step - 1) / span.step : 0;
     const int nloc = groups * span.entries;
@@ -342,17 +344,7 @@ __device__ __forceinline__ void self_emit(const ListArgs& l, const SelfBits& s, 
     for (int i = tid; i < nloc; i += NT) {
         const int q = self_div(i, inv_e);
         const int j = (span.begin + q * span.step) * span.entries + (i - q * span.entries);
-        int p = -1;
-        uint32_t t = 0;
-        if (j < count) {
-            p = self_select(s, j);
-            if (taps != nullptr && l.want_taps) {
-                t = self_taps(l, s.ibits, s.in_words, p);
-                if (l.m_b != nullptr && self_b_flag(l, p)) t |= 1u << 30;
-            }
-        }
-        px[i] = p;
-        if (taps != nullptr && l.want_taps) taps[i] = t;
+        px[i] = j < count ? self_select(s, j) : -1;
     }
     // shares of what other kernels read
     if (blockIdx.y == 0) {
@@ -404,7 +396,7 @@ __device__ __forceinline__ void self_emit(const ListArgs& l, const SelfBits& s, 
 }
 
 // ---- blocks of pixels that a workgroup compacts for itself ----------------------------------------------------------------
-// A kernel does not need the map's list to know its work, only some cut of it.  Here the map is cut into blocks of 8 .. 32
+// A kernel does not need the map's list to know its work, only some cut of it.  Here the map is cut into blocks of 8 .. 64
 // pixels that are dealt to the workgroups in turn; a workgroup tests the windows of its own pixels (a byte per tap and lane,
 // one round trip), packs the flagged ones together in LDS and walks those.  No workgroup repeats another's work and none
 // waits for a scan of the map.  What belongs to the whole map -- the ascending list, its length, the input's list -- is

@@ -36,12 +36,9 @@ __device__ __forceinline__ int64_t tile_list_count(const ListParam<SELF>& l, uns
     if constexpr (SELF) return local_build<kTileThreads>(l, smem + l.lds_list, own.px, own.taps);
     else return list_count(l);
 }
-// Blocks, grid and dynamic LDS of such a launch behind `used` bytes of the kernel's own (a writer uses the space from 0 on).  A
-// block is what the workgroup walks in one iteration, `group` entries if all are listed, or more on maps that would have more than
-// 1024 of them: four workgroups fit a compute unit.
+// Blocks, grid and dynamic LDS of such a launch behind `used` bytes of the kernel's own (a writer uses the space from 0 on).
 static size_t tile_list_place(ListArgs& l, size_t used, int group, int* grid) {
-    int shift = 3;
-    while (shift < 6 && ((1 << shift) < (group < 32 ? group : 32) || cdiv(l.m_out_px, 1 << shift) > 1024)) ++shift;
+    const int shift = tile_local_shift(l.m_out_px, group);
     const LocalShape s = local_shape(l.m_out_px, shift, INT32_MAX, group);
     l.writers = local_writers(l);
     l.local_shift = shift;

@@ -7,47 +7,70 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 PROGRAM = r"""
-#include "common.h"
+#include "conv_plan.h"
+#include <vector>
 using namespace dcnn;
 static int bad = 0;
-// the groups a workgroup walks, by the kernels' rules, against the entries there is room for
-static void check(const char* what, int px, int count, int64_t room_groups, int64_t groups, int64_t entries, int grid, bool per_xcd) {
-    const int64_t room = self_local_entries(room_groups * entries, entries, grid, per_xcd);
+#define BAD(...) do { if (++bad < 10) printf(__VA_ARGS__); } while (0)
+
+// the list that the plain convolution kernel cuts up (windows other than 1x1 and 3x3): entries of the groups a workgroup walks, by the
+// kernel's rule, against the room that its launcher gives it
+static void list(int px, int count, int slots, int grid, int spread) {
+    const int64_t room = self_local_entries(px, slots * kTile, grid);
+    const uint32_t ntiles = (uint32_t)cdiv(count, kTile);
+    const int tiles = ws_slots(ntiles, spread, slots);
+    const int64_t groups = cdiv(count, tiles * kTile);
     for (int b = 0; b < grid; ++b) {
-        int64_t mine = 0;
-        if (per_xcd) {
-            const WgTileRange r = tile_range(groups, b, grid);
-            mine = r.begin < r.end ? (r.end - r.begin + r.step - 1) / r.step : 0;
-        } else {
-            mine = b < groups ? (groups - b + grid - 1) / grid : 0;
+        const WgTileRange r = tile_range(groups, b, grid);
+        const int64_t mine = r.begin < r.end ? (r.end - r.begin + r.step - 1) / r.step : 0;
+        if (mine * tiles * kTile > room)
+            BAD("list of %d of %d pixels, workgroup %d of %d: %d entries, room for %d\n", count, px, b, grid, (int)(mine * tiles * kTile), (int)room);
+    }
+}
+// blocks that workgroups compact for themselves: every pixel has one owner, within its slots, and the entries it walks have room
+static void blocks(const char* what, int px, int shift, int cap, int group, int tiles) {
+    const LocalShape s = local_shape(px, shift, cap, group);
+    if (s.owners < 1 || s.owners > cap || s.entries < s.slots || s.entries % group != 0 || s.slots % (1 << shift) != 0)
+        BAD("%s: %d pixels: %d owners, %d slots, %d entries\n", what, px, s.owners, s.slots, s.entries);
+    std::vector<uint8_t> seen(px);
+    for (int owner = 0; owner < s.owners; ++owner)
+        for (int slot = 0; slot < s.slots; ++slot) {
+            const int p = ((owner + (slot >> shift) * s.owners) << shift) + (slot & ((1 << shift) - 1));
+            if (p < px) ++seen[p];
         }
-        if (mine * entries > room && ++bad < 10)
-            printf("%s: %d pixels, %d listed, workgroup %d of %d: %d entries, room for %d\n", what, px, count, b, grid, (int)(mine * entries), (int)room);
+    for (int p = 0; p < px; ++p)
+        if (seen[p] != 1) { BAD("%s: pixel %d of %d has %d owners\n", what, p, px, seen[p]); break; }
+    // (rounds of up to `tiles` tiles, fewer where the workgroup lists fewer)
+    for (int count = 1; tiles > 0 && count <= s.slots; ++count) {
+        const int n = (int)cdiv(count, kTile), per = n < tiles ? n : tiles;
+        if ((int)cdiv(n, per) * per * kTile > s.entries) BAD("%s: %d entries in rounds of %d tiles, room for %d\n", what, count, per, s.entries);
     }
 }
 int main() {
-    const int num_cu = 256;
-    auto up8 = [](int64_t g) { return (int)(cdiv(g, kXcd) * kXcd); };
-    auto least = [](int64_t a, int64_t b) { return a < b ? a : b; };
-    for (int px = 1; px <= (int)kSelfMaxPixels; px += px < 4096 ? 1 : 61) {
-        const int counts[] = {1, px / 2, px - 1, px};
-        for (int count : counts) {
-            if (count < 1) continue;
-            check("wide activation", px, count, wide_groups(px), wide_groups(count), kWideRun, (int)least(wide_groups(px), num_cu * 8), false);
-            check("upsampling", px, count, cdiv(px, 32), cdiv(count, 32), 32, (int)least(cdiv(px, 32), num_cu * 4), false);
-            for (int run = 8; run <= kTile; run *= 2)
-                check("activation, depthwise", px, count, run_groups(px, run), run_groups(count, run), kTileWaves * run,
-                      up8(least(cdiv(px, kTileWaves * run), num_cu * 4)), true);
-            for (int tiles = 1; tiles <= 16; ++tiles)                        // convolutions: whole tiles, per XCD
-                for (int cap : {num_cu, 2 * num_cu, 4 * num_cu})
-                    check("convolution", px, count, cdiv(px, tiles * kTile), cdiv(cdiv(count, kTile), tiles), tiles * kTile,
-                          up8(least(cdiv(px, tiles * kTile), cap)), true);
-        }
+    const int cus = 256;
+    for (int px = 1; px <= 2500; px += px < 300 ? 1 : 13)
+        for (int slots = 1; slots <= 8; slots *= 2)
+            for (int cap : {cus, 2 * cus, 4 * cus}) {
+                const int tiles = (int)cdiv(px, kTile), want = (int)cdiv(tiles, slots);
+                const int spread_out = want < cus ? (tiles < cus ? tiles : cus) : want;           // (resident weights)
+                for (int w : {want, spread_out}) {
+                    const int grid = (int)(cdiv(w < cap ? w : cap, kXcd) * kXcd);
+                    for (int count : {1, px / 3 + 1, px / 2 + 1, px - 1, px})
+                        if (count >= 1 && count <= px) list(px, count, slots, grid, grid < cus ? grid : cus);
+                }
+            }
+    for (int px = 1; px <= (int)kLocalMaxPixels; px += px < 1000 ? 1 : (px < 17000 ? 331 : 3989)) {
+        for (int tiles = 1; tiles <= 8; tiles *= 2)
+            for (int cap : {cus, 2 * cus, 4 * cus})
+                for (int writers : {0, 1, 8})
+                    blocks("convolution", px, conv_local_shift(px, cap), cap - writers, tiles * kTile, tiles);
+        for (int run = 1; run <= kTile; run *= 2) blocks("activation, depthwise", px, tile_local_shift(px, kTileWaves * run), INT32_MAX, kTileWaves * run, 0);
+        blocks("wide activation", px, tile_local_shift(px, kWideRun), INT32_MAX, kWideRun, 0);
+        blocks("upsampling", px, tile_local_shift(px, 32), INT32_MAX, 32, 0);
     }
     return bad ? 1 : 0;
 }
 """
-
 RUNS = r"""
 #include "common.h"
 #include <vector>
