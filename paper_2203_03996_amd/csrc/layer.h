@@ -39,7 +39,7 @@ struct dcnn_layer {
     mutable bool xt_flags_stale = false;  // the state memory was handed out: the flags are rebuilt from x^T before the next step
     // The row flags describe x^T as it lies in memory: a first frame has gone through and nobody outside can write x^T, so the next
     // first frame clears the rows that hold values only.  From 64 MB of x^T on: there the stores count (64 streams of 128x128, 64 to 256
-    // channels, 134-537 MB a layer: first frame 906 -> 844 us when no row holds any), below it reading the flags and a clearing launch of
+    // channels, 134-537 MB a layer: first frame 906 -> 844 us when no row holds any, 901 -> 855 after 1 to 64 sparse steps), below it reading the flags and a clearing launch of
     // their own do (layers of 4-16 MB, ResNet-50-shaped: 947 -> 959 us).
     bool xt_flags_hold = false;
     mutable bool xt_shared = false;       // x^T was handed out once (dcnn_layer_state): whoever has it may write it at any time
