@@ -268,7 +268,9 @@ __global__ __launch_bounds__(kWsWaves* kWave) void conv_ws_kernel(ListParam<SELF
                 auto row_of = [&](uint32_t m) { return kgroups == 1 ? m : m & (m & 7u ? 7u : (m & 070u ? 070u : 0700u)); };   // (one group: all taps are a row)
                 auto start = [&]() { return Cursor{wave_taps, first_tap(wave_taps), 0, row_of(wave_taps), row_of(wave_taps)}; };
                 auto advance = [&](Cursor& cu) {
-                    if constexpr (ROWS) {
+                    // (two column blocks per wave leave room for one group of K-steps only: the plain order is the same one)
+                    static_assert(!ROWS || NB != 2 || KS * KS * (GK + 1) * 2 * COLS * 16 + 2 * NP * kTile * (COLS * ES + kStagePad) > (int)kLdsBytes);
+                    if constexpr (ROWS && NB == 1) {
                         cu.row &= cu.row - 1;
                         if (cu.row == 0) {
                             if (++cu.kg >= kgroups) { cu.kg = 0; cu.rest &= ~cu.all; cu.all = row_of(cu.rest); }
