@@ -4,21 +4,25 @@
 // pixels AND channels -- which is what the sparse kernels, whose tail wants the whole pixel, cannot do.
 //
 // A wave owns 64 pixels x 64 output channels (2 x 2 MFMA 32x32 blocks; x 32 where the last tile would be half empty, see
-// launch_conv_first_t): four 16-byte operands per lane and K-step feed four
-// MFMAs, straight from global memory / L2 into registers, a ring of kFirstRing K-steps in flight.  With enough such
+// launch_conv_first_t), operands straight from global memory / L2 into registers.  Four K-steps of a pixel -- a 128-byte line of one
+// tap -- are fetched by quads of lanes (quad_transpose: a load instruction then takes 16 clocks of the memory path instead of 64, and
+// the gathers of a K-step 32 beside 32 of weights instead of 128).  Once a group's vectors are dealt out the next group's travel in
+// their place, and its weights in place of each K-step's as it is multiplied: 64 sums, 64 vectors of pixels and 32 of weights fit two
+// waves per SIMD (two whole sets of both spilled: 64->64 on 64 streams of 128x128 3x3 478 us, not 223).  With enough such
 // tiles the four waves of a workgroup take four pixel tiles of the same channels (they share the weights in the
-// vector cache); with too few -- the deep stages of a backbone: 512 pixels, K = 4608 -- they split the K-steps of ONE
+// vector cache); with too few -- the deep stages of a backbone: 512 pixels, K = 4608 -- they split the groups of ONE
 // tile and add their partial sums in LDS in a fixed order.
 // Bound: HBM for the narrow layers of wide maps (64 streams of 128x128, 64->256 with its projection, x^A, x^T and O: 1.6 GB
-// written and 0.27 GB read in 530 us, 3.5 TB/s; two launches of the plain kernel took 1030 us, the projection's result
-// going through memory), memory latency for the deep ones (3x3 512->512 on 512 pixels 30 us, was 79).
+// written and 0.27 GB read in 480 us, 3.9 TB/s), memory latency for the deep ones.  Kernels with a lane per pixel and a ring of four
+// K-steps -> quads, us: 3x3 256->256 on 8 streams of 64x64 104 -> 64, 512->512 on 512 pixels 29 -> 17, 1x1 64->64 and 3x3 64->64 on 64
+// streams of 128x128 together 321 -> 255.
 #include "conv_plan.h"
 
 namespace dcnn {
 
 constexpr int kFirstWaves = 4;
 constexpr int kFirstPx = 64;                                   // tile of a wave: pixels; its channels are 32 * TC
-constexpr int kFirstRing = 4;                                  // K-steps whose operands are in registers or on their way
+constexpr int kFirstGroup = 4;                                 // K-steps whose operands are requested together (quad_transpose); two groups in registers or on their way
 
 struct FirstArgs {
     int nb;                        // column blocks per packed channel group (the layer's plan)
@@ -32,13 +36,16 @@ struct FirstArgs {
 
 template <typename T> constexpr int first_stage_stride(int channels) { return channels * (int)sizeof(T) + kStagePad; }
 
-template <typename T, int SPLIT, int TC, bool XT>
+// STEPS: K-steps of a tap's group that can hold channels.  4 or 2 (rows of up to 64 bytes): a group is a 128-byte line of one tap.
+// 1 (windows over rows of up to 32 bytes): a group is four taps, of which every lane fetches its own pixel -- 3x3 16->16 on 64 streams of
+// 128x128 56 us, by quads of lanes that are three quarters idle 75.
+template <typename T, int SPLIT, int TC, bool XT, int STEPS>
 __global__ __launch_bounds__(kFirstWaves* kWave, 2) void conv_first_kernel(ConvArgs c, EpilogueArgs e, FirstArgs f) {
     typedef typename Mma<T>::Vec Vec;
     constexpr int V = Elem<T>::VEC;
     typedef typename RawOf<T, V>::type Raw;
     constexpr int ES = (int)sizeof(T);
-    constexpr int TP = kFirstPx / 32, kFirstCh = TC * 32, D = kFirstRing;
+    constexpr int TP = kFirstPx / 32, kFirstCh = TC * 32;
     constexpr int stage_stride = first_stage_stride<T>(kFirstCh);
     static_assert(SPLIT == 1 || SPLIT == kFirstWaves, "one tile per wave or one tile per workgroup");
     static_assert(SPLIT == 1 || TP * TC <= kFirstWaves, "after a split a wave sums one block");
@@ -56,6 +63,7 @@ __global__ __launch_bounds__(kFirstWaves* kWave, 2) void conv_first_kernel(ConvA
     const int lane = threadIdx.x % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int col = lane % 32, g = lane / 32;
+    const uint32_t place = (uint32_t)(lane % 4) * 32u + (uint32_t)g * 16u;   // this lane's 16 bytes of a group, load 0
     const int64_t pg = unit / f.cgroups;
     const int cg = (int)(unit - pg * f.cgroups);
     const int64_t pt = SPLIT == 1 ? pg * (kFirstWaves / f.wc) + wave / f.wc : pg;
@@ -82,10 +90,10 @@ __global__ __launch_bounds__(kFirstWaves* kWave, 2) void conv_first_kernel(ConvA
         const int ox = (int)(pu - t1 * (uint32_t)c.ow);
         const uint32_t n = fast_div(t1, c.div_oh);
         const int oy = (int)(t1 - n * (uint32_t)c.oh);
-        px[i].iy0 = oy * c.stride - c.pad;
+        px[i].iy0 = px[i].on ? oy * c.stride - c.pad : INT32_MIN / 2;   // (off: outside the map at every tap)
         px[i].ix0 = ox * c.stride - c.pad;
-        px[i].base = (uint32_t)(((int)n * c.h + px[i].iy0) * c.w + px[i].ix0) * (uint32_t)cin_bytes + (uint32_t)g * 16u;
-        px[i].base2 = (uint32_t)(((int)n * c.h2 + oy * c.stride2) * c.w2 + ox * c.stride2) * (uint32_t)cin2_bytes + (uint32_t)g * 16u;
+        px[i].base = (uint32_t)(((int)n * c.h + oy * c.stride - c.pad) * c.w + px[i].ix0) * (uint32_t)cin_bytes;
+        px[i].base2 = (uint32_t)(((int)n * c.h2 + oy * c.stride2) * c.w2 + ox * c.stride2) * (uint32_t)cin2_bytes;
     }
     // column blocks of the tile in the packed weights (a block past the last one repeats it; its channels are not stored)
     auto block_of = [&](int b) {
@@ -102,8 +110,9 @@ __global__ __launch_bounds__(kFirstWaves* kWave, 2) void conv_first_kernel(ConvA
 #pragma unroll
                 for (int q = 0; q < 16; ++q) acc[i][b][q] = 0.0f;
     };
-    // acc += window of `data` x packed weights, over this wave's share of the K-steps.  `proj`: the 1x1 second input.
-    auto k_loop = [&](bool proj) __attribute__((always_inline)) {
+    // acc += window of `data` x packed weights, over this wave's share of the groups of K-steps.  `proj`: the 1x1 second input.
+    auto k_loop = [&](auto pc) __attribute__((always_inline)) {
+        constexpr bool proj = decltype(pc)::value;
         const int ksz = proj ? 1 : c.k, kch = proj ? c.kch2 : c.kch;
         const int rowb = proj ? cin2_bytes : cin_bytes, iw = proj ? c.w2 : c.w;
         const int ksteps = ksz * ksz * kch;
@@ -117,56 +126,104 @@ __global__ __launch_bounds__(kFirstWaves* kWave, 2) void conv_first_kernel(ConvA
             wlane[b] = ((uint32_t)(cb / f.nb) * (uint32_t)ksteps * 2u * (uint32_t)cols + (uint32_t)g * (uint32_t)cols +
                         (uint32_t)(cb % f.nb) * 32u + (uint32_t)col) * 16u;
         }
+        const uint32_t wrow = (uint32_t)(2 * cols * 16);       // weights of one K-step
+        const int kgroups = (kch + kFirstGroup - 1) / kFirstGroup;
+        const int groups = STEPS == 1 ? (ksteps + kFirstGroup - 1) / kFirstGroup : ksz * ksz * kgroups;
         const int share = SPLIT == 1 ? 0 : wave;
-        const int first = (int)((int64_t)ksteps * share / SPLIT), last = (int)((int64_t)ksteps * (share + 1) / SPLIT);
-        struct Cur { int s, kc, dy, dx; };
-        Cur cu;
-        cu.s = first;
+        const int first = groups * share / SPLIT, last = groups * (share + 1) / SPLIT;
+        if (first == last) return;
+        int kg, dy, dx;
         {
-            const int tap = first / kch;
-            cu.kc = first - tap * kch;
-            cu.dy = tap / ksz; cu.dx = tap - cu.dy * ksz;
+            const int tap = STEPS == 1 ? first * kFirstGroup : first / kgroups;
+            kg = STEPS == 1 ? 0 : first - tap * kgroups;
+            dy = tap / ksz; dx = tap - dy * ksz;
         }
-        // Every load is issued unconditionally: a pixel outside the map, padding channels and steps past the end read zeros
-        // from an offset outside the descriptor, so the number of loads in flight at each wait is known.
-        auto issue = [&](Vec (&x)[TP], Vec (&w)[TC]) {
-            const bool live = cu.s < last;
-            const bool chan_ok = live && (2 * cu.kc + g) * 16 < rowb;
-            const uint32_t uni = (uint32_t)((cu.dy * iw + cu.dx) * rowb + cu.kc * 32);
+        // Every load is issued unconditionally: a pixel outside the map and padding channels read zeros from an offset outside
+        // the descriptor, so the number of loads in flight at each wait is known.
+        constexpr int WSTEPS = STEPS == 1 ? kFirstGroup : STEPS;   // K-steps of a group
+        Vec x[TP][kFirstGroup], w[WSTEPS][TC];
+        auto request_x = [&]() __attribute__((always_inline)) {
+            if constexpr (STEPS == 1) {
+                int ty = dy, tx = dx;
+#pragma unroll
+                for (int u = 0; u < kFirstGroup; ++u) {
+                    const uint32_t uni = (uint32_t)((ty * iw + tx) * rowb + g * 16);
+#pragma unroll
+                    for (int i = 0; i < TP; ++i) {
+                        const bool in = ty < ksz && g * 16 < rowb && (unsigned)(px[i].iy0 + ty) < (unsigned)c.h && (unsigned)(px[i].ix0 + tx) < (unsigned)c.w;
+                        uint32_t o = in ? px[i].base + uni : kOob;
+                        asm volatile("" : "+v"(o));
+                        x[i][u] = ws_load16<Vec>(rs_in, o);
+                    }
+                    if (++tx == ksz) { tx = 0; ++ty; }
+                }
+                return;
+            }
+            const int left = rowb - kg * (kFirstGroup * 32);
+            const uint32_t uni = (uint32_t)((dy * iw + dx) * rowb + kg * (kFirstGroup * 32));
 #pragma unroll
             for (int i = 0; i < TP; ++i) {
-                const bool in = proj || ((unsigned)(px[i].iy0 + cu.dy) < (unsigned)c.h && (unsigned)(px[i].ix0 + cu.dx) < (unsigned)c.w);
-                uint32_t off = (chan_ok && px[i].on && in) ? (proj ? px[i].base2 : px[i].base) + uni : kOob;
-                asm volatile("" : "+v"(off));
-                x[i] = ws_load16<Vec>(rs_in, off);
+                uint32_t off;
+                if constexpr (proj) off = px[i].on ? px[i].base2 + uni : kOob;
+                else off = ((unsigned)(px[i].iy0 + dy) < (unsigned)c.h && (unsigned)(px[i].ix0 + dx) < (unsigned)c.w) ? px[i].base + uni : kOob;
+                auto load = [&](auto jc) __attribute__((always_inline)) {
+                    constexpr int J = decltype(jc)::value;
+                    const uint32_t at = quad_place<J>(place, 32u);
+                    uint32_t o = quad_bcast<J>(off) + at;
+                    o = (int)at < left ? o : kOob;
+                    asm volatile("" : "+v"(o));                // one load at a computed offset, not a load per case
+                    x[i][J] = ws_load16<Vec>(rs_in, o);
+                };
+                load(std::integral_constant<int, 0>{}); load(std::integral_constant<int, 1>{});
+                load(std::integral_constant<int, 2>{}); load(std::integral_constant<int, 3>{});
             }
-            const uint32_t wstep = (uint32_t)(live ? cu.s : first) * (uint32_t)(2 * cols * 16);
-#pragma unroll
-            for (int b = 0; b < TC; ++b) w[b] = ws_load16<Vec>(rs_w, wlane[b] + wstep);
-            ++cu.s;
-            if (++cu.kc == kch) {
-                cu.kc = 0;
-                if (++cu.dx == ksz) { cu.dx = 0; ++cu.dy; }
-            }
-            __builtin_amdgcn_sched_barrier(0);
         };
-        auto mma = [&](const Vec (&x)[TP], const Vec (&w)[TC]) {
+        auto request_w = [&](int u) __attribute__((always_inline)) {
+            const uint32_t step = (uint32_t)((dy * ksz + dx) * kch + kg * kFirstGroup + u) * wrow;
+#pragma unroll
+            for (int b = 0; b < TC; ++b) w[u][b] = ws_load16<Vec>(rs_w, (STEPS == 1 ? dy * ksz + dx : kg * kFirstGroup) + u < (STEPS == 1 ? ksteps : kch) ? wlane[b] : kOob, step);
+        };
+        auto mma = [&](int u, int steps, const Vec (&v)[TP][kFirstGroup]) __attribute__((always_inline)) {
+            if (STEPS == kFirstGroup && u > 0 && u >= steps) return;   // (a group's last steps may be padding)
 #pragma unroll
             for (int b = 0; b < TC; ++b)
 #pragma unroll
-                for (int i = 0; i < TP; ++i) Mma<T>::run(acc[i][b], w[b], x[i]);
-            __builtin_amdgcn_sched_barrier(0);
+                for (int i = 0; i < TP; ++i) Mma<T>::run(acc[i][b], w[u][b], v[i][u]);
         };
-        Vec x[D][TP], w[D][TC];
+        request_x();
 #pragma unroll
-        for (int i = 0; i < D - 1; ++i) issue(x[i], w[i]);
-        for (int s = first; s < last; s += D) {
+        for (int u = 0; u < WSTEPS; ++u) request_w(u);
+        for (int s = first + 1; s < last; ++s) {
+            // the next group's pixels take the place of the vectors as fetched, its weights that of the ones just multiplied
+            Vec xt[TP][kFirstGroup];
 #pragma unroll
-            for (int j = 0; j < D; ++j) {
-                issue(x[(j + D - 1) % D], w[(j + D - 1) % D]);
-                mma(x[j], w[j]);
+            for (int i = 0; i < TP; ++i) {
+                if constexpr (STEPS != 1) quad_transpose(x[i], lane);
+#pragma unroll
+                for (int u = 0; u < kFirstGroup; ++u) xt[i][u] = x[i][u];
+            }
+            const int steps = kch - kg * kFirstGroup;
+            if constexpr (STEPS == 1) {
+                dx += kFirstGroup;
+                while (dx >= ksz) { dx -= ksz; ++dy; }
+            } else if (++kg == kgroups) {
+                kg = 0;
+                if (++dx == ksz) { dx = 0; ++dy; }
+            }
+            request_x();
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < WSTEPS; ++u) {
+                mma(u, steps, xt);
+                request_w(u);
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
+#pragma unroll
+        for (int i = 0; i < TP; ++i)
+            if constexpr (STEPS != 1) quad_transpose(x[i], lane);
+#pragma unroll
+        for (int u = 0; u < WSTEPS; ++u) mma(u, kch - kg * kFirstGroup, x);
     };
 
     // staging tile [pixel][channel] in the storage type: one per wave, or one for the workgroup behind the partial sums
@@ -234,11 +291,11 @@ __global__ __launch_bounds__(kFirstWaves* kWave, 2) void conv_first_kernel(ConvA
     };
 
     zero_acc();
-    k_loop(false);
+    k_loop(std::false_type{});
     deliver(static_cast<const T*>(e.bias), false);
     if (c.in2_data != nullptr) {                               // the projection: rounded on its own, then added
         zero_acc();
-        k_loop(true);
+        k_loop(std::true_type{});
         deliver(static_cast<const T*>(f.bias2), true);
     }
     lds_wave_sync();
@@ -350,9 +407,10 @@ static dcnn_status launch_conv_first_t(dcnn_ctx* ctx, const ConvArgs& c, const E
     const int64_t grid = split ? cdiv(f.units, kXcd) * kXcd : cdiv(f.units / f.cgroups, kXcd) * kXcd * f.cgroups;
     if (grid > INT32_MAX) return fail(ctx, DCNN_ESHAPE, "first frame: %lld workgroups", (long long)grid);
     hipError_t err = hipSuccess;
-#define DCNN_FIRST_LAUNCH_X(SPLIT, TC, XT)                                                                               \
+    const bool thin = c.kch <= 2 && (c.in2_data == nullptr || c.kch2 <= 2), taps = c.kch == 1 && c.k > 1 && c.in2_data == nullptr;
+#define DCNN_FIRST_LAUNCH_X(SPLIT, TC, XT, STEPS)                                                                        \
     do {                                                                                                         \
-        auto kern = conv_first_kernel<T, SPLIT, TC, XT>;                                                                 \
+        auto kern = conv_first_kernel<T, SPLIT, TC, XT, STEPS>;                                                          \
         static bool attr_set = false;                                                                            \
         if (!attr_set) {                                                                                         \
             err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes); \
@@ -360,10 +418,11 @@ static dcnn_status launch_conv_first_t(dcnn_ctx* ctx, const ConvArgs& c, const E
         }                                                                                                        \
         if (err == hipSuccess) hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kFirstWaves * kWave), lds, ctx->stream, c, e, f); \
     } while (0)
-#define DCNN_FIRST_LAUNCH(SPLIT, TC) do { if (e.xt_flags) DCNN_FIRST_LAUNCH_X(SPLIT, TC, true); else DCNN_FIRST_LAUNCH_X(SPLIT, TC, false); } while (0)
-    if (split) { if (narrow) DCNN_FIRST_LAUNCH(kFirstWaves, 1); else DCNN_FIRST_LAUNCH(kFirstWaves, 2); }
-    else if (narrow) DCNN_FIRST_LAUNCH(1, 1);
-    else DCNN_FIRST_LAUNCH(1, 2);
+#define DCNN_FIRST_LAUNCH(SPLIT, TC, STEPS) do { if (e.xt_flags) DCNN_FIRST_LAUNCH_X(SPLIT, TC, true, STEPS); else DCNN_FIRST_LAUNCH_X(SPLIT, TC, false, STEPS); } while (0)
+#define DCNN_FIRST_STEPS(SPLIT, TC) do { if (taps) DCNN_FIRST_LAUNCH(SPLIT, TC, 1); else if (thin) DCNN_FIRST_LAUNCH(SPLIT, TC, 2); else DCNN_FIRST_LAUNCH(SPLIT, TC, kFirstGroup); } while (0)
+    if (split) { if (narrow) DCNN_FIRST_STEPS(kFirstWaves, 1); else DCNN_FIRST_STEPS(kFirstWaves, 2); }
+    else { if (narrow) DCNN_FIRST_STEPS(1, 1); else DCNN_FIRST_STEPS(1, 2); }
+#undef DCNN_FIRST_STEPS
 #undef DCNN_FIRST_LAUNCH
 #undef DCNN_FIRST_LAUNCH_X
     if (err != hipSuccess) return check_hip(ctx, err, "hipFuncSetAttribute(conv_first_kernel)");

@@ -509,6 +509,38 @@ template <typename Raw> __device__ __forceinline__ Raw ws_load16(__amdgpu_buffer
 template <typename Raw> __device__ __forceinline__ Raw ws_load16(__amdgpu_buffer_rsrc_t r, uint32_t off) {
     return __builtin_bit_cast(Raw, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
 }
+// ---- gathers by quads of lanes -------------------------------------------------------------------------------------
+// The matrix cores want operand vector u (16 bytes: K-step u of a pixel) in the lane of its pixel, but four neighbouring lanes that load
+// from four pixels cost four passes through the address coalescer: 64 clocks of the compute unit's memory path for a load instruction of
+// 1 KB, 38 GB/s, with the lines in L1 or not.  Where the lanes of a quad load from ONE 128-byte line it takes 16 clocks, 150 GB/s (measured
+// on one compute unit and on all, 2 MB of scattered rows of 512 bytes: 9.8 TB/s against 37; lanes 16 apart on one line do not help).
+// So load j of four fetches pixel j of the quad, K-step r ^ j by lane r, and quad_transpose deals the vectors out.
+// ~180 clocks of a SIMD's vector issue for what saves 192 of the memory path that four SIMDs share.
+template <int J> __device__ __forceinline__ uint32_t quad_bcast(uint32_t v) {   // the quad's lane J
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, J * 0x55, 0xf, 0xf, true);
+}
+// off: the lane's own pixel (or kOob); place: this lane's 16 bytes of load 0, (lane % 4) * step + ...; `step`, the bytes between two
+// K-steps of a lane, is a power of two
+template <int J> __device__ __forceinline__ uint32_t quad_place(uint32_t place, uint32_t step) { return place ^ (uint32_t)J * step; }
+// x[j] of lane r: K-step r ^ j of the quad's pixel j  ->  x[u]: K-step u of the lane's own pixel
+template <typename Vec> __device__ __forceinline__ void quad_transpose(Vec (&x)[4], int lane) {
+    const bool odd = lane & 1, hi = lane & 2;
+    u32x4 v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = __builtin_bit_cast(u32x4, x[j]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        // register u of lane r <- register r ^ u, which belongs to lane r ^ u
+        const uint32_t a0 = odd ? v[1][i] : v[0][i], a1 = odd ? v[0][i] : v[1][i], a2 = odd ? v[3][i] : v[2][i], a3 = odd ? v[2][i] : v[3][i];
+        const uint32_t b0 = hi ? a2 : a0, b1 = hi ? a3 : a1, b2 = hi ? a0 : a2, b3 = hi ? a1 : a3;
+        v[0][i] = b0;
+        v[1][i] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)b1, 0xB1, 0xf, 0xf, true);    // quad_perm 1,0,3,2
+        v[2][i] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)b2, 0x4E, 0xf, 0xf, true);    // 2,3,0,1
+        v[3][i] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)b3, 0x1B, 0xf, 0xf, true);    // 3,2,1,0
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) x[j] = __builtin_bit_cast(Vec, v[j]);
+}
 template <typename Raw> __device__ __forceinline__ void ws_store16(__amdgpu_buffer_rsrc_t r, uint32_t off, Raw v) {
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, (int)off, 0, 0);
 }

@@ -971,6 +971,22 @@ def test_first_frame_tiles(S, k, stride, cin, cout, nhw, mode):
     assert np.array_equal(alone[0], got[n - 1])
 
 
+@pytest.mark.parametrize("S,k,stride,cin,cout,nhw,mode", [
+    ("f16", 1, 1, 40, 64, (1, 9, 7), "act"),             # lines of 128 bytes: part of one, a whole one and a part, four and a part
+    ("f16", 3, 1, 72, 40, (2, 10, 11), "plain"),
+    ("f16", 1, 1, 264, 64, (1, 9, 13), "residual"),
+    ("f32", 3, 2, 36, 32, (1, 13, 12), "act"),
+    ("f16", 3, 1, 32, 96, (2, 9, 14), "act"),            # rows of up to 64 bytes, whole and split sums
+    ("f16", 5, 1, 24, 32, (1, 8, 9), "plain"),
+    ("f16", 3, 1, 16, 64, (2, 9, 14), "act"),            # up to 32: four taps together, whole and split sums
+    ("f32", 3, 2, 4, 20, (1, 11, 12), "plain"),
+    ("f16", 7, 1, 8, 72, (1, 9, 8), "act"),
+])
+def test_first_frame_lines_of_a_pixel(S, k, stride, cin, cout, nhw, mode):
+    """How the first frame's kernel fetches a pixel's channels: by quads of lanes, or a pixel per lane, at the ends of its groups."""
+    test_first_frame_tiles(S, k, stride, cin, cout, nhw, mode)
+
+
 def test_first_frame_of_a_batch_past_2_gib_has_the_bits_of_single_streams():
     """3x3 64->16 on 112x112 with its K-steps split over four waves: 1400 streams hold 2.09 GiB of input (two launches); the first,
     the one at the border of the launches and the last stream against the same streams alone."""
