@@ -127,17 +127,26 @@ __global__ __launch_bounds__(kFirstWaves* kWave, 2) void conv_first_kernel(ConvA
                         (uint32_t)(cb % f.nb) * 32u + (uint32_t)col) * 16u;
         }
         const uint32_t wrow = (uint32_t)(2 * cols * 16);       // weights of one K-step
-        const int kgroups = (kch + kFirstGroup - 1) / kFirstGroup;
-        const int groups = STEPS == 1 ? (ksteps + kFirstGroup - 1) / kFirstGroup : ksz * ksz * kgroups;
+        // This wave's K-steps and the groups that hold them (a group at either end may hold another wave's too).
         const int share = SPLIT == 1 ? 0 : wave;
-        const int first = groups * share / SPLIT, last = groups * (share + 1) / SPLIT;
-        if (first == last) return;
+        const int k_first = (int)((int64_t)ksteps * share / SPLIT), k_last = (int)((int64_t)ksteps * (share + 1) / SPLIT);
+        if (k_first == k_last) return;
+        const int kgroups = (kch + kFirstGroup - 1) / kFirstGroup;
+        auto group_of = [&](int k) { return k / kch * kgroups + k % kch / kFirstGroup; };
+        const int first = STEPS == 1 ? 0 : group_of(k_first);
+        const int last = STEPS == 1 ? (k_last - k_first + kFirstGroup - 1) / kFirstGroup : group_of(k_last - 1) + 1;
         int kg, dy, dx;
         {
-            const int tap = STEPS == 1 ? first * kFirstGroup : first / kgroups;
-            kg = STEPS == 1 ? 0 : first - tap * kgroups;
+            const int tap = k_first / kch;
+            kg = STEPS == 1 ? 0 : k_first % kch / kFirstGroup;
             dy = tap / ksz; dx = tap - dy * ksz;
         }
+        struct Part { int lo, hi; };                           // the K-steps of the current group that are this wave's
+        auto part_of = [&]() {
+            const int base = (dy * ksz + dx) * kch + kg * kFirstGroup, end = STEPS == 1 ? kFirstGroup : kch - kg * kFirstGroup;
+            if constexpr (SPLIT == 1) return Part{0, STEPS == 1 ? k_last - base : end};
+            return Part{k_first - base, min(k_last - base, end)};
+        };
         // Every load is issued unconditionally: a pixel outside the map and padding channels read zeros from an offset outside
         // the descriptor, so the number of loads in flight at each wait is known.
         constexpr int WSTEPS = STEPS == 1 ? kFirstGroup : STEPS;   // K-steps of a group
@@ -183,8 +192,9 @@ __global__ __launch_bounds__(kFirstWaves* kWave, 2) void conv_first_kernel(ConvA
 #pragma unroll
             for (int b = 0; b < TC; ++b) w[u][b] = ws_load16<Vec>(rs_w, (STEPS == 1 ? dy * ksz + dx : kg * kFirstGroup) + u < (STEPS == 1 ? ksteps : kch) ? wlane[b] : kOob, step);
         };
-        auto mma = [&](int u, int steps, const Vec (&v)[TP][kFirstGroup]) __attribute__((always_inline)) {
-            if (STEPS == kFirstGroup && u > 0 && u >= steps) return;   // (a group's last steps may be padding)
+        auto mma = [&](int u, const Part& part, const Vec (&v)[TP][kFirstGroup]) __attribute__((always_inline)) {
+            if (SPLIT != 1 && (u < part.lo || u >= part.hi)) return;
+            if (SPLIT == 1 && STEPS == kFirstGroup && u > 0 && u >= part.hi) return;   // (a group's last steps may be padding, which meets zeros)
 #pragma unroll
             for (int b = 0; b < TC; ++b)
 #pragma unroll
@@ -202,7 +212,7 @@ __global__ __launch_bounds__(kFirstWaves* kWave, 2) void conv_first_kernel(ConvA
 #pragma unroll
                 for (int u = 0; u < kFirstGroup; ++u) xt[i][u] = x[i][u];
             }
-            const int steps = kch - kg * kFirstGroup;
+            const Part part = part_of();
             if constexpr (STEPS == 1) {
                 dx += kFirstGroup;
                 while (dx >= ksz) { dx -= ksz; ++dy; }
@@ -214,7 +224,7 @@ __global__ __launch_bounds__(kFirstWaves* kWave, 2) void conv_first_kernel(ConvA
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int u = 0; u < WSTEPS; ++u) {
-                mma(u, steps, xt);
+                mma(u, part, xt);
                 request_w(u);
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -222,8 +232,9 @@ __global__ __launch_bounds__(kFirstWaves* kWave, 2) void conv_first_kernel(ConvA
 #pragma unroll
         for (int i = 0; i < TP; ++i)
             if constexpr (STEPS != 1) quad_transpose(x[i], lane);
+        const Part part = part_of();
 #pragma unroll
-        for (int u = 0; u < WSTEPS; ++u) mma(u, kch - kg * kFirstGroup, x);
+        for (int u = 0; u < WSTEPS; ++u) mma(u, part, x);
     };
 
     // staging tile [pixel][channel] in the storage type: one per wave, or one for the workgroup behind the partial sums
