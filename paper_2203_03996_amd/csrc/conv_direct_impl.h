@@ -1,27 +1,250 @@
 // Sparse delta convolution whose weights do not fit LDS, long work lists: register-blocked gather-GEMM.
 //
-// When a layer's packed weights exceed LDS, every wave that multiplies a pixel tile has to fetch the weight
-// operands of all K-steps from L2.  With one tile of 32 pixels per wave that is one 16-byte weight vector per
-// lane and MFMA -- the L2 and the vector cache, not the matrix cores, set the pace.  Here a wave owns TI pixel
-// tiles at once and multiplies every weight operand it has fetched with the gathered operands of all TI tiles
-// (a TI*32 x NB*32 register block), which divides the weight traffic per pixel by TI.  No LDS and no barrier in
-// the K loop: the operands of the next K-steps are in flight while the current one is multiplied, two
-// waves per SIMD cover each other's tails (Section 3.1, Eqs. 4-6; the tail is the one the plain kernel uses).
+// When a layer's packed weights exceed LDS, every wave that multiplies a pixel tile has to fetch the weight operands of all K-steps from
+// L2.  fp16 (conv_direct_body): the waves of a tile share its gathered operands through LDS (gather_tiles.h), on long lists two or four
+// tiles per wave, so that every weight operand is multiplied with all of them.  What bounds it: the vector memory path of a compute unit
+// with weights (short lists: 22 clocks per KB, 16 in flight per wave; 777 clocks per four K-steps of a 3x3 256->256 tile, 1047 before the
+// cursors moved by selects and the loop had one way out), the matrix cores and LDS about equally on long ones.  Kernels whose waves gathered for
+// themselves, a pixel per lane -> this, us a step with input and output layer: 3x3 256->256 + ReLU on 8 streams of 16x16, all / a tenth
+// flagged 56 / 48 -> 45 / 44, 1x1 1024->256 there 51 / 43 -> 46 / 39, 3x3 128->128 on 8 of 256x256 439 / 242 -> 375 / 217, with ReLU
+// 542 / 306 -> 484 / 287, 256->512 on 16 of 64x64 404 / 250 -> 313 / 223.  Known cost: 128->64 on 8 of 128x128 with 2 % flagged 57 -> 60.
+// fp32 (conv_lane_body): every wave for itself.
 //
 // Addressing is by 32-bit byte offsets against buffer descriptors (tensors below 2 GiB): a lane whose tap is not
 // flagged, whose entry lies beyond the list or whose K-step is channel padding gets an offset outside the
 // descriptor and reads zeros, so unflagged memory is never touched and the loop has no branches.  Window taps
-// that no lane of the wave needs are skipped altogether.  Sparse steps of 1x1 / 3x3 layers with 16-byte aligned
+// that no pixel of the wave or workgroup needs are skipped altogether.  Sparse steps of 1x1 / 3x3 layers with 16-byte aligned
 // channels only; which taps an entry needs comes with the work list (one word per entry).
 #pragma once
 
 #include "conv_plan.h"
+#include "gather_tiles.h"
 #include "self_list.h"
 
 namespace dcnn {
 
 constexpr int kDirectWaves = 4;
+constexpr int direct_pow2_ceil(int v) { int p = 1; while (p < v) p <<= 1; return p; }
+// pixel tiles per wave on long lists (a register block of 128 sums; 64 where an fp16 tile has one wave, whose operands nobody shares)
+__host__ __device__ constexpr int direct_tiles(int nb, int es, int sh) { return nb <= 2 && (es > 2 || sh > 1) ? 4 : 2; }
+// LDS: operands of the tiles, then their rounded sums in the same space (a wave with tiles of its own waits for nobody before it puts
+// them there: it has a part of the space to itself) | partial maxima | a tap word per wave | an iteration's entries
+__host__ __device__ constexpr int direct_space(int nb, int es, int ti, int sh) {
+    const int x = kDirectWaves / sh * 2 * ti * kGatherTile, y = kDirectWaves * ti * kTile * (nb * 32 * es + kStagePad);
+    return x > y ? x : y;
+}
+inline size_t direct_lds_bytes(int nb, int es, int sh, bool self) {
+    if (es > 2) return (size_t)kDirectWaves * kTile * (nb * 32 * es + kStagePad) + conv_xchg_bytes(kDirectWaves);
+    return (size_t)direct_space(nb, es, self ? 1 : direct_tiles(nb, es, sh), sh) + conv_xchg_bytes(kDirectWaves) + 2 * kDirectWaves * sizeof(uint32_t) * (1 + 3 * kWave);
+}
 
+// The work of one workgroup with TI pixel tiles per wave; SH waves (the plan's `cs`) share a tile and split its output channels.
+template <typename T, int NB, int KS, int TI, int SH, bool SELF>
+__device__ __forceinline__ void conv_direct_body(const ListParam<SELF>& l, const ConvArgs& c, const EpilogueArgs& e, int npass,
+                                                 int64_t count, unsigned char* smem, const int32_t* self_px, const uint32_t* self_tap) {
+    typedef typename Mma<T>::Vec Vec;
+    constexpr int V = Elem<T>::VEC;
+    typedef typename RawOf<T, V>::type Raw;
+    constexpr int COLS = NB * 32;
+    constexpr int ES = (int)sizeof(T);
+    constexpr int NW = kDirectWaves, SLOTS = NW / SH;
+    constexpr int N = GatherShare<TI, SH>::kLoads;
+    constexpr int LP = direct_pow2_ceil(COLS / V), NIT = kTile / (kWave / LP);   // lanes per pixel of the tail, rows of a tile per lane
+    constexpr int UB = TI == 1 || NIT < 4 ? 2 : 4;              // rows of a batch (of a single tile two: less code)
+    constexpr int PIECES = COLS * ES / 64;                     // 64-byte pieces of a row of this wave's channels
+    static_assert(LP >= 2 && LP <= kWave, "a pixel's channels on neighbouring lanes");
+    static_assert(sizeof(Vec) == 16, "16-byte operand vectors");
+
+    const int64_t ntiles = (count + kTile - 1) / kTile;
+    // tile slots in use: as few as go round the grid once (a compute unit's memory path is what a short list waits for)
+    const int slots = TI > 1 ? SLOTS : SELF ? (int)min(ntiles, (int64_t)SLOTS) : ws_slots((uint32_t)ntiles, gridDim.x, SLOTS);
+    const int64_t groups = (ntiles + slots * TI - 1) / (slots * TI);
+    const WgTileRange r = SELF ? WgTileRange{0, groups, 1} : wg_tile_range(groups);
+    if (r.begin >= r.end) return;
+
+    const int lane = threadIdx.x % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int col = lane % 32, g = lane / 32;
+    const int slot = wave / SH, part = wave % SH;
+    const int kch = c.kch;
+    const int ksteps = KS * KS * kch;
+    const bool full_tail = npass == 1;
+    constexpr int stage_stride = COLS * ES + kStagePad;
+    // (a tile's rounded sums wait in the space of its operands)
+    constexpr int space = direct_space(NB, ES, TI, SH);
+    unsigned char* buf = smem + (SH == 1 ? (size_t)wave * (space / NW) : (size_t)slot * 2 * TI * kGatherTile);
+    unsigned char* stage = SH == 1 ? buf : smem + (size_t)wave * TI * kTile * stage_stride;
+    unsigned char* behind = smem + space;
+    float* xchg = reinterpret_cast<float*>(behind) + (size_t)slot * 2 * SH * kTile;
+    uint32_t* wave_words;
+    // [3][a thread each]; these and the words twice: a wave may be an iteration ahead of one that still reads them
+    int32_t* entries;
+    int phase = 0;
+
+    const int cin_bytes = c.cin * ES;
+    const __amdgpu_buffer_rsrc_t rs_in = ws_rsrc(c.in_data, (uint64_t)c.n * c.h * c.w * cin_bytes);
+    const __amdgpu_buffer_rsrc_t rs_w = ws_rsrc(c.wpacked, (uint64_t)npass * SH * ksteps * 2 * COLS * 16);
+
+    auto origin = [&](int p32) {
+        // pixel index of tap (0,0) of the entry's window (only used when that tap is in bounds)
+        const uint32_t pu = p32 >= 0 ? (uint32_t)p32 : 0u;
+        const uint32_t t1 = fast_div(pu, c.div_ow);
+        const int ox = (int)(pu - t1 * (uint32_t)c.ow);
+        const uint32_t n = fast_div(t1, c.div_oh);
+        const int oy = (int)(t1 - n * (uint32_t)c.oh);
+        return ((int)n * c.h + oy * c.stride - c.pad) * c.w + ox * c.stride - c.pad;
+    };
+    auto tile_of = [&](int64_t wt, int ti) { return (wt * slots + slot) * TI + ti; };
+    const int mine_n = slots * TI * kTile;                     // entries of an iteration
+    // An iteration's entries, one per thread, are requested an iteration ahead -- entry after entry by the lanes that need them, a wait
+    // each, 16384 tiles of a 3x3 128->128 layer spent half their time on lists -- and meet in LDS: pixel, offset of its window, tap word.
+    static_assert(SLOTS * TI * kTile <= NW * kWave, "an entry per thread");
+    struct Entry { int p; uint32_t tap; };
+    const __amdgpu_buffer_rsrc_t rs_list = ws_rsrc(l.list, SELF ? 0 : (uint64_t)count * 4), rs_taps = ws_rsrc(l.taps, SELF ? 0 : (uint64_t)count * 4);
+    const int me = threadIdx.x;
+    auto request_entry = [&](int64_t wt) -> Entry {
+        const int64_t j = wt * mine_n + me;
+        const bool on = wt < r.end && me < mine_n && j < count;
+        if constexpr (SELF) return on ? Entry{self_px[j], self_tap ? self_tap[j] : 1u} : Entry{-1, 0u};
+        const uint32_t off = on ? (uint32_t)j * 4u : kOob;
+        return Entry{(int)__builtin_amdgcn_raw_buffer_load_b32(rs_list, (int)off, 0, 0), (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs_taps, (int)off, 0, 0)};
+    };
+    Entry ahead = request_entry(r.begin);
+
+    int survivors = 0;
+    for (int64_t wt = r.begin; wt < r.end; wt += r.step) {
+        uint32_t any;
+        wave_words = reinterpret_cast<uint32_t*>(behind + conv_xchg_bytes(NW)) + phase * NW;
+        entries = reinterpret_cast<int32_t*>(behind + conv_xchg_bytes(NW)) + 2 * NW + phase * 3 * NW * kWave;
+        phase ^= 1;
+        {
+            const int64_t j = wt * mine_n + me;
+            const bool on = me < mine_n && j < count;   // (what lies behind belongs to the run's next workgroup)
+            const int p32 = !on ? -1 : (SELF || l.list != nullptr) ? ahead.p : (int)j;
+            any = !on ? 0u : (SELF || l.taps != nullptr) ? ahead.tap & ((1u << (KS * KS)) - 1u) : 1u;   // (no words: a 1x1 layer on its input's own list)
+            if (me < mine_n) {
+                entries[me] = p32;
+                entries[NW * kWave + me] = (int)((uint32_t)origin(p32) * (uint32_t)cin_bytes);
+                entries[2 * NW * kWave + me] = (int)any;
+            }
+        }
+        // window taps that a pixel of the workgroup needs; a slot without entries only keeps the barriers
+        if constexpr (SH > 1) {
+            uint32_t wave_taps = 0;
+#pragma unroll
+            for (int t = 0; t < KS * KS; ++t)
+                if (__ballot((any >> t) & 1)) wave_taps |= 1u << t;
+            if (lane == 0) wave_words[wave] = wave_taps;
+        }
+        lds_block_sync();
+        ahead = request_entry(wt + r.step);
+        uint32_t taps = 0;
+        if constexpr (SH > 1) {
+#pragma unroll
+            for (int i = 0; i < NW; ++i) taps |= (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_words[i]);
+        }
+        const bool mine = slot < slots && tile_of(wt, 0) * kTile < count;
+        uint32_t base[N], need[GatherShare<TI, SH>::kWords];    // the pixels this wave fetches
+#pragma unroll
+        for (int i = 0; i < GatherShare<TI, SH>::kWords; ++i) need[i] = 0;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int at = (slot * TI + GatherShare<TI, SH>::tile(part, i)) * kTile + col / 4 * 4 + GatherShare<TI, SH>::pixel(part, i);
+            base[i] = (uint32_t)entries[NW * kWave + at];
+            need[i / 3] |= (uint32_t)entries[2 * NW * kWave + at] << (9 * (i % 3));
+        }
+        if constexpr (SH == 1) {
+            uint32_t own = 0;
+#pragma unroll
+            for (int i = 0; i < N; ++i) own |= need[i / 3] >> (9 * (i % 3)) & 0x1ffu;
+#pragma unroll
+            for (int t = 0; t < KS * KS; ++t)
+                if (__ballot((own >> t) & 1)) taps |= 1u << t;
+        }
+
+        for (int pass = 0; pass < npass; ++pass) {
+            const int cgroup = pass * SH + part;               // which group of COLS output channels
+            const int ch0 = cgroup * COLS;
+            int nch = e.c - ch0;
+            nch = nch < 0 ? 0 : (nch > COLS ? COLS : nch);
+            f32x16 acc[TI][NB];
+#pragma unroll
+            for (int ti = 0; ti < TI; ++ti)
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) acc[ti][b][i] = 0.0f;
+
+            if (pass > 0) lds_block_sync();                    // (the tail before has left the space)
+            // The tail's batches wait for their state rows one after the other: a word of every 64 bytes of them is touched ahead of the
+            // sums, x^A by the lower half of the wave, x^T by the upper one.  (Lists with several tiles per wave have others' sums to wait behind.)
+            uint32_t touched[PIECES];
+            auto touch_rows = [&](int ti) {
+                const unsigned char* rows = static_cast<const unsigned char*>(g == 0 ? e.xA : e.xT);
+                const int p32 = mine ? entries[(slot * TI + ti) * kTile + col] : -1;
+#pragma unroll
+                for (int i = 0; i < PIECES; ++i) {
+                    touched[i] = 0;
+                    if (rows != nullptr && p32 >= 0 && i * 64 < nch * ES)
+                        touched[i] = *reinterpret_cast<const uint32_t*>(rows + ((int64_t)p32 * e.c + ch0) * ES + i * 64);
+                }
+            };
+            auto rows_arrived = [&]() {
+#pragma unroll
+                for (int i = 0; i < PIECES; ++i) asm volatile("" ::"v"(touched[i]));
+            };
+            if constexpr (TI == 1) touch_rows(0);
+            gather_tiles<T, NB, KS, TI, SH, (TI == 1 ? 4 : 1), (TI == 1 && NB <= 2 ? 8 : TI == 4 ? 2 : 4)>(
+                acc, rs_in, rs_w, base, need, taps, kch, cin_bytes, c.w * cin_bytes,
+                (uint32_t)cgroup * (uint32_t)ksteps * (uint32_t)(2 * COLS * 16) + (uint32_t)(g * COLS + col) * 16u, (uint32_t)(2 * COLS * 16),
+                buf, part, lane, mine);
+            if constexpr (TI == 1) rows_arrived();
+
+            // ---- tail: this wave's channel slice of each of its tiles -------------------------------
+            // (all tiles are staged first: their sums leave the registers to the state rows)
+            if constexpr (SH > 1) lds_block_sync(); else lds_wave_sync();   // (operands and staged sums share the space)
+#pragma unroll
+            for (int ti = 0; ti < TI; ++ti) stage_accumulators<T, NB>(acc[ti], stage + (size_t)(ti * kTile + col) * stage_stride, g);
+            lds_wave_sync();
+            if (e.act == DCNN_ACT_NONE && e.res_data == nullptr) {   // nothing to do to the sums
+                const int nvec = (nch + V - 1) / V, sub = lane % LP, grp = lane / LP;
+#pragma unroll 1
+                for (int ti = 0; ti < TI; ++ti) {
+#pragma unroll
+                    for (int it = 0; it < NIT; ++it) {
+                        const int ent = it * (kWave / LP) + grp, pe = mine ? entries[(slot * TI + ti) * kTile + ent] : -1;
+                        if (pe >= 0 && sub < nvec)
+                            raw_store<T, V>(static_cast<T*>(e.out_data) + (int64_t)pe * e.c + ch0 + sub * V,
+                                            raw_load<T, V>(reinterpret_cast<const T*>(stage + (size_t)(ti * kTile + ent) * stage_stride) + sub * V));
+                    }
+                }
+                continue;
+            }
+            const MaxExchange mx{xchg, SH, part};
+            const bool exchange = SH > 1 && full_tail && e.act != DCNN_ACT_NONE;
+#pragma unroll 1
+            for (int ti = 0; ti < TI; ++ti) {
+                const int p32 = mine ? entries[(slot * TI + ti) * kTile + col] : -1;
+                auto dx = [&](int ent, int64_t, int c0) -> Raw {
+                    return raw_load<T, V>(reinterpret_cast<const T*>(stage + (size_t)(ti * kTile + ent) * stage_stride) + (c0 - ch0));
+                };
+                uint32_t bits;
+                if (SH > 1 && exchange) bits = act_trunc_tile<T, V, 1, UB, true>(e, false, p32, lane, dx, ch0, nch, COLS, mx);
+                else bits = act_trunc_tile<T, V, 1, UB, false>(e, false, p32, lane, dx, ch0, nch, COLS, mx);
+                const int64_t tile = tile_of(wt, ti);
+                if (mine && full_tail && part == 0 && tile * kTile < count) {
+                    if (e.surv) { if (lane == 0) e.surv[tile] = bits; }
+                    else survivors += __popc(bits);
+                }
+            }
+        }
+    }
+    // one atomic per wave: a counter bumped once per tile by every wave serialises in L2
+    if (e.out_count && !e.surv && lane == 0 && survivors) atomicAdd(e.out_count, survivors);
+}
+
+// fp32: the matrix cores take sixteen times as long over a K-step as the vector memory path over its gathers, so every wave gathers for itself and
+// none waits for another (3x3 64->64 on 87 K pixels, a tenth flagged: 101 us, with shared operands 111).
 // The work of one workgroup with TI pixel tiles per wave and a ring of D operand sets (D - 1 K-steps in flight).
 // ROW (3x3, stride 1, padding 1): one gather per window ROW instead of one per tap.  The work list is ascending and
 // holds every output pixel with a flagged tap, so if an entry's left tap (dy, 0) is flagged, the output pixel to its
@@ -31,7 +254,7 @@ constexpr int kDirectWaves = 4;
 // per tile (the two edges are different lanes).  A third of the gather traffic of a kernel that L2 bounds, and the
 // weight operands of a row's three taps are multiplied with the same gathered registers.
 template <typename T, int NB, int KS, int TI, int D, bool ROW, bool SELF>
-__device__ __forceinline__ void conv_direct_body(const ListParam<SELF>& l, const ConvArgs& c, const EpilogueArgs& e, int npass, int cs,
+__device__ __forceinline__ void conv_lane_body(const ListParam<SELF>& l, const ConvArgs& c, const EpilogueArgs& e, int npass, int cs,
                                                  int64_t count, unsigned char* smem, const int32_t* self_px, const uint32_t* self_tap) {
     typedef typename Mma<T>::Vec Vec;
     constexpr int V = Elem<T>::VEC;
@@ -287,11 +510,13 @@ __device__ __forceinline__ void conv_direct_body(const ListParam<SELF>& l, const
 
 // Lists too short to keep the chip busy with TI tiles per wave run one tile per wave and a deeper ring instead
 // (more waves, more loads in flight); the length of the list is only known on the device.
-template <typename T, int NB, int KS, int TI, bool SELF>
+template <typename T, int NB, int KS, bool SELF>
 __global__ __launch_bounds__(kDirectWaves* kWave, 2) void conv_direct_kernel(ListParam<SELF> l, ConvArgs c, EpilogueArgs e, int npass, int cs,
                                                                              int blocked_min_tiles) {
     extern __shared__ __align__(16) unsigned char smem[];
     clear_ahead(e);
+    WarmL2 warm;
+    warm.request<kDirectWaves * kWave>(c.wpacked, (uint64_t)npass * cs * KS * KS * c.kch * (2 * NB * 32 * 16));
     if constexpr (SELF) {
         if ((int)blockIdx.x < l.writers) {
             local_write<kDirectWaves * kWave>(l, smem + l.lds_scratch);
@@ -308,27 +533,44 @@ __global__ __launch_bounds__(kDirectWaves* kWave, 2) void conv_direct_kernel(Lis
         const int all = local_run(l, smem + l.lds_list, rp.run, rp.part == 0, px, tap);
         const int share = run_share(all, l.run_parts, l.run_even), from = rp.part * share;
         const int count = min(all - from, share);              // (none where the run lists fewer)
+        warm.arrived();
         if (count <= 0) return;
-        conv_direct_body<T, NB, KS, 1, (NB >= 4 ? 6 : 8), false, SELF>(l, c, e, npass, cs, count, smem, px + from, l.want_taps ? tap + from : nullptr);
+        px += from;
+        tap = l.want_taps ? tap + from : nullptr;
+        if constexpr (sizeof(T) == 4) conv_lane_body<T, NB, KS, 1, (NB >= 4 ? 6 : 8), false, SELF>(l, c, e, npass, cs, count, smem, px, tap);
+        else if (cs == 4) conv_direct_body<T, NB, KS, 1, 4, true>(l, c, e, npass, count, smem, px, tap);
+        else if (cs == 2) conv_direct_body<T, NB, KS, 1, 2, true>(l, c, e, npass, count, smem, px, tap);
+        else conv_direct_body<T, NB, KS, 1, 1, true>(l, c, e, npass, count, smem, px, tap);
     } else {
         const int64_t count = list_count(l);
-        if (count >= (int64_t)blocked_min_tiles * kTile) {
-            if constexpr (KS == 3 && NB <= 2) {
-                // Row gathers pay when most taps of the listed windows are flagged.  Every flagged input pixel is a tap
-                // of (up to) nine listed outputs, so flagged inputs / listed outputs IS the mean fraction of flagged taps
-                // per window.  Measured on 3x3 128->128, 256x256 maps, uniform-random masks: all taps flagged 0.40 ->
-                // 0.30 ms, half of them 0.231 -> 0.243 ms, a tenth 0.127 -> 0.156 ms; hence three quarters.
-                // (an input that comes without a count: the rule of the resident-weight kernel, most of the map listed)
-                const bool dense_taps = c.in_count ? (int64_t)*c.in_count * 4 >= count * 3
-                                                   : count * 4 >= (int64_t)c.n * c.oh * c.ow * 3;
-                if (c.stride == 1 && c.pad == 1 && dense_taps) {
-                    conv_direct_body<T, NB, KS, (TI > 3 ? 3 : TI), 2, true, SELF>(l, c, e, npass, cs, count, smem, nullptr, nullptr);   // 3 tiles: two operand sets of 12 vectors fit beside 96 accumulators
-                    return;
+        warm.arrived();
+        const bool blocked = count >= (int64_t)blocked_min_tiles * kTile;
+        if constexpr (sizeof(T) == 4) {
+            if (blocked) {
+                if constexpr (KS == 3 && NB <= 2) {
+                    // Row gathers pay when most taps of the listed windows are flagged.  Every flagged input pixel is a tap
+                    // of (up to) nine listed outputs, so flagged inputs / listed outputs IS the mean fraction of flagged taps
+                    // per window; three quarters, as measured when fp16 layers took them too (halves: 4 % slower).
+                    // (an input that comes without a count: the rule of the resident-weight kernel, most of the map listed)
+                    const bool dense_taps = c.in_count ? (int64_t)*c.in_count * 4 >= count * 3
+                                                       : count * 4 >= (int64_t)c.n * c.oh * c.ow * 3;
+                    if (c.stride == 1 && c.pad == 1 && dense_taps) {
+                        conv_lane_body<T, NB, KS, 3, 2, true, SELF>(l, c, e, npass, cs, count, smem, nullptr, nullptr);   // 3 tiles: two operand sets of 12 vectors fit beside 96 accumulators
+                        return;
+                    }
                 }
+                conv_lane_body<T, NB, KS, direct_tiles(NB, 4, 4), 3, false, SELF>(l, c, e, npass, cs, count, smem, nullptr, nullptr);
+            } else {
+                conv_lane_body<T, NB, KS, 1, (NB >= 4 ? 6 : 8), false, SELF>(l, c, e, npass, cs, count, smem, nullptr, nullptr);
             }
-            conv_direct_body<T, NB, KS, TI, 3, false, SELF>(l, c, e, npass, cs, count, smem, nullptr, nullptr);
+        } else if (blocked) {
+            if (cs == 4) conv_direct_body<T, NB, KS, direct_tiles(NB, 2, 4), 4, false>(l, c, e, npass, count, smem, nullptr, nullptr);
+            else if (cs == 2) conv_direct_body<T, NB, KS, direct_tiles(NB, 2, 2), 2, false>(l, c, e, npass, count, smem, nullptr, nullptr);
+            else conv_direct_body<T, NB, KS, direct_tiles(NB, 2, 1), 1, false>(l, c, e, npass, count, smem, nullptr, nullptr);
         } else {
-            conv_direct_body<T, NB, KS, 1, (NB >= 4 ? 6 : 8), false, SELF>(l, c, e, npass, cs, count, smem, nullptr, nullptr);
+            if (cs == 4) conv_direct_body<T, NB, KS, 1, 4, false>(l, c, e, npass, count, smem, nullptr, nullptr);
+            else if (cs == 2) conv_direct_body<T, NB, KS, 1, 2, false>(l, c, e, npass, count, smem, nullptr, nullptr);
+            else conv_direct_body<T, NB, KS, 1, 1, false>(l, c, e, npass, count, smem, nullptr, nullptr);
         }
     }
 }

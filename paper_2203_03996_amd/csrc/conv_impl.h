@@ -628,8 +628,8 @@ static dcnn_status launch_conv_nb(dcnn_ctx* ctx, bool init, const ListArgs& l_in
     const bool blocked = p.stream && !init && (!direct || p.npass == 1) && vec_out && aligned && (c.k == 1 || c.k == 3) && ws_taps &&
                          in_bytes <= kWsMaxBytes && p.w_bytes <= kWsMaxBytes;
     if (blocked) {
-        constexpr int TI = NB <= 2 ? 4 : 2;               // pixel tiles per wave: a register block of 128 accumulators
-        const size_t b_lds = conv_stage_bytes(kDirectWaves, NB, sizeof(T) == 2 ? DCNN_F16 : DCNN_F32) + conv_xchg_bytes(kDirectWaves);
+        const int TI = direct_tiles(NB, (int)sizeof(T), p.cs);
+        const size_t b_lds = direct_lds_bytes(NB, (int)sizeof(T), p.cs, l.self != 0);
         const int64_t b_want = cdiv(max_tiles, kDirectWaves / p.cs);
         // TI tiles per wave once that still gives every SIMD of the chip a wave (the list's length is read on the device)
         const int blocked_min_tiles = (int)((int64_t)ctx->num_cu * 4 * TI / p.cs);
@@ -650,7 +650,7 @@ static dcnn_status launch_conv_nb(dcnn_ctx* ctx, bool init, const ListArgs& l_in
         if (b_all > kLdsBytes) return fail(ctx, DCNN_EUNSUPPORTED, "conv: a work list built in place does not fit LDS");
 #define DCNN_BLOCKED_LAUNCH(KS, SELF)                                                                            \
     do {                                                                                                         \
-        auto kern = conv_direct_kernel<T, NB, KS, TI, SELF>;                                                           \
+        auto kern = conv_direct_kernel<T, NB, KS, SELF>;                                                           \
         static bool attr_set = false;                                                                            \
         if (!attr_set) {                                                                                         \
             err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, \

@@ -82,7 +82,7 @@ struct ConvPlan {
 };
 
 inline size_t conv_stage_bytes(int waves, int nb, int dtype) { return (size_t)waves * kTile * (nb * 32 * dtype_size(dtype) + kStagePad); }
-inline size_t conv_xchg_bytes(int waves) { return (size_t)2 * waves * kTile * sizeof(float); }
+inline constexpr __host__ __device__ size_t conv_xchg_bytes(int waves) { return (size_t)2 * waves * kTile * sizeof(float); }
 
 // A k x k window over fewer channels than one 16-byte vector holds (network stems: 3 channels) would spend one
 // K-step per tap on mostly padding.  Its k*k*cin values are one flat K dimension instead: the weights

@@ -317,7 +317,9 @@ def test_conv3x3_row_gathers_on_structured_masks(pattern, nhw):
     check_delta(out, want, S, f"row gathers, {pattern}", slack=sum_slack(ref, d.zero_filled()))
 
 
-@pytest.mark.parametrize("S,cin,cout", [("f16", 64, 64), ("f16", 136, 24), ("f16", 24, 64), ("f32", 20, 40)])
+@pytest.mark.parametrize("S,cin,cout", [("f16", 64, 64), ("f16", 136, 24), ("f16", 24, 64), ("f32", 20, 40)] + [
+    # weights too large for LDS, tiles of one, two and four waves with one to four column blocks, whole and broken lines of channels
+    ("f16", 136, 64), ("f16", 128, 96), ("f16", 128, 128), ("f16", 104, 192), ("f16", 72, 256), ("f16", 64, 384), ("f16", 264, 32), ("f32", 72, 64)])
 def test_conv3x3_of_a_stream_has_the_same_bits_alone_and_in_a_batch(S, cin, cout):
     """One stream of 7 K pixels compacts blocks in place and gathers tap by tap; ten of them take a list from memory and, with most
     of the map listed, one gather per window row.  One to five groups of K-steps, the last one whole or not."""
