@@ -1,8 +1,7 @@
 // Sparse delta convolution on small maps with weights too large for LDS: one wave per (pixel tile, 32 output channels).
 //
 // The deep layers of a backbone multiply a few hundred listed pixels with megabytes of weights.  What sets the pace there
-// is the vector memory path of the compute units that take part: ~70 GB/s each (a 1 KB load instruction occupies it for
-// ~35 clocks whether its lines hit or not), so a 3x3 512->512 layer on 16 tiles that ran on 32 workgroups of four waves,
+// is the vector memory path of the compute units that take part, so a 3x3 512->512 layer on 16 tiles that ran on 32 workgroups of four waves,
 // each pulling 0.9 MB, took 54 us.  Here the work is cut as fine as it goes without splitting a sum -- the order of
 // every sum is tap by tap, as in the other kernels that serve such layers, so a stream gives the same bits whichever its batch size
 // selects (but for the register-blocked kernel's row gathers, on lists of tens of thousands of pixels with most taps flagged) --
@@ -14,11 +13,19 @@
 // 8192 21 / 28 / 32 -> 15 / 24 / 31.  3x3 256->256 on 4096 12.6 / 14.7 / 15.9 -> 11.4 / 15.3 / 16.2, with a quarter of it in one region 11.6 -> 14.0:
 // there every tile has a SIMD to itself.
 //
+// fp16 workgroups fetch their tile's operands once and share them through LDS (gather_tiles.h).  A wave each, a pixel
+// per lane -> shared, us a step with input and output layer, 2 / 10 / 50 / 100 % flagged at random: 3x3 128->512 on 8 streams of 32x32
+// 26 / 37 / 54 / 69 -> 23 / 32 / 41 / 41, 256->256 on 8 of 24x24 35 / 37 / 41 / 47 -> 30 / 31 / 33 / 34, 1x1 512->2048 on 2 of 64x64
+// 27 / 36 / 80 / 125 -> 25 / 30 / 56 / 83, 256->1024 on 8 of 28x28 19 / 21 / 33 / 46 -> 18 / 20 / 29 / 38.  A single wave takes that way too, for its sixteen weight operands in
+// flight: in a network, where a layer's weights come from beyond L2, a ResNet-50-shaped step is 1069 us instead of 1092 (alone, with its weights
+// in L2 from the step before, 3x3 512->512 on 512 pixels takes 37-39 us instead of 29-36).
+//
 // Layers without an activation only: a decision needs all channels of a pixel.  (Groups that leave their sums in memory and
 // a tail done by the last of a tile to arrive were built: the device-scope release and acquire that it takes cost
 // ~15 us a layer, 3x3 256->256 44 us against 32 in one workgroup.)
 #include "conv_plan.h"
 #include "conv_ws_impl.h"
+#include "gather_tiles.h"
 #include "self_list.h"
 
 namespace dcnn {
@@ -34,11 +41,15 @@ struct UnitArgs {
     uint32_t map_bytes, out_pixels;
 };
 
-// LDS: staging rows per wave | flags and prefix sums of a list built here
+// LDS: gathered operands of the tile (fp16) | staging rows per wave | flags and prefix sums of a list built here
 constexpr int kUnitStageRow(int es) { return 32 * es + kStagePad; }
-inline size_t unit_stage_bytes(int waves, int dtype) { return (size_t)waves * kTile * kUnitStageRow((int)dtype_size(dtype)); }
+constexpr int kUnitOperands(int es) { return es == 2 ? 2 * kGatherTile : 0; }
+inline size_t unit_stage_bytes(int waves, int dtype) {
+    return (size_t)kUnitOperands((int)dtype_size(dtype)) + (size_t)waves * kTile * kUnitStageRow((int)dtype_size(dtype));
+}
 
-template <typename T, int KS>
+// SH: the waves of the workgroup, which share the gathered operands of their tile (gather_tiles.h); 0: every wave gathers for itself (fp32)
+template <typename T, int KS, int SH>
 __global__ __launch_bounds__(kUnitMaxWaves* kWave) void conv_unit_kernel(ListArgs l, ConvArgs c, EpilogueArgs e, UnitArgs a) {
     typedef typename Mma<T>::Vec Vec;
     constexpr int V = Elem<T>::VEC;
@@ -51,7 +62,7 @@ __global__ __launch_bounds__(kUnitMaxWaves* kWave) void conv_unit_kernel(ListArg
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int nwaves = a.waves;
     const int col = lane % 32, g = lane / 32;
-    unsigned char* stage = smem + (size_t)wave * kTile * stage_row;
+    unsigned char* stage = smem + kUnitOperands(ES) + (size_t)wave * kTile * stage_row;
 
     // Units of this workgroup: u = first, first + step, ... below end.  Where blocks are compacted here they are the tiles of its share
     // of a run's entries, `tile_px` each, for one group of channels.
@@ -116,7 +127,7 @@ __global__ __launch_bounds__(kUnitMaxWaves* kWave) void conv_unit_kernel(ListArg
             const int ox = (int)(pu - t1 * (uint32_t)c.ow);
             const uint32_t n = fast_div(t1, c.div_oh);
             const int oy = (int)(t1 - n * (uint32_t)c.oh);
-            base = (uint32_t)(((int)n * c.h + oy * c.stride - c.pad) * c.w + ox * c.stride - c.pad) * (uint32_t)cin_bytes + (uint32_t)g * 16u;
+            base = (uint32_t)(((int)n * c.h + oy * c.stride - c.pad) * c.w + ox * c.stride - c.pad) * (uint32_t)cin_bytes + (SH > 0 ? 0u : (uint32_t)g * 16u);
         }
         uint32_t wave_taps = 0;                                // taps any lane of the wave needs
 #pragma unroll
@@ -124,9 +135,24 @@ __global__ __launch_bounds__(kUnitMaxWaves* kWave) void conv_unit_kernel(ListArg
             if (__ballot((taps >> t) & 1)) wave_taps |= 1u << t;
         const uint32_t wlane = ((uint32_t)(cb_on ? cb / a.nb : 0) * (uint32_t)ksteps * 2u * (uint32_t)cols + (uint32_t)g * (uint32_t)cols +
                                 (uint32_t)(cb_on ? cb % a.nb : 0) * 32u + (uint32_t)col) * 16u;
-        f32x16 acc[1];
+        f32x16 acc[1][1];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) acc[0][i] = 0.0f;
+        for (int i = 0; i < 16; ++i) acc[0][0][i] = 0.0f;
+        if constexpr (SH > 0) {
+            // the pixels this wave fetches, from the lanes whose columns they are
+            typedef GatherShare<1, SH> Share;
+            uint32_t from[Share::kLoads], need[Share::kWords];
+#pragma unroll
+            for (int i = 0; i < Share::kWords; ++i) need[i] = 0;
+#pragma unroll
+            for (int i = 0; i < Share::kLoads; ++i) {
+                const int at = col / 4 * 4 + Share::pixel(wave, i);
+                from[i] = (uint32_t)__shfl((int)base, at, kWave);
+                need[i / 3] |= ((uint32_t)__shfl((int)taps, at, kWave) & ((1u << (KS * KS)) - 1u)) << (9 * (i % 3));
+            }
+            gather_tiles<T, 1, KS, 1, SH, 4, 16>(acc, rs_in, rs_w, from, need, wave_taps, kch, cin_bytes, c.w * cin_bytes, cb_on ? wlane : kOob, wstride,
+                                                 smem, wave, lane, true);
+        } else {
         // Groups of kUnitGroup K-steps of one tap, two register sets.  One wave per SIMD has its own instructions to wait for
         // (4-8 clocks each), so a group's addresses are formed once: the gathers of its steps differ by an immediate, the
         // weights by a scalar offset.  With a cursor advanced and an address formed per step the loop took 310 clocks a
@@ -170,7 +196,7 @@ __global__ __launch_bounds__(kUnitMaxWaves* kWave) void conv_unit_kernel(ListArg
         };
         auto mma = [&](const Set& st) __attribute__((always_inline)) {
 #pragma unroll
-            for (int i = 0; i < kUnitGroup; ++i) Mma<T>::run(acc[0], st.w[i], st.x[i]);
+            for (int i = 0; i < kUnitGroup; ++i) Mma<T>::run(acc[0][0], st.w[i], st.x[i]);
             __builtin_amdgcn_sched_barrier(0);
         };
         if (cb_on && wave_taps) {
@@ -186,8 +212,9 @@ __global__ __launch_bounds__(kUnitMaxWaves* kWave) void conv_unit_kernel(ListArg
                 left -= 2;
             }
         }
+        }
         // rounded sums -> staging rows -> the pixels' rows, 16 bytes per lane
-        stage_accumulators<T, 1>(acc, stage + (size_t)col * stage_row, g);
+        stage_accumulators<T, 1>(acc[0], stage + (size_t)col * stage_row, g);
         lds_wave_sync();
         constexpr int LPB = 32 / V;                            // lanes per pixel
 #pragma unroll
@@ -271,8 +298,16 @@ static dcnn_status launch_conv_unit_t(dcnn_ctx* ctx, const ListArgs& l_in, const
         if (scratch > lds) lds = scratch;
     }
     const dim3 g(grid), b((l.self ? kUnitMaxWaves : waves) * kWave);
-    if (c.k == 1) hipLaunchKernelGGL((conv_unit_kernel<T, 1>), g, b, lds, ctx->stream, l, c, e, a);
-    else hipLaunchKernelGGL((conv_unit_kernel<T, 3>), g, b, lds, ctx->stream, l, c, e, a);
+#define DCNN_UNIT_LAUNCH(SH)                                                                                     \
+    do {                                                                                                         \
+        if (c.k == 1) hipLaunchKernelGGL((conv_unit_kernel<T, 1, SH>), g, b, lds, ctx->stream, l, c, e, a);      \
+        else hipLaunchKernelGGL((conv_unit_kernel<T, 3, SH>), g, b, lds, ctx->stream, l, c, e, a);               \
+    } while (0)
+    if constexpr (sizeof(T) == 4) DCNN_UNIT_LAUNCH(0);
+    else if (waves == 4) DCNN_UNIT_LAUNCH(4);
+    else if (waves == 2) DCNN_UNIT_LAUNCH(2);
+    else DCNN_UNIT_LAUNCH(1);
+#undef DCNN_UNIT_LAUNCH
     return check_hip(ctx, hipGetLastError(), "conv_unit_kernel launch");
 }
 
