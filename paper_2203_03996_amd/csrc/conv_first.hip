@@ -379,6 +379,14 @@ static bool first_splits(const ConvArgs& c) {
 // channels: 5x5 128->32 240 us, now 154, plain kernel 178).
 static bool first_narrow(const ConvArgs& c) { return c.cout <= 32; }
 
+// ... and where tiles of 64 leave compute units without a workgroup (their width changes no sum): a step of the layer's network, 64 -> 32
+// channels a tile: 3x3 512->512 on 512 pixels 30.5 -> 28.0 us, 128->128 on 100x100 32.3 -> 26.6, 1x1 64->256 on 64x64 17.4 -> 14.9,
+// fp32 3x3 256->256 on 2048 pixels 59.9 -> 44.5; the first frame of a ResNet-50-shaped network of 8 streams 757 -> 703.
+static bool first_halves(const ConvArgs& c, bool split, int64_t pixels, int num_cu) {
+    const int64_t tiles = cdiv(pixels, kFirstPx) * cdiv(c.cout, 64);
+    return (split ? tiles : cdiv(tiles, kFirstWaves)) < num_cu;
+}
+
 // (What decides between sums in one chain and split ones looks at one stream; kernels that sum in one chain give the same bits.)
 bool conv_first_supported(int dtype, const ConvArgs& c, const ConvPlan& p) {
     const size_t es = dtype_size(dtype);
@@ -408,8 +416,8 @@ static dcnn_status launch_conv_first_t(dcnn_ctx* ctx, const ConvArgs& c, const E
     f.pixels = (int64_t)c.n * c.oh * c.ow;
     f.bias2 = bias2;
     const int64_t ptiles = cdiv(f.pixels, kFirstPx);
-    const bool split = first_splits(c), narrow = first_narrow(c);
-    const int ctiles = narrow ? 1 : (int)cdiv(e.c, 64);
+    const bool split = first_splits(c), narrow = first_narrow(c) || first_halves(c, split, f.pixels, ctx->num_cu);
+    const int ctiles = (int)cdiv(e.c, narrow ? 32 : 64);
     f.wc = split ? 1 : (ctiles % 4 == 0 ? 4 : (ctiles % 2 == 0 ? 2 : 1));      // (no wave without channels)
     f.cgroups = (int)cdiv(ctiles, f.wc);
     f.units = (split ? ptiles : cdiv(ptiles, kFirstWaves / f.wc)) * f.cgroups;
