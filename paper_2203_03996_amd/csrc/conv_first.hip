@@ -379,13 +379,13 @@ static bool first_splits(const ConvArgs& c) {
 // channels: 5x5 128->32 240 us, now 154, plain kernel 178).
 static bool first_narrow(const ConvArgs& c) { return c.cout <= 32; }
 
-// ... and where tiles of 64 leave compute units with fewer than two workgroups (their width changes no sum): a step of the layer's network, 64 -> 32
+// ... and where tiles of 64 leave compute units without a workgroup, or with fewer than two of whole sums (their width changes no sum): a step of the layer's network, 64 -> 32
 // channels a tile: 3x3 512->512 on 512 pixels 30.5 -> 28.0 us, 128->128 on 100x100 32.3 -> 26.6, 1x1 64->256 on 64x64 17.4 -> 14.9,
 // fp32 3x3 256->256 on 2048 pixels 59.9 -> 44.5; the first frame of a ResNet-50-shaped network of 8 streams
-// 757 -> 695 (703 with the line at one workgroup: 1x1 128->512 on 8192 pixels 31.4 -> 29.6, 3x3 96->160 on 6400 21.4 -> 19.9).
+// 757 -> 692 (703 with the line at one workgroup for both, 695 at two).
 static bool first_halves(const ConvArgs& c, bool split, int64_t pixels, int num_cu) {
     const int64_t tiles = cdiv(pixels, kFirstPx) * cdiv(c.cout, 64);
-    return (split ? tiles : cdiv(tiles, kFirstWaves)) < 2 * num_cu;
+    return split ? tiles < num_cu : cdiv(tiles, kFirstWaves) < 2 * num_cu;
 }
 
 // (What decides between sums in one chain and split ones looks at one stream; kernels that sum in one chain give the same bits.)
