@@ -4,7 +4,7 @@
 // is the vector memory path of the compute units that take part, so a 3x3 512->512 layer on 16 tiles that ran on 32 workgroups of four waves,
 // each pulling 0.9 MB, took 54 us.  Here the work is cut as fine as it goes without splitting a sum -- the order of
 // every sum is tap by tap, as in the other kernels that serve such layers, so a stream gives the same bits whichever its batch size
-// selects (but for the register-blocked kernel's row gathers, on lists of tens of thousands of pixels with most taps flagged) --
+// selects (but for the register-blocked kernel's row gathers in fp32, on lists of tens of thousands of pixels with most taps flagged) --
 // and spread over the chip: unit u = (tile u / G, channel group u % G), and since workgroup b runs on XCD b % 8, a group's
 // weights are fetched into the L2 of one XCD only (of 8 / G, for fewer than 8 groups).  A layer that compacts blocks in place does so
 // by runs of 256 pixels (local_run): tiles of 32 pixels as they lie hold a few listed ones each when flags are scattered and cost their
