@@ -16,9 +16,11 @@
 // fp16 workgroups fetch their tile's operands once and share them through LDS (gather_tiles.h).  A wave each, a pixel
 // per lane -> shared, us a step with input and output layer, 2 / 10 / 50 / 100 % flagged at random: 3x3 128->512 on 8 streams of 32x32
 // 26 / 37 / 54 / 69 -> 23 / 32 / 41 / 41, 256->256 on 8 of 24x24 35 / 37 / 41 / 47 -> 30 / 31 / 33 / 34, 1x1 512->2048 on 2 of 64x64
-// 27 / 36 / 80 / 125 -> 25 / 30 / 56 / 83, 256->1024 on 8 of 28x28 19 / 21 / 33 / 46 -> 18 / 20 / 29 / 38.  A single wave takes that way too, for its sixteen weight operands in
-// flight: in a network, where a layer's weights come from beyond L2, a ResNet-50-shaped step is 1069 us instead of 1092 (alone, with its weights
-// in L2 from the step before, 3x3 512->512 on 512 pixels takes 37-39 us instead of 29-36).
+// 27 / 36 / 80 / 125 -> 25 / 30 / 56 / 83, 256->1024 on 8 of 28x28 19 / 21 / 33 / 46 -> 18 / 20 / 29 / 38.  A single wave takes that way on sums of
+// kUnitLongSum K-steps and more, for its sixteen weight operands in flight: in a network, where a layer's weights come from beyond L2, a
+// ResNet-50-shaped step of 8 streams is 1069 us instead of 1092 (alone, with its weights in L2 from the step before, 3x3 512->512 on 512 pixels
+// takes 37-39 us instead of 29-36).  Shorter ones only wait for LDS: MobileNet-shaped steps of 1 / 2 / 4 small streams 276 / 269 / 333 us
+// that way and 274 / 266 / 330 with a gather per lane, ResNet-50-shaped ones of 1 / 3 streams 930 / 952 and 914 / 931.
 //
 // Layers without an activation only: a decision needs all channels of a pixel.  (Groups that leave their sums in memory and
 // a tail done by the last of a tile to arrive were built: the device-scope release and acquire that it takes cost
@@ -32,6 +34,7 @@ namespace dcnn {
 
 constexpr int kUnitGroup = 8;                                  // K-steps whose operands are requested together
 constexpr int kUnitMaxWaves = 4;
+constexpr int kUnitLongSum = 96;                               // K-steps from which a single wave goes through LDS (fp16)
 
 struct UnitArgs {
     int nb;                        // column blocks per packed channel group (the layer's plan)
@@ -303,7 +306,7 @@ static dcnn_status launch_conv_unit_t(dcnn_ctx* ctx, const ListArgs& l_in, const
         if (c.k == 1) hipLaunchKernelGGL((conv_unit_kernel<T, 1, SH>), g, b, lds, ctx->stream, l, c, e, a);      \
         else hipLaunchKernelGGL((conv_unit_kernel<T, 3, SH>), g, b, lds, ctx->stream, l, c, e, a);               \
     } while (0)
-    if constexpr (sizeof(T) == 4) DCNN_UNIT_LAUNCH(0);
+    if (sizeof(T) == 4 || (waves == 1 && c.k * c.k * c.kch < kUnitLongSum)) DCNN_UNIT_LAUNCH(0);
     else if (waves == 4) DCNN_UNIT_LAUNCH(4);
     else if (waves == 2) DCNN_UNIT_LAUNCH(2);
     else DCNN_UNIT_LAUNCH(1);

@@ -1119,6 +1119,17 @@ def test_conv_per_channel_block(S, k, stride, cin, cout, nhw, res):
         check_delta(out, want.poisoned(), S, f"density {dens}", slack=slack)
 
 
+@pytest.mark.parametrize("S,k,stride,cin,cout,nhw,res", [
+    ("f16", 3, 1, 72, 392, (3, 40, 41), False),      # four waves to a tile, the last of 13 channel blocks alone; a line and a part
+    ("f16", 3, 1, 72, 392, (1, 50, 51), False),      # two
+    ("f16", 1, 1, 520, 1048, (2, 32, 37), True),     # four, nine lines with a residual
+    ("f16", 1, 1, 1552, 264, (1, 9, 10), False),     # one, a sum long enough to go through LDS
+])
+def test_conv_per_channel_block_with_shared_operands(S, k, stride, cin, cout, nhw, res):
+    """fp16 units whose waves share the gathered operands of their tile."""
+    test_conv_per_channel_block(S, k, stride, cin, cout, nhw, res)
+
+
 @pytest.mark.parametrize("S,kind,k,stride,cin,cout,nhw", [
     ("f16", "conv", 3, 1, 32, 32, (1, 20, 23)),          # resident weights
     ("f16", "conv", 3, 2, 64, 128, (2, 21, 18)),
