@@ -17,6 +17,7 @@
 // K-steps -> quads, us: 3x3 256->256 on 8 streams of 64x64 104 -> 64, 512->512 on 512 pixels 29 -> 17, 1x1 64->64 and 3x3 64->64 on 64
 // streams of 128x128 together 321 -> 255.
 #include "conv_plan.h"
+#include "kstep.h"
 
 namespace dcnn {
 
@@ -188,9 +189,11 @@ __global__ __launch_bounds__(kFirstWaves* kWave, 2) void conv_first_kernel(ConvA
             }
         };
         auto request_w = [&](int u) __attribute__((always_inline)) {
-            const uint32_t step = (uint32_t)((dy * ksz + dx) * kch + kg * kFirstGroup + u) * wrow;
+            const int tap = dy * ksz + dx;                     // (STEPS 1, one K-step a tap: the taps are the steps of a single one)
+            const int of = STEPS == 1 ? 0 : tap, steps = STEPS == 1 ? ksteps : kch, at = (STEPS == 1 ? tap : kg * kFirstGroup) + u;
+            const uint32_t step = (uint32_t)weight_step(of, steps, at) * wrow;
 #pragma unroll
-            for (int b = 0; b < TC; ++b) w[u][b] = ws_load16<Vec>(rs_w, (STEPS == 1 ? dy * ksz + dx : kg * kFirstGroup) + u < (STEPS == 1 ? ksteps : kch) ? wlane[b] : kOob, step);
+            for (int b = 0; b < TC; ++b) w[u][b] = ws_load16<Vec>(rs_w, at < steps ? wlane[b] : kOob, step);
         };
         auto mma = [&](int u, const Part& part, const Vec (&v)[TP][kFirstGroup]) __attribute__((always_inline)) {
             if (SPLIT != 1 && (u < part.lo || u >= part.hi)) return;

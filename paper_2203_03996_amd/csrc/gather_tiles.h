@@ -12,6 +12,7 @@
 #pragma once
 
 #include "conv_plan.h"
+#include "kstep.h"
 
 namespace dcnn {
 
@@ -96,7 +97,7 @@ __device__ __forceinline__ void gather_tiles(f32x16 (&acc)[TI][NB], __amdgpu_buf
     };
     auto request_w = [&](const Cur& cu, int u, Vec (&w)[NB]) __attribute__((always_inline)) {
         const int kc = cu.kg * GK + u;                         // (a group's last steps may be padding, which meets zeros)
-        const uint32_t voff = kc < kch ? wlane : kOob, soff = (uint32_t)((cu.t == kNoTap ? 0 : cu.t) * kch + kc) * wstep;
+        const uint32_t voff = kc < kch ? wlane : kOob, soff = (uint32_t)weight_step(cu.t == kNoTap ? 0 : cu.t, kch, kc) * wstep;
 #pragma unroll
         for (int b = 0; b < NB; ++b) w[b] = ws_load16<Vec>(rs_w, voff + (uint32_t)b * (32u * 16u), soff);
     };
