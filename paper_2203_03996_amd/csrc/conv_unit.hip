@@ -60,6 +60,7 @@ __global__ __launch_bounds__(kUnitMaxWaves* kWave) void conv_unit_kernel(ListArg
     constexpr int ES = (int)sizeof(T);
     constexpr int kNoTap = 31;
     constexpr int stage_row = kUnitStageRow(ES);
+    static_assert(SH == 0 || kUnitOperands(ES) > 0, "shared operands have a space of their own");
     extern __shared__ __align__(16) unsigned char smem[];
     const int lane = threadIdx.x % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -306,7 +307,8 @@ static dcnn_status launch_conv_unit_t(dcnn_ctx* ctx, const ListArgs& l_in, const
         if (c.k == 1) hipLaunchKernelGGL((conv_unit_kernel<T, 1, SH>), g, b, lds, ctx->stream, l, c, e, a);      \
         else hipLaunchKernelGGL((conv_unit_kernel<T, 3, SH>), g, b, lds, ctx->stream, l, c, e, a);               \
     } while (0)
-    if (sizeof(T) == 4 || (waves == 1 && c.k * c.k * c.kch < kUnitLongSum)) DCNN_UNIT_LAUNCH(0);
+    if constexpr (sizeof(T) == 4) DCNN_UNIT_LAUNCH(0);
+    else if (waves == 1 && c.k * c.k * c.kch < kUnitLongSum) DCNN_UNIT_LAUNCH(0);
     else if (waves == 4) DCNN_UNIT_LAUNCH(4);
     else if (waves == 2) DCNN_UNIT_LAUNCH(2);
     else DCNN_UNIT_LAUNCH(1);
