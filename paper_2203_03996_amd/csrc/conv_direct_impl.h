@@ -52,6 +52,8 @@ __device__ __forceinline__ void conv_direct_body(const ListParam<SELF>& l, const
     constexpr int LP = direct_pow2_ceil(COLS / V), NIT = kTile / (kWave / LP);   // lanes per pixel of the tail, rows of a tile per lane
     constexpr int UB = TI == 1 || NIT < 4 ? 2 : 4;              // rows of a batch (of a single tile two: less code)
     constexpr int PIECES = COLS * ES / 64;                     // 64-byte pieces of a row of this wave's channels
+    // K-steps of weights in flight (more spill: eight of two blocks beside the sixteen vectors of a tile that a wave fetches alone)
+    constexpr int kAheadW = TI == 4 ? 2 : TI == 1 && NB <= 2 && NB <= SH ? 8 : 4;
     static_assert(LP >= 2 && LP <= kWave, "a pixel's channels on neighbouring lanes");
     static_assert(sizeof(Vec) == 16, "16-byte operand vectors");
 
@@ -194,7 +196,7 @@ __device__ __forceinline__ void conv_direct_body(const ListParam<SELF>& l, const
                 for (int i = 0; i < PIECES; ++i) asm volatile("" ::"v"(touched[i]));
             };
             if constexpr (TI == 1) touch_rows(0);
-            gather_tiles<T, NB, KS, TI, SH, (TI == 1 ? 4 : 1), (TI == 1 && NB <= 2 ? 8 : TI == 4 ? 2 : 4)>(
+            gather_tiles<T, NB, KS, TI, SH, (TI == 1 ? 4 : 1), kAheadW>(
                 acc, rs_in, rs_w, base, need, taps, kch, cin_bytes, c.w * cin_bytes,
                 (uint32_t)cgroup * (uint32_t)ksteps * (uint32_t)(2 * COLS * 16) + (uint32_t)(g * COLS + col) * 16u, (uint32_t)(2 * COLS * 16),
                 buf, part, lane, mine);
@@ -203,11 +205,14 @@ __device__ __forceinline__ void conv_direct_body(const ListParam<SELF>& l, const
             // ---- tail: this wave's channel slice of each of its tiles -------------------------------
             // (all tiles are staged first: their sums leave the registers to the state rows)
             if constexpr (SH > 1) lds_block_sync(); else lds_wave_sync();   // (operands and staged sums share the space)
+            int tlane = lane;
+            if constexpr (TI == 4 || SH == 1) asm volatile("" : "+v"(tlane));   // (what the tail derives from it is formed here, not kept through the sums)
+            const int tcol = tlane % 32;
 #pragma unroll
-            for (int ti = 0; ti < TI; ++ti) stage_accumulators<T, NB>(acc[ti], stage + (size_t)(ti * kTile + col) * stage_stride, g);
+            for (int ti = 0; ti < TI; ++ti) stage_accumulators<T, NB>(acc[ti], stage + (size_t)(ti * kTile + tcol) * stage_stride, tlane / 32);
             lds_wave_sync();
             if (e.act == DCNN_ACT_NONE && e.res_data == nullptr) {   // nothing to do to the sums
-                const int nvec = (nch + V - 1) / V, sub = lane % LP, grp = lane / LP;
+                const int nvec = (nch + V - 1) / V, sub = tlane % LP, grp = tlane / LP;
 #pragma unroll 1
                 for (int ti = 0; ti < TI; ++ti) {
 #pragma unroll
@@ -224,16 +229,16 @@ __device__ __forceinline__ void conv_direct_body(const ListParam<SELF>& l, const
             const bool exchange = SH > 1 && full_tail && e.act != DCNN_ACT_NONE;
 #pragma unroll 1
             for (int ti = 0; ti < TI; ++ti) {
-                const int p32 = mine ? entries[(slot * TI + ti) * kTile + col] : -1;
+                const int p32 = mine ? entries[(slot * TI + ti) * kTile + tcol] : -1;
                 auto dx = [&](int ent, int64_t, int c0) -> Raw {
                     return raw_load<T, V>(reinterpret_cast<const T*>(stage + (size_t)(ti * kTile + ent) * stage_stride) + (c0 - ch0));
                 };
                 uint32_t bits;
-                if (SH > 1 && exchange) bits = act_trunc_tile<T, V, 1, UB, true>(e, false, p32, lane, dx, ch0, nch, COLS, mx);
-                else bits = act_trunc_tile<T, V, 1, UB, false>(e, false, p32, lane, dx, ch0, nch, COLS, mx);
+                if (SH > 1 && exchange) bits = act_trunc_tile<T, V, 1, UB, true>(e, false, p32, tlane, dx, ch0, nch, COLS, mx);
+                else bits = act_trunc_tile<T, V, 1, UB, false>(e, false, p32, tlane, dx, ch0, nch, COLS, mx);
                 const int64_t tile = tile_of(wt, ti);
                 if (mine && full_tail && part == 0 && tile * kTile < count) {
-                    if (e.surv) { if (lane == 0) e.surv[tile] = bits; }
+                    if (e.surv) { if (tlane == 0) e.surv[tile] = bits; }
                     else survivors += __popc(bits);
                 }
             }
@@ -510,9 +515,13 @@ __device__ __forceinline__ void conv_lane_body(const ListParam<SELF>& l, const C
 
 // Lists too short to keep the chip busy with TI tiles per wave run one tile per wave and a deeper ring instead
 // (more waves, more loads in flight); the length of the list is only known on the device.
-template <typename T, int NB, int KS, bool SELF>
+// SH (fp16): the waves that share a tile, the plan's `cs`, one kernel each: with the bodies of all three in one kernel it spilled (28-36 bytes
+// of scratch a lane for two column blocks, 100 KB of code); 3x3 128->128 on 8 streams of 256x256 with a tenth of the pixels new, a
+// step 204 us -> 201, 128->64 on 8 of 128x128 with 2 % flagged 60 -> 58.  fp32, whose waves share nothing: 0, and `cs` as the kernel finds it.
+template <typename T, int NB, int KS, int SH, bool SELF>
 __global__ __launch_bounds__(kDirectWaves* kWave, 2) void conv_direct_kernel(ListParam<SELF> l, ConvArgs c, EpilogueArgs e, int npass, int cs,
                                                                              int blocked_min_tiles) {
+    static_assert((SH == 0) == (sizeof(T) == 4), "fp16 tiles are shared by a fixed number of waves");
     extern __shared__ __align__(16) unsigned char smem[];
     clear_ahead(e);
     WarmL2 warm;
@@ -538,9 +547,7 @@ __global__ __launch_bounds__(kDirectWaves* kWave, 2) void conv_direct_kernel(Lis
         px += from;
         tap = l.want_taps ? tap + from : nullptr;
         if constexpr (sizeof(T) == 4) conv_lane_body<T, NB, KS, 1, (NB >= 4 ? 6 : 8), false, SELF>(l, c, e, npass, cs, count, smem, px, tap);
-        else if (cs == 4) conv_direct_body<T, NB, KS, 1, 4, true>(l, c, e, npass, count, smem, px, tap);
-        else if (cs == 2) conv_direct_body<T, NB, KS, 1, 2, true>(l, c, e, npass, count, smem, px, tap);
-        else conv_direct_body<T, NB, KS, 1, 1, true>(l, c, e, npass, count, smem, px, tap);
+        else conv_direct_body<T, NB, KS, 1, SH, true>(l, c, e, npass, count, smem, px, tap);
     } else {
         const int64_t count = list_count(l);
         warm.arrived();
@@ -564,13 +571,9 @@ __global__ __launch_bounds__(kDirectWaves* kWave, 2) void conv_direct_kernel(Lis
                 conv_lane_body<T, NB, KS, 1, (NB >= 4 ? 6 : 8), false, SELF>(l, c, e, npass, cs, count, smem, nullptr, nullptr);
             }
         } else if (blocked) {
-            if (cs == 4) conv_direct_body<T, NB, KS, direct_tiles(NB, 2, 4), 4, false>(l, c, e, npass, count, smem, nullptr, nullptr);
-            else if (cs == 2) conv_direct_body<T, NB, KS, direct_tiles(NB, 2, 2), 2, false>(l, c, e, npass, count, smem, nullptr, nullptr);
-            else conv_direct_body<T, NB, KS, direct_tiles(NB, 2, 1), 1, false>(l, c, e, npass, count, smem, nullptr, nullptr);
+            conv_direct_body<T, NB, KS, direct_tiles(NB, 2, SH), SH, false>(l, c, e, npass, count, smem, nullptr, nullptr);
         } else {
-            if (cs == 4) conv_direct_body<T, NB, KS, 1, 4, false>(l, c, e, npass, count, smem, nullptr, nullptr);
-            else if (cs == 2) conv_direct_body<T, NB, KS, 1, 2, false>(l, c, e, npass, count, smem, nullptr, nullptr);
-            else conv_direct_body<T, NB, KS, 1, 1, false>(l, c, e, npass, count, smem, nullptr, nullptr);
+            conv_direct_body<T, NB, KS, 1, SH, false>(l, c, e, npass, count, smem, nullptr, nullptr);
         }
     }
 }

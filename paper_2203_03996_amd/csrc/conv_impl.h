@@ -648,9 +648,11 @@ static dcnn_status launch_conv_nb(dcnn_ctx* ctx, bool init, const ListArgs& l_in
             if (scratch > b_all) b_all = scratch;
         }
         if (b_all > kLdsBytes) return fail(ctx, DCNN_EUNSUPPORTED, "conv: a work list built in place does not fit LDS");
-#define DCNN_BLOCKED_LAUNCH(KS, SELF)                                                                            \
+        bool b_launched = false;
+#define DCNN_BLOCKED_LAUNCH(KS, SH, SELF)                                                                        \
     do {                                                                                                         \
-        auto kern = conv_direct_kernel<T, NB, KS, SELF>;                                                           \
+        b_launched = true;                                                                                       \
+        auto kern = conv_direct_kernel<T, NB, KS, SH, SELF>;                                                     \
         static bool attr_set = false;                                                                            \
         if (!attr_set) {                                                                                         \
             err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, \
@@ -661,9 +663,20 @@ static dcnn_status launch_conv_nb(dcnn_ctx* ctx, bool init, const ListArgs& l_in
             hipLaunchKernelGGL(kern, dim3(b_grid), dim3(kDirectWaves* kWave), b_all, ctx->stream, l, c, e, p.npass, p.cs, \
                                blocked_min_tiles);                                                       \
     } while (0)
-        if (c.k == 1) { if (l.self) DCNN_BLOCKED_LAUNCH(1, true); else DCNN_BLOCKED_LAUNCH(1, false); }
-        else { if (l.self) DCNN_BLOCKED_LAUNCH(3, true); else DCNN_BLOCKED_LAUNCH(3, false); }
+#define DCNN_BLOCKED_PICK(SH)                                                                                    \
+    do {                                                                                                         \
+        if (c.k == 1) { if (l.self) DCNN_BLOCKED_LAUNCH(1, SH, true); else DCNN_BLOCKED_LAUNCH(1, SH, false); }  \
+        else { if (l.self) DCNN_BLOCKED_LAUNCH(3, SH, true); else DCNN_BLOCKED_LAUNCH(3, SH, false); }           \
+    } while (0)
+        // (plans of streamed weights: two waves with two blocks go before one with four, one with two before two with one)
+        if constexpr (NB <= 3) {
+            if constexpr (sizeof(T) == 4) DCNN_BLOCKED_PICK(0);
+            else if (p.cs == 1) DCNN_BLOCKED_PICK(1);
+            else if constexpr (NB > 1) { if (p.cs == 4) DCNN_BLOCKED_PICK(4); else DCNN_BLOCKED_PICK(2); }
+        }
+#undef DCNN_BLOCKED_PICK
 #undef DCNN_BLOCKED_LAUNCH
+        if (!b_launched) return fail(ctx, DCNN_EUNSUPPORTED, "conv: no register-blocked kernel for %d column blocks on %d waves", NB, p.cs);
         if (err != hipSuccess) return check_hip(ctx, err, "hipFuncSetAttribute(conv_direct_kernel)");
         return check_hip(ctx, hipGetLastError(), "conv_direct_kernel launch");
     }
