@@ -13,14 +13,16 @@
 // 8192 21 / 28 / 32 -> 15 / 24 / 31.  3x3 256->256 on 4096 12.6 / 14.7 / 15.9 -> 11.4 / 15.3 / 16.2, with a quarter of it in one region 11.6 -> 14.0:
 // there every tile has a SIMD to itself.
 //
-// fp16 workgroups fetch their tile's operands once and share them through LDS (gather_tiles.h).  A wave each, a pixel
+// fp16 workgroups of four waves fetch their tile's operands once and share them through LDS (gather_tiles.h).  A wave each, a pixel
 // per lane -> shared, us a step with input and output layer, 2 / 10 / 50 / 100 % flagged at random: 3x3 128->512 on 8 streams of 32x32
-// 26 / 37 / 54 / 69 -> 23 / 32 / 41 / 41, 256->256 on 8 of 24x24 35 / 37 / 41 / 47 -> 30 / 31 / 33 / 34, 1x1 512->2048 on 2 of 64x64
-// 27 / 36 / 80 / 125 -> 25 / 30 / 56 / 83, 256->1024 on 8 of 28x28 19 / 21 / 33 / 46 -> 18 / 20 / 29 / 38.  A single wave takes that way on sums of
-// kUnitLongSum K-steps and more, for its sixteen weight operands in flight: in a network, where a layer's weights come from beyond L2, a
-// ResNet-50-shaped step of 8 streams is 1069 us instead of 1092 (alone, with its weights in L2 from the step before, 3x3 512->512 on 512 pixels
-// takes 37-39 us instead of 29-36).  Shorter ones only wait for LDS: MobileNet-shaped steps of 1 / 2 / 4 small streams 276 / 269 / 333 us
-// that way and 274 / 266 / 330 with a gather per lane, ResNet-50-shaped ones of 1 / 3 streams 930 / 952 and 914 / 931.
+// 25 / 37 / 54 / 69 -> 23 / 32 / 42 / 43, 72->392 on 2 of 60x60 24 / 35 / 44 / 44 -> 22 / 30 / 38 / 37, 1x1 512->2048 on 2 of 64x64
+// 27 / 36 / 80 / 124 -> 26 / 30 / 57 / 84, 256->1024 on 8 of 16x16 18 / 19 / 23 / 25 -> 18 / 18 / 21 / 22.  Smaller workgroups are those of layers
+// that give a SIMD a wave or two, which wait for each other and for LDS: there every wave gathers for itself.  A wave each -> shared: two waves,
+// 3x3 128->512 on 56x56 19 / 25 / 33 / 40 -> 21 / 30 / 35 / 35, 72->392 on 50x50 19 / 22 / 25 / 26 -> 20 / 23 / 30 / 30, 1x1 256->512 on 8 of 16x16
+// 17 / 17 / 19 / 21 -> 17 / 18 / 21 / 22; one wave, 3x3 512->512 on 16x16 29 / 30 / 33 / 37 -> 38 / 39 / 40 / 40.  (Sixteen weight operands in flight
+// helped where weights come from beyond every cache: three ResNet-50-shaped networks of 8 streams stepped in turn, 1077 us a step that way,
+// 1088 this way; one such network stepped alone 1009 and 991.  Three or four register sets per wave, the same: 3x3 512->512 on 16x16
+// 28, but 256->256 on 8 of 16x16 with everything flagged 29 -> 33 / 37, for want of a second workgroup per compute unit.)
 //
 // Layers without an activation only: a decision needs all channels of a pixel.  (Groups that leave their sums in memory and
 // a tail done by the last of a tile to arrive were built: the device-scope release and acquire that it takes cost
@@ -34,7 +36,6 @@ namespace dcnn {
 
 constexpr int kUnitGroup = 8;                                  // K-steps whose operands are requested together
 constexpr int kUnitMaxWaves = 4;
-constexpr int kUnitLongSum = 96;                               // K-steps from which a single wave goes through LDS (fp16)
 
 struct UnitArgs {
     int nb;                        // column blocks per packed channel group (the layer's plan)
@@ -51,7 +52,8 @@ inline size_t unit_stage_bytes(int waves, int dtype) {
     return (size_t)kUnitOperands((int)dtype_size(dtype)) + (size_t)waves * kTile * kUnitStageRow((int)dtype_size(dtype));
 }
 
-// SH: the waves of the workgroup, which share the gathered operands of their tile (gather_tiles.h); 0: every wave gathers for itself (fp32)
+// SH: the waves of the workgroup, which share the gathered operands of their tile (gather_tiles.h); 0: every wave gathers for itself (fp32,
+// and fewer than four waves)
 template <typename T, int KS, int SH>
 __global__ __launch_bounds__(kUnitMaxWaves* kWave) void conv_unit_kernel(ListArgs l, ConvArgs c, EpilogueArgs e, UnitArgs a) {
     typedef typename Mma<T>::Vec Vec;
@@ -308,10 +310,8 @@ static dcnn_status launch_conv_unit_t(dcnn_ctx* ctx, const ListArgs& l_in, const
         else hipLaunchKernelGGL((conv_unit_kernel<T, 3, SH>), g, b, lds, ctx->stream, l, c, e, a);               \
     } while (0)
     if constexpr (sizeof(T) == 4) DCNN_UNIT_LAUNCH(0);
-    else if (waves == 1 && c.k * c.k * c.kch < kUnitLongSum) DCNN_UNIT_LAUNCH(0);
-    else if (waves == 4) DCNN_UNIT_LAUNCH(4);
-    else if (waves == 2) DCNN_UNIT_LAUNCH(2);
-    else DCNN_UNIT_LAUNCH(1);
+    else if (waves == kUnitMaxWaves) DCNN_UNIT_LAUNCH(kUnitMaxWaves);
+    else DCNN_UNIT_LAUNCH(0);
 #undef DCNN_UNIT_LAUNCH
     return check_hip(ctx, hipGetLastError(), "conv_unit_kernel launch");
 }

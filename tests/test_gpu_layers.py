@@ -1121,9 +1121,9 @@ def test_conv_per_channel_block(S, k, stride, cin, cout, nhw, res):
 
 @pytest.mark.parametrize("S,k,stride,cin,cout,nhw,res", [
     ("f16", 3, 1, 72, 392, (3, 40, 41), False),      # four waves to a tile, the last of 13 channel blocks alone; a line and a part
-    ("f16", 3, 1, 72, 392, (1, 50, 51), False),      # two
+    ("f16", 3, 1, 72, 392, (1, 50, 51), False),      # two waves, each for itself
     ("f16", 1, 1, 520, 1048, (2, 32, 37), True),     # four, nine lines with a residual
-    ("f16", 1, 1, 1552, 264, (1, 9, 10), False),     # one, a sum long enough to go through LDS
+    ("f16", 1, 1, 1552, 264, (1, 9, 10), False),     # one, a long sum
 ])
 def test_conv_per_channel_block_with_shared_operands(S, k, stride, cin, cout, nhw, res):
     """fp16 units whose waves share the gathered operands of their tile."""
