@@ -45,11 +45,12 @@ struct UnitArgs {
     uint32_t map_bytes, out_pixels;
 };
 
-// LDS: gathered operands of the tile (fp16) | staging rows per wave | flags and prefix sums of a list built here
+// LDS: gathered operands of the tile (where shared) | staging rows per wave | flags and prefix sums of a list built here
 constexpr int kUnitStageRow(int es) { return 32 * es + kStagePad; }
-constexpr int kUnitOperands(int es) { return es == 2 ? 2 * kGatherTile : 0; }
-inline size_t unit_stage_bytes(int waves, int dtype) {
-    return (size_t)kUnitOperands((int)dtype_size(dtype)) + (size_t)waves * kTile * kUnitStageRow((int)dtype_size(dtype));
+constexpr int kUnitOperands(int sh) { return sh > 0 ? 2 * kGatherTile : 0; }
+inline bool unit_shares(int waves, int es) { return es == 2 && waves == kUnitMaxWaves; }
+inline size_t unit_stage_bytes(int waves, int es) {
+    return (size_t)kUnitOperands(unit_shares(waves, es) ? waves : 0) + (size_t)waves * kTile * kUnitStageRow(es);
 }
 
 // SH: the waves of the workgroup, which share the gathered operands of their tile (gather_tiles.h); 0: every wave gathers for itself (fp32,
@@ -62,13 +63,13 @@ __global__ __launch_bounds__(kUnitMaxWaves* kWave) void conv_unit_kernel(ListArg
     constexpr int ES = (int)sizeof(T);
     constexpr int kNoTap = 31;
     constexpr int stage_row = kUnitStageRow(ES);
-    static_assert(SH == 0 || kUnitOperands(ES) > 0, "shared operands have a space of their own");
+    static_assert(SH == 0 || (SH == kUnitMaxWaves && ES == 2), "as unit_shares");
     extern __shared__ __align__(16) unsigned char smem[];
     const int lane = threadIdx.x % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int nwaves = a.waves;
     const int col = lane % 32, g = lane / 32;
-    unsigned char* stage = smem + kUnitOperands(ES) + (size_t)wave * kTile * stage_row;
+    unsigned char* stage = smem + kUnitOperands(SH) + (size_t)wave * kTile * stage_row;
 
     // Units of this workgroup: u = first, first + step, ... below end.  Where blocks are compacted here they are the tiles of its share
     // of a run's entries, `tile_px` each, for one group of channels.
@@ -278,7 +279,6 @@ bool conv_unit_supported(const dcnn_ctx* ctx, int dtype, const ListArgs& l, cons
 template <typename T>
 static dcnn_status launch_conv_unit_t(dcnn_ctx* ctx, const ListArgs& l_in, const ConvArgs& c, const EpilogueArgs& e, const ConvPlan& p) {
     ListArgs l = l_in;
-    const int dtype = sizeof(T) == 2 ? DCNN_F16 : DCNN_F32;
     const int64_t out_px = (int64_t)c.n * c.oh * c.ow, tiles = cdiv(out_px, kTile);
     UnitArgs a{};
     a.nb = p.nb;
@@ -290,7 +290,7 @@ static dcnn_status launch_conv_unit_t(dcnn_ctx* ctx, const ListArgs& l_in, const
     a.waves = waves;
     const int64_t want = tiles * a.groups, cap = (int64_t)ctx->num_cu * 8;
     int grid = (int)(cdiv(want < cap ? want : cap, kXcd) * kXcd);
-    size_t lds = unit_stage_bytes(waves, dtype);
+    size_t lds = unit_stage_bytes(waves, (int)sizeof(T));
     if (l.self) {
         // (multiples of 8 keep a channel group on its XCD; writers form the flags of the whole map: four waves.  LDS: entries behind
         // the staging rows; a writer uses the space from 0 on)
@@ -309,9 +309,12 @@ static dcnn_status launch_conv_unit_t(dcnn_ctx* ctx, const ListArgs& l_in, const
         if (c.k == 1) hipLaunchKernelGGL((conv_unit_kernel<T, 1, SH>), g, b, lds, ctx->stream, l, c, e, a);      \
         else hipLaunchKernelGGL((conv_unit_kernel<T, 3, SH>), g, b, lds, ctx->stream, l, c, e, a);               \
     } while (0)
-    if constexpr (sizeof(T) == 4) DCNN_UNIT_LAUNCH(0);
-    else if (waves == kUnitMaxWaves) DCNN_UNIT_LAUNCH(kUnitMaxWaves);
-    else DCNN_UNIT_LAUNCH(0);
+    bool shared = false;
+    if constexpr (sizeof(T) == 2) {
+        shared = unit_shares(waves, (int)sizeof(T));
+        if (shared) DCNN_UNIT_LAUNCH(kUnitMaxWaves);
+    }
+    if (!shared) DCNN_UNIT_LAUNCH(0);
 #undef DCNN_UNIT_LAUNCH
     return check_hip(ctx, hipGetLastError(), "conv_unit_kernel launch");
 }
