@@ -38,8 +38,7 @@ struct FirstArgs {
 template <typename T> constexpr int first_stage_stride(int channels) { return channels * (int)sizeof(T) + kStagePad; }
 
 // STEPS: K-steps of a tap's group that can hold channels.  4 or 2 (rows of up to 64 bytes): a group is a 128-byte line of one tap.
-// 1 (windows over rows of up to 32 bytes): a group is four taps, of which every lane fetches its own pixel -- 3x3 16->16 on 64 streams of
-// 128x128 56 us, by quads of lanes that are three quarters idle 75.
+// 1: a group is four K-steps in a row, of whichever taps, and every lane fetches its own pixel's (first_by_lanes has the rule and both sides of it).
 template <typename T, int SPLIT, int TC, bool XT, int STEPS>
 __global__ __launch_bounds__(kFirstWaves* kWave, 2) void conv_first_kernel(ConvArgs c, EpilogueArgs e, FirstArgs f) {
     typedef typename Mma<T>::Vec Vec;
@@ -139,12 +138,13 @@ __global__ __launch_bounds__(kFirstWaves* kWave, 2) void conv_first_kernel(ConvA
         int kg, dy, dx;
         {
             const int tap = k_first / kch;
-            kg = STEPS == 1 ? 0 : k_first % kch / kFirstGroup;
+            kg = STEPS == 1 ? k_first % kch : k_first % kch / kFirstGroup;
             dy = tap / ksz; dx = tap - dy * ksz;
         }
+        int next_kg = 0, next_dy = 0, next_dx = 0;             // (STEPS 1) where the group's steps end
         struct Part { int lo, hi; };                           // the K-steps of the current group that are this wave's
         auto part_of = [&]() {
-            const int base = (dy * ksz + dx) * kch + kg * kFirstGroup, end = STEPS == 1 ? kFirstGroup : kch - kg * kFirstGroup;
+            const int base = (dy * ksz + dx) * kch + (STEPS == 1 ? kg : kg * kFirstGroup), end = STEPS == 1 ? kFirstGroup : kch - kg * kFirstGroup;
             if constexpr (SPLIT == 1) return Part{0, STEPS == 1 ? k_last - base : end};
             return Part{k_first - base, min(k_last - base, end)};
         };
@@ -154,19 +154,23 @@ __global__ __launch_bounds__(kFirstWaves* kWave, 2) void conv_first_kernel(ConvA
         Vec x[TP][kFirstGroup], w[WSTEPS][TC];
         auto request_x = [&]() __attribute__((always_inline)) {
             if constexpr (STEPS == 1) {
-                int ty = dy, tx = dx;
+                int ty = dy, tx = dx, kc = kg;
 #pragma unroll
                 for (int u = 0; u < kFirstGroup; ++u) {
-                    const uint32_t uni = (uint32_t)((ty * iw + tx) * rowb + g * 16);
+                    const uint32_t uni = (uint32_t)((ty * iw + tx) * rowb + kc * 32 + g * 16);
 #pragma unroll
                     for (int i = 0; i < TP; ++i) {
-                        const bool in = ty < ksz && g * 16 < rowb && (unsigned)(px[i].iy0 + ty) < (unsigned)c.h && (unsigned)(px[i].ix0 + tx) < (unsigned)c.w;
+                        const bool in = ty < ksz && kc * 32 + g * 16 < rowb && (unsigned)(px[i].iy0 + ty) < (unsigned)c.h && (unsigned)(px[i].ix0 + tx) < (unsigned)c.w;
                         uint32_t o = in ? px[i].base + uni : kOob;
                         asm volatile("" : "+v"(o));
                         x[i][u] = ws_load16<Vec>(rs_in, o);
                     }
-                    if (++tx == ksz) { tx = 0; ++ty; }
+                    const bool row = kc + 1 == kch, end = row && tx + 1 == ksz;
+                    kc = row ? 0 : kc + 1;
+                    tx = end ? 0 : row ? tx + 1 : tx;
+                    ty = end ? ty + 1 : ty;
                 }
+                next_kg = kc; next_dy = ty; next_dx = tx;
                 return;
             }
             const int left = rowb - kg * (kFirstGroup * 32);
@@ -189,8 +193,8 @@ __global__ __launch_bounds__(kFirstWaves* kWave, 2) void conv_first_kernel(ConvA
             }
         };
         auto request_w = [&](int u) __attribute__((always_inline)) {
-            const int tap = dy * ksz + dx;                     // (STEPS 1, one K-step a tap: the taps are the steps of a single one)
-            const int of = STEPS == 1 ? 0 : tap, steps = STEPS == 1 ? ksteps : kch, at = (STEPS == 1 ? tap : kg * kFirstGroup) + u;
+            const int tap = dy * ksz + dx;                     // (STEPS 1: the steps of all taps are those of a single one)
+            const int of = STEPS == 1 ? 0 : tap, steps = STEPS == 1 ? ksteps : kch, at = (STEPS == 1 ? tap * kch + kg : kg * kFirstGroup) + u;
             const uint32_t step = (uint32_t)weight_step(of, steps, at) * wrow;
 #pragma unroll
             for (int b = 0; b < TC; ++b) w[u][b] = ws_load16<Vec>(rs_w, at < steps ? wlane[b] : kOob, step);
@@ -217,8 +221,7 @@ __global__ __launch_bounds__(kFirstWaves* kWave, 2) void conv_first_kernel(ConvA
             }
             const Part part = part_of();
             if constexpr (STEPS == 1) {
-                dx += kFirstGroup;
-                while (dx >= ksz) { dx -= ksz; ++dy; }
+                kg = next_kg; dy = next_dy; dx = next_dx;
             } else if (++kg == kgroups) {
                 kg = 0;
                 if (++dx == ksz) { dx = 0; ++dy; }
@@ -307,7 +310,7 @@ __global__ __launch_bounds__(kFirstWaves* kWave, 2) void conv_first_kernel(ConvA
     zero_acc();
     k_loop(std::false_type{});
     deliver(static_cast<const T*>(e.bias), false);
-    if (c.in2_data != nullptr) {                               // the projection: rounded on its own, then added
+    if (STEPS != 1 && c.in2_data != nullptr) {                 // the projection: rounded on its own, then added
         zero_acc();
         k_loop(std::true_type{});
         deliver(static_cast<const T*>(f.bias2), true);
@@ -382,12 +385,23 @@ static bool first_splits(const ConvArgs& c) {
 // channels: 5x5 128->32 240 us, now 154, plain kernel 178).
 static bool first_narrow(const ConvArgs& c) { return c.cout <= 32; }
 
+// Windows over few channels: by quads of lanes most of a 128-byte line is nothing, and a lane whose half of a K-step is empty costs the memory path
+// little when it asks for its own pixel's.  First frames of one layer on 16 streams of 128x128, fp16, quads -> lanes, us: 3x3 24->24 31.2 -> 28.7,
+// 24->48 43.1 -> 40.2, 24->64 46.5 -> 42.5, 5x5 24->48 71 -> 65, 3x3 40->48 50.7 -> 49.7, 40->96 92 -> 85, on 64 streams 16->16 75 -> 56; but where
+// K-steps are whole 32->96 65 -> 72, fp32 16->32 50.5 -> 54, and 1x1 24->96 45 -> 49.
+static bool first_by_lanes(const ConvArgs& c, size_t es) {
+    return c.k > 1 && c.in2_data == nullptr && (c.kch == 1 || (es == 2 && c.kch <= 3 && (size_t)c.cin * es % 32 != 0));
+}
+
 // ... and where tiles of 64 leave compute units without a workgroup, or with fewer than two of whole sums (their width changes no sum): a step of the layer's network, 64 -> 32
 // channels a tile: 3x3 512->512 on 512 pixels 30.5 -> 28.0 us, 128->128 on 100x100 32.3 -> 26.6, 1x1 64->256 on 64x64 17.4 -> 14.9,
 // fp32 3x3 256->256 on 2048 pixels 59.9 -> 44.5; the first frame of a ResNet-50-shaped network of 8 streams
-// 757 -> 692 (703 with the line at one workgroup for both, 695 at two).
+// 757 -> 692 (703 with the line at one workgroup for both, 695 at two).  And 96 channels: three tiles instead of two with half of the last one
+// padding (16 streams of 128x128, 64 -> 32 channels a tile: 1x1 48->96 52.7 -> 48.0, 72->96 59.5 -> 53.5, 3x3 24->96 63 -> 54, 64->96 106 -> 99; fp32
+// the same; not 160: 3x3 96->160 on 8 streams 113 -> 126; nor rows that tiles of 32 cut within 64-byte pieces: 1x1 64->72 66 -> 82).
 static bool first_halves(const ConvArgs& c, bool split, int64_t pixels, int num_cu) {
     const int64_t tiles = cdiv(pixels, kFirstPx) * cdiv(c.cout, 64);
+    if (!split && c.cout < 128 && c.cout % 64 == 32) return true;
     return split ? tiles < num_cu : cdiv(tiles, kFirstWaves) < 2 * num_cu;
 }
 
@@ -430,7 +444,7 @@ static dcnn_status launch_conv_first_t(dcnn_ctx* ctx, const ConvArgs& c, const E
     const int64_t grid = split ? cdiv(f.units, kXcd) * kXcd : cdiv(f.units / f.cgroups, kXcd) * kXcd * f.cgroups;
     if (grid > INT32_MAX) return fail(ctx, DCNN_ESHAPE, "first frame: %lld workgroups", (long long)grid);
     hipError_t err = hipSuccess;
-    const bool thin = c.kch <= 2 && (c.in2_data == nullptr || c.kch2 <= 2), taps = c.kch == 1 && c.k > 1 && c.in2_data == nullptr;
+    const bool thin = c.kch <= 2 && (c.in2_data == nullptr || c.kch2 <= 2), taps = first_by_lanes(c, sizeof(T));
 #define DCNN_FIRST_LAUNCH_X(SPLIT, TC, XT, STEPS)                                                                        \
     do {                                                                                                         \
         auto kern = conv_first_kernel<T, SPLIT, TC, XT, STEPS>;                                                          \

@@ -983,6 +983,10 @@ def test_first_frame_tiles(S, k, stride, cin, cout, nhw, mode):
     ("f16", 3, 1, 16, 64, (2, 9, 14), "act"),            # up to 32: four taps together, whole and split sums
     ("f32", 3, 2, 4, 20, (1, 11, 12), "plain"),
     ("f16", 7, 1, 8, 72, (1, 9, 8), "act"),
+    ("f16", 3, 1, 24, 40, (2, 13, 15), "act"),           # windows whose last K-step of two or three is half empty, whole and split sums
+    ("f16", 3, 2, 40, 64, (1, 15, 14), "plain"),
+    ("f16", 5, 1, 40, 24, (1, 8, 9), "residual"),
+    ("f16", 7, 1, 24, 72, (1, 9, 8), "act"),
     ("f16", 1, 1, 24, 200, (1, 70, 61), "act"),          # tiles of 32 channels on small maps: whole sums, a last tile of 8, and beyond
     ("f16", 1, 1, 24, 256, (4, 64, 64), "projection"),   # them the first map on tiles of 64
     ("f32", 3, 1, 40, 72, (1, 50, 41), "residual"),
