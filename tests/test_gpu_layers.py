@@ -988,11 +988,24 @@ def test_first_frame_tiles(S, k, stride, cin, cout, nhw, mode):
     ("f16", 5, 1, 40, 24, (1, 8, 9), "residual"),
     ("f16", 7, 1, 24, 72, (1, 9, 8), "act"),
     ("f16", 1, 1, 24, 200, (1, 70, 61), "act"),          # tiles of 32 channels on small maps: whole sums, a last tile of 8, and beyond
-    ("f16", 1, 1, 24, 256, (4, 64, 64), "projection"),   # them the first map on tiles of 64
+    ("f16", 1, 1, 24, 256, (4, 64, 64), "projection"),   # them 1024 tiles of 64, which are split too
     ("f32", 3, 1, 40, 72, (1, 50, 41), "residual"),
 ])
 def test_first_frame_lines_of_a_pixel(S, k, stride, cin, cout, nhw, mode):
     """How the first frame's kernel fetches a pixel's channels: by quads of lanes, or a pixel per lane, at the ends of its groups."""
+    test_first_frame_tiles(S, k, stride, cin, cout, nhw, mode)
+
+
+@pytest.mark.parametrize("S,k,stride,cin,cout,nhw,mode", [
+    # 2048 tiles of 64 pixels x 64 channels: the batch on tiles of 64 channels, a stream alone on tiles of 32, whole sums
+    ("f16", 1, 1, 24, 256, (8, 64, 64), "projection"),   # one line of two K-steps, for the projection too
+    ("f16", 1, 1, 72, 256, (8, 64, 65), "projection"),   # a line and a part
+    ("f16", 1, 1, 128, 256, (8, 64, 64), "residual"),    # whole lines
+    ("f16", 3, 1, 32, 64, (8, 127, 130), "act"),         # one line of two K-steps over a window
+    ("f32", 1, 1, 40, 256, (8, 64, 64), "residual"),
+])
+def test_first_frame_tile_widths_and_fetches(S, k, stride, cin, cout, nhw, mode):
+    """Whole sums on tiles of 64 channels, against the oracle and against tiles of 32."""
     test_first_frame_tiles(S, k, stride, cin, cout, nhw, mode)
 
 
