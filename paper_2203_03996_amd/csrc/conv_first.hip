@@ -3,17 +3,18 @@
 // f(v); Fig. 2).  No pixel is decided on, so the output channels need not meet and the work splits freely over
 // pixels AND channels -- which is what the sparse kernels, whose tail wants the whole pixel, cannot do.
 //
-// A wave owns 64 pixels x 64 output channels (2 x 2 MFMA 32x32 blocks; x 32 where the last tile would be half empty, see
-// launch_conv_first_t), operands straight from global memory / L2 into registers.  Four K-steps of a pixel -- a 128-byte line of one
+// A wave owns 64 pixels x 64 output channels (2 x 2 MFMA 32x32 blocks; x 32 where the last tile would be half empty or compute units idle:
+// first_narrow, first_halves), operands straight from global memory / L2 into registers.  Four K-steps of a pixel -- a 128-byte line of one
 // tap -- are fetched by quads of lanes (quad_transpose: a load instruction then takes 16 clocks of the memory path instead of 64, and
 // the gathers of a K-step 32 beside 32 of weights instead of 128).  Once a group's vectors are dealt out the next group's travel in
 // their place, and its weights in place of each K-step's as it is multiplied: 64 sums, 64 vectors of pixels and 32 of weights fit two
 // waves per SIMD (two whole sets of both spilled: 64->64 on 64 streams of 128x128 3x3 478 us, not 223).  With enough such
 // tiles the four waves of a workgroup take four pixel tiles of the same channels (they share the weights in the
-// vector cache); with too few -- the deep stages of a backbone: 512 pixels, K = 4608 -- they split the groups of ONE
+// vector cache); with too few -- the deep stages of a backbone: 512 pixels, K = 4608 -- they split the K-steps of ONE
 // tile and add their partial sums in LDS in a fixed order.
-// Bound: HBM for the narrow layers of wide maps (64 streams of 128x128, 64->256 with its projection, x^A, x^T and O: 1.6 GB
-// written and 0.27 GB read in 480 us, 3.9 TB/s), memory latency for the deep ones.  Kernels with a lane per pixel and a ring of four
+// Bound: 64 streams of 128x128, 64->256 with its projection, x^A and O (rows of x^T that hold zeros stay): 1.07 GB written and 0.27 GB read in
+// 480 us, 2.8 TB/s of the 5.3 that a copy reaches -- sums of one group leave nothing to ask for ahead, so a tile's operands, the projection's and its
+// stores follow each other on two waves per SIMD.  Memory latency for the deep layers.  Kernels with a lane per pixel and a ring of four
 // K-steps -> quads, us: 3x3 256->256 on 8 streams of 64x64 104 -> 64, 512->512 on 512 pixels 29 -> 17, 1x1 64->64 and 3x3 64->64 on 64
 // streams of 128x128 together 321 -> 255.
 #include "conv_plan.h"
@@ -24,6 +25,7 @@ namespace dcnn {
 constexpr int kFirstWaves = 4;
 constexpr int kFirstPx = 64;                                   // tile of a wave: pixels; its channels are 32 * TC
 constexpr int kFirstGroup = 4;                                 // K-steps whose operands are requested together (quad_transpose); two groups in registers or on their way
+constexpr int kFirstRing = 4;                                  // where every lane fetches its own pixel: K-steps in registers or on their way
 
 struct FirstArgs {
     int nb;                        // column blocks per packed channel group (the layer's plan)
@@ -38,7 +40,8 @@ struct FirstArgs {
 template <typename T> constexpr int first_stage_stride(int channels) { return channels * (int)sizeof(T) + kStagePad; }
 
 // STEPS: K-steps of a tap's group that can hold channels.  4 or 2 (rows of up to 64 bytes): a group is a 128-byte line of one tap.
-// 1: a group is four K-steps in a row, of whichever taps, and every lane fetches its own pixel's (first_by_lanes has the rule and both sides of it).
+// 1: single K-steps, of which every lane fetches its own pixel's 16 bytes, kFirstRing of them in registers or on their way: three waves per SIMD
+// instead of two, and none of the work on the padding of a group (first_by_lanes has the rule and both sides of it).
 template <typename T, int SPLIT, int TC, bool XT, int STEPS>
 __global__ __launch_bounds__(kFirstWaves* kWave, 2) void conv_first_kernel(ConvArgs c, EpilogueArgs e, FirstArgs f) {
     typedef typename Mma<T>::Vec Vec;
@@ -127,52 +130,76 @@ __global__ __launch_bounds__(kFirstWaves* kWave, 2) void conv_first_kernel(ConvA
                         (uint32_t)(cb % f.nb) * 32u + (uint32_t)col) * 16u;
         }
         const uint32_t wrow = (uint32_t)(2 * cols * 16);       // weights of one K-step
-        // This wave's K-steps and the groups that hold them (a group at either end may hold another wave's too).
         const int share = SPLIT == 1 ? 0 : wave;
         const int k_first = (int)((int64_t)ksteps * share / SPLIT), k_last = (int)((int64_t)ksteps * (share + 1) / SPLIT);
         if (k_first == k_last) return;
+        if constexpr (STEPS == 1) {
+            constexpr int D = kFirstRing;
+            int s_next = k_first, kc, dy, dx;                  // the K-step to ask for
+            {
+                const int tap = k_first / kch;
+                kc = k_first - tap * kch;
+                dy = tap / ksz; dx = tap - dy * ksz;
+            }
+            // Every load is issued unconditionally: a pixel outside the map, padding channels and steps past the end read zeros
+            // from an offset outside the descriptor, so the number of loads in flight at each wait is known.
+            auto issue = [&](Vec (&x)[TP], Vec (&w)[TC]) __attribute__((always_inline)) {
+                const bool live = s_next < k_last;
+                const bool chan_ok = live && (2 * kc + g) * 16 < rowb;
+                const uint32_t uni = (uint32_t)((dy * iw + dx) * rowb + kc * 32 + g * 16);
+#pragma unroll
+                for (int i = 0; i < TP; ++i) {
+                    const bool in = (unsigned)(px[i].iy0 + dy) < (unsigned)c.h && (unsigned)(px[i].ix0 + dx) < (unsigned)c.w;
+                    uint32_t off = chan_ok && in ? px[i].base + uni : kOob;
+                    asm volatile("" : "+v"(off));
+                    x[i] = ws_load16<Vec>(rs_in, off);
+                }
+                const uint32_t step = (uint32_t)weight_step(0, k_last, s_next) * wrow;
+#pragma unroll
+                for (int b = 0; b < TC; ++b) w[b] = ws_load16<Vec>(rs_w, live ? wlane[b] : kOob, step);
+                ++s_next;
+                if (++kc == kch) {
+                    kc = 0;
+                    if (++dx == ksz) { dx = 0; ++dy; }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            Vec x[D][TP], w[D][TC];
+#pragma unroll
+            for (int j = 0; j < D - 1; ++j) issue(x[j], w[j]);
+            for (int s = k_first; s < k_last; s += D) {
+#pragma unroll
+                for (int j = 0; j < D; ++j) {
+                    issue(x[(j + D - 1) % D], w[(j + D - 1) % D]);
+#pragma unroll
+                    for (int b = 0; b < TC; ++b)
+#pragma unroll
+                        for (int i = 0; i < TP; ++i) Mma<T>::run(acc[i][b], w[j][b], x[j][i]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            return;
+        }
+        // The groups that hold this wave's K-steps (a group at either end may hold another wave's too).
         const int kgroups = (kch + kFirstGroup - 1) / kFirstGroup;
         auto group_of = [&](int k) { return k / kch * kgroups + k % kch / kFirstGroup; };
-        const int first = STEPS == 1 ? 0 : group_of(k_first);
-        const int last = STEPS == 1 ? (k_last - k_first + kFirstGroup - 1) / kFirstGroup : group_of(k_last - 1) + 1;
+        const int first = group_of(k_first), last = group_of(k_last - 1) + 1;
         int kg, dy, dx;
         {
             const int tap = k_first / kch;
-            kg = STEPS == 1 ? k_first % kch : k_first % kch / kFirstGroup;
+            kg = k_first % kch / kFirstGroup;
             dy = tap / ksz; dx = tap - dy * ksz;
         }
-        int next_kg = 0, next_dy = 0, next_dx = 0;             // (STEPS 1) where the group's steps end
         struct Part { int lo, hi; };                           // the K-steps of the current group that are this wave's
         auto part_of = [&]() {
-            const int base = (dy * ksz + dx) * kch + (STEPS == 1 ? kg : kg * kFirstGroup), end = STEPS == 1 ? kFirstGroup : kch - kg * kFirstGroup;
-            if constexpr (SPLIT == 1) return Part{0, STEPS == 1 ? k_last - base : end};
+            const int base = (dy * ksz + dx) * kch + kg * kFirstGroup, end = kch - kg * kFirstGroup;
+            if constexpr (SPLIT == 1) return Part{0, end};
             return Part{k_first - base, min(k_last - base, end)};
         };
         // Every load is issued unconditionally: a pixel outside the map and padding channels read zeros from an offset outside
         // the descriptor, so the number of loads in flight at each wait is known.
-        constexpr int WSTEPS = STEPS == 1 ? kFirstGroup : STEPS;   // K-steps of a group
-        Vec x[TP][kFirstGroup], w[WSTEPS][TC];
+        Vec x[TP][kFirstGroup], w[STEPS][TC];
         auto request_x = [&]() __attribute__((always_inline)) {
-            if constexpr (STEPS == 1) {
-                int ty = dy, tx = dx, kc = kg;
-#pragma unroll
-                for (int u = 0; u < kFirstGroup; ++u) {
-                    const uint32_t uni = (uint32_t)((ty * iw + tx) * rowb + kc * 32 + g * 16);
-#pragma unroll
-                    for (int i = 0; i < TP; ++i) {
-                        const bool in = ty < ksz && kc * 32 + g * 16 < rowb && (unsigned)(px[i].iy0 + ty) < (unsigned)c.h && (unsigned)(px[i].ix0 + tx) < (unsigned)c.w;
-                        uint32_t o = in ? px[i].base + uni : kOob;
-                        asm volatile("" : "+v"(o));
-                        x[i][u] = ws_load16<Vec>(rs_in, o);
-                    }
-                    const bool row = kc + 1 == kch, end = row && tx + 1 == ksz;
-                    kc = row ? 0 : kc + 1;
-                    tx = end ? 0 : row ? tx + 1 : tx;
-                    ty = end ? ty + 1 : ty;
-                }
-                next_kg = kc; next_dy = ty; next_dx = tx;
-                return;
-            }
             const int left = rowb - kg * (kFirstGroup * 32);
             const uint32_t uni = (uint32_t)((dy * iw + dx) * rowb + kg * (kFirstGroup * 32));
 #pragma unroll
@@ -193,11 +220,10 @@ __global__ __launch_bounds__(kFirstWaves* kWave, 2) void conv_first_kernel(ConvA
             }
         };
         auto request_w = [&](int u) __attribute__((always_inline)) {
-            const int tap = dy * ksz + dx;                     // (STEPS 1: the steps of all taps are those of a single one)
-            const int of = STEPS == 1 ? 0 : tap, steps = STEPS == 1 ? ksteps : kch, at = (STEPS == 1 ? tap * kch + kg : kg * kFirstGroup) + u;
-            const uint32_t step = (uint32_t)weight_step(of, steps, at) * wrow;
+            const int at = kg * kFirstGroup + u;
+            const uint32_t step = (uint32_t)weight_step(dy * ksz + dx, kch, at) * wrow;
 #pragma unroll
-            for (int b = 0; b < TC; ++b) w[u][b] = ws_load16<Vec>(rs_w, at < steps ? wlane[b] : kOob, step);
+            for (int b = 0; b < TC; ++b) w[u][b] = ws_load16<Vec>(rs_w, at < kch ? wlane[b] : kOob, step);
         };
         auto mma = [&](int u, const Part& part, const Vec (&v)[TP][kFirstGroup]) __attribute__((always_inline)) {
             if (SPLIT != 1 && (u < part.lo || u >= part.hi)) return;
@@ -209,38 +235,35 @@ __global__ __launch_bounds__(kFirstWaves* kWave, 2) void conv_first_kernel(ConvA
         };
         request_x();
 #pragma unroll
-        for (int u = 0; u < WSTEPS; ++u) request_w(u);
+        for (int u = 0; u < STEPS; ++u) request_w(u);
         for (int s = first + 1; s < last; ++s) {
             // the next group's pixels take the place of the vectors as fetched, its weights that of the ones just multiplied
             Vec xt[TP][kFirstGroup];
 #pragma unroll
             for (int i = 0; i < TP; ++i) {
-                if constexpr (STEPS != 1) quad_transpose(x[i], lane);
+                quad_transpose(x[i], lane);
 #pragma unroll
                 for (int u = 0; u < kFirstGroup; ++u) xt[i][u] = x[i][u];
             }
             const Part part = part_of();
-            if constexpr (STEPS == 1) {
-                kg = next_kg; dy = next_dy; dx = next_dx;
-            } else if (++kg == kgroups) {
+            if (++kg == kgroups) {
                 kg = 0;
                 if (++dx == ksz) { dx = 0; ++dy; }
             }
             request_x();
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int u = 0; u < WSTEPS; ++u) {
+            for (int u = 0; u < STEPS; ++u) {
                 mma(u, part, xt);
                 request_w(u);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
 #pragma unroll
-        for (int i = 0; i < TP; ++i)
-            if constexpr (STEPS != 1) quad_transpose(x[i], lane);
+        for (int i = 0; i < TP; ++i) quad_transpose(x[i], lane);
         const Part part = part_of();
 #pragma unroll
-        for (int u = 0; u < WSTEPS; ++u) mma(u, part, x);
+        for (int u = 0; u < STEPS; ++u) mma(u, part, x);
     };
 
     // staging tile [pixel][channel] in the storage type: one per wave, or one for the workgroup behind the partial sums
@@ -385,24 +408,52 @@ static bool first_splits(const ConvArgs& c) {
 // channels: 5x5 128->32 240 us, now 154, plain kernel 178).
 static bool first_narrow(const ConvArgs& c) { return c.cout <= 32; }
 
-// Windows over few channels: by quads of lanes most of a 128-byte line is nothing, and a lane whose half of a K-step is empty costs the memory path
-// little when it asks for its own pixel's.  First frames of one layer on 16 streams of 128x128, fp16, quads -> lanes, us: 3x3 24->24 31.2 -> 28.7,
-// 24->48 43.1 -> 40.2, 24->64 46.5 -> 42.5, 5x5 24->48 71 -> 65, 3x3 40->48 50.7 -> 49.7, 40->96 92 -> 85, on 64 streams 16->16 75 -> 56; but where
-// K-steps are whole 32->96 65 -> 72, fp32 16->32 50.5 -> 54, and 1x1 24->96 45 -> 49.
-static bool first_by_lanes(const ConvArgs& c, size_t es) {
-    return c.k > 1 && c.in2_data == nullptr && (c.kch == 1 || (es == 2 && c.kch <= 3 && (size_t)c.cin * es % 32 != 0));
+// Whole long sums whose workgroups (tiles of 64 channels) fill at least half of the compute units, one each.
+constexpr int kFirstLongSum = 45;                              // K-steps; see first_halves for both sides
+static bool first_single(const ConvArgs& c, int64_t workgroups, int num_cu) {
+    return workgroups > num_cu / 2 && workgroups <= num_cu && c.k * c.k * c.kch >= kFirstLongSum;
 }
 
-// ... and where tiles of 64 leave compute units without a workgroup, or with fewer than two of whole sums (their width changes no sum): a step of the layer's network, 64 -> 32
-// channels a tile: 3x3 512->512 on 512 pixels 30.5 -> 28.0 us, 128->128 on 100x100 32.3 -> 26.6, 1x1 64->256 on 64x64 17.4 -> 14.9,
-// fp32 3x3 256->256 on 2048 pixels 59.9 -> 44.5; the first frame of a ResNet-50-shaped network of 8 streams
-// 757 -> 692 (703 with the line at one workgroup for both, 695 at two).  And 96 channels: three tiles instead of two with half of the last one
-// padding (16 streams of 128x128, 64 -> 32 channels a tile: 1x1 48->96 52.7 -> 48.0, 72->96 59.5 -> 53.5, 3x3 24->96 63 -> 54, 64->96 106 -> 99; fp32
-// the same; not 160: 3x3 96->160 on 8 streams 113 -> 126; nor rows that tiles of 32 cut within 64-byte pieces: 1x1 64->72 66 -> 82).
-static bool first_halves(const ConvArgs& c, bool split, int64_t pixels, int num_cu) {
-    const int64_t tiles = cdiv(pixels, kFirstPx) * cdiv(c.cout, 64);
-    if (!split && c.cout < 128 && c.cout % 64 == 32) return true;
-    return split ? tiles < num_cu : cdiv(tiles, kFirstWaves) < 2 * num_cu;
+// Where every lane fetches its own pixel (STEPS 1) instead of a quad of lanes a line: where much of a line is nothing, and where a third wave per
+// SIMD hides more than the quads save.  First frames of one layer with its input layer, MI355X, us, quads -> lanes:
+// * windows over few channels: on 16 streams of 128x128 3x3 24->24 31.2 -> 25.5, 24->64 46.5 -> 40.8, 40->64 51 -> 49, 16->256 91 -> 80; on 12 of 120x128
+//   5x5 24->96 95 -> 78, 7x7 24->256 260 -> 219.  Not for whole K-steps (3x3 32->96 65 -> 72) nor 40 channels to one block (3x3 40->32 27.6 -> 29.7).
+// * `padded` lines, a K-step in four and more empty: split sums over 3x3 on 4 of 64x66 72->64 17.4 -> 16.5, 72->256 36.7 -> 35.5, and whatever the
+//   window where no compute unit has two workgroups: 5x5 72->96 on 2 of 60x50 20.1 -> 17.2 (but 5x5 72->96 on 4 of 64x66 35.9 -> 37.7).
+//   fp32, whose sums the matrix cores bound and whose quads only add to: 5x5 36->64 35.7 -> 31.3, 100->64 66 -> 61, 3x3 52->64 23.5 -> 21.5.
+// * wide fp16 layers, whose stores want the third wave: on 12 of 120x128 1x1 40->192 49.8 -> 45, 72->512 201 -> 188, 96->512 324 -> 314, 3x3 72->256
+//   182 -> 163, 48->512 383 -> 353, 5x5 48->256 224 -> 199; and 1x1 layers whose workgroups are one round of three per compute unit but
+//   not of two: 56->64 28.9 -> 27.5, 96->64 36.3 -> 34.6.  (Not 3x3 72->128 nor 56->192: 100.7 and 111 by quads, 101 and 122.)
+static bool first_by_lanes(const ConvArgs& c, size_t es, bool split, int64_t tiles, int num_cu) {
+    if (c.in2_data != nullptr) return false;
+    const int kch = c.kch, kgroups = (int)cdiv(kch, kFirstGroup);
+    const bool half_words = es == 2, padded = kFirstGroup * kgroups - kch >= kgroups;
+    if (c.k > 1 && (kch == 1 || (half_words && (size_t)c.cin * es % 32 != 0 && (kch == 2 || (kch == 3 && c.cout > 32))))) return true;
+    if ((size_t)c.cin * es % 128 == 0) return false;
+    if (split) return half_words ? padded && ((c.k == 3 && kch == 5) || tiles <= num_cu) : kch % 2 == 1 && kch <= 13;
+    if (!half_words) return false;
+    const int64_t workgroups = cdiv(tiles, kFirstWaves);
+    if (padded && first_single(c, workgroups, num_cu)) return true;
+    if (c.k == 1 && kch >= 3 && kch <= 9 && (c.cout >= 512 || (workgroups > 2 * num_cu && workgroups <= 3 * num_cu))) return true;
+    return c.cout >= 128 && (kch == 3 || (c.k == 1 && kch == 4) || (kch == 5 && (c.k == 1 || cdiv(c.cout, 64) % 4 == 0)));
+}
+
+// Tiles of 32 channels also where tiles of 64 leave compute units idle, if those of 32 are one round of workgroups (split sums) or a second one does not
+// wait behind long sums (whole ones, first_single): their width changes no sum.  64 -> 32 channels a tile, us: 3x3 512->512 on 512 pixels 30.5 -> 28.0,
+// 128->128 on 100x100 32.3 -> 26.6, 1x1 64->256 on 64x64 17.4 -> 14.9, fp32 3x3 256->256 on 2048 pixels 59.9 -> 44.5; the first frame of a
+// ResNet-50-shaped network of 8 streams 757 -> 692.  But split 5x5 72->128 on 2 of 60x50 (188 tiles, 376 of half the width) 17.7 -> 20.9, and whole sums of
+// between half a workgroup and one per compute unit: 5x5 144->256 on 96x97 61 -> 71, 128->384 52 -> 55; short ones 3x3 32->384 20 -> 19.2, 1x1 128->384 17.6 -> 16.1;
+// by lanes also above that: 5x5 72->256 on 4 of 64x66 59 -> 64.
+// And 96 channels over short sums: three tiles instead of two with half of the last one padding (16 streams of 128x128: 1x1 48->96 52.7 -> 48.0, 72->96
+// 59.5 -> 53.5, 3x3 32->96 of 12 of 120x128 49 -> 48; not 5x5 32->96 90 -> 96, 3x3 112->96 116 -> 121, nor lanes over 24 and 40 channels;
+// not 160: 3x3 96->160 on 8 streams 113 -> 126; nor rows that tiles of 32 cut within 64-byte pieces: 1x1 64->72 66 -> 82).
+static bool first_halves(const ConvArgs& c, bool split, bool lanes, int64_t tiles, int64_t halves, int num_cu) {
+    if (split) return halves <= num_cu;
+    const bool long_sum = c.k * c.k * c.kch >= kFirstLongSum;
+    if (c.cout < 128 && c.cout % 64 == 32 && (!lanes || c.kch == 1) && !long_sum) return true;
+    const int64_t workgroups = cdiv(tiles, kFirstWaves);
+    if (lanes && long_sum && workgroups > num_cu / 2) return false;
+    return workgroups < 2 * num_cu && !first_single(c, workgroups, num_cu);
 }
 
 // (What decides between sums in one chain and split ones looks at one stream; kernels that sum in one chain give the same bits.)
@@ -434,7 +485,9 @@ static dcnn_status launch_conv_first_t(dcnn_ctx* ctx, const ConvArgs& c, const E
     f.pixels = (int64_t)c.n * c.oh * c.ow;
     f.bias2 = bias2;
     const int64_t ptiles = cdiv(f.pixels, kFirstPx);
-    const bool split = first_splits(c), narrow = first_narrow(c) || first_halves(c, split, f.pixels, ctx->num_cu);
+    const int64_t tiles = ptiles * cdiv(c.cout, 64), halves = ptiles * cdiv(c.cout, 32);
+    const bool split = first_splits(c), lanes = first_by_lanes(c, sizeof(T), split, tiles, ctx->num_cu);
+    const bool narrow = first_narrow(c) || first_halves(c, split, lanes, tiles, halves, ctx->num_cu);
     const int ctiles = (int)cdiv(e.c, narrow ? 32 : 64);
     f.wc = split ? 1 : (ctiles % 4 == 0 ? 4 : (ctiles % 2 == 0 ? 2 : 1));      // (no wave without channels)
     f.cgroups = (int)cdiv(ctiles, f.wc);
@@ -444,7 +497,7 @@ static dcnn_status launch_conv_first_t(dcnn_ctx* ctx, const ConvArgs& c, const E
     const int64_t grid = split ? cdiv(f.units, kXcd) * kXcd : cdiv(f.units / f.cgroups, kXcd) * kXcd * f.cgroups;
     if (grid > INT32_MAX) return fail(ctx, DCNN_ESHAPE, "first frame: %lld workgroups", (long long)grid);
     hipError_t err = hipSuccess;
-    const bool thin = c.kch <= 2 && (c.in2_data == nullptr || c.kch2 <= 2), taps = first_by_lanes(c, sizeof(T));
+    const bool thin = c.kch <= 2 && (c.in2_data == nullptr || c.kch2 <= 2);
 #define DCNN_FIRST_LAUNCH_X(SPLIT, TC, XT, STEPS)                                                                        \
     do {                                                                                                         \
         auto kern = conv_first_kernel<T, SPLIT, TC, XT, STEPS>;                                                          \
@@ -456,7 +509,7 @@ static dcnn_status launch_conv_first_t(dcnn_ctx* ctx, const ConvArgs& c, const E
         if (err == hipSuccess) hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kFirstWaves * kWave), lds, ctx->stream, c, e, f); \
     } while (0)
 #define DCNN_FIRST_LAUNCH(SPLIT, TC, STEPS) do { if (e.xt_flags) DCNN_FIRST_LAUNCH_X(SPLIT, TC, true, STEPS); else DCNN_FIRST_LAUNCH_X(SPLIT, TC, false, STEPS); } while (0)
-#define DCNN_FIRST_STEPS(SPLIT, TC) do { if (taps) DCNN_FIRST_LAUNCH(SPLIT, TC, 1); else if (thin) DCNN_FIRST_LAUNCH(SPLIT, TC, 2); else DCNN_FIRST_LAUNCH(SPLIT, TC, kFirstGroup); } while (0)
+#define DCNN_FIRST_STEPS(SPLIT, TC) do { if (lanes) DCNN_FIRST_LAUNCH(SPLIT, TC, 1); else if (thin) DCNN_FIRST_LAUNCH(SPLIT, TC, 2); else DCNN_FIRST_LAUNCH(SPLIT, TC, kFirstGroup); } while (0)
     if (split) { if (narrow) DCNN_FIRST_STEPS(kFirstWaves, 1); else DCNN_FIRST_STEPS(kFirstWaves, 2); }
     else { if (narrow) DCNN_FIRST_STEPS(1, 1); else DCNN_FIRST_STEPS(1, 2); }
 #undef DCNN_FIRST_STEPS

@@ -1003,9 +1003,21 @@ def test_first_frame_lines_of_a_pixel(S, k, stride, cin, cout, nhw, mode):
     ("f16", 1, 1, 128, 256, (8, 64, 64), "residual"),    # whole lines
     ("f16", 3, 1, 32, 64, (8, 127, 130), "act"),         # one line of two K-steps over a window
     ("f32", 1, 1, 40, 256, (8, 64, 64), "residual"),
+    # ... of which every lane fetches its own pixel
+    ("f16", 3, 1, 16, 64, (8, 128, 128), "residual"),
+    ("f16", 3, 1, 24, 64, (8, 128, 129), "act"),
+    ("f16", 1, 1, 40, 256, (8, 64, 64), "residual"),     # wide layers over broken lines
+    ("f16", 3, 1, 72, 256, (8, 64, 64), "plain"),
+    ("f16", 1, 1, 56, 64, (9, 121, 128), "act"),         # one round of three workgroups per compute unit
+    ("f16", 1, 1, 88, 512, (1, 30, 41), "plain"),        # (tiles of 32: few pixels)
+    # padded lines: split sums over 3x3, over any window with few tiles, fp32; whole sums of one workgroup per compute unit
+    ("f16", 3, 1, 72, 64, (4, 40, 41), "act"),
+    ("f16", 5, 1, 88, 40, (1, 20, 21), "plain"),
+    ("f32", 3, 1, 100, 64, (2, 21, 20), "residual"),
+    ("f16", 3, 1, 96, 384, (1, 80, 76), "act"),
 ])
 def test_first_frame_tile_widths_and_fetches(S, k, stride, cin, cout, nhw, mode):
-    """Whole sums on tiles of 64 channels, against the oracle and against tiles of 32."""
+    """Both widths of a tile and both ways to fetch a pixel, on both sides of the rules that choose them."""
     test_first_frame_tiles(S, k, stride, cin, cout, nhw, mode)
 
 
