@@ -7,7 +7,9 @@
 // cursors moved by selects and the loop had one way out), the matrix cores and LDS about equally on long ones.  Kernels whose waves gathered for
 // themselves, a pixel per lane -> this, us a step with input and output layer: 3x3 256->256 + ReLU on 8 streams of 16x16, all / a tenth
 // flagged 56 / 48 -> 45 / 44, 1x1 1024->256 there 51 / 43 -> 46 / 39, 3x3 128->128 on 8 of 256x256 439 / 242 -> 375 / 217, with ReLU
-// 542 / 306 -> 484 / 287, 256->512 on 16 of 64x64 404 / 250 -> 313 / 223.  Known cost: 128->64 on 8 of 128x128 with 2 % flagged 57 -> 60.
+// 542 / 306 -> 484 / 287, 256->512 on 16 of 64x64 404 / 250 -> 313 / 223.  128->64 on 8 of 128x128 with 1 / 2 /
+// 10 % flagged 43.5 / 45.2 / 67.7 -> 40.6 / 44.5 / 60.5.  Known cost: lines that are mostly padding on short lists, 3x3 72->256 + ReLU on 8 of 96x100 with 2 % flagged 56 -> 58,
+// 104->192 57 -> 60 (with half of them flagged they gain).
 // fp32 (conv_lane_body): every wave for itself.
 //
 // Addressing is by 32-bit byte offsets against buffer descriptors (tensors below 2 GiB): a lane whose tap is not

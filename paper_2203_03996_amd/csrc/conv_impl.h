@@ -621,9 +621,10 @@ static dcnn_status launch_conv_nb(dcnn_ctx* ctx, bool init, const ListArgs& l_in
         return check_hip(ctx, hipGetLastError(), "conv_ws_kernel launch");
     }
     // Streamed weights, 1x1 / 3x3 windows whose tap words are known, tensors within 32-bit byte offsets: the
-    // register-blocked kernel -- several pixel tiles per wave share every weight operand on long lists, one tile per
-    // wave on a deep ring on short ones (it reads tap words instead of testing the window against the mask, and was
-    // measured 9-12 % ahead of the direct mode above on 3x3 256->256 with ~5000 listed pixels, equal elsewhere).
+    // register-blocked kernel -- several pixel tiles per wave share every weight operand on long lists; on short ones a wave has one tile,
+    // whose gathered operands the waves of the tile share through LDS (fp16) or each fetches for itself on a deep ring (fp32).
+    // It reads tap words instead of testing the window against the mask, and its ring form was
+    // measured 9-12 % ahead of the direct mode above on 3x3 256->256 with ~5000 listed pixels, equal elsewhere.
     // Short lists with several passes stay with the direct mode, which spreads the passes over the grid.
     const bool blocked = p.stream && !init && (!direct || p.npass == 1) && vec_out && aligned && (c.k == 1 || c.k == 3) && ws_taps &&
                          in_bytes <= kWsMaxBytes && p.w_bytes <= kWsMaxBytes;
