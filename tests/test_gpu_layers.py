@@ -322,7 +322,7 @@ def test_conv3x3_row_gathers_on_structured_masks(pattern, nhw):
     ("f16", 136, 64), ("f16", 128, 96), ("f16", 128, 128), ("f16", 104, 192), ("f16", 72, 256), ("f16", 64, 384), ("f16", 264, 32), ("f32", 72, 64)])
 def test_conv3x3_of_a_stream_has_the_same_bits_alone_and_in_a_batch(S, cin, cout):
     """One stream of 7 K pixels compacts blocks in place and gathers tap by tap; ten of them take a list from memory and, with most
-    of the map listed, one gather per window row.  One to five groups of K-steps, the last one whole or not."""
+    of the map listed and weights resident in LDS, one gather per window row.  One to five groups of K-steps, the last one whole or not."""
     rng = np.random.default_rng(cin)
     n, h, w = 10, 89, 83
     dt = NP_DTYPE[S]
@@ -350,8 +350,9 @@ def test_conv3x3_of_a_stream_has_the_same_bits_alone_and_in_a_batch(S, cin, cout
 @pytest.mark.parametrize("S,cin,cout", [("f16", 128, 128), ("f32", 64, 128)])
 def test_conv3x3_row_gathers_on_the_register_blocked_kernel(S, cin, cout, pattern):
     """The same window-row gathers on a layer whose weights do not fit LDS, with a list long enough for several
-    pixel tiles per wave (more than 65,536 entries) and at least three quarters of all window taps flagged: three
-    tiles per wave, left / right taps from neighbouring lanes, the tiles' edge columns fetched separately."""
+    pixel tiles per wave (more than 65,536 entries) and at least three quarters of all window taps flagged.  fp32: three
+    tiles per wave, left / right taps from neighbouring lanes, the tiles' edge columns fetched separately.  fp16, whose
+    waves share their gathers through LDS: the same lists tap by tap."""
     nhw = (5, 128, 136)
     rng = np.random.default_rng(len(pattern) * 11 + cin)
     n, h, w = nhw
