@@ -19,10 +19,9 @@
 // 27 / 36 / 80 / 124 -> 26 / 30 / 57 / 84, 256->1024 on 8 of 16x16 18 / 19 / 23 / 25 -> 18 / 18 / 21 / 22.  Smaller workgroups are those of layers
 // that give a SIMD a wave or two, which wait for each other and for LDS: there every wave gathers for itself.  A wave each -> shared: two waves,
 // 3x3 128->512 on 56x56 19 / 25 / 33 / 40 -> 21 / 30 / 35 / 35, 72->392 on 50x50 19 / 22 / 25 / 26 -> 20 / 23 / 30 / 30, 1x1 256->512 on 8 of 16x16
-// 17 / 17 / 19 / 21 -> 17 / 18 / 21 / 22; one wave, 3x3 512->512 on 16x16 29 / 30 / 33 / 37 -> 38 / 39 / 40 / 40.  (Sixteen weight operands in flight
-// helped where weights come from beyond every cache: three ResNet-50-shaped networks of 8 streams stepped in turn, 1077 us a step that way,
-// 1088 this way; one such network stepped alone 1009 and 991.  Three or four register sets per wave, the same: 3x3 512->512 on 16x16
-// 28, but 256->256 on 8 of 16x16 with everything flagged 29 -> 33 / 37, for want of a second workgroup per compute unit.)
+// 17 / 17 / 19 / 21 -> 17 / 18 / 21 / 22; one wave, 3x3 512->512 on 16x16 29 / 30 / 33 / 37 -> 38 / 39 / 40 / 40.  (These with two register sets of
+// eight K-steps a wave; now eight sets of two, see the kernel.  Through LDS a single wave has sixteen K-steps of weights in flight at all times: three
+// ResNet-50-shaped networks of 8 streams stepped in turn 1075 us a step, 1081 this way, but one alone 1025 and 1014, of 1 stream 920 and 914.)
 //
 // Layers without an activation only: a decision needs all channels of a pixel.  (Groups that leave their sums in memory and
 // a tail done by the last of a tile to arrive were built: the device-scope release and acquire that it takes cost
@@ -34,7 +33,9 @@
 
 namespace dcnn {
 
-constexpr int kUnitGroup = 8;                                  // K-steps whose operands are requested together
+// Where every wave gathers for itself: K-steps whose operands are requested together, and groups in registers or on their way -- sixteen K-steps either way.
+constexpr int kUnitGroup(int es) { return es == 2 ? 2 : 8; }
+constexpr int kUnitSets(int es) { return es == 2 ? 8 : 2; }
 constexpr int kUnitMaxWaves = 4;
 
 struct UnitArgs {
@@ -105,7 +106,6 @@ __global__ __launch_bounds__(kUnitMaxWaves* kWave) void conv_unit_kernel(ListArg
     const __amdgpu_buffer_rsrc_t rs_w = ws_rsrc(c.wpacked, (uint64_t)(c.cout_pad / cols) * ksteps * 2 * cols * 16);
     const __amdgpu_buffer_rsrc_t rs_out = ws_rsrc(e.out_data, a.map_bytes), rs_res = ws_rsrc(e.res_data, a.map_bytes);
     const __amdgpu_buffer_rsrc_t rs_rmask = ws_rsrc(e.res_mask, a.out_pixels);
-    const bool whole_groups = kch % kUnitGroup == 0 && kch * 32 == cin_bytes;   // no K-step of a group reaches past the pixel's channels
     const uint32_t wstride = (uint32_t)(2 * cols * 16);        // weights of one K-step
     const uint32_t row_bytes = (uint32_t)e.c * ES;
 
@@ -160,40 +160,45 @@ __global__ __launch_bounds__(kUnitMaxWaves* kWave) void conv_unit_kernel(ListArg
             gather_tiles<T, 1, KS, 1, SH, 4, 16>(acc, rs_in, rs_w, from, need, wave_taps, kch, cin_bytes, c.w * cin_bytes, cb_on ? wlane : kOob, wstride,
                                                  smem, wave, lane, true);
         } else {
-        // Groups of kUnitGroup K-steps of one tap, two register sets.  One wave per SIMD has its own instructions to wait for
+        // Groups of K-steps of one tap, in a ring of register sets.  One wave per SIMD has its own instructions to wait for
         // (4-8 clocks each), so a group's addresses are formed once: the gathers of its steps differ by an immediate, the
-        // weights by a scalar offset.  With a cursor advanced and an address formed per step the loop took 310 clocks a
-        // step, whatever the memory did (requesting all lines ahead, by either operand, changed nothing).
+        // weights by a scalar offset, and the cursor moves by selects.  fp16: eight sets of two steps, of which seven are on their way at any wait, not eight of
+        // sixteen steps as with two sets of eight.  Two of eight -> eight of two, us a step: three ResNet-50-shaped networks of 8 streams in turn, whose
+        // weights leave every cache between steps, 1095 -> 1081, one alone 1019 -> 1014, three of 3 streams 1032 -> 1021, HRNet-shaped 989 -> 985, 1x1
+        // 2048->512 on 512 pixels 36 / 39 / 45 / 53 -> 36 / 38 / 44 / 51 (2 / 10 / 50 / 100 % flagged); but 3x3 512->512 on 512 pixels stepped alone, its weights in L2,
+        // 27 / 28 / 31 / 35 -> 33 / 33 / 34 / 35, for the address arithmetic.  Four of four, sixteen single steps, and twenty or twenty-four steps (200 and 232
+        // registers) were slower in networks: 1036, 1057, 1020-1025.  Lines touched ahead by a load of their own 1025.  fp32, which the matrix cores bound: two of eight.
+        constexpr int G = kUnitGroup(ES), SETS = kUnitSets(ES);
+        const int kgroups = (kch + G - 1) / G;
+        const bool whole_groups = kch % G == 0 && kch * 32 == cin_bytes;   // no K-step of a group reaches past the pixel's channels
         struct Cur { uint32_t rest; int t, kg; };
-        const int kgroups = (kch + kUnitGroup - 1) / kUnitGroup;
         auto advance = [&](Cur& q) __attribute__((always_inline)) {
-            if (++q.kg == kgroups) {
-                q.kg = 0;
-                q.rest &= q.rest - 1;
-                q.t = q.rest ? __builtin_ctz(q.rest) : kNoTap;
-            }
+            const bool wrap = q.kg + 1 == kgroups;
+            q.kg = wrap ? 0 : q.kg + 1;
+            q.rest = wrap ? q.rest & (q.rest - 1) : q.rest;
+            q.t = __builtin_ctz(q.rest | 1u << kNoTap);
         };
-        struct Set { Vec x[kUnitGroup], w[kUnitGroup]; };
+        struct Set { Vec x[G], w[G]; };
         // Every load is issued unconditionally: a lane whose tap is not flagged, channel padding and groups past the end
         // read zeros from an offset outside the descriptor.
         auto issue = [&](const Cur& q, Set& st) __attribute__((always_inline)) {
             const bool live = q.t != kNoTap;
             const int t = live ? q.t : 0;
             const int dy = t / KS, dx = t - dy * KS;
-            uint32_t off = (live && ((taps >> t) & 1u)) ? base + (uint32_t)((dy * c.w + dx) * cin_bytes + q.kg * (kUnitGroup * 32)) : kOob;
+            uint32_t off = (live && ((taps >> t) & 1u)) ? base + (uint32_t)((dy * c.w + dx) * cin_bytes + q.kg * (G * 32)) : kOob;
             asm volatile("" : "+v"(off));                      // one load at a computed offset, not a load per case
-            uint32_t wstep = (uint32_t)(t * kch + q.kg * kUnitGroup) * wstride;
+            uint32_t wstep = (uint32_t)(t * kch + q.kg * G) * wstride;
             if (whole_groups) {
 #pragma unroll
-                for (int i = 0; i < kUnitGroup; ++i) {
+                for (int i = 0; i < G; ++i) {
                     st.x[i] = ws_load16<Vec>(rs_in, off + (uint32_t)i * 32u);
                     st.w[i] = ws_load16<Vec>(rs_w, wlane, wstep);
                     wstep += wstride;
                 }
             } else {
 #pragma unroll
-                for (int i = 0; i < kUnitGroup; ++i) {
-                    const int kc = q.kg * kUnitGroup + i;
+                for (int i = 0; i < G; ++i) {
+                    const int kc = q.kg * G + i;
                     st.x[i] = ws_load16<Vec>(rs_in, (2 * kc + g) * 16 < cin_bytes ? off + (uint32_t)i * 32u : kOob);
                     st.w[i] = ws_load16<Vec>(rs_w, wlane, wstep);
                     if (kc + 1 < kch) wstep += wstride;        // (a step past the last one repeats its weights and meets zeros)
@@ -203,20 +208,20 @@ __global__ __launch_bounds__(kUnitMaxWaves* kWave) void conv_unit_kernel(ListArg
         };
         auto mma = [&](const Set& st) __attribute__((always_inline)) {
 #pragma unroll
-            for (int i = 0; i < kUnitGroup; ++i) Mma<T>::run(acc[0][0], st.w[i], st.x[i]);
+            for (int i = 0; i < G; ++i) Mma<T>::run(acc[0][0], st.w[i], st.x[i]);
             __builtin_amdgcn_sched_barrier(0);
         };
         if (cb_on && wave_taps) {
-            Set sa, sb2;
+            Set st[SETS];
             Cur cg{wave_taps, __builtin_ctz(wave_taps), 0};
-            int left = __popc(wave_taps) * kgroups;
-            issue(cg, sa); advance(cg);
-            while (left > 0) {
-                issue(cg, sb2); advance(cg);
-                mma(sa);
-                issue(cg, sa); advance(cg);
-                mma(sb2);
-                left -= 2;
+#pragma unroll
+            for (int d = 0; d < SETS - 1; ++d) { issue(cg, st[d]); advance(cg); }
+            for (int left = __popc(wave_taps) * kgroups; left > 0; left -= SETS) {
+#pragma unroll
+                for (int d = 0; d < SETS; ++d) {
+                    issue(cg, st[(d + SETS - 1) % SETS]); advance(cg);
+                    mma(st[d]);
+                }
             }
         }
         }
