@@ -418,7 +418,7 @@ static bool first_single(const ConvArgs& c, int64_t workgroups, int num_cu) {
 // SIMD hides more than the quads save.  First frames of one layer with its input layer, MI355X, us, quads -> lanes:
 // * windows over few channels: on 16 streams of 128x128 3x3 24->24 31.2 -> 25.5, 24->64 46.5 -> 40.8, 40->64 51 -> 49, 16->256 91 -> 80; on 12 of 120x128
 //   5x5 24->96 95 -> 78, 7x7 24->256 260 -> 219.  Not for whole K-steps (3x3 32->96 65 -> 72) nor 40 channels to one block (3x3 40->32 27.6 -> 29.7).
-// * `padded` lines, a K-step in four and more empty: split sums over 3x3 on 4 of 64x66 72->64 17.4 -> 16.5, 72->256 36.7 -> 35.5, and whatever the
+// * `padded` lines, a K-step in four and more empty: split sums over 3x3 on 4 of 64x66 72->64 17.4 -> 16.5, 72->128 24.3 -> 23.6, and whatever the
 //   window where no compute unit has two workgroups: 5x5 72->96 on 2 of 60x50 20.1 -> 17.2 (but 5x5 72->96 on 4 of 64x66 35.9 -> 37.7).
 //   fp32, whose sums the matrix cores bound and whose quads only add to: 5x5 36->64 35.7 -> 31.3, 100->64 66 -> 61, 3x3 52->64 23.5 -> 21.5.
 // * wide fp16 layers, whose stores want the third wave: on 12 of 120x128 1x1 40->192 49.8 -> 45, 72->512 201 -> 188, 96->512 324 -> 314, 3x3 72->256
